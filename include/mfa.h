@@ -202,8 +202,9 @@ MFA_API mfa_status mfa_out_proj(mfa_ctx* ctx, const float* attn_out, const void*
  *   max_seq_len_hint  host-side upper bound of seq_lens, used only to size the
  *            launch; 1 <= hint <= cfg.max_seq_len
  *   out      fp32 [B, n_q_heads, head_dim]      (written)
- * Scores and sums are accumulated in fp32; attention weights are rounded to
- * bf16 before they multiply V.  For a given build, device and arguments the
+ * Scores and sums are accumulated in fp32; attention weights keep at least the 8
+ * significant bits of bf16 where they multiply V (bf16, or two e4m3 terms over
+ * long 8-bit and 4-bit caches).  For a given build, device and arguments the
  * result is bitwise reproducible from call to call.
  * Work distribution: for B <= 4096 the 64-token tiles of all sequences, laid end
  * to end, are cut into equal ranges over at most 256 workgroups, whatever the

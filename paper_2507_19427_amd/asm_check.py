@@ -1,26 +1,26 @@
 """Host-side checks of the compiled attention kernels (no GPU needed).
 
-The kernels for the 8-bit and 4-bit caches load cache data with inline-assembly loads and wait for them with
-an inline-assembly s_waitcnt (a counted wait that leaves the youngest step's loads in flight; left to the
-compiler the wait would drain the pipeline every tile).  Between the two statements the compiler does not
-know that the destination registers are still in flight.  The code gives it no reason to touch them, but
-nothing in the language forbids the register allocator from copying, spilling or reusing such a register
-before the wait, which would silently use a value that has not arrived.  So the build checks the machine
-code it has just produced:
+The kernels for the 8-bit and 4-bit caches load cache data with inline-assembly loads (to LDS) and wait for them with
+inline-assembly s_waitcnt, counted where several stages are in flight (left to the compiler the wait would drain the
+pipeline every stage).  The compiler does not know about these loads.  So the build checks the machine code it has
+just produced:
 
-  * between a pipeline load and the explicit wait that covers it, no instruction of any kind names one of
-    the load's destination registers (as a source or as a destination);
-  * no compiler-made vector-memory wait inside the pipeline loop reaches the pipeline's own loads;
-  * the kernels use no scratch memory (a spill of an in-flight register would go there) -- for every
-    attention kernel, since scratch also costs every wave its set-up.
+  * where an inline-assembly load writes registers: between it and the explicit wait that covers it, no instruction of any
+    kind names one of its destination registers (as a source or as a destination);
+  * no compiler-made vector-memory wait inside a pipeline loop: it would wait for the pipeline's own loads;
+  * the kernels use no scratch memory -- for every attention kernel, since scratch also costs every wave its set-up,
+    and a reload inside a pipeline loop waits for everything in flight.
 
 build.py runs check_attention_asm() on the assembly of every build and fails the build on a violation;
 tests/test_build_asm.py runs the same functions, and the checker itself against planted mistakes.
 """
 import re
 
-PIPELINE_KERNELS = [(paged, q_len, bits) for bits in (8, 4) for q_len in (1, 2) for paged in (0, 1)]
-OPS_PER_STEP = {8: 5, 4: 3}
+# Kernels that keep two stages in flight: their counted wait leaves the operations of the younger one outstanding (8 direct
+# loads and a load of scales).  (8 bit with one query token keeps one stage in flight and waits for everything, 4 bit
+# with two query tokens keeps four.)
+PIPELINE_KERNELS = [(paged, q_len, bits) for bits, q_len in ((8, 2), (4, 1)) for paged in (0, 1)]
+OPS_PER_STEP = {8: 9, 4: 9}
 
 _REG = re.compile(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b")
 
@@ -96,7 +96,26 @@ def check_pipeline(lines, ops_per_step=5):
             continue
         touched = registers_named(rest)
         assert not (touched & in_flight()), f"in-flight register touched before its wait: {t}"
-    assert partial_waits >= 2, "the two steps of the unrolled loop each wait for all but the youngest step's loads"
+    assert partial_waits >= 1, "the loop waits for all but the youngest stage's loads"
+
+
+def check_no_compiler_wait_in_loop(lines, mfmas=32):
+    """Raises AssertionError if a basic block with at least `mfmas` matrix instructions (a pipeline loop's body) holds a
+    compiler-made vector-memory wait."""
+    blocks, in_asm = [[0, None]], False
+    for ln in lines:
+        t = ln.strip()
+        if t.startswith(";;#ASMSTART") or t.startswith(";;#ASMEND"):
+            in_asm = t.startswith(";;#ASMSTART")
+        elif t.startswith(".LBB"):
+            blocks.append([0, None])
+        elif "mfma" in t and not t.startswith(";"):
+            blocks[-1][0] += 1
+        elif t.startswith("s_waitcnt") and "vmcnt" in t and not in_asm:
+            blocks[-1][1] = t
+    assert any(n >= mfmas for n, _ in blocks), "no pipeline loop found"
+    for n, wait in blocks:
+        assert n < mfmas or wait is None, f"compiler-made vector-memory wait in a pipeline loop: {wait}"
 
 
 def scratch_bytes(text):
@@ -122,6 +141,14 @@ def check_attention_asm(text):
             check_pipeline(kernel_body(text, name), OPS_PER_STEP[bits])
         except AssertionError as e:
             raise AssertionError(f"{name}: {e}") from None
+    for bits in (8, 4):
+        for q_len in (1, 2):
+            for paged in (0, 1):
+                name = lowbit_kernel_name(paged, q_len, bits)
+                try:
+                    check_no_compiler_wait_in_loop(kernel_body(text, name))
+                except AssertionError as e:
+                    raise AssertionError(f"{name}: {e}") from None
     scratch = scratch_bytes(text)
     decode = {k: v for k, v in scratch.items() if "decode_" in k}
     assert len(decode) == 16, f"expected 16 attention kernels, found {sorted(decode)}"

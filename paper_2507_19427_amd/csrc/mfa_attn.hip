@@ -2,7 +2,7 @@
 // shared key head and one shared value head (paper, Section 2), one query token
 // per sequence (or a pair, Section 5.2), independent sequences (Section 7.1).
 //
-// Work decomposition.  A workgroup of 8 waves works off segments: pieces
+// Work decomposition.  A workgroup works off segments: pieces
 // [t0, t1) of one sequence's tokens, streamed once from HBM (mfa_attn_core.hpp:
 // which segments a workgroup gets, how the waves share a tile, the MFMA operand
 // layouts).  A segment that covers its whole sequence writes the final output;
@@ -15,44 +15,16 @@
 // of the direct load because its LDS side is fixed to base + 16*lane.
 //
 // 8-bit and 4-bit caches (e4m3 / e2m1 codes, one fp32 scale per token per
-// tensor): the key codes go by direct loads into a three-slot ring and are
-// multiplied as they are on the 8-bit MFMA against a two-term e4m3 query; the
-// value codes travel through registers two tiles ahead and are expanded to bf16
-// (exactly) into one of two value images for the same weighted-sum path as bf16.
+// tensor): mfa_lowbit.hpp and, for little work per workgroup, mfa_lowbit_short.hpp.
 // The key scale multiplies the score column of its token, the value scale rides
 // on the attention weight of its token.
 #include <hip/hip_ext.h>
-#include <type_traits>
 
-#include "mfa_attn_core.hpp"
+#include "mfa_lowbit_short.hpp"
 
 namespace mfa {
 
-constexpr int kSlotBytes = 2 * kUnitBytes;            // one 64-token tile: two unit images
 constexpr int kLoadsPerTileAndWave = 8;               // direct loads a wave of decode_bf16_kernel issues per tile (4 rows pairs x K, V)
-static_assert(kLoadsPerTileAndWave == 8, "schedule_begin waits with s_waitcnt vmcnt(8) for the loads older than a tile's");
-constexpr int kAttnLdsBytes = 2 * kSlotBytes;         // bf16 kernel: 128 KB
-
-
-// Page id of the tile that starts at token tile_t0 (paged cache only).  Looked up one tile ahead
-// of its use so that the table read is never on the critical path of issuing a tile's loads.
-template <bool PAGED>
-__device__ __forceinline__ int lookup_page(const AttnArgs& a, int b, int tile_t0)
-{
-    // read through the constant address space: the table is not written while the kernel runs, and a
-    // uniform index then makes this a scalar load, which the vector-memory waits do not have to cover
-    typedef const __attribute__((address_space(4))) int32_t* const_table_t;
-    if (!PAGED) return 0;
-    const int page = ((const_table_t)a.block_table)[(size_t)b * a.max_blocks_per_seq + tile_t0 / kPage];
-    return page < 0 ? 0 : (page >= a.n_pages ? a.n_pages - 1 : page);      // a bad id reads a wrong page, never outside the pool
-}
-
-template <bool PAGED>
-__device__ __forceinline__ int64_t tile_row0(const AttnArgs& a, int b, int tile_t0, int page)
-{
-    return PAGED ? (int64_t)page * kPage : (int64_t)b * a.seq_stride_tokens + tile_t0;
-}
-
 // QL = query tokens per sequence.  1: wave = 4*(token half of the tile) + head group.  2: wave =
 // 4*(query token of the pair q0, q0 + 1) + head group, and every wave works through both halves of each
 // tile; query token j of q_len attends to the first len - (q_len - 1 - j) cached tokens (the new tokens are
@@ -101,7 +73,7 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
             }
         }
     };
-    auto load_q = [&](QFrags<16>& q, const Segment& sg) {
+    auto load_q = [&](QFrags& q, const Segment& sg) {
         load_q_fragments(q.f, a.q, QL == 2 ? a.q_len * sg.b + a.q0 + grp : sg.b, 16 * wq + n, g);
     };
 
@@ -115,20 +87,22 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
     // those 64 KB are on their way (the lengths, requested earlier, arrive earlier).  When the schedule
     // disagrees (ragged lengths), the right tile goes into the other slot and the guessed one is never looked
     // at; the guess only ever names whole tiles below the hint, i.e. memory the caller has vouched for.
-    stage_lengths(a, lds_base);
+    stage_lengths(a, lds_base, kBf16SchedOffset);
     const FirstTileGuess guess = guess_first_tile(a);
     if (guess.valid) {
         Segment gs;
         gs.b = guess.b; gs.t0 = guess.t0; gs.t1 = guess.t0 + kTile;
         issue_tile(gs, 0, 0, lookup_page<PAGED>(a, guess.b, guess.t0), true);   // kLoadsPerTileAndWave loads
     }
-    Schedule sched = schedule_begin(a, lds_base, guess.valid ? kLoadsPerTileAndWave : 0);
+    Lengths lens;
+    staged_lengths<kLoadsPerTileAndWave>(a, lds_base, kBf16SchedOffset, guess.valid, lens);
+    Schedule sched = schedule_begin<kAttnThreads>(a, lds_base, kBf16SchedOffset, lens);
     Segment r, r_next;
-    if (!schedule_next(a, lds_base, sched, r)) {
+    if (!schedule_next<kAttnThreads>(a, sched, r)) {
         wait_vmem_all();                              // nothing may still be writing into this workgroup's LDS when it ends
         return;
     }
-    QFrags<16> q;
+    QFrags q;
     load_q(q, r);
     int slot0 = 0;                                    // slot of the segment's first tile
     if (!(guess.valid && r.b == guess.b && r.t0 == guess.t0 && r.t0 + kTile <= r.t1)) {
@@ -150,20 +124,20 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
                 issue_tile(r, it + 1, slot ^ 1, page_next);
                 if (it + 2 < r.n_tiles) page_next = lookup_page<PAGED>(a, r.b, r.t0 + (it + 2) * kTile);
             } else {
-                more = schedule_next(a, lds_base, sched, r_next);
+                more = schedule_next<kAttnThreads>(a, sched, r_next);
                 if (more) issue_tile(r_next, 0, slot ^ 1, lookup_page<PAGED>(a, r_next.b, r_next.t0));
             }
             if (QL == 2) {
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const int unit = slot * kSlotBytes + u * kUnitBytes;
-                    process_unit<16>(st, q, lds_base, unit, unit + kUnitVOffset, r.t0 + it * kTile + u * kUnitTokens,
-                                     t1_mine, a.scale_log2e, n, g, 0, 0);
+                    process_unit(st, q, lds_base, unit, unit + kUnitVOffset, r.t0 + it * kTile + u * kUnitTokens,
+                                 t1_mine, a.scale_log2e, n, g);
                 }
             } else {
                 const int unit = slot * kSlotBytes + grp * kUnitBytes;
-                process_unit<16>(st, q, lds_base, unit, unit + kUnitVOffset, r.t0 + it * kTile + grp * kUnitTokens,
-                                 t1_mine, a.scale_log2e, n, g, 0, 0);
+                process_unit(st, q, lds_base, unit, unit + kUnitVOffset, r.t0 + it * kTile + grp * kUnitTokens,
+                             t1_mine, a.scale_log2e, n, g);
             }
         }
         const int last_slot = (slot0 + r.n_tiles - 1) & 1;
@@ -221,7 +195,7 @@ __global__ __launch_bounds__(kMultiThreads) void decode_bf16_multi_kernel(AttnAr
             load_to_lds_16B(v_tile, (uint32_t)(in_tile * 512 + cv * 16), dst + kUnitVOffset);
         }
     };
-    QFrags<16> q[NT];
+    QFrags q[NT];
     auto load_q = [&](const Segment& sg) {
         int lane_now = lane;                                          // (addresses formed here, once per segment)
         asm volatile("" : "+v"(lane_now));
@@ -231,12 +205,13 @@ __global__ __launch_bounds__(kMultiThreads) void decode_bf16_multi_kernel(AttnAr
 
     // A word of LDS behind the schedule's tables: set by a wave whose unit was refused (a score more than
     // 2^kFixedReferenceLag above its head's reference exponent), seen by all waves after the next barrier.
-    constexpr int kRestartFlag = kAttnLdsTotal - 4;
-    stage_lengths(a, lds_base);
-    Schedule sched = schedule_begin(a, lds_base);
+    stage_lengths(a, lds_base, kBf16SchedOffset);
+    Lengths lens;
+    staged_lengths<0>(a, lds_base, kBf16SchedOffset, false, lens);
+    Schedule sched = schedule_begin<kMultiThreads>(a, lds_base, kBf16SchedOffset, lens);
     Segment r;
     bool first_segment = true;
-    while (schedule_next(a, lds_base, sched, r)) {
+    while (schedule_next<kMultiThreads>(a, sched, r)) {
         if (!first_segment) __syncthreads();          // every wave is done with the previous segment's tiles
         first_segment = false;
         // Every segment leaves a partial result, also one that covers its whole sequence: partials are stored
@@ -260,7 +235,7 @@ __global__ __launch_bounds__(kMultiThreads) void decode_bf16_multi_kernel(AttnAr
         // scores never get here; correctness does not depend on that.
         for (bool again = true; again;) {
             again = false;
-            if (threadIdx.x == 0) *LDS_AT(int, lds_base, kRestartFlag) = 0;
+            if (threadIdx.x == 0) *LDS_AT(int, lds_base, kBf16RestartFlag) = 0;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 init_state(st[t]);
@@ -273,7 +248,7 @@ __global__ __launch_bounds__(kMultiThreads) void decode_bf16_multi_kernel(AttnAr
                 const int slot = it & 1;
                 wait_vmem_all();
                 __syncthreads();                       // tile it has landed; the flag store of attempt start / of a refusal is visible
-                if (*LDS_AT(int, lds_base, kRestartFlag) != 0) { again = true; break; }
+                if (*LDS_AT(int, lds_base, kBf16RestartFlag) != 0) { again = true; break; }
                 if (it + 1 < r.n_tiles) {
                     issue_tile(r, it + 1, slot ^ 1, page_next);
                     if (it + 2 < r.n_tiles) page_next = lookup_page<PAGED>(a, r.b, r.t0 + (it + 2) * kTile);
@@ -287,7 +262,7 @@ __global__ __launch_bounds__(kMultiThreads) void decode_bf16_multi_kernel(AttnAr
                                                 t1_mine, a.scale_log2e, n, g, m_wanted)) {
 #pragma unroll
                         for (int t = 0; t < NT; ++t) m_floor[t] = fmaxf(m_floor[t], m_wanted[t]);
-                        if (lane == 0) *LDS_AT(int, lds_base, kRestartFlag) = 1;
+                        if (lane == 0) *LDS_AT(int, lds_base, kBf16RestartFlag) = 1;
                         refused = true;
                         break;
                     }
@@ -296,7 +271,7 @@ __global__ __launch_bounds__(kMultiThreads) void decode_bf16_multi_kernel(AttnAr
             if (!again) {
                 // the last tile's refusal (if any) has not met a barrier yet
                 __syncthreads();
-                again = *LDS_AT(int, lds_base, kRestartFlag) != 0;
+                again = *LDS_AT(int, lds_base, kBf16RestartFlag) != 0;
             }
             if (again) {
                 wait_vmem_all();                       // a tile may still be on its way into the ring
@@ -310,244 +285,6 @@ __global__ __launch_bounds__(kMultiThreads) void decode_bf16_multi_kernel(AttnAr
             finish_segment_two(st[t], a, r, t, wq, lane_now);
             __builtin_amdgcn_sched_barrier(0);        // one query token's accumulators at a time through ordinary registers
         }
-    }
-}
-
-// ---- 8-bit and 4-bit caches (BITS = 8: e4m3 codes, 256 B per row; BITS = 4: e2m1 codes two per byte,
-// 128 B per row; one fp32 scale per token and tensor beside either).
-// Keys stay codes all the way: each tile's rows go by direct loads into a ring of three LDS slots and
-// are multiplied on the fp8/fp4 MFMA against the two-term query.  Values are multiplied by bf16
-// weights, so their codes are converted once per tile: every thread carries 32 bytes (8 bit: two
-// 16-byte pieces; 4 bit: one) of V and one per-token scale in registers from HBM, converts (exactly:
-// every e4m3 and e2m1 value is a bf16 value) and writes the bf16 rows into one of two value images
-// (padded rows in plain order: pv_unit).
-//
-// LDS: value image P (P = tile & 1) at P*34 KB, its unit g at + g*17 KB; key slot k (tile % 3) at
-// 68 KB + k*16 KB (4 bit: the first 8 KB of it); scale set P at 116 KB + P*512 B (64 key scales, then
-// 64 value scales).
-constexpr int kLbVImageBytes = 2 * kPaddedVUnitBytes;    // two units of 32 padded bf16 rows
-constexpr int kLbKBase = 2 * kLbVImageBytes;
-constexpr int kLbKSlotBytes = kTile * 256;
-constexpr int kLbKSlots = 3;
-constexpr int kLbScaleBase = kLbKBase + kLbKSlots * kLbKSlotBytes;
-constexpr int kLbLdsBytes = kLbScaleBase + 2 * 512;
-static_assert(kLbLdsBytes <= kSchedLdsOffset && kAttnLdsBytes <= kSchedLdsOffset && kAttnLdsTotal <= 160 * 1024,
-              "the schedule's prefix sums live behind the tile memory of both kernels");
-
-struct LowbitTileRegs {
-    u32x4 piece[2];       // 8 bit: V rows prow and prow + 32, 16-byte chunk pchunk; 4 bit: piece[0] only,
-                          // V row tid / 8, 16-byte chunk tid % 8 (32 elements)
-    float scale;          // threads 0..63: key scale of token tid; 64..127: value scale of token tid - 64
-};
-// Every step of the pipeline issues, per wave and in this order, the register loads of a tile
-// (8 bit: two pieces and a scale; 4 bit: one piece and a scale) and the direct loads of a key tile
-// (8 bit: two; 4 bit: one).  They are inline assembly, awaited with an explicit vmcnt that leaves
-// exactly the youngest step's loads in flight: left to the compiler, the wait would be widened to
-// vmcnt(0) at the loop's control-flow joins and drain the pipeline every tile.  The registers pass
-// through the waiting statement, so no use of them can be scheduled before it.
-template <int BITS> constexpr int kLowbitOpsPerStep = BITS == 8 ? 5 : 3;
-// (address = wave-uniform base in scalar registers + 32-bit byte offset per lane; non-temporal: read once)
-__device__ __forceinline__ void load_regs_16B(u32x4& dst, const void* sbase, uint32_t voff)
-{
-    asm volatile("global_load_dwordx4 %0, %1, %2 nt" : "=&v"(dst) : "v"(voff), "s"(sbase) : "memory");
-}
-__device__ __forceinline__ void load_regs_4B(float& dst, const void* sbase, uint32_t voff)
-{
-    asm volatile("global_load_dword %0, %1, %2 nt" : "=&v"(dst) : "v"(voff), "s"(sbase) : "memory");
-}
-template <int BITS>
-__device__ __forceinline__ void wait_all_but_youngest_step(LowbitTileRegs& t)
-{
-    if constexpr (BITS == 8) {
-        static_assert(kLowbitOpsPerStep<8> == 5, "the wait below leaves 5 operations in flight");
-        asm volatile("s_waitcnt vmcnt(5)" : "+v"(t.piece[0]), "+v"(t.piece[1]), "+v"(t.scale) :: "memory");
-    } else {
-        static_assert(kLowbitOpsPerStep<4> == 3, "the wait below leaves 3 operations in flight");
-        asm volatile("s_waitcnt vmcnt(3)" : "+v"(t.piece[0]), "+v"(t.scale) :: "memory");
-    }
-}
-// Wait for every load in flight while both register sets are still owned by the pipeline: no
-// register of theirs may be handed to other code before its load has landed.
-template <int BITS>
-__device__ __forceinline__ void drain_tiles(LowbitTileRegs& t, LowbitTileRegs& u)
-{
-    if constexpr (BITS == 8)
-        asm volatile("s_waitcnt vmcnt(0)"
-                     : "+v"(t.piece[0]), "+v"(t.piece[1]), "+v"(t.scale), "+v"(u.piece[0]), "+v"(u.piece[1]), "+v"(u.scale)
-                     :: "memory");
-    else
-        asm volatile("s_waitcnt vmcnt(0)" : "+v"(t.piece[0]), "+v"(t.scale), "+v"(u.piece[0]), "+v"(u.scale) :: "memory");
-}
-
-template <bool PAGED, int QL, int BITS>
-__global__ __launch_bounds__(kAttnThreads) void decode_lowbit_kernel(AttnArgs a)
-{
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    const lds_ptr_t lds_base = (lds_ptr_t)smem;
-    const uint32_t lds_addr0 = (uint32_t)(uintptr_t)lds_base;
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wq = wave & 3;
-    const int grp = wave >> 2;
-    const int n = lane & 15;
-    const int g = lane >> 4;
-
-    stage_lengths(a, lds_base);
-    Schedule sched = schedule_begin(a, lds_base);
-    Segment r;
-    bool first_segment = true;
-    while (schedule_next(a, lds_base, sched, r)) {
-        if (!first_segment) __syncthreads();          // the previous segment's exchange area is the tile memory
-        first_segment = false;
-
-        // Tiles past the end of the segment repeat its last tile (never consumed), so that every step
-        // issues the same number of loads.  Rows at or past t1 re-read the last valid token.
-        constexpr int kRowBytes = BITS == 8 ? 256 : 128;                   // one cached row of K or V
-        const int prow = BITS == 8 ? threadIdx.x >> 4 : threadIdx.x >> 3;  // 8 bit: 0..31 (and + 32); 4 bit: 0..63
-        const int pchunk = BITS == 8 ? threadIdx.x & 15 : threadIdx.x & 7; // 16-byte chunk of the row
-        auto tile_origin = [&](int tile, int& tile_t0, int64_t& row0, int& last) {
-            if (tile >= r.n_tiles) tile = r.n_tiles - 1;
-            tile = __builtin_amdgcn_readfirstlane(tile);                   // keeps the page lookup a scalar load
-            tile_t0 = r.t0 + tile * kTile;
-            row0 = tile_row0<PAGED>(a, r.b, tile_t0, lookup_page<PAGED>(a, r.b, tile_t0));
-            last = r.t1 - 1 - tile_t0;                                    // last valid row of this tile (>= 0)
-        };
-        auto load_tile = [&](LowbitTileRegs& t, int tile) {
-            int tile_t0, last; int64_t row0;
-            tile_origin(tile, tile_t0, row0, last);
-#pragma unroll
-            for (int i = 0; i < (BITS == 8 ? 2 : 1); ++i) {
-                const int row = prow + 32 * i;
-                const int in_tile = row > last ? last : row;
-                load_regs_16B(t.piece[i], (const unsigned char*)a.v + row0 * kRowBytes, (uint32_t)(in_tile * kRowBytes + pchunk * 16));
-            }
-            const int tok = lane;                                          // waves 2.. repeat those of waves 0 and 1
-            const int in_tile = tok > last ? last : tok;
-            load_regs_4B(t.scale, ((wave & 1) ? a.v_scale : a.k_scale) + row0, (uint32_t)(in_tile * 4));
-        };
-        // Keys of a tile.  8 bit: 16 direct loads of 4 rows, wave w issues loads 2w and 2w + 1, 16-byte
-        // chunk c of row r lands at c ^ (r & 15).  4 bit: 8 direct loads of 8 rows, one per wave, chunk c
-        // of row r lands at c ^ ((r >> 1) & 7): 16 consecutive rows then spread one chunk column over all
-        // 64 banks.
-        auto issue_keys = [&](int tile, int kslot) {
-            int tile_t0, last; int64_t row0;
-            tile_origin(tile, tile_t0, row0, last);
-            if constexpr (BITS == 8) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int first_row = 4 * (2 * wave + i);                     // wave-uniform
-                    const int row = first_row + (lane >> 4);
-                    const int in_tile = row > last ? last : row;
-                    const int c16 = (lane & 15) ^ (row & 15);
-                    load_to_lds_16B((const unsigned char*)a.k + row0 * 256, (uint32_t)(in_tile * 256 + c16 * 16),
-                                    lds_addr0 + kLbKBase + kslot * kLbKSlotBytes + first_row * 256);
-                }
-            } else {
-                const int first_row = 8 * wave;                                   // wave-uniform
-                const int row = first_row + (lane >> 3);
-                const int in_tile = row > last ? last : row;
-                const int c16 = (lane & 7) ^ ((row >> 1) & 7);
-                load_to_lds_16B((const unsigned char*)a.k + row0 * 128, (uint32_t)(in_tile * 128 + c16 * 16),
-                                lds_addr0 + kLbKBase + kslot * kLbKSlotBytes + first_row * 128);
-            }
-        };
-        // Convert a tile's value codes to bf16 and write them into image `image`; the scales go beside it.
-        auto store_tile = [&](const LowbitTileRegs& t, int image) {
-            if constexpr (BITS == 8) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    bf16x8 half[2];
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                        const bf16x2 p01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(t.piece[i][w], 1.0f, false);
-                        const bf16x2 p23 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(t.piece[i][w], 1.0f, true);
-                        half[w >> 1][4 * (w & 1) + 0] = p01[0];
-                        half[w >> 1][4 * (w & 1) + 1] = p01[1];
-                        half[w >> 1][4 * (w & 1) + 2] = p23[0];
-                        half[w >> 1][4 * (w & 1) + 3] = p23[1];
-                    }
-                    // (halves swapped in some chunks: see pv_unit)
-                    const int off = image * kLbVImageBytes + i * kPaddedVUnitBytes + prow * kPaddedVRow + (pchunk << 5) + (padded_v_halves_swapped(pchunk) ? 16 : 0);
-                    *LDS_AT(bf16x8, lds_base, off) = half[0];
-                    *LDS_AT(bf16x8, lds_base, off ^ 16) = half[1];
-                }
-            } else {
-                // 32 elements = bf16 chunks 2*pchunk and 2*pchunk + 1 (32 bytes each) of row prow
-                const int row_off = image * kLbVImageBytes + (prow >> 5) * kPaddedVUnitBytes + (prow & 31) * kPaddedVRow;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {                                  // word w: elements 8w .. 8w + 7
-                    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                    const bf16x2 p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(t.piece[0][w], 1.0f, 0);
-                    const bf16x2 p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(t.piece[0][w], 1.0f, 1);
-                    const bf16x2 p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(t.piece[0][w], 1.0f, 2);
-                    const bf16x2 p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(t.piece[0][w], 1.0f, 3);
-                    const bf16x8 eight = {p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
-                    // piece w of this thread's 64-byte group, rotated within the group (see pv_unit)
-                    *LDS_AT(bf16x8, lds_base, row_off + (pchunk << 6) + (((w + padded_v_rotation(pchunk)) & 3) << 4)) = eight;
-                }
-            }
-            if (threadIdx.x < 128) *LDS_AT(float, lds_base, kLbScaleBase + image * 512 + threadIdx.x * 4) = t.scale;
-        };
-
-        WaveState st;
-        init_state(st);
-
-        // Step t consumes tile t (value image t & 1, key slot t % 3) while it converts the values of
-        // tile t+1 into the other image and has the registers of tiles t+2, t+3 and the keys of tiles
-        // t+1, t+2 in flight.  Prologue: what steps -2 and -1 would have issued.
-        LowbitTileRegs regs[2];
-        load_tile(regs[0], 0);
-        load_tile(regs[1], 1);
-        issue_keys(0, 0);
-        // The query fragments are loaded by ordinary loads: the compiler completes them, and with them
-        // everything above, right here instead of inside the loop.
-        QFrags<BITS> q;
-        load_split_q<BITS>(q, a.q, QL == 2 ? a.q_len * r.b + a.q0 + grp : r.b, 16 * wq + n, g);
-        const int end_mine = r.len - (a.q_len - 1 - a.q0 - grp);      // QL == 2: grp = query token of the pair
-        const int t1_mine = QL == 2 ? (r.t1 < end_mine ? r.t1 : end_mine) : r.t1;
-        asm volatile("" : "+v"(q.hi[0]), "+v"(q.hi[1]), "+v"(q.lo[0]), "+v"(q.lo[1]));
-        drain_tiles<BITS>(regs[0], regs[1]);
-        store_tile(regs[0], 0);
-        load_tile(regs[0], 2);
-        issue_keys(1, 1);
-
-        int kslot = 0;                                                     // t % 3
-        auto step = [&](auto parity_c, int t) {
-            constexpr int P = decltype(parity_c)::value;                    // t & 1
-            wait_all_but_youngest_step<BITS>(regs[P ^ 1]);       // registers of tile t+1 and keys of tile t have landed
-            __syncthreads();                               // ... for every wave; everyone is done with tile t-1
-            const int kb = kLbKBase + kslot * kLbKSlotBytes;
-            const int vb = P * kLbVImageBytes;
-            const int scales = kLbScaleBase + P * 512;
-            // The score products of this wave's (first) unit are issued ahead of the conversion of the next tile's
-            // values: the MFMA pipe and the LDS work while the vector ALU converts (4 % on the 8-bit workload,
-            // compared on one box).
-            const int u0 = QL == 2 ? 0 : grp;
-            const RawScores raw0 = qk_unit<BITS>(q, lds_base, kb + u0 * kUnitTokens * kRowBytes, n, g);
-            store_tile(regs[P ^ 1], P ^ 1);                                 // values of tile t+1
-            load_tile(regs[P ^ 1], t + 3);
-            issue_keys(t + 2, kslot == 0 ? 2 : kslot - 1);                  // (t + 2) % 3, the slot tile t-1 has left
-            {
-                const bf16x8 pf = softmax_unit<BITS>(st, q, raw0, lds_base, r.t0 + t * kTile + u0 * kUnitTokens, t1_mine,
-                                                     a.scale_log2e, g, scales + u0 * kUnitTokens * 4, scales + 256 + u0 * kUnitTokens * 4);
-                pv_unit<BITS>(st, lds_base, vb + u0 * kPaddedVUnitBytes, pf, n, g);
-            }
-            if (QL == 2)
-                process_unit<BITS>(st, q, lds_base, kb + kUnitTokens * kRowBytes, vb + kPaddedVUnitBytes,
-                                   r.t0 + t * kTile + kUnitTokens, t1_mine, a.scale_log2e, n, g,
-                                   scales + kUnitTokens * 4, scales + 256 + kUnitTokens * 4);
-            kslot = kslot == 2 ? 0 : kslot + 1;
-        };
-        for (int t = 0; t < r.n_tiles; t += 2) {
-            step(std::integral_constant<int, 0>{}, t);
-            if (t + 1 >= r.n_tiles) break;
-            step(std::integral_constant<int, 1>{}, t + 1);
-        }
-        drain_tiles<BITS>(regs[0], regs[1]);  // the repeats of the last tile issued past the end
-        if (QL == 2) finish_segment_two(st, a, r, grp, wq, lane);
-        else         finish_segment(st, lds_base, 0, a, r, wq, grp, lane);
     }
 }
 
@@ -710,21 +447,40 @@ int32_t balanced_workgroups(int32_t B, int32_t max_seq_len_hint, int32_t target_
 
 namespace {
 
-template <int QL>
-const void* attn_kernel(mfa_kv_dtype kv_dtype, bool paged)
+struct AttnKernel { const void* fn; unsigned threads, lds_bytes; };
+
+template <int QL, int BITS>
+AttnKernel lowbit_kernel(bool paged, bool short_work)
 {
-    if (kv_dtype == MFA_KV_BF16) return paged ? (const void*)decode_bf16_kernel<true, QL> : (const void*)decode_bf16_kernel<false, QL>;
-    if (kv_dtype == MFA_KV_FP4_E2M1) return paged ? (const void*)decode_lowbit_kernel<true, QL, 4> : (const void*)decode_lowbit_kernel<false, QL, 4>;
-    return paged ? (const void*)decode_lowbit_kernel<true, QL, 8> : (const void*)decode_lowbit_kernel<false, QL, 8>;
+    if (short_work) return {paged ? (const void*)short_lowbit_kernel<true, QL, BITS> : (const void*)short_lowbit_kernel<false, QL, BITS>, kAttnThreads, kBf16LdsBytes};
+    return {paged ? (const void*)decode_lowbit_kernel<true, QL, BITS> : (const void*)decode_lowbit_kernel<false, QL, BITS>, kLowbitThreads, LowbitShape<QL, BITS>::kLdsBytes};
 }
-
-}  // namespace
-
-namespace {
+template <int QL>
+AttnKernel attn_kernel(mfa_kv_dtype kv_dtype, bool paged, bool short_work)
+{
+    if (kv_dtype == MFA_KV_BF16) return {paged ? (const void*)decode_bf16_kernel<true, QL> : (const void*)decode_bf16_kernel<false, QL>, kAttnThreads, kBf16LdsBytes};
+    return kv_dtype == MFA_KV_FP4_E2M1 ? lowbit_kernel<QL, 4>(paged, short_work) : lowbit_kernel<QL, 8>(paged, short_work);
+}
 const void* multi_kernel(int q_len, bool paged)
 {
     if (q_len == 3) return paged ? (const void*)decode_bf16_multi_kernel<true, 3> : (const void*)decode_bf16_multi_kernel<false, 3>;
     return paged ? (const void*)decode_bf16_multi_kernel<true, 4> : (const void*)decode_bf16_multi_kernel<false, 4>;
+}
+
+// Which of its two kernels a low-bit cache takes: short_lowbit_kernel below so many 64-token tiles per workgroup, counted at the length of
+// the hint (the host knows no other).  Equal lengths favour decode_lowbit_kernel from 16 tiles on; ragged ones, half the
+// hint on average and with a segment boundary in most workgroups, later, and the line lies where they no longer lose.
+// us per call, short / decode, lengths equal to the hint and drawn from 100 .. hint:
+//                                16 tiles                  32 tiles                  48 tiles                    64 tiles
+//   8 bit, one token    41.1/38.0  42.0/42.8    63.6/57.8  54.2/54.2     89.6/81.6  66.0/65.5    114.0/102.4   83.7/82.6
+//   8 bit, two tokens   56.9/53.4  52.6/55.5    96.3/85.0  73.3/74.0    138.4/120.4 94.5/88.8    175.6/154.5  121.2/111.8
+//   4 bit, one token    33.5/32.2  38.1/40.7    52.8/46.3  48.1/50.0     74.5/63.1  57.8/56.6     95.0/78.8    73.6/73.1
+//   4 bit, two tokens   50.4/48.2  48.2/52.2    82.9/73.5  65.4/68.8    118.2/105.3 84.6/82.4    154.0/132.5  107.3/103.7
+bool short_lowbit_work(const AttnArgs& a, mfa_kv_dtype kv_dtype)
+{
+    const int64_t tiles_per_seq = (a.max_seq_len_hint + kTile - 1) / kTile;
+    const int64_t tiles = a.n_wgs > 0 ? a.B * tiles_per_seq / a.n_wgs : a.chunk_tokens / kTile;
+    return tiles < (kv_dtype == MFA_KV_FP4_E2M1 ? 48 : 30);
 }
 }  // namespace
 
@@ -732,15 +488,15 @@ hipError_t prepare_decode_attn_kernels()
 {
     for (int q_len = 3; q_len <= 4; ++q_len)
         for (int paged = 0; paged < 2; ++paged) {
-            const hipError_t e = hipFuncSetAttribute(multi_kernel(q_len, paged != 0), hipFuncAttributeMaxDynamicSharedMemorySize, kAttnLdsTotal);
+            const hipError_t e = hipFuncSetAttribute(multi_kernel(q_len, paged != 0), hipFuncAttributeMaxDynamicSharedMemorySize, kBf16LdsBytes);
             if (e != hipSuccess) return e;
         }
     for (int dt = 0; dt < 3; ++dt)
-        for (int paged = 0; paged < 2; ++paged) {
+        for (int form = 0; form < 8; ++form) {
             const mfa_kv_dtype kvd = dt == 0 ? MFA_KV_BF16 : (dt == 1 ? MFA_KV_FP8_E4M3 : MFA_KV_FP4_E2M1);
-            hipError_t e = hipFuncSetAttribute(attn_kernel<1>(kvd, paged != 0), hipFuncAttributeMaxDynamicSharedMemorySize, kAttnLdsTotal);
-            if (e != hipSuccess) return e;
-            e = hipFuncSetAttribute(attn_kernel<2>(kvd, paged != 0), hipFuncAttributeMaxDynamicSharedMemorySize, kAttnLdsTotal);
+            const bool paged = (form & 1) != 0, short_work = (form & 2) != 0;
+            const AttnKernel k = (form & 4) ? attn_kernel<2>(kvd, paged, short_work) : attn_kernel<1>(kvd, paged, short_work);
+            const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds_bytes);
             if (e != hipSuccess) return e;
         }
     return hipSuccess;
@@ -750,7 +506,6 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
                               hipEvent_t ev_before, hipEvent_t ev_after)
 {
     const dim3 grid((unsigned)(a.n_wgs > 0 ? a.n_wgs : a.B * a.n_splits));
-    const dim3 block(kAttnThreads);
     if (kv_dtype != MFA_KV_BF16 && kv_dtype != MFA_KV_FP8_E4M3 && kv_dtype != MFA_KV_FP4_E2M1) return hipErrorNotSupported;
     if (a.q_len < 1 || a.q_len > kMaxQueryTokens) return hipErrorNotSupported;
     if (a.q_len != 1 && a.n_wgs == 0) return hipErrorNotSupported;     // several query tokens: balanced schedule only
@@ -758,7 +513,6 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
     // times at which that kernel starts and ends on the device, with no launch gap inside the interval.
     // (With more than two query tokens: the first pair's.)
     if (!(ev_before && ev_after)) ev_before = ev_after = nullptr;
-    const unsigned lds_bytes = a.n_wgs > 0 ? kAttnLdsTotal : kSchedLdsOffset;   // the schedule's arrays only if used
     const unsigned merge_blocks_per_token = (unsigned)(((size_t)a.B * kHeads * (kHeadDim / 4) + 255) / 256);
     // Three and four query tokens over a bf16 cache, batches the per-wave schedule covers: one pass over the cache
     // by the kernel that keeps all of a sequence's query tokens in one wave.
@@ -768,14 +522,15 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
         args.n_here = a.q_len;
         void* params[] = {&args};
         hipError_t e = hipExtLaunchKernel(multi_kernel(a.q_len, a.block_table != nullptr), grid, dim3(kMultiThreads), params,
-                                          kAttnLdsTotal, stream, ev_before, ev_after, 0);
+                                          kBf16LdsBytes, stream, ev_before, ev_after, 0);
         if (e != hipSuccess) return e;
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(merge_splits_kernel, dim3(merge_blocks_per_token * a.q_len), dim3(256), 0, stream, args);
         return hipGetLastError();
     }
-    const void* kernel = a.q_len >= 2 ? attn_kernel<2>(kv_dtype, a.block_table != nullptr) : attn_kernel<1>(kv_dtype, a.block_table != nullptr);
+    const bool short_work = kv_dtype != MFA_KV_BF16 && short_lowbit_work(a, kv_dtype);
+    const AttnKernel kernel = a.q_len >= 2 ? attn_kernel<2>(kv_dtype, a.block_table != nullptr, short_work) : attn_kernel<1>(kv_dtype, a.block_table != nullptr, short_work);
     const int n_here = a.q_len == 1 ? 1 : 2;
     // Otherwise query tokens are worked off in pairs (q0, q0 + 1), one pass over the cache each; an odd count ends
     // with the pair (q_len - 2, q_len - 1), which computes token q_len - 2 a second time with the same result.
@@ -785,7 +540,7 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
         args.q0 = q0 + n_here <= a.q_len ? q0 : a.q_len - n_here;
         args.n_here = n_here;
         void* params[] = {&args};
-        hipError_t e = hipExtLaunchKernel(kernel, grid, block, params, lds_bytes, stream, q0 == 0 ? ev_before : nullptr,
+        hipError_t e = hipExtLaunchKernel(kernel.fn, grid, dim3(kernel.threads), params, kernel.lds_bytes, stream, q0 == 0 ? ev_before : nullptr,
                                           q0 == 0 ? ev_after : nullptr, 0);
         if (e != hipSuccess) return e;
         e = hipGetLastError();

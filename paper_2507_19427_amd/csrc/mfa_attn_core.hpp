@@ -22,6 +22,9 @@
 // second product (8 tokens of its own head), so attention weights never move between lanes and
 // the per-head statistics live in the lanes of that head.
 #pragma once
+#include <type_traits>
+#include <utility>
+
 #include "mfa_internal.hpp"
 
 namespace mfa {
@@ -39,6 +42,13 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // s_waitcnt that constrains only the vector-memory counter: vmcnt(0).
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// ... leaving the N youngest operations in flight (gfx950: vmcnt is bits 3:0 and 15:14 of the immediate)
+template <int N> __device__ __forceinline__ void wait_vmem_but()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+}
+
 // Direct global->LDS load: 16 bytes per lane land at lds_addr + 16*lane (lds_addr is wave-uniform
 // and travels in M0).  The global address is a wave-uniform base (scalar registers) plus a 32-bit
 // byte offset per lane: no 64-bit vector arithmetic per load.  Issued as inline assembly so that
@@ -52,6 +62,21 @@ __device__ __forceinline__ void load_to_lds_16B(const void* sbase, uint32_t voff
 {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                  :: "v"(voff), "s"(sbase), "s"(lds_addr) : "memory");
+}
+
+// The same without the non-temporal hint, for rows that other workgroups read too.
+__device__ __forceinline__ void load_to_lds_16B_keep(const void* sbase, uint32_t voff, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(voff), "s"(sbase), "s"(lds_addr) : "memory");
+}
+
+// The same with the LDS address as a base plus a compile-time offset.
+template <int OFFSET>
+__device__ __forceinline__ void load_to_lds_16B_at(const void* sbase, uint32_t voff, uint32_t lds_base)
+{
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+                 :: "v"(voff), "s"(sbase), "s"(lds_base), "n"(OFFSET) : "memory", "scc");
 }
 
 // The same with the whole address in a pair of vector registers (for a base the compiler keeps there).
@@ -112,129 +137,28 @@ __device__ __forceinline__ void load_q_fragments(bf16x8 (&qf)[8], const void* q,
     for (int ks = 0; ks < 8; ++ks) qf[ks] = qp[ks * 4];
 }
 
-// Query operands of one wave (its 16 heads).
-//   bf16 cache: the bf16 fragments as loaded; a lane holds head n, d = 32*ks + 8*g + j.
-//   fp8 cache:  the scores are taken on the fp8 MFMA (v_mfma_f32_16x16x128_f8f6f4, twice the bf16
-//               rate) straight from the cache's codes, so the query is split into two e4m3 terms,
-//               q * 2^e = hi + lo with e chosen per head so that the largest |q| of the head lands in
-//               [128, 256): hi is the nearest e4m3 value and lo the remainder, which e4m3 holds
-//               exactly (the 8 significant bits of bf16 are 4 + 4) down to 2^-9, i.e. to 2^-17 of the
-//               head's largest element.  A lane holds head n, d = 128*c + 32*g + j (j = 0..31, one
-//               byte each, in register order); inv_scale = 2^-e.
-//   4-bit cache: the same split; the keys enter the same MFMA as e2m1 operands (16 bytes per lane
-//               and 128 elements).  Measured on the device with one-hot operands: with an e2m1 A and
-//               an e4m3 B operand, element j of A's lane group g multiplies byte 16*(g >> 1) + (j & 15)
-//               of B's lane group 2*(g & 1) + (j >> 4).  The keys keep the plain order (a lane holds
-//               d = 128*c + 32*g + j, one 16-byte read), so the query takes the matching one: a lane
-//               holds d = 128*c + 64*(j >> 4) + 16*g + (j & 15).
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-struct SplitQuery { i32x8 hi[2]; i32x8 lo[2]; float inv_scale; };
-template <int BITS> struct QFrags;                    // BITS: width of a cache element (16, 8 or 4)
-template <> struct QFrags<16> { bf16x8 f[8]; };
-template <> struct QFrags<8> : SplitQuery {};
-template <> struct QFrags<4> : SplitQuery {};
-
-template <int BITS>
-__device__ __forceinline__ void load_split_q(QFrags<BITS>& q, const void* qptr, int b, int head, int g)
-{
-    static_assert(BITS == 8 || BITS == 4, "the split query serves the 8-bit and 4-bit caches");
-    const bf16x8* qp = (const bf16x8*)((const uint16_t*)qptr + ((size_t)b * kHeads + head) * kHeadDim + (BITS == 8 ? 32 : 16) * g);
-    bf16x8 qf[2][4];
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) qf[c][i] = qp[c * 16 + (BITS == 8 ? i : 8 * (i >> 1) + (i & 1))];
-    float amax = 0.f;
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) amax = fmaxf(amax, fabsf((float)qf[c][i][j]));
-    amax = head_max(amax);
-    int e = (int)((__float_as_uint(amax) >> 23) & 0xFFu);          // biased exponent of the largest element
-    e = e < 24 ? 24 : e;                                           // (all-zero or vanishing heads: any scale will do)
-    const float scale = __uint_as_float((uint32_t)(261 - e) << 23);   // amax * scale in [128, 256)
-    q.inv_scale = __uint_as_float((uint32_t)(e - 7) << 23);
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int w = 0; w < 2; ++w) {
-                float x[4], r[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) x[j] = (float)qf[c][i][4 * w + j] * scale;
-                int h = __builtin_amdgcn_cvt_pk_fp8_f32(x[0], x[1], 0, false);
-                h = __builtin_amdgcn_cvt_pk_fp8_f32(x[2], x[3], h, true);
-                const auto h01 = __builtin_amdgcn_cvt_pk_f32_fp8(h, false);
-                const auto h23 = __builtin_amdgcn_cvt_pk_f32_fp8(h, true);
-                r[0] = x[0] - h01[0]; r[1] = x[1] - h01[1]; r[2] = x[2] - h23[0]; r[3] = x[3] - h23[1];
-                int l = __builtin_amdgcn_cvt_pk_fp8_f32(r[0], r[1], 0, false);
-                l = __builtin_amdgcn_cvt_pk_fp8_f32(r[2], r[3], l, true);
-                q.hi[c][2 * i + w] = h;
-                q.lo[c][2 * i + w] = l;
-            }
-}
+// Query operands of one wave (its 16 heads): a lane holds head n, d = 32*ks + 8*g + j.
+struct QFrags { bf16x8 f[8]; };
 
 // One 32-token unit: scores, online softmax, weighted sum.
-//   kbase      LDS byte offset of the unit's keys:
-//                bf16:  32 rows of 512 B, 16-byte chunk c of row r stored at c ^ (r & 15)
-//                8 bit: 32 rows of 256 B of e4m3 codes, 16-byte chunk c of row r at c ^ (r & 15)
-//                4 bit: 32 rows of 128 B of packed e2m1 codes, 16-byte chunk c of row r at c ^ ((r >> 1) & 7)
-//   vbase      LDS byte offset of the unit's values in bf16 (8 / 4 bit: the codes expanded, unscaled); layout
-//              at pv_unit
+//   kbase      LDS byte offset of the unit's keys:   32 rows of 512 B, 16-byte chunk c of row r stored at c ^ (r & 15)
+//   vbase      LDS byte offset of the unit's values: 32 rows of 512 B, 32-byte chunk c of row r stored at c ^ (r & 15)
 //   unit_t0    index (within the sequence) of the unit's first token; tokens >= t1 are masked
-//   8 / 4 bit  kscale/vscale point (LDS byte offsets) at the fp32 per-token scales of the unit's 32 tokens
 //
 // Raw scores of a unit (2 blocks of 16 tokens), before any scale: q . k for this lane's head and its 8 tokens.
 struct RawScores { f32x4 s[2]; };
-template <int BITS>
-__device__ __forceinline__ RawScores qk_unit(const QFrags<BITS>& q, lds_ptr_t lds_base, int kbase, int n, int g)
+__device__ __forceinline__ RawScores qk_unit(const QFrags& q, lds_ptr_t lds_base, int kbase, int n, int g)
 {
     f32x4 s[2] = {(f32x4){0.f, 0.f, 0.f, 0.f}, (f32x4){0.f, 0.f, 0.f, 0.f}};
-    if constexpr (BITS == 4) {
-        // e2m1 keys x e4m3 query terms with unit block scales (E8M0 exponent 127)
-        constexpr int kOne = 0x7F7F7F7F;
-        // both query terms go into one accumulator per 16-token block: two independent chains keep the MFMA
-        // pipe fed, and the small term is added first
+    const int k_lane_off = n * 512;                     // K: row n of a 16-token block, swizzle key n
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
+    for (int ks = 0; ks < 8; ++ks) {
 #pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-                const int row = kbase + tb * 2048 + n * 128;
-                const u32x4 k4 = *LDS_AT(u32x4, lds_base, row + (((4 * c + g) ^ ((n >> 1) & 7)) << 4));
-                const i32x8 kf = {(int)k4[0], (int)k4[1], (int)k4[2], (int)k4[3], 0, 0, 0, 0};
-                s[tb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(kf, q.lo[c], s[tb], 4, 0, 0, kOne, 0, kOne);
-                s[tb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(kf, q.hi[c], s[tb], 4, 0, 0, kOne, 0, kOne);
-            }
-        }
-    } else if constexpr (BITS == 8) {
-        // e4m3 x e4m3 with unit block scales (E8M0 exponent 127)
-        constexpr int kOne = 0x7F7F7F7F;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-                const int row = kbase + tb * 4096 + n * 256;
-                const int m = 8 * c + 2 * g;                       // first of this lane's two 16-byte chunks
-                union { i32x8 v; u32x4 h[2]; } kf;
-                kf.h[0] = *LDS_AT(u32x4, lds_base, row + ((m ^ n) << 4));
-                kf.h[1] = *LDS_AT(u32x4, lds_base, row + (((m + 1) ^ n) << 4));
-                s[tb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(kf.v, q.lo[c], s[tb], 0, 0, 0, kOne, 0, kOne);
-                s[tb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(kf.v, q.hi[c], s[tb], 0, 0, 0, kOne, 0, kOne);
-            }
-        }
-    } else {
-        const int k_lane_off = n * 512;                 // K: row n of a 16-token block, swizzle key n
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-                const int off = kbase + tb * 8192 + k_lane_off + (((4 * ks + g) ^ n) << 4);
-                const bf16x8 kf = *LDS_AT(bf16x8, lds_base, off);
-                s[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, q.f[ks], s[tb], 0, 0, 0);
-            }
+        for (int tb = 0; tb < 2; ++tb) {
+            const int off = kbase + tb * 8192 + k_lane_off + (((4 * ks + g) ^ n) << 4);
+            const bf16x8 kf = *LDS_AT(bf16x8, lds_base, off);
+            s[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, q.f[ks], s[tb], 0, 0, 0);
         }
     }
     RawScores r;
@@ -244,23 +168,9 @@ __device__ __forceinline__ RawScores qk_unit(const QFrags<BITS>& q, lds_ptr_t ld
 }
 // Online softmax of a unit from its raw scores, and the rescale of what has been accumulated so far.
 // Returns the unit's attention weights as the B operand of the weighted sum (8 tokens of this lane's head).
-template <int BITS>
-__device__ __forceinline__ bf16x8 softmax_unit(WaveState& st, const QFrags<BITS>& q, const RawScores& raw, lds_ptr_t lds_base,
-                                               int unit_t0, int t1, float scale_log2e, int g, int kscale_off, int vscale_off)
+__device__ __forceinline__ bf16x8 softmax_unit(WaveState& st, const RawScores& raw, int unit_t0, int t1, float scale_log2e, int g)
 {
-    constexpr bool FP8 = BITS != 16;                     // 8-bit arithmetic on the scores, scales beside the codes
-    f32x4 s[2] = {raw.s[0], raw.s[1]};
-    if constexpr (FP8) scale_log2e *= q.inv_scale;
-    f32x4 vsc[2];
-    if (FP8) {
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
-            const f32x4 ksc = *LDS_AT(f32x4, lds_base, kscale_off + (16 * tb + 4 * g) * 4);
-            vsc[tb] = *LDS_AT(f32x4, lds_base, vscale_off + (16 * tb + 4 * g) * 4);
-            s[tb] *= ksc;
-        }
-    }
-
+    const f32x4 s[2] = {raw.s[0], raw.s[1]};
     // ---- online softmax in the log2 domain.  The raw scores are compared first and scaled inside the
     // exponent's fused multiply-add (the scale is positive); only a unit that reaches past t1, the last
     // of a sequence at most, spends instructions on masking.
@@ -293,27 +203,17 @@ __device__ __forceinline__ bf16x8 softmax_unit(WaveState& st, const QFrags<BITS>
 
     bf16x8 pf;
     float psum = 0.f;
-    if (FP8) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            // the value scale rides on the weight; the normaliser sums the unscaled weight
-            const float p = fast_exp2(__builtin_fmaf(sv[j], scale_log2e, -m_safe));
-            pf[j] = (__bf16)(p * vsc[j >> 2][j & 3]);
-            psum += p;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; j += 2) {
-            // normalise by the sum of the rounded weights actually multiplied into V
-            const float p0 = fast_exp2(__builtin_fmaf(sv[j], scale_log2e, -m_safe));
-            const float p1 = fast_exp2(__builtin_fmaf(sv[j + 1], scale_log2e, -m_safe));
-            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-            const bf16x2 pb = {(__bf16)p0, (__bf16)p1};
-            pf[j] = pb[0];
-            pf[j + 1] = pb[1];
-            const uint32_t bits = __builtin_bit_cast(uint32_t, pb);
-            psum += __uint_as_float(bits << 16) + __uint_as_float(bits & 0xFFFF0000u);
-        }
+    for (int j = 0; j < 8; j += 2) {
+        // normalise by the sum of the rounded weights actually multiplied into V
+        const float p0 = fast_exp2(__builtin_fmaf(sv[j], scale_log2e, -m_safe));
+        const float p1 = fast_exp2(__builtin_fmaf(sv[j + 1], scale_log2e, -m_safe));
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        const bf16x2 pb = {(__bf16)p0, (__bf16)p1};
+        pf[j] = pb[0];
+        pf[j + 1] = pb[1];
+        const uint32_t bits = __builtin_bit_cast(uint32_t, pb);
+        psum += __uint_as_float(bits << 16) + __uint_as_float(bits & 0xFFFF0000u);
     }
     st.l = st.l * alpha + psum;
 
@@ -324,66 +224,20 @@ __device__ __forceinline__ bf16x8 softmax_unit(WaveState& st, const QFrags<BITS>
     return pf;
 }
 
-// Scores and softmax of a unit in one go.
-template <int BITS>
-__device__ __forceinline__ bf16x8 score_unit(WaveState& st, const QFrags<BITS>& q, lds_ptr_t lds_base, int kbase,
-                                             int unit_t0, int t1, float scale_log2e, int n, int g,
-                                             int kscale_off, int vscale_off)
-{
-    const RawScores raw = qk_unit<BITS>(q, lds_base, kbase, n, g);
-    return softmax_unit<BITS>(st, q, raw, lds_base, unit_t0, t1, scale_log2e, g, kscale_off, vscale_off);
-}
-
 // Second half of a unit: O^T += V^T P^T over the unit's 32 tokens.
-//   BITS = 16 (bf16 cache, rows written by direct loads): 512-byte rows, 32-byte chunk c of row r at c ^ (r & 15).
-//   BITS = 8 / 4 (rows written from registers): rows kPaddedVRow = 544 bytes apart.  The 32 bytes of padding shift
-//                  consecutive rows by eight banks, which spreads a transposing read (4 rows x 32 bytes per 16 lanes,
-//                  8 rows per half wave) over all 64 banks as the XOR does, and every operand address is then one
-//                  lane register plus a compile-time offset.  Within a row the 16-byte pieces are placed so that the
-//                  lanes of one 16-byte store instruction (store_tile in decode_lowbit_kernel) spread over the banks
-//                  whether the hardware takes them 8 or 16 at a time; in the plain order they collide two by two:
-//                    8 bit: a thread owns the 32-byte chunk c of a row; its two 16-byte halves are swapped when
-//                           bits 2 and 3 of c differ (chunks 4..11);
-//                    4 bit: a thread owns the 64-byte group c of four pieces; piece w sits at position
-//                           (w + (c >> 1)) & 3 of the group.
-//                  A reader knows the chunk (db) at compile time, so undoing this costs it lane registers (one more
-//                  for 8 bit, three for 4 bit) and no instruction.
-constexpr int kPaddedVRow = 544;
-constexpr int kPaddedVUnitBytes = kUnitTokens * kPaddedVRow;      // 17408
-__host__ __device__ constexpr bool padded_v_halves_swapped(int chunk32) { return (((chunk32 >> 2) ^ (chunk32 >> 3)) & 1) != 0; }
-__host__ __device__ constexpr int padded_v_rotation(int group64) { return (group64 >> 1) & 3; }
-template <int BITS>
 __device__ __forceinline__ void pv_unit(WaveState& st, lds_ptr_t lds_base, int vbase, const bf16x8& pf, int n, int g)
 {
-    constexpr bool PADDED = BITS != 16;
     const int v_row = 4 * g + (n >> 2);                 // V: row within a 16-token block (= swizzle key)
-    const int piece = n & 3;                            // which 8 bytes of the 32-byte chunk this lane supplies
-    const int v_lane_off = v_row * (PADDED ? kPaddedVRow : 512) + (piece << 3);
-    // 8 bit: [1] = halves swapped.  4 bit: [k] = the chunk's first piece sits at position k of its 64-byte group
-    // (offsets relative to the group).
-    int v_lane_alt[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        v_lane_alt[k] = BITS == 8 ? (k == 1 ? v_lane_off ^ 16 : v_lane_off)
-                                  : v_row * kPaddedVRow + 16 * ((k + (piece >> 1)) & 3) + 8 * (piece & 1);
+    const int v_lane_off = v_row * 512 + ((n & 3) << 3);   // (n & 3: which 8 bytes of the 32-byte chunk this lane supplies)
     union VFrag { bf16x8 v; s16x4 h[2]; };
     auto read_v = [&](VFrag& f, int db) {
-        int lane_off = v_lane_off, place = db << 5;
-        if (BITS == 8) lane_off = v_lane_alt[padded_v_halves_swapped(db) ? 1 : 0];
-        if (BITS == 4) {
-            lane_off = v_lane_alt[(2 * (db & 1) + padded_v_rotation(db >> 1)) & 3];
-            place = (db >> 1) << 6;
-        }
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
-            const int off = PADDED ? vbase + tb * 16 * kPaddedVRow + lane_off + place
-                                   : vbase + tb * 8192 + v_lane_off + ((db ^ v_row) << 5);
-            f.h[tb] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_AT(s16x4, lds_base, off));
-        }
+        for (int tb = 0; tb < 2; ++tb)
+            f.h[tb] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_AT(s16x4, lds_base, vbase + tb * 8192 + v_lane_off + ((db ^ v_row) << 5)));
     };
     // The operands of kAhead output blocks are on their way while one block is multiplied: an LDS read takes
     // several times as long as the MFMA it feeds, and a wave has only one other wave on its SIMD to hide it.
-    constexpr int kAhead = PADDED ? 4 : 2;
+    constexpr int kAhead = 2;
     VFrag f[kAhead];
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) read_v(f[i], i);
@@ -396,13 +250,12 @@ __device__ __forceinline__ void pv_unit(WaveState& st, lds_ptr_t lds_base, int v
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int BITS>
-__device__ __forceinline__ void process_unit(WaveState& st, const QFrags<BITS>& q, lds_ptr_t lds_base, int kbase,
-                                             int vbase, int unit_t0, int t1, float scale_log2e, int n, int g,
-                                             int kscale_off, int vscale_off)
+__device__ __forceinline__ void process_unit(WaveState& st, const QFrags& q, lds_ptr_t lds_base, int kbase, int vbase, int unit_t0,
+                                             int t1, float scale_log2e, int n, int g)
 {
-    const bf16x8 pf = score_unit<BITS>(st, q, lds_base, kbase, unit_t0, t1, scale_log2e, n, g, kscale_off, vscale_off);
-    pv_unit<BITS>(st, lds_base, vbase, pf, n, g);
+    const RawScores raw = qk_unit(q, lds_base, kbase, n, g);
+    const bf16x8 pf = softmax_unit(st, raw, unit_t0, t1, scale_log2e, g);
+    pv_unit(st, lds_base, vbase, pf, n, g);
 }
 
 // ---- One 32-token unit for NT query tokens held by one wave (the one-pass kernel for three and four query
@@ -426,7 +279,7 @@ __device__ __forceinline__ void mfma_bf16_into_vgprs(f32x4& acc, const bf16x8& a
     asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
 template <int NT>
-__device__ __forceinline__ bool process_unit_multi(WaveState (&st)[NT], const QFrags<16> (&q)[NT], lds_ptr_t lds_base, int kbase,
+__device__ __forceinline__ bool process_unit_multi(WaveState (&st)[NT], const QFrags (&q)[NT], lds_ptr_t lds_base, int kbase,
                                                    int vbase, int unit_t0, const int (&t1)[NT], float scale_log2e, int n, int g,
                                                    float (&m_wanted)[NT])
 {
@@ -616,9 +469,29 @@ __device__ __forceinline__ void finish_segment_two(WaveState& st, const AttnArgs
     }
 }
 
+// Page id of the tile that starts at token tile_t0 (paged cache only).  Looked up one tile ahead
+// of its use so that the table read is never on the critical path of issuing a tile's loads.
+template <bool PAGED>
+__device__ __forceinline__ int lookup_page(const AttnArgs& a, int b, int tile_t0)
+{
+    // read through the constant address space: the table is not written while the kernel runs, and a
+    // uniform index then makes this a scalar load, which the vector-memory waits do not have to cover
+    typedef const __attribute__((address_space(4))) int32_t* const_table_t;
+    if (!PAGED) return 0;
+    const int page = ((const_table_t)a.block_table)[(size_t)b * a.max_blocks_per_seq + tile_t0 / kPage];
+    return page < 0 ? 0 : (page >= a.n_pages ? a.n_pages - 1 : page);      // a bad id reads a wrong page, never outside the pool
+}
+
+template <bool PAGED>
+__device__ __forceinline__ int64_t tile_row0(const AttnArgs& a, int b, int tile_t0, int page)
+{
+    return PAGED ? (int64_t)page * kPage : (int64_t)b * a.seq_stride_tokens + tile_t0;
+}
+
 __device__ __forceinline__ int clamped_len(const AttnArgs& a, int b)
 {
-    const int L = a.seq_lens[b];
+    // (constant address space: not written while the kernel runs, and a uniform index makes it a scalar load)
+    const int L = ((const __attribute__((address_space(4))) int32_t*)a.seq_lens)[b];
     return L < 0 ? 0 : (L > a.max_seq_len_hint ? a.max_seq_len_hint : L);
 }
 
@@ -636,21 +509,26 @@ __device__ __forceinline__ int clamped_len(const AttnArgs& a, int b)
 // workgroup holding a sequence's first tile records (first slot, number of partials) for the
 // merge; a sequence held by one workgroup is written finally and needs no merge.  Sequences
 // without tokens are zero-filled by the merge kernel.
-constexpr int kSchedLdsOffset = 2 * 2 * kUnitBytes + 1024;                // behind both kernels' tile memory
-constexpr int kSchedTotalsOffset = kSchedLdsOffset + (kMaxBalancedBatch + 1) * 4 + 12;   // 8 wave totals
-constexpr int kSchedFoundOffset = kSchedTotalsOffset + 8 * 4;                           // result of the search
-constexpr int kSchedRemOffset = kSchedFoundOffset + 16;     // per sequence: tokens in its last tile, minus one (a byte)
-constexpr int kSchedLdsBytes = kSchedRemOffset + kMaxBalancedBatch - kSchedLdsOffset;
-constexpr int kAttnLdsTotal = kSchedLdsOffset + kSchedLdsBytes;
+//
+// LDS of the schedule, from a kernel-given offset `base` on: the staged lengths of batches of up to 512 sequences, eight
+// wave totals and the result of the search of larger ones.
+constexpr int kSchedTotals = 2048;
+constexpr int kSchedFound = kSchedTotals + 8 * 4;
+constexpr int kSchedLdsBytes = kSchedFound + 16;
+
+constexpr int kSlotBytes = 2 * kUnitBytes;            // one 64-token tile: two unit images
+// LDS of the bf16 kernels (and, from kBf16SchedOffset on, of short_lowbit_kernel): two tile slots, a KB for the per-head (m, l) exchanged at the end of a segment, the
+// schedule, and the restart flag of the multi-token kernel
+constexpr int kBf16SchedOffset = 2 * kSlotBytes + 1024;
+constexpr int kBf16RestartFlag = kBf16SchedOffset + kSchedLdsBytes;
+constexpr int kBf16LdsBytes = kBf16RestartFlag + 16;
 
 struct Schedule {
-    int lo, hi;         // balanced: my tile range; fixed: hi > lo while my one segment is still to do
+    int lo, hi;         // balanced: my tile range (lo moves on as segments are handed out); fixed: hi > lo while my one segment is still to do
     int n_tiles_all;    // N
     int n_wgs;          // G: workgroups that have a range (min of the grid size and N)
-    int my_lo;          // start of my range (lo moves on as segments are handed out)
-    bool first_known;   // the first segment's sequence is described below (no table lookup needed)
-    int first_seq0, first_seq1, first_len;
-    int b;              // next sequence to look at
+    int my_lo;          // start of my range
+    int b, seq0, len;   // the sequence that lo may fall into, the tiles before it, and its (clamped) length
 };
 
 // floor(a / d) for 32-bit operands without the long emulated integer division (some hundred scalar
@@ -670,10 +548,16 @@ __device__ __forceinline__ int scaled_floor(int x, int N, int G)
     if (N < (1 << 20) && x <= (1 << 11)) return (int)div_floor_u32((unsigned)x * (unsigned)N, (unsigned)G);
     return (int)((unsigned long long)x * (unsigned long long)N / (unsigned long long)G);
 }
+// ((t + 1) * G - 1) / N: at most G <= 4096, so a double-precision estimate is off by at most one whatever the size of the product.
 __device__ __forceinline__ int wg_of_tile(int t, int G, int N)
 {
-    if (N < (1 << 20) && G <= (1 << 11)) return (int)div_floor_u32(((unsigned)t + 1u) * (unsigned)G - 1u, (unsigned)N);
-    return (int)((((unsigned long long)t + 1ull) * (unsigned long long)G - 1ull) / (unsigned long long)N);
+    asm volatile("" : "+s"(N));                       // (formed where it is used, once per sequence, not ahead of the segment loop)
+    const unsigned long long a = ((unsigned long long)t + 1ull) * (unsigned)G - 1ull;
+    unsigned q = (unsigned)((double)a * __builtin_amdgcn_rcp((double)N));
+    const unsigned long long prod = (unsigned long long)q * (unsigned)N;
+    if (prod > a) --q;
+    else if (prod + (unsigned)N <= a) ++q;
+    return (int)q;
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave with data-parallel-primitive moves: shifts by
@@ -703,26 +587,24 @@ __device__ __forceinline__ int range_index()
 
 // All threads of the workgroup call this; the values returned are the same in every thread.
 //
-// Batches of up to 512 sequences: every wave scans the whole batch by itself (eight lengths per
-// lane at most), so the way to a workgroup's first segment crosses no barrier and no LDS; wave 0
-// also leaves the tables in LDS for the later segments, which are requested only after the
-// barriers of the first one.  Larger batches: one cooperative scan through LDS.
+// Batches of up to 512 sequences: every wave scans the whole batch by itself (eight lengths per lane at most), so the way
+// to a workgroup's first segment crosses no barrier.  Larger batches: one cooperative scan, a run of consecutive
+// sequences per thread.  Only the first sequence of a range is searched for; from there the lengths are read on as the segments
+// are handed out.
 constexpr int kWaveScanChunks = 8;
 // The lengths of such a batch reach the waves through LDS: every wave copies seq_lens[0 .. B) there with direct
 // loads (all waves write the same bytes to the same place, so a wave that has waited for its own loads has the
 // lengths without a barrier).  Direct loads are counted like every vector-memory operation but wait for nothing
 // themselves, so a kernel can ask for the lengths, then for its first tile, and work the schedule out as soon as
-// the lengths -- the older loads -- are there: stage_lengths(), further loads, schedule_begin(.., loads issued
-// since).  The staging area is the part of the prefix-sum table that only larger batches use.
-constexpr int kSchedStagedLensOffset = kSchedLdsOffset + 8192;
-static_assert(kSchedStagedLensOffset >= kSchedLdsOffset + (kWaveScanChunks * 64 + 1) * 4 &&
-              kSchedStagedLensOffset + kWaveScanChunks * 256 <= kSchedTotalsOffset, "staged lengths lie in the unused part of the table");
+// the lengths -- the older loads -- are there: stage_lengths(), further loads, staged_lengths(.., loads issued
+// since).
+static_assert(kWaveScanChunks * 256 <= kSchedTotals, "staged lengths");
 __device__ __forceinline__ bool lengths_are_staged(const AttnArgs& a) { return a.n_wgs != 0 && a.B <= kWaveScanChunks * 64; }
-__device__ __forceinline__ void stage_lengths(const AttnArgs& a, lds_ptr_t lds_base)
+__device__ __forceinline__ void stage_lengths(const AttnArgs& a, lds_ptr_t lds_base, int base)
 {
     if (!lengths_are_staged(a)) return;
     const int lane = threadIdx.x & 63;
-    const uint32_t dst = (uint32_t)(uintptr_t)lds_base + kSchedStagedLensOffset;
+    const uint32_t dst = (uint32_t)(uintptr_t)lds_base + base;
 #pragma unroll
     for (int c = 0; c < kWaveScanChunks; ++c)
         if (c * 64 < a.B) {
@@ -730,26 +612,39 @@ __device__ __forceinline__ void stage_lengths(const AttnArgs& a, lds_ptr_t lds_b
             load_to_lds_4B(a.seq_lens, (uint32_t)i * 4u, dst + c * 256);
         }
 }
-// later_loads: vector-memory operations this wave has issued since stage_lengths (0 or 8: a tile)
-__device__ __forceinline__ Schedule schedule_begin(const AttnArgs& a, lds_ptr_t lds_base, int later_loads = 0)
+// The same lengths in registers: lane l of a wave holds those of sequences 64c + l.
+struct Lengths { int v[kWaveScanChunks]; };
+// LATER: vector-memory operations this wave has issued since stage_lengths when `later` (a tile asked for ahead)
+template <int LATER>
+__device__ __forceinline__ void staged_lengths(const AttnArgs& a, lds_ptr_t lds_base, int base, bool later, Lengths& lens)
+{
+    if (!lengths_are_staged(a)) return;
+    // the staged lengths have landed once only the loads issued after them are outstanding
+    if (later) wait_vmem_but<LATER>();
+    else       wait_vmem_but<0>();
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int c = 0; c < kWaveScanChunks; ++c) {
+        lens.v[c] = 0;
+        if (c * 64 < a.B) lens.v[c] = *LDS_AT(int, lds_base, base + (c * 64 + lane) * 4);
+    }
+}
+template <int THREADS>
+__device__ __forceinline__ Schedule schedule_begin(const AttnArgs& a, lds_ptr_t lds_base, int base, const Lengths& lens)
 {
     Schedule s;
-    s.first_known = false;
-    s.first_seq0 = s.first_seq1 = s.first_len = 0;
-    if (a.n_wgs == 0) { s.lo = s.my_lo = 0; s.hi = 1; s.n_tiles_all = 0; s.n_wgs = 0; s.b = 0; return s; }
+    s.b = s.seq0 = s.len = s.n_tiles_all = s.n_wgs = s.lo = s.my_lo = 0;
+    s.hi = 1;
+    if (a.n_wgs == 0) return s;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
 
     if (a.B <= kWaveScanChunks * 64) {
-        // the staged lengths have landed once only the loads issued after them are outstanding
-        if (later_loads == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else                  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         int len[kWaveScanChunks], p1[kWaveScanChunks];
 #pragma unroll
         for (int c = 0; c < kWaveScanChunks; ++c) {
             const int i = c * 64 + lane;
-            int L = 0;
-            if (c * 64 < a.B && i < a.B) L = *LDS_AT(int, lds_base, kSchedStagedLensOffset + i * 4);
+            const int L = i < a.B ? lens.v[c] : 0;
             len[c] = L < 0 ? 0 : (L > a.max_seq_len_hint ? a.max_seq_len_hint : L);
         }
         int N = 0;
@@ -762,88 +657,70 @@ __device__ __forceinline__ Schedule schedule_begin(const AttnArgs& a, lds_ptr_t 
                 N += __builtin_amdgcn_readlane(incl, 63);
             }
         }
-        if (wave == 0) {
-            if (lane == 0) *LDS_AT(int, lds_base, kSchedLdsOffset) = 0;
-#pragma unroll
-            for (int c = 0; c < kWaveScanChunks; ++c) {
-                const int i = c * 64 + lane;
-                if (i < a.B) {
-                    *LDS_AT(int, lds_base, kSchedLdsOffset + (i + 1) * 4) = p1[c];
-                    *LDS_AT(unsigned char, lds_base, kSchedRemOffset + i) = (unsigned char)((len[c] - 1) & (kTile - 1));
-                }
-            }
-        }
         const int G = a.n_wgs < N ? a.n_wgs : N;      // with fewer tiles than workgroups the last ones idle
         s.n_tiles_all = N;
         s.n_wgs = G;
-        if (range_index() >= G) { s.lo = s.hi = s.b = s.my_lo = 0; return s; }
+        if (range_index() >= G) { s.lo = s.hi = 0; return s; }
         s.lo = s.my_lo = __builtin_amdgcn_readfirstlane(scaled_floor(range_index(), N, G));
         s.hi = __builtin_amdgcn_readfirstlane(scaled_floor(range_index() + 1, N, G));
-        s.b = 0;
 #pragma unroll
         for (int c = 0; c < kWaveScanChunks; ++c) {
+            if (c * 64 >= a.B) break;
             const int x = (len[c] + kTile - 1) / kTile;
             const unsigned long long hit = __ballot(p1[c] - x <= s.lo && s.lo < p1[c]);   // at most one lane of one chunk
             if (hit) {
                 const int src = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
                 s.b = c * 64 + src;
-                s.first_seq1 = __builtin_amdgcn_readlane(p1[c], src);
-                s.first_seq0 = s.first_seq1 - __builtin_amdgcn_readlane(x, src);
-                s.first_len = __builtin_amdgcn_readlane(len[c], src);
-                s.first_known = true;
+                s.seq0 = __builtin_amdgcn_readlane(p1[c], src) - __builtin_amdgcn_readlane(x, src);
+                s.len = __builtin_amdgcn_readlane(len[c], src);
             }
         }
         return s;
     }
 
-    constexpr int totals = kSchedTotalsOffset;
-    constexpr int found = kSchedFoundOffset;
-    if (threadIdx.x == 0) *LDS_AT(int, lds_base, kSchedLdsOffset) = 0;
-    int carry = 0;
-    for (int base = 0; base < a.B; base += kAttnThreads) {
-        const int i = base + threadIdx.x;
-        const int len = i < a.B ? clamped_len(a, i) : 0;
-        const int x = (len + kTile - 1) / kTile;
-        if (i < a.B) *LDS_AT(unsigned char, lds_base, kSchedRemOffset + i) = (unsigned char)((len - 1) & (kTile - 1));
-        const int incl = wave_inclusive_scan(x);
-        if (lane == 63) *LDS_AT(int, lds_base, totals + wave * 4) = incl;
-        __syncthreads();
-        int before = carry, all = 0;
+    // thread t scans sequences run*t .. run*t + run - 1
+    const int run = (a.B + THREADS - 1) / THREADS;
+    const int first = run * (int)threadIdx.x;
+    int mine = 0;
+    for (int i = first; i < first + run && i < a.B; ++i) mine += (clamped_len(a, i) + kTile - 1) / kTile;
+    const int incl = wave_inclusive_scan(mine);
+    if (lane == 63) *LDS_AT(int, lds_base, base + kSchedTotals + wave * 4) = incl;
+    __syncthreads();
+    int before = incl - mine, N = 0;
 #pragma unroll
-        for (int w = 0; w < kAttnThreads / 64; ++w) {
-            const int tw = *LDS_AT(int, lds_base, totals + w * 4);
-            all += tw;
-            if (w < wave) before += tw;
-        }
-        if (i < a.B) *LDS_AT(int, lds_base, kSchedLdsOffset + (i + 1) * 4) = before + incl;    // P[i + 1]
-        carry += all;
-        __syncthreads();
+    for (int w = 0; w < THREADS / 64; ++w) {
+        const int tw = *LDS_AT(int, lds_base, base + kSchedTotals + w * 4);
+        N += tw;
+        if (w < wave) before += tw;
     }
-    const int N = carry;
     const int G = a.n_wgs < N ? a.n_wgs : N;
     s.n_tiles_all = __builtin_amdgcn_readfirstlane(N);
     s.n_wgs = __builtin_amdgcn_readfirstlane(G);
-    if (range_index() >= G) { s.lo = s.hi = s.b = s.my_lo = 0; return s; }
+    if (range_index() >= G) { s.lo = s.hi = 0; return s; }
     s.lo = s.my_lo = __builtin_amdgcn_readfirstlane(scaled_floor(range_index(), N, G));
     s.hi = __builtin_amdgcn_readfirstlane(scaled_floor(range_index() + 1, N, G));
-    for (int base = 0; base < a.B; base += kAttnThreads) {
-        const int i = base + threadIdx.x;
-        if (i < a.B) {
-            const int p0 = *LDS_AT(int, lds_base, kSchedLdsOffset + i * 4);
-            const int p1 = *LDS_AT(int, lds_base, kSchedLdsOffset + (i + 1) * 4);
-            if (p0 <= s.lo && s.lo < p1) *LDS_AT(int, lds_base, found) = i;
+    if (before <= s.lo && s.lo < before + mine)                       // exactly one thread
+        for (int i = first, at = before; i < first + run && i < a.B; ++i) {
+            const int len = clamped_len(a, i);
+            const int x = (len + kTile - 1) / kTile;
+            if (at <= s.lo && s.lo < at + x) {
+                *LDS_AT(int, lds_base, base + kSchedFound) = i;
+                *LDS_AT(int, lds_base, base + kSchedFound + 4) = at;
+                *LDS_AT(int, lds_base, base + kSchedFound + 8) = len;
+            }
+            at += x;
         }
-    }
     __syncthreads();
-    s.b = __builtin_amdgcn_readfirstlane(*LDS_AT(int, lds_base, found));   // the one sequence with P[b] <= lo < P[b + 1]
+    s.b = __builtin_amdgcn_readfirstlane(*LDS_AT(int, lds_base, base + kSchedFound));   // the one sequence with P[b] <= lo < P[b + 1]
+    s.seq0 = __builtin_amdgcn_readfirstlane(*LDS_AT(int, lds_base, base + kSchedFound + 4));
+    s.len = __builtin_amdgcn_readfirstlane(*LDS_AT(int, lds_base, base + kSchedFound + 8));
     return s;
 }
 
 // Where this workgroup's first tile lies if every sequence has the length of the hint: computed from the
-// launch arguments alone (no device memory is read), with the same arithmetic as the schedule.  Only whole
-// tiles below the hint are named, so that a load of the guessed tile stays inside memory the caller has
-// vouched for (rows below max_seq_len_hint of a sequence below B; paged: a table entry below
-// ceil(hint / 64), clamped into the pool like every other).
+// launch arguments alone (no device memory is read), with the same arithmetic as the schedule.  A load of rows from t0 up
+// to the hint stays inside memory the caller has vouched for (rows below max_seq_len_hint of a sequence below B;
+// paged: a table entry below ceil(hint / 64), clamped into the pool like every other).
 struct FirstTileGuess { int b, t0; bool valid; };
 __device__ __forceinline__ FirstTileGuess guess_first_tile(const AttnArgs& a)
 {
@@ -861,13 +738,14 @@ __device__ __forceinline__ FirstTileGuess guess_first_tile(const AttnArgs& a)
     gs.t0 = (lo - gs.b * T) * kTile;
     gs.b = __builtin_amdgcn_readfirstlane(gs.b);
     gs.t0 = __builtin_amdgcn_readfirstlane(gs.t0);
-    gs.valid = gs.b < a.B && gs.t0 + kTile <= a.max_seq_len_hint;
+    gs.valid = gs.b < a.B && gs.t0 + kTile <= a.max_seq_len_hint;     // whole tiles only
     return gs;
 }
 
 // The next segment of this workgroup, or false when it has none left.  A false return for the very
 // first request of a fixed-split workgroup on an empty sequence has written the zero result.
-__device__ __forceinline__ bool schedule_next(const AttnArgs& a, lds_ptr_t lds_base, Schedule& s, Segment& r)
+template <int THREADS>
+__device__ __forceinline__ bool schedule_next(const AttnArgs& a, Schedule& s, Segment& r)
 {
     if (s.lo >= s.hi) return false;
     if (a.n_wgs == 0) {
@@ -885,25 +763,23 @@ __device__ __forceinline__ bool schedule_next(const AttnArgs& a, lds_ptr_t lds_b
         if (r.t0 >= r.t1) {
             if (split == 0) {
                 float4* o = (float4*)(a.out + (size_t)r.b * kHeads * kHeadDim);
-                for (int i = threadIdx.x; i < kHeads * kHeadDim / 4; i += kAttnThreads) o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int i = threadIdx.x; i < kHeads * kHeadDim / 4; i += THREADS) o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
             return false;
         }
         make_uniform(r);
         return true;
     }
-    int b = s.b, seq0, seq1, L;
-    if (s.first_known) {
-        s.first_known = false;
-        seq0 = s.first_seq0; seq1 = s.first_seq1; L = s.first_len;
-    } else {
-        while (*LDS_AT(int, lds_base, kSchedLdsOffset + (b + 1) * 4) <= s.lo) ++b;     // sequences without tiles
-        seq0 = __builtin_amdgcn_readfirstlane(*LDS_AT(int, lds_base, kSchedLdsOffset + b * 4));
-        seq1 = __builtin_amdgcn_readfirstlane(*LDS_AT(int, lds_base, kSchedLdsOffset + (b + 1) * 4));
-        b = __builtin_amdgcn_readfirstlane(b);
-        const int rem = __builtin_amdgcn_readfirstlane((int)*LDS_AT(unsigned char, lds_base, kSchedRemOffset + b));
-        L = (seq1 - seq0 - 1) * kTile + rem + 1;                      // the sequence's (clamped) length
+    int b = s.b, L = s.len;
+    while (L == 0) {                                                  // sequences without tiles (one with tiles follows: lo < hi)
+        const int lane = threadIdx.x & 63;
+        const int ahead = b + 1 + lane < a.B ? clamped_len(a, b + 1 + lane) : 0;
+        const unsigned long long hit = __ballot(ahead != 0);
+        const int src = hit ? __builtin_ctzll(hit) : 63;
+        b = __builtin_amdgcn_readfirstlane(b + 1 + src);
+        L = __builtin_amdgcn_readlane(ahead, __builtin_amdgcn_readfirstlane(src));
     }
+    const int seq0 = s.seq0, seq1 = seq0 + (L + kTile - 1) / kTile;
     const int end = s.hi < seq1 ? s.hi : seq1;
     r.b = b;
     r.t0 = (s.lo - seq0) * kTile;
@@ -920,7 +796,10 @@ __device__ __forceinline__ bool schedule_next(const AttnArgs& a, lds_ptr_t lds_b
         }
     }
     s.lo = end;
+    s.seq0 = seq1;
     s.b = b + 1;
+    // (asked for now, used when the next segment is: through the constant address space, a scalar load)
+    if (end < s.hi) s.len = clamped_len(a, b + 1);
     make_uniform(r);
     return true;
 }

@@ -1,0 +1,88 @@
+"""The two kernels over the 8-bit and 4-bit caches.  Which one a call takes follows from the tiles per workgroup at the length of
+the hint: a context of few workgroups takes decode_lowbit_kernel for what a context of 256 gives to short_lowbit_kernel.
+
+Tolerance: TOL_FP8 as for every low-bit case; both kernels are also held to 4e-3, from their operands: a weight carries 8
+significant bits (relative error at most 2^-9), the query 8 as well down to 2^-17 of its largest element, and the rows of
+these cases are means over N(0, 1) values whose largest output is at least half their root sum of squared weights."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_19427_amd as mfa
+import paper_2507_19427_amd.workloads as W
+
+import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+TOL = 4e-3
+
+
+def _run(ctx, case, qm, hint):
+    d = U.to_dev
+    if case.paged:
+        out = mfa.mfa_decode_attn_paged_multi(ctx, d(qm), d(case.k_pool), d(case.v_pool), d(case.block_table), d(case.seq_lens), hint,
+                                              d(case.k_scale_pool), d(case.v_scale_pool))
+    else:
+        out = mfa.mfa_decode_attn_multi(ctx, d(qm), d(case.k), d(case.v), d(case.seq_lens), hint, d(case.k_scale), d(case.v_scale))
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+def _oracle(case, qm):
+    q_len = qm.shape[1]
+    outs = []
+    for j in range(q_len):
+        lens = torch.clamp(case.seq_lens - (q_len - 1 - j), min=0).to(torch.int32)
+        outs.append(U.run_oracle(dataclasses.replace(case, q=qm[:, j].contiguous(), seq_lens=lens)))
+    return np.stack(outs, axis=1)
+
+
+def _compare(case, q_len, hint, workgroups, schedule=None):
+    qm = W.make_multi_query(case, q_len, 41) if q_len > 1 else case.q.unsqueeze(1).contiguous()
+    ref = _oracle(case, qm)
+    kw = {} if schedule is None else {"schedule": schedule}
+    for n in workgroups:
+        ctx = mfa.mfa_decode_init(mfa.MfaConfig(max_batch=16, max_seq_len=32768, target_workgroups=n, **kw))
+        print(f"[case] {case.kv_dtype} {q_len} query tokens, {n} workgroups", flush=True)
+        got = _run(ctx, case, qm, hint)
+        err = U.row_normalised_error(got, ref)
+        print(f"   row-normalised max error {err:.3e}", flush=True)
+        assert err <= TOL
+        assert np.array_equal(got, _run(ctx, case, qm, hint))
+        ctx.close()
+
+
+# every remainder of a tile and of a pair of tiles, empty and one-token sequences, and runs long enough for the steady loop
+LENS = [4133, 1, 0, 63, 64, 65, 127, 128, 129, 640, 1500, 2]
+
+
+@pytest.mark.parametrize("q_len", [1, 2, 3])
+@pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
+@pytest.mark.parametrize("paged", [False, True])
+def test_both_kernels_at_the_edges_of_tiles_and_stages(kv_dtype, q_len, paged):
+    if paged:
+        case = W.make_paged_case("lowbit", 61, seq_lens=LENS, kv_dtype=kv_dtype)
+    else:
+        case = W.make_contiguous_case("lowbit", 61, B=len(LENS), S=max(LENS), seq_lens=LENS, kv_dtype=kv_dtype, poison=True)
+    _compare(case, q_len, max(LENS), (256, 7, 1))
+
+
+@pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
+def test_both_kernels_under_the_fixed_schedule(kv_dtype):
+    case = W.make_contiguous_case("lowbitfixed", 62, B=len(LENS), S=max(LENS), seq_lens=LENS, kv_dtype=kv_dtype, poison=True)
+    _compare(case, 1, max(LENS), (256, 12), mfa.MFA_SCHEDULE_FIXED)
+
+
+@pytest.mark.parametrize("q_len", [1, 2])
+@pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
+def test_scores_that_outrun_the_reference_exponent(kv_dtype, q_len):
+    """Tokens whose key scale is raised until their scores lie hundreds above (and below) the rest, so that the segment is streamed
+    again with the maxima it has seen: late in a run of tiles, twice in a row, in the last tile, for one sequence only."""
+    lens = [4000, 900, 130, 2000]
+    case = W.make_contiguous_case("lowbitrestart", 63, B=len(lens), S=4000, seq_lens=lens, kv_dtype=kv_dtype, poison=True)
+    for b, pos, gain in ((0, 3333, 300.0), (1, 77, 100.0), (1, 500, 400.0), (3, 1999, 300.0)):
+        case.k_scale[b, pos] *= gain
+    _compare(case, q_len, 4000, (256, 3, 1))
