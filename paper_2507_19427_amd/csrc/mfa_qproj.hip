@@ -66,9 +66,20 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_stream_kernel(const uint16_
     constexpr int kSubBytes = kSubRows * kRowBytes;       // one strip's part of a stage buffer
     constexpr int kStepsPerStage = kSubRows / 32;
     constexpr int kCols = kColBlocks * NS;                // 16-column blocks of the workgroup
-    const int n0 = blockIdx.x * kStripN * NS;
+    // Groups of strips (the output projection): the workgroups are numbered die by die (workgroup i runs on die i % 8; nothing but speed depends on it): a die's
+    // workgroups then share one or two slices of x, and its lines of W lie side by side (16384 -> 7168: 53.3 -> 50.9 us a call at 64
+    // rows, 70.7 -> 67.1 at 128).  Single strips over a k split (2048 or 512 columns) lose 0.2 .. 0.7 us by it.
+    int strip_group = blockIdx.x, kz = blockIdx.z;
+    const int n_groups = gridDim.x;
+    constexpr bool by_die = NS > 1;
+    if (by_die) {
+        const int n_wgs = n_groups * gridDim.z, id = blockIdx.x + n_groups * blockIdx.z, die = id & 7, rest = n_wgs & 7;
+        const int place = die * (n_wgs >> 3) + (die < rest ? die : rest) + (id >> 3);
+        kz = __builtin_amdgcn_readfirstlane(place / n_groups);
+        strip_group = place - kz * n_groups;
+    }
+    const int n0 = strip_group * kStripN * NS;
     const int m0 = blockIdx.y * 64 * MB;
-    const int kz = blockIdx.z;
     const int k_begin = kz * k_per_split;
     const int k_end = (k_begin + k_per_split < K) ? k_begin + k_per_split : K;
     const int n_stages = (k_end - k_begin + kSubRows - 1) / kSubRows;
@@ -189,7 +200,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_stream_kernel(const uint16_
     // Workgroups walk the stages of their k range starting at different points (strip index modulo
     // the stage count) and wrapping round: at any moment the strips that share an L2 then ask it for
     // different parts of x instead of all for the same lines.
-    const int phase = (int)((blockIdx.x >> 3) % (unsigned)n_stages);   // workgroups 8 apart share an XCD's L2
+    const int phase = (int)((unsigned)(by_die ? strip_group : strip_group >> 3) % (unsigned)n_stages);   // (without a k split, workgroups 8 apart share an L2)
     auto stage_of = [&](int it) { const int s = it + phase; return s < n_stages ? s : s - n_stages; };
     issue_stage(stage_of(0), 0);
     load_x_stage(stage_of(0), 0);
@@ -378,31 +389,47 @@ __global__ __launch_bounds__(kHeadDim) void kv_record_kernel(const float* __rest
 }
 static_assert(kHeadDim == 256, "kv_record_kernel reduces over four waves");
 
-// fp32 [M, K] -> bf16, k-step-major: element (m, k) at ((k/32)*rows_pad + m)*32 + k%32.
+// fp32 [M, K] -> bf16, k-step-major: element (m, k) at ((k/32)*rows_pad + m)*32 + k%32.  A wave takes 16 rows of one k step: reads
+// whole 128-byte lines, writes one contiguous KB.  (A thread per four elements, with a 64-bit division each and 8-byte
+// stores: with the like change to
+// reduce_partials_bf16_kernel a call of 1 .. 16 rows takes 1.3 us less; 64 rows the same.)
 __global__ __launch_bounds__(256) void to_bf16_tiled_kernel(const float* __restrict__ src, __bf16* __restrict__ dst, int M, int K,
                                                             int rows_pad)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;          // over M * K / 4
-    if (i >= (size_t)M * K / 4) return;
-    const int m = (int)(i / (K / 4));
-    const int k = (int)(i % (K / 4)) * 4;
-    const f32x4 v = *(const f32x4*)(src + (size_t)m * K + k);
-    union { __bf16 h[4]; uint2 u; } o;
+    const int lane = threadIdx.x & 63;
+    const int ks = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int m = blockIdx.y * 16 + (lane >> 2);
+    if (ks >= K / 32 || m >= M) return;
+    const int k = 8 * (lane & 3);
+    const f32x4* s = (const f32x4*)(src + (size_t)m * K + 32 * ks + k);
+    const f32x4 lo = s[0], hi = s[1];
+    bf16x8 o;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) o.h[j] = (__bf16)v[j];
-    *(uint2*)(dst + ((size_t)(k >> 5) * rows_pad + m) * 32 + (k & 31)) = o.u;
+    for (int j = 0; j < 4; ++j) { o[j] = (__bf16)lo[j]; o[4 + j] = (__bf16)hi[j]; }
+    *(bf16x8*)(dst + ((size_t)ks * rows_pad + m) * 32 + k) = o;
 }
 
-// y[m][n] = bf16(sum over splits, in split order, of the fp32 partials).
-__global__ __launch_bounds__(256) void reduce_partials_bf16_kernel(const float* __restrict__ parts, __bf16* __restrict__ y, int M, int N,
+// y[m][n] = bf16(sum over splits, in split order, of the fp32 partials); eight splits' loads in flight together.
+__global__ __launch_bounds__(256) void reduce_partials_bf16_kernel(const float* __restrict__ parts, __bf16* __restrict__ y, int N,
                                                                    int split_k, int rows_pad)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;          // over M * N / 4
-    if (i >= (size_t)M * N / 4) return;
-    const int m = (int)(i / (N / 4));
-    const int n = (int)(i % (N / 4)) * 4;
+    const int m = blockIdx.y;
+    const int n = (blockIdx.x * 256 + threadIdx.x) * 4;
+    if (n >= N) return;
+    const float* p = parts + (size_t)m * N + n;
+    const size_t split_stride = (size_t)rows_pad * N;
     f32x4 c = {0.f, 0.f, 0.f, 0.f};
-    for (int z = 0; z < split_k; ++z) c += *(const f32x4*)(parts + ((size_t)z * rows_pad + m) * N + n);
+    for (int z0 = 0; z0 < split_k; z0 += 8) {
+        f32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int z = z0 + u < split_k ? z0 + u : split_k - 1;
+            v[u] = *(const f32x4*)(p + (size_t)z * split_stride);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (z0 + u < split_k) c += v[u];
+    }
     union { __bf16 h[4]; uint2 u; } o;
 #pragma unroll
     for (int j = 0; j < 4; ++j) o.h[j] = (__bf16)c[j];
@@ -543,16 +570,14 @@ hipError_t launch_out_proj(const OutProjArgs& a, hipStream_t stream)
 {
     const int m_blocks = (a.B + kQProjRows - 1) / kQProjRows;
     const int rows_pad = m_blocks * kQProjRows;
-    const size_t n4 = (size_t)a.B * a.n_in / 4;
-    hipLaunchKernelGGL(to_bf16_tiled_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream, a.attn, (__bf16*)a.ws_act,
+    hipLaunchKernelGGL(to_bf16_tiled_kernel, dim3((a.n_in / 32 + 3) / 4, (a.B + 15) / 16), dim3(256), 0, stream, a.attn, (__bf16*)a.ws_act,
                        a.B, a.n_in, rows_pad);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     e = launch_gemm<false, true>(a.ws_act, a.w_o, a.ws_c, a.B, a.n_in, a.d_model, a.plan, a.plan.split_k, rows_pad, stream);
     if (e != hipSuccess) return e;
-    const size_t o4 = (size_t)a.B * a.d_model / 4;
-    hipLaunchKernelGGL(reduce_partials_bf16_kernel, dim3((unsigned)((o4 + 255) / 256)), dim3(256), 0, stream, (const float*)a.ws_c,
-                       (__bf16*)a.y, a.B, a.d_model, a.plan.split_k, rows_pad);
+    hipLaunchKernelGGL(reduce_partials_bf16_kernel, dim3((a.d_model / 4 + 255) / 256, a.B), dim3(256), 0, stream, (const float*)a.ws_c,
+                       (__bf16*)a.y, a.d_model, a.plan.split_k, rows_pad);
     return hipGetLastError();
 }
 
