@@ -1,7 +1,7 @@
 """Host-side checks of the compiled attention kernels (no GPU needed).
 
-The kernels for the 8-bit and 4-bit caches load cache data with inline-assembly loads (to LDS) and wait for them with
-inline-assembly s_waitcnt, counted where several stages are in flight (left to the compiler the wait would drain the
+The attention kernels load cache data with inline-assembly loads (to LDS; short_lowbit_kernel also to registers) and wait for them
+with inline-assembly s_waitcnt, counted where several stages are in flight (left to the compiler the wait would drain the
 pipeline every stage).  The compiler does not know about these loads.  So the build checks the machine code it has
 just produced:
 
@@ -21,12 +21,22 @@ import re
 # with two query tokens keeps four.)
 PIPELINE_KERNELS = [(paged, q_len, bits) for bits, q_len in ((8, 2), (4, 1)) for paged in (0, 1)]
 OPS_PER_STEP = {8: 9, 4: 9}
+# short_lowbit_kernel loads to registers in two unrolled steps, each of which waits for all but the youngest step's loads.
+SHORT_OPS_PER_STEP = {8: 5, 4: 3}
 
 _REG = re.compile(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b")
 
 
 def lowbit_kernel_name(paged, q_len, bits):
     return f"_ZN3mfa20decode_lowbit_kernelILb{paged}ELi{q_len}ELi{bits}EEEvNS_8AttnArgsE"
+
+
+def short_lowbit_kernel_name(paged, q_len, bits):
+    return f"_ZN3mfa19short_lowbit_kernelILb{paged}ELi{q_len}ELi{bits}EEEvNS_8AttnArgsE"
+
+
+def multi_kernel_name(paged, q_len):
+    return f"_ZN3mfa24decode_bf16_multi_kernelILb{paged}ELi{q_len}EEEvNS_8AttnArgsE"
 
 
 def kernel_body(text, mangled):
@@ -45,7 +55,7 @@ def registers_named(operand_text):
     return regs
 
 
-def check_pipeline(lines, ops_per_step=5):
+def check_pipeline(lines, ops_per_step=5, steps=1):
     """Raises AssertionError when the register pipeline of a kernel body (lines of assembly) is disturbed."""
     in_asm = False
     queue = []                 # vector-memory operations in issue order: the registers each one writes
@@ -96,7 +106,7 @@ def check_pipeline(lines, ops_per_step=5):
             continue
         touched = registers_named(rest)
         assert not (touched & in_flight()), f"in-flight register touched before its wait: {t}"
-    assert partial_waits >= 1, "the loop waits for all but the youngest stage's loads"
+    assert partial_waits >= steps, "every unrolled step waits for all but the youngest stage's loads"
 
 
 def check_no_compiler_wait_in_loop(lines, mfmas=32):
@@ -135,22 +145,22 @@ def scratch_bytes(text):
 
 def check_attention_asm(text):
     """All checks on the assembly text of mfa_attn.hip.  Raises AssertionError naming the first violation."""
-    for paged, q_len, bits in PIPELINE_KERNELS:
-        name = lowbit_kernel_name(paged, q_len, bits)
+    checks = [(lowbit_kernel_name(*k), check_pipeline, (OPS_PER_STEP[k[2]],)) for k in PIPELINE_KERNELS]
+    for paged in (0, 1):
+        for q_len in (1, 2):
+            for bits in (8, 4):
+                checks.append((lowbit_kernel_name(paged, q_len, bits), check_no_compiler_wait_in_loop, (32,)))
+                checks.append((short_lowbit_kernel_name(paged, q_len, bits), check_pipeline, (SHORT_OPS_PER_STEP[bits], 2)))
+            checks.append((multi_kernel_name(paged, q_len + 2), check_no_compiler_wait_in_loop, (64,)))
+    for name, check, args in checks:
         try:
-            check_pipeline(kernel_body(text, name), OPS_PER_STEP[bits])
+            check(kernel_body(text, name), *args)
         except AssertionError as e:
             raise AssertionError(f"{name}: {e}") from None
-    for bits in (8, 4):
-        for q_len in (1, 2):
-            for paged in (0, 1):
-                name = lowbit_kernel_name(paged, q_len, bits)
-                try:
-                    check_no_compiler_wait_in_loop(kernel_body(text, name))
-                except AssertionError as e:
-                    raise AssertionError(f"{name}: {e}") from None
     scratch = scratch_bytes(text)
     decode = {k: v for k, v in scratch.items() if "decode_" in k}
     assert len(decode) == 16, f"expected 16 attention kernels, found {sorted(decode)}"
-    for name, nbytes in decode.items():
+    short = {k: v for k, v in scratch.items() if "short_" in k}
+    assert len(short) == 10, f"expected 10 attention kernels for little work, found {sorted(short)}"
+    for name, nbytes in {**decode, **short}.items():
         assert nbytes == 0, f"{name} uses {nbytes} bytes of scratch per lane (register spills)"

@@ -21,6 +21,7 @@
 #include <hip/hip_ext.h>
 
 #include "mfa_lowbit_short.hpp"
+#include "mfa_multi_short.hpp"
 
 namespace mfa {
 
@@ -148,142 +149,6 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
         if (more) {
             r = r_next;
             slot0 = last_slot ^ 1;
-        }
-    }
-}
-
-// ---- Three or four query tokens per sequence in ONE pass over a bf16 cache (Section 5.2: the new tokens of a
-// multi-token step share the cache read, which multiplies the arithmetic per byte by their number).
-// A workgroup is four waves, one per SIMD, wave = head group: a wave holds all NT query tokens of its 16 heads
-// (NT x 32 registers of query fragments, NT x 64 accumulator registers: only one wave fits a SIMD's register
-// file) and works through both units of every tile; key and value fragments read from LDS are shared by the NT
-// tokens (process_unit_multi).  Same tiles, same two-slot ring and same schedule as decode_bf16_kernel; each wave
-// brings 16 rows of a tile.  Query token j attends to the first len - (q_len - 1 - j) cached tokens.  Batches of
-// at most 512 sequences (every wave works the schedule out by itself).
-constexpr int kMultiThreads = 256;
-template <bool PAGED, int NT>
-__global__ __launch_bounds__(kMultiThreads) void decode_bf16_multi_kernel(AttnArgs a)
-{
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    const lds_ptr_t lds_base = (lds_ptr_t)smem;
-    const uint32_t lds_addr0 = (uint32_t)(uintptr_t)lds_base;
-
-    const int lane = threadIdx.x & 63;
-    const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 15;
-    const int g = lane >> 4;
-
-    auto issue_tile = [&](const Segment& sg, int tile, int slot, int page) {
-        const int tile_t0 = sg.t0 + tile * kTile;
-        const int64_t row0 = tile_row0<PAGED>(a, sg.b, tile_t0, page);
-        const unsigned char* k_tile = (const unsigned char*)a.k + row0 * 512;
-        const unsigned char* v_tile = (const unsigned char*)a.v + row0 * 512;
-        int lane_now = lane;                                          // (the lane's offsets are formed here, per tile, not
-        asm volatile("" : "+v"(lane_now));                            // ahead of the tile loop and kept in scarce registers)
-        const int p16 = lane_now & 31;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int row = 16 * wq + 2 * u + (lane_now >> 5);        // row of the tile this lane fills
-            int in_tile = row;
-            if (tile_t0 + row > sg.t1 - 1) in_tile = sg.t1 - 1 - tile_t0;
-            const int key = row & 15;
-            const int ck = p16 ^ key;
-            const int cv = ((((p16 >> 1) ^ key) << 1) | (p16 & 1));
-            const int first_row = 16 * wq + 2 * u;                     // wave-uniform
-            const uint32_t dst = lds_addr0 + slot * kSlotBytes + (first_row >> 5) * kUnitBytes + (first_row & 31) * 512;
-            load_to_lds_16B(k_tile, (uint32_t)(in_tile * 512 + ck * 16), dst);
-            load_to_lds_16B(v_tile, (uint32_t)(in_tile * 512 + cv * 16), dst + kUnitVOffset);
-        }
-    };
-    QFrags q[NT];
-    auto load_q = [&](const Segment& sg) {
-        int lane_now = lane;                                          // (addresses formed here, once per segment)
-        asm volatile("" : "+v"(lane_now));
-#pragma unroll
-        for (int t = 0; t < NT; ++t) load_q_fragments(q[t].f, a.q, a.q_len * sg.b + a.q0 + t, 16 * wq + (lane_now & 15), lane_now >> 4);
-    };
-
-    // A word of LDS behind the schedule's tables: set by a wave whose unit was refused (a score more than
-    // 2^kFixedReferenceLag above its head's reference exponent), seen by all waves after the next barrier.
-    stage_lengths(a, lds_base, kBf16SchedOffset);
-    Lengths lens;
-    staged_lengths<0>(a, lds_base, kBf16SchedOffset, false, lens);
-    Schedule sched = schedule_begin<kMultiThreads>(a, lds_base, kBf16SchedOffset, lens);
-    Segment r;
-    bool first_segment = true;
-    while (schedule_next<kMultiThreads>(a, sched, r)) {
-        if (!first_segment) __syncthreads();          // every wave is done with the previous segment's tiles
-        first_segment = false;
-        // Every segment leaves a partial result, also one that covers its whole sequence: partials are stored
-        // straight from the accumulation registers, while a final result would have to pass all of them through
-        // ordinary registers to be normalised.  The merge kernel normalises (AttnArgs::n_here >= 3).
-        r.final_result = false;
-        load_q(r);
-        int t1_mine[NT];
-        float m_floor[NT];                            // reference exponents handed to the next attempt (-inf: none)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int end_mine = r.len - (a.q_len - 1 - a.q0 - t);
-            t1_mine[t] = r.t1 < end_mine ? r.t1 : end_mine;
-            m_floor[t] = -INFINITY;
-        }
-        WaveState st[NT];
-        // One attempt streams the segment with fixed reference exponents.  If a unit is refused, its wave notes the
-        // exponents it needs, raises the flag and stops computing; at the next barrier all waves see the flag and
-        // the segment is streamed again from its first tile (every attempt ends with a higher reference for some
-        // head, and a reference never exceeds the head's largest score: the attempts end).  Plausible attention
-        // scores never get here; correctness does not depend on that.
-        for (bool again = true; again;) {
-            again = false;
-            if (threadIdx.x == 0) *LDS_AT(int, lds_base, kBf16RestartFlag) = 0;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                init_state(st[t]);
-                st[t].m = m_floor[t];
-            }
-            issue_tile(r, 0, 0, lookup_page<PAGED>(a, r.b, r.t0));
-            int page_next = r.n_tiles > 1 ? lookup_page<PAGED>(a, r.b, r.t0 + kTile) : 0;
-            bool refused = false;
-            for (int it = 0; it < r.n_tiles; ++it) {
-                const int slot = it & 1;
-                wait_vmem_all();
-                __syncthreads();                       // tile it has landed; the flag store of attempt start / of a refusal is visible
-                if (*LDS_AT(int, lds_base, kBf16RestartFlag) != 0) { again = true; break; }
-                if (it + 1 < r.n_tiles) {
-                    issue_tile(r, it + 1, slot ^ 1, page_next);
-                    if (it + 2 < r.n_tiles) page_next = lookup_page<PAGED>(a, r.b, r.t0 + (it + 2) * kTile);
-                }
-                if (refused) continue;
-#pragma unroll 1
-                for (int u = 0; u < 2; ++u) {
-                    const int unit = slot * kSlotBytes + u * kUnitBytes;
-                    float m_wanted[NT];
-                    if (!process_unit_multi<NT>(st, q, lds_base, unit, unit + kUnitVOffset, r.t0 + it * kTile + u * kUnitTokens,
-                                                t1_mine, a.scale_log2e, n, g, m_wanted)) {
-#pragma unroll
-                        for (int t = 0; t < NT; ++t) m_floor[t] = fmaxf(m_floor[t], m_wanted[t]);
-                        if (lane == 0) *LDS_AT(int, lds_base, kBf16RestartFlag) = 1;
-                        refused = true;
-                        break;
-                    }
-                }
-            }
-            if (!again) {
-                // the last tile's refusal (if any) has not met a barrier yet
-                __syncthreads();
-                again = *LDS_AT(int, lds_base, kBf16RestartFlag) != 0;
-            }
-            if (again) {
-                wait_vmem_all();                       // a tile may still be on its way into the ring
-                __syncthreads();                       // every wave has read the flag and left the tile loop
-            }
-        }
-        int lane_now = lane;                          // (the result's addresses are formed here, once per segment)
-        asm volatile("" : "+v"(lane_now));
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            finish_segment_two(st[t], a, r, t, wq, lane_now);
-            __builtin_amdgcn_sched_barrier(0);        // one query token's accumulators at a time through ordinary registers
         }
     }
 }
@@ -461,14 +326,26 @@ AttnKernel attn_kernel(mfa_kv_dtype kv_dtype, bool paged, bool short_work)
     if (kv_dtype == MFA_KV_BF16) return {paged ? (const void*)decode_bf16_kernel<true, QL> : (const void*)decode_bf16_kernel<false, QL>, kAttnThreads, kBf16LdsBytes};
     return kv_dtype == MFA_KV_FP4_E2M1 ? lowbit_kernel<QL, 4>(paged, short_work) : lowbit_kernel<QL, 8>(paged, short_work);
 }
-const void* multi_kernel(int q_len, bool paged)
+AttnKernel multi_kernel(int q_len, bool paged, bool short_work)
 {
-    if (q_len == 3) return paged ? (const void*)decode_bf16_multi_kernel<true, 3> : (const void*)decode_bf16_multi_kernel<false, 3>;
-    return paged ? (const void*)decode_bf16_multi_kernel<true, 4> : (const void*)decode_bf16_multi_kernel<false, 4>;
+    if (short_work) return {paged ? (const void*)short_bf16_multi_kernel<true> : (const void*)short_bf16_multi_kernel<false>, kMultiThreads, kShortMultiLdsBytes};
+    if (q_len == 3) return {paged ? (const void*)decode_bf16_multi_kernel<true, 3> : (const void*)decode_bf16_multi_kernel<false, 3>, kMultiThreads, kMultiLdsBytes};
+    return {paged ? (const void*)decode_bf16_multi_kernel<true, 4> : (const void*)decode_bf16_multi_kernel<false, 4>, kMultiThreads, kMultiLdsBytes};
 }
 
+// 64-token tiles per workgroup at the length of the hint (the host knows no other).
+int64_t tiles_per_workgroup(const AttnArgs& a)
+{
+    const int64_t tiles_per_seq = (a.max_seq_len_hint + kTile - 1) / kTile;
+    return a.n_wgs > 0 ? a.B * tiles_per_seq / a.n_wgs : a.chunk_tokens / kTile;
+}
+// Three query tokens over a bf16 cache: short_bf16_multi_kernel below 16 tiles per workgroup (four tokens: decode_bf16_multi_kernel is never
+// slower).  us per call, short / decode, lengths equal to the hint and drawn from 100 .. hint:
+//   4 tiles  43.7/40.9  45.5/47.0     8 tiles  60.4/51.6  58.9/62.3     16 tiles  94.0/79.3  77.9/73.9
+bool short_multi_work(const AttnArgs& a) { return a.q_len == 3 && tiles_per_workgroup(a) < 16; }
+
 // Which of its two kernels a low-bit cache takes: short_lowbit_kernel below so many 64-token tiles per workgroup, counted at the length of
-// the hint (the host knows no other).  Equal lengths favour decode_lowbit_kernel from 16 tiles on; ragged ones, half the
+// the hint.  Equal lengths favour decode_lowbit_kernel from 16 tiles on; ragged ones, half the
 // hint on average and with a segment boundary in most workgroups, later, and the line lies where they no longer lose.
 // us per call, short / decode, lengths equal to the hint and drawn from 100 .. hint:
 //                                16 tiles                  32 tiles                  48 tiles                    64 tiles
@@ -478,19 +355,17 @@ const void* multi_kernel(int q_len, bool paged)
 //   4 bit, two tokens   50.4/48.2  48.2/52.2    82.9/73.5  65.4/68.8    118.2/105.3 84.6/82.4    154.0/132.5  107.3/103.7
 bool short_lowbit_work(const AttnArgs& a, mfa_kv_dtype kv_dtype)
 {
-    const int64_t tiles_per_seq = (a.max_seq_len_hint + kTile - 1) / kTile;
-    const int64_t tiles = a.n_wgs > 0 ? a.B * tiles_per_seq / a.n_wgs : a.chunk_tokens / kTile;
-    return tiles < (kv_dtype == MFA_KV_FP4_E2M1 ? 48 : 30);
+    return tiles_per_workgroup(a) < (kv_dtype == MFA_KV_FP4_E2M1 ? 48 : 30);
 }
 }  // namespace
 
 hipError_t prepare_decode_attn_kernels()
 {
-    for (int q_len = 3; q_len <= 4; ++q_len)
-        for (int paged = 0; paged < 2; ++paged) {
-            const hipError_t e = hipFuncSetAttribute(multi_kernel(q_len, paged != 0), hipFuncAttributeMaxDynamicSharedMemorySize, kBf16LdsBytes);
-            if (e != hipSuccess) return e;
-        }
+    for (int form = 0; form < 6; ++form) {            // three and four tokens, three tokens for little work; paged or not
+        const AttnKernel k = multi_kernel(form / 2 == 1 ? 4 : 3, (form & 1) != 0, form / 2 == 2);
+        const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds_bytes);
+        if (e != hipSuccess) return e;
+    }
     for (int dt = 0; dt < 3; ++dt)
         for (int form = 0; form < 8; ++form) {
             const mfa_kv_dtype kvd = dt == 0 ? MFA_KV_BF16 : (dt == 1 ? MFA_KV_FP8_E4M3 : MFA_KV_FP4_E2M1);
@@ -521,8 +396,8 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
         args.q0 = 0;
         args.n_here = a.q_len;
         void* params[] = {&args};
-        hipError_t e = hipExtLaunchKernel(multi_kernel(a.q_len, a.block_table != nullptr), grid, dim3(kMultiThreads), params,
-                                          kBf16LdsBytes, stream, ev_before, ev_after, 0);
+        const AttnKernel k = multi_kernel(a.q_len, a.block_table != nullptr, short_multi_work(a));
+        hipError_t e = hipExtLaunchKernel(k.fn, grid, dim3(k.threads), params, k.lds_bytes, stream, ev_before, ev_after, 0);
         if (e != hipSuccess) return e;
         e = hipGetLastError();
         if (e != hipSuccess) return e;
