@@ -8,20 +8,21 @@ namespace mfa {
 
 constexpr int kThree = 3;                             // query tokens
 
-// ---- One 32-token unit for kThree query tokens held by one wave (short_bf16_multi_kernel): every key fragment read from LDS feeds kThree score products and every value fragment kThree weighted-sum
-// products, so the LDS traffic is that of a single token; the kThree accumulator chains are independent, which
+// ---- One 32-token unit for three query tokens held by one wave (short_bf16_multi_kernel): every key fragment read from LDS
+// feeds three score products and every value fragment three weighted-sum
+// products, so the LDS traffic is that of a single token; the three accumulator chains are independent, which
 // keeps the MFMA pipe busy from one wave.
 //
-// Registers.  kThree x 64 accumulator registers and kThree x 32 of query fragments leave a wave (the only one on its
-// SIMD) about 130 of its 512 registers for everything else, and only if the accumulators sit in the accumulation
+// Registers.  3 x 64 accumulator registers and 3 x 32 of query fragments leave a wave (the only one on its
+// SIMD) some 220 of its 512 registers for everything else, and only if the accumulators sit in the accumulation
 // half of the file (where just MFMAs reach them) and nothing else does:
 //   * the score products are written out as instructions with ordinary destination registers (the compiler gives
-//     every MFMA of such a kernel an accumulation-register destination, which for kThree = 4 alone oversubscribes
+//     every MFMA of such a kernel an accumulation-register destination, which oversubscribes
 //     that half); the wait states between the last of them and the first read of a score are inserted by hand;
 //   * the accumulators are never rescaled: the reference exponent of a head is set by its first unit with a token
 //     (or handed in) and then stays, and the weights of later tokens may grow to 2^kFixedReferenceLag relative to
 //     it, harmless in bf16 and fp32.  A unit that would exceed that changes nothing and reports the exponents it
-//     would need; the caller starts the segment again with them (decode_bf16_multi_kernel).
+//     would need; the caller starts the segment again with them (short_bf16_multi_kernel).
 __device__ __forceinline__ void mfma_bf16_into_vgprs(f32x4& acc, const bf16x8& a, const bf16x8& b)
 {
     asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
@@ -117,9 +118,9 @@ __device__ __forceinline__ bool process_unit_three(WaveState (&st)[kThree], cons
 // ---- Three query tokens per sequence in ONE pass over a bf16 cache (Section 5.2: the new tokens of a
 // multi-token step share the cache read, which multiplies the arithmetic per byte by their number).
 // A workgroup is four waves, one per SIMD, wave = head group: a wave holds all kThree query tokens of its 16 heads
-// (kThree x 32 registers of query fragments, kThree x 64 accumulator registers: only one wave fits a SIMD's register
+// (3 x 32 registers of query fragments, 3 x 64 accumulator registers: only one wave fits a SIMD's register
 // file) and works through both units of every tile; key and value fragments read from LDS are shared by the kThree
-// tokens (process_unit_multi).  Same tiles, same two-slot ring and same schedule as decode_bf16_kernel; each wave
+// tokens (process_unit_three).  Same tiles, same two-slot ring and same schedule as decode_bf16_kernel; each wave
 // brings 16 rows of a tile.  Query token j attends to the first len - (q_len - 1 - j) cached tokens.  Batches of
 // at most 512 sequences (every wave works the schedule out by itself).
 constexpr int kShortMultiFlag = kBf16LdsBytes;
