@@ -18,7 +18,8 @@
 //
 // The reference exponent of a column is set by its first unit and then stays: weights may grow to 2^kFixedReferenceLag relative to
 // it, harmless in bf16 and fp32.  The true maximum is tracked beside it; if it ends up further ahead than that, the
-// workgroup streams the segment once more with the maxima it has seen as references.
+// workgroup streams the segment once more with the maxima it has seen as references.  A first unit of nothing but -inf leaves
+// the reference at -inf: any finite score after it is ahead of that, so such a segment takes the same way.
 #pragma once
 #include "mfa_lowbit.hpp"
 
@@ -344,7 +345,7 @@ __global__ __launch_bounds__(kMultiThreads) __attribute__((amdgpu_waves_per_eu(1
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb) {
                     m_true[cb] = half_max(st.half[cb].s_max) * c;
-                    outrun = outrun || (st.half[cb].m != -INFINITY && m_true[cb] > st.half[cb].m + kFixedReferenceLag);
+                    outrun = outrun || m_true[cb] > st.half[cb].m + kFixedReferenceLag;
                 }
                 outrun = outrun && !retried;
                 if (outrun) *LDS_AT(int, lds, kMultiFlag) = 1;
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(kMultiThreads) __attribute__((amdgpu_waves_per_eu(1
                 if (computes) {
 #pragma unroll
                     for (int cb = 0; cb < 2; ++cb)
-                        if (m_true[cb] > st.half[cb].m + kFixedReferenceLag && st.half[cb].m != -INFINITY) st.half[cb].m = m_true[cb];
+                        if (m_true[cb] > st.half[cb].m + kFixedReferenceLag) st.half[cb].m = m_true[cb];
                 }
                 retried = true;
                 __syncthreads();                      // the flag has been read

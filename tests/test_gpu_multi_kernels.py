@@ -29,8 +29,10 @@ def _run(ctx, case, qm):
     return out.cpu().numpy()
 
 
-def _compare(case, q_len):
+def _compare(case, q_len, mask_dim=None):
     qm = W.make_multi_query(case, q_len, 43)
+    if mask_dim is not None:
+        qm[..., mask_dim] = 1.0
     ref = []
     for j in range(q_len):
         lens = torch.clamp(case.seq_lens - (q_len - 1 - j), min=0).to(torch.int32)
@@ -65,3 +67,14 @@ def test_scores_that_outrun_the_reference_exponent(q_len):
     for b, pos, gain in ((0, 3333, 256.0), (1, 77, 64.0), (1, 500, 512.0), (3, 1999, 256.0)):
         case.k[b, pos] = case.k[b, pos] * gain
     _compare(case, q_len)
+
+
+@pytest.mark.parametrize("q_len", [3, 4])
+@pytest.mark.parametrize("n_masked", [31, 32, 33, 200, 4000])
+def test_scores_of_minus_infinity_ahead_of_finite_ones(q_len, n_masked):
+    """Keys whose scores are -inf for every head (dimension 0 used as a mask: -inf in the key, positive in the query) at the start of a
+    sequence: their weight is 0, whatever unit, segment or kernel they begin."""
+    lens = [4100, 900, 300, 2000]
+    case = W.make_contiguous_case("multimask", 73, B=len(lens), S=max(lens), seq_lens=lens, poison=True)
+    case.k[:, :n_masked, 0] = torch.where(torch.arange(n_masked) < case.seq_lens[:, None] - 4, float("-inf"), case.k[:, :n_masked, 0].float()).to(case.k.dtype)
+    _compare(case, q_len, mask_dim=0)
