@@ -286,9 +286,10 @@ __device__ __forceinline__ void finish_half(WaveState& st, lds_ptr_t lds_base, i
     __syncthreads();
     const float m_o = *LDS_AT(float, lds_base, kMlOff + ((wq * 2 + (grp ^ 1)) * 2 + 0) * 64 + n * 4);
     const float l_o = *LDS_AT(float, lds_base, kMlOff + ((wq * 2 + (grp ^ 1)) * 2 + 1) * 64 + n * 4);
-    const float m = fmaxf(st.m, m_o);                 // finite: the segment has a token, seen by grp 0
-    const float w_s = fast_exp2(st.m - m);
-    const float w_o = fast_exp2(m_o - m);
+    const float m = fmaxf(st.m, m_o);                 // -inf if every score of the segment is: a partial without weight
+    const float m_safe = m == -INFINITY ? 0.f : m;
+    const float w_s = fast_exp2(st.m - m_safe);
+    const float w_o = fast_exp2(m_o - m_safe);
     const float l = st.l * w_s + l_o * w_o;
     const float inv = 1.0f / l;
     float* o = a.out + ((size_t)b * kHeads + head) * kHeadDim + 4 * g;

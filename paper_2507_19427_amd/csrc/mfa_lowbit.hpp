@@ -504,9 +504,10 @@ __device__ __forceinline__ void finish_lowbit_half(LowbitState& st, lds_ptr_t ld
     __syncthreads();
     const float m_o = *LDS_AT(float, lds, kMl + theirs * 256 + n * 4);
     const float l_o = *LDS_AT(float, lds, kMl + theirs * 256 + 128 + n * 4);
-    const float m = fmaxf(st.m, m_o);                 // finite: the segment has a token, seen by tp 0
-    float w_s = fast_exp2(st.m - m);
-    float w_o = fast_exp2(m_o - m);
+    const float m = fmaxf(st.m, m_o);                 // -inf if every score of the segment is: a partial without weight
+    const float m_safe = m == -INFINITY ? 0.f : m;
+    float w_s = fast_exp2(st.m - m_safe);
+    float w_o = fast_exp2(m_o - m_safe);
     const float l = st.l * w_s + l_o * w_o;
     f32x4* dst;
     if (r.final_result) {                             // dims 4*dq.. of the row, dq = 8*(block) + 2*(quad) + h: 2 float4 apart per quad

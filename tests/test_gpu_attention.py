@@ -196,3 +196,19 @@ def test_page_ids_outside_the_pool_touch_nothing_outside_it():
     for b in (0, 2, 3):
         want[int(case.block_table[b, int(at[b]) // 64]), int(at[b]) % 64] = True
     assert torch.equal(changed, want)
+
+
+@pytest.mark.parametrize("n_masked", [63, 64, 65, 200, 4000])
+@pytest.mark.parametrize("workgroups", [256, 7, 1])
+def test_scores_of_minus_infinity_ahead_of_finite_ones(workgroups, n_masked):
+    """Keys whose scores are -inf for every head (dimension 0 used as a mask) at the start of a sequence: weight 0, also where they
+    make up whole segments of the schedule."""
+    _announce(f"{n_masked} masked tokens, {workgroups} workgroups")
+    lens = [4100, 900, 300, 2000, 65]
+    case = W.make_contiguous_case("mask", 27, B=len(lens), S=max(lens), seq_lens=lens, poison=True)
+    case.q[..., 0] = 1.0
+    for b, n in enumerate(lens):
+        case.k[b, :min(n_masked, n - 1), 0] = float("-inf")
+    ctx = mfa.mfa_decode_init(mfa.MfaConfig(max_batch=8, max_seq_len=8192, target_workgroups=workgroups))
+    assert U.row_normalised_error(U.run_gpu(ctx, case), U.run_oracle(case)) <= U.TOL_BF16
+    ctx.close()
