@@ -788,9 +788,10 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
             pv_tile<BITS>(st.acc, w, values, [](auto) {});
         }
         // A column whose largest score has outrun its reference too far: the workgroup streams the segment once more, the
-        // maxima as references.  (st.m is -inf for a column without tokens; it then stays so.)
+        // maxima as references.  (A reference of -inf, left by a first tile of nothing but -inf, is outrun by any finite score;
+        // a column without tokens has s_max = -inf too and keeps it.)
         const float m_true = half_max(st.s_max) * c;
-        const bool outrun = !retried && st.m != -INFINITY && m_true > st.m + kFixedReferenceLag;
+        const bool outrun = !retried && m_true > st.m + kFixedReferenceLag;
         if (outrun) *LDS_AT(int, lds, S::kFlag) = 1;
         __syncthreads();                              // every wave is done reading the tile memory
         again = !retried && *LDS_AT(int, lds, S::kFlag) != 0;

@@ -110,4 +110,4 @@ def test_scores_of_minus_infinity_ahead_of_finite_ones(kv_dtype, q_len, n_masked
     case = W.make_contiguous_case("lowbitmask", 64, B=len(lens), S=max(lens), seq_lens=lens, kv_dtype=kv_dtype, poison=True)
     for b, n in enumerate(lens):
         _mask_tokens(case, b, min(n_masked, n - 40))
-    _compare(case, q_len, 4100, (256,), mask_dim=0, tol=2 * 2.0 ** -8)
+    _compare(case, q_len, 4100, (256, 7, 3, 1), mask_dim=0, tol=2 * 2.0 ** -8)
