@@ -214,11 +214,15 @@ __device__ __forceinline__ LowbitLanes<BITS> lowbit_lanes(int lane)
 // 2^kFixedReferenceLag relative to it, which costs nothing (the weights enter the product with a power-of-two scale per tile, and
 // sums are fp32), and the accumulators never pass through vector registers to be rescaled.  The true maximum is
 // tracked beside it; if it ends up further ahead than that, the workgroup streams the segment once more with the
-// maxima it has seen as references (decode_lowbit_kernel).
+// maxima it has seen as references (decode_lowbit_kernel).  So it does if a weight times its value scale has passed kLargeWeight, from
+// where on sums could leave fp32, and a lower reference is to blame: 2^24 tokens times the largest code, 448, stay finite
+// below 2^95.
+constexpr float kLargeWeight = 1.2089258e24f;        // 2^80
 struct LowbitState {
     f32x16 acc[8];       // [32-dim block]; element i: d = 32*db + 8*(i/4) + 4*h + i%4
     float m;             // reference exponent, log2 domain (-inf: the column has no token here)
     float s_max;         // this lane's largest score so far, key scale applied (not yet c)
+    float w_top;         // this lane's largest weight times value scale so far (magnitude)
     float l;             // this lane's share of the sum of weights
 };
 
@@ -409,7 +413,11 @@ struct ScoresToWeights {
         pin(st.s_max);
         weigh(x0, x1, v);
     }
-    __device__ __forceinline__ void sum_up() { st.l += psum[0] + psum[1]; }
+    __device__ __forceinline__ void sum_up()
+    {
+        st.l += psum[0] + psum[1];
+        st.w_top = fmaxf(st.w_top, w_max);
+    }
     // The segment's first tile, in one go: sets the reference.
     __device__ __forceinline__ void first()
     {
@@ -703,6 +711,7 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
         for (int i = 0; i < 8; ++i) st.acc[i] = (f32x16)(0.f);
         output_ready(st.acc);
         st.s_max = -INFINITY;
+        st.w_top = 0.f;
         st.l = 0.f;
         float wt[32];                                                  // weights (times value scales) of stage s's tile
         float w_max, m_safe;
@@ -791,7 +800,7 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
         // maxima as references.  (A reference of -inf, left by a first tile of nothing but -inf, is outrun by any finite score;
         // a column without tokens has s_max = -inf too and keeps it.)
         const float m_true = half_max(st.s_max) * c;
-        const bool outrun = !retried && m_true > st.m + kFixedReferenceLag;
+        const bool outrun = !retried && (m_true > st.m + kFixedReferenceLag || (m_true > st.m && half_max(st.w_top) > kLargeWeight));
         if (outrun) *LDS_AT(int, lds, S::kFlag) = 1;
         __syncthreads();                              // every wave is done reading the tile memory
         again = !retried && *LDS_AT(int, lds, S::kFlag) != 0;

@@ -111,3 +111,21 @@ def test_scores_of_minus_infinity_ahead_of_finite_ones(kv_dtype, q_len, n_masked
     for b, n in enumerate(lens):
         _mask_tokens(case, b, min(n_masked, n - 40))
     _compare(case, q_len, 4100, (256, 7, 3, 1), mask_dim=0, tol=2 * 2.0 ** -8)
+
+
+@pytest.mark.parametrize("q_len", [1, 2])
+@pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
+@pytest.mark.parametrize("vscale_log2", [40, 100, 110])
+def test_large_values_under_scores_that_grow(kv_dtype, q_len, vscale_log2):
+    """Value scales far above 1 and a late token whose score lies some 2^36 above the first ones, which the reference exponent allows: the
+    weights, or their sums with the codes, would leave fp32, while the result (2^120 at most) does not.  Tolerance: as above, a row is
+    about one token's value."""
+    lens = [4000, 900, 130, 2000]
+    case = W.make_contiguous_case("lowbitlarge", 65, B=len(lens), S=4000, seq_lens=lens, kv_dtype=kv_dtype, poison=True)
+    case.v_scale *= 2.0 ** vscale_log2
+    for b, pos in ((0, 3333), (1, 500), (3, 1998)):
+        codes = case.k.view(torch.uint8)[b, pos]
+        codes.zero_()
+        codes[0] = 0x38 if kv_dtype == "fp8" else 0x02                 # 1.0 in dimension 0, where every query holds 1
+        case.k_scale[b, pos] = 36 * 16 / 1.4427
+    _compare(case, q_len, 4000, (256, 3, 1), mask_dim=0, tol=2 * 2.0 ** -8)
