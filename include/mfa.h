@@ -199,13 +199,25 @@ MFA_API mfa_status mfa_out_proj(mfa_ctx* ctx, const float* attn_out, const void*
  *   k_scale, v_scale  fp32 [B, kv_seq_stride_tokens]; NULL for bf16
  *   kv_seq_stride_tokens  rows between consecutive sequences (>= max_seq_len_hint)
  *   seq_lens int32 [B] on the DEVICE (never read by the host)
- *   max_seq_len_hint  host-side upper bound of seq_lens, used only to size the
- *            launch; 1 <= hint <= cfg.max_seq_len
+ *   max_seq_len_hint  host-side upper bound of seq_lens; 1 <= hint <= cfg.max_seq_len.  It
+ *            sizes the launch and, with B, selects the kernel: results for different
+ *            hints may differ in rounding, and a hint far above the lengths costs time
+ *            (up to a fifth where the real work is a few tiles per workgroup)
  *   out      fp32 [B, n_q_heads, head_dim]      (written)
- * Scores and sums are accumulated in fp32; attention weights keep at least the 8
- * significant bits of bf16 where they multiply V (bf16, or two e4m3 terms over
- * long 8-bit and 4-bit caches).  For a given build, device and arguments the
- * result is bitwise reproducible from call to call.
+ * Scores and sums are accumulated in fp32.  Attention weights are rounded where they
+ * multiply V:
+ *   bf16 caches, and 8-bit and 4-bit ones with little work per workgroup at the length of
+ *     the hint: to bf16 (8 significant bits; the value scale of a token multiplied in before);
+ *   long 8-bit and 4-bit caches: weight times value scale to two e4m3 terms with one power
+ *     of two per head and 64-token tile, i.e. to at least 8 significant bits down to 2^-13
+ *     of the tile's largest, and to 2^-22 of that largest below.
+ * Against a row's largest output the second form's error is the smaller one on caches whose
+ * value scales are alike (6e-4 against 1.7e-3 of it at 8192 tokens).  It is the larger one in a
+ * single element to which the heaviest tokens of a tile contribute nothing (codes of 0) while
+ * the tokens that make it up are more than 2^13 lighter, by attention or by value scale: such
+ * an element is itself that much smaller than its row.  A value scale that is inf or NaN makes
+ * its sequence's rows non-finite in either form (inf or NaN in the first, NaN in the second).
+ * For a given build, device and arguments the result is bitwise reproducible from call to call.
  * Work distribution: for B <= 4096 the 64-token tiles of all sequences, laid end
  * to end, are cut into equal ranges over at most 256 workgroups, whatever the
  * individual lengths are (they are read on the device); larger batches, or a

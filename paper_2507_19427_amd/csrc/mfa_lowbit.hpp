@@ -450,8 +450,10 @@ struct ScoresToWeights {
 
 // ... -> two e4m3 terms with one power-of-two scale per column and tile (the scale operand of the matrix instruction
 // undoes it): w = hi * 2^k + lo * 2^(k-5), k such that the largest |w| of the tile's 64 tokens lies in [128, 256) * 2^k.
-// hi keeps 4 significant bits, the remainder (at most half a step of hi) 4 more and its sign: at least the 8 bits of
-// a bf16 weight, down to 2^-12 of the tile's largest.  scale() picks k, step(i), i = 0 .. 7, converts four values.
+// hi keeps 4 significant bits, the remainder (at most half a step of hi) 4 more and its sign: at least the 8 bits of a bf16
+// weight down to 2^-13 of the tile's largest (where hi becomes subnormal), below that an error of at most 2^-22 of the
+// largest (half a subnormal step of lo).  A bf16 weight would keep its 8 bits there too; it shows only in dims where the heavy
+// tokens' codes are 0 (test_light_tokens_beside_a_heavy_one).  scale() picks k, step(i), i = 0 .. 7, converts four values.
 struct WeightsToOperands {
     float (&p)[32];
     SplitWeights& w;

@@ -129,3 +129,56 @@ def test_large_values_under_scores_that_grow(kv_dtype, q_len, vscale_log2):
         codes[0] = 0x38 if kv_dtype == "fp8" else 0x02                 # 1.0 in dimension 0, where every query holds 1
         case.k_scale[b, pos] = 36 * 16 / 1.4427
     _compare(case, q_len, 4000, (256, 3, 1), mask_dim=0, tol=2 * 2.0 ** -8)
+
+
+def _weight_rounding_bound(case, row_q, b, n):
+    """Per element of the [64, 256] output of sequence b: what the rounding of the weights may cost, from exact weights.  Weight times value
+    scale w of token t is held to 2^-8 of itself or to 2^-22 of the largest of its head and 64-token tile, whichever is larger (two e4m3
+    terms under one power of two).  Beside it: 2^-9 of each weight for the scores, and 2^-12 of the largest product of a
+    tile for the matrix instruction's sums, which keep 2^-13 of it."""
+    codes = {"fp8": lambda x: x.double(), "fp4": _e2m1}[case.kv_dtype]
+    k, v = codes(case.k[b, :n]), codes(case.v[b, :n])
+    s = (row_q.double() @ k.T) * case.k_scale[b, :n].double() * case.scale
+    p = torch.softmax(s, dim=-1)
+    w = p * case.v_scale[b, :n].double().abs()
+    tiles = torch.nn.functional.pad(w, (0, -n % 64)).view(64, -1, 64)
+    top = tiles.amax(-1).repeat_interleave(64, dim=-1)[:, :n]
+    rounding = torch.maximum(2.0 ** -8 * w, 2.0 ** -22 * top) + 2.0 ** -9 * w
+    product = w.unsqueeze(-1) * v.abs().unsqueeze(0)                                    # [64, n, 256]
+    largest = torch.nn.functional.pad(product, (0, 0, 0, -n % 64)).view(64, -1, 64, 256).amax(2).sum(1)
+    return ((p * case.v_scale[b, :n].double()) @ v).numpy(), (rounding @ v.abs() + 2.0 ** -12 * largest).numpy()
+
+
+def _e2m1(rows):
+    grid = torch.tensor([0, .5, 1, 1.5, 2, 3, 4, 6, -0., -.5, -1, -1.5, -2, -3, -4, -6], dtype=torch.float64)
+    return torch.stack([grid[(rows & 15).long()], grid[(rows >> 4).long()]], dim=-1).flatten(-2)
+
+
+@pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
+@pytest.mark.parametrize("by", ["value scale", "attention"])
+@pytest.mark.parametrize("log2", [10, 13, 16, 20, 26])
+def test_light_tokens_beside_a_heavy_one(kv_dtype, by, log2):
+    """One token of a tile is 2^log2 heavier than the rest, by its value scale or by its weight, and its codes are 0 in half of the
+    dimensions: those hold the light tokens' sum alone, to the precision the header states.  Both kernels."""
+    lens = [700, 130]
+    case = W.make_contiguous_case("lowbitheavy", 66, B=len(lens), S=3200, seq_lens=lens, kv_dtype=kv_dtype, poison=True)
+    case.q[..., 0] = 1.0
+    for b, pos in ((0, 333), (1, 17)):
+        case.v.view(torch.uint8)[b, pos, case.v.shape[-1] // 2:] = 0
+        if by == "value scale":
+            case.v_scale[b, pos] *= 2.0 ** log2
+        else:
+            codes = case.k.view(torch.uint8)[b, pos]
+            codes.zero_()
+            codes[0] = 0x38 if kv_dtype == "fp8" else 0x02             # 1.0 in dimension 0
+            case.k_scale[b, pos] = log2 * 16 / 1.4427
+    for n in (256, 1):
+        ctx = mfa.mfa_decode_init(mfa.MfaConfig(max_batch=16, max_seq_len=8192, target_workgroups=n))
+        got = _run(ctx, case, case.q.unsqueeze(1).contiguous(), 3200)[:, 0]
+        ctx.close()
+        for b, length in enumerate(lens):
+            ref, bound = _weight_rounding_bound(case, case.q[b], b, length)
+            share = np.abs(got[b] - ref) / bound
+            zero_half = np.abs(got[b] - ref)[:, 128:] / np.abs(ref[:, 128:]).max()
+            print(f"[case] {n} workgroups, {length} tokens: {share.max():.2f} of the bound, zero half {zero_half.max():.1e} of its largest", flush=True)
+            assert share.max() <= 1.0
