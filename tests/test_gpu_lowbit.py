@@ -47,7 +47,7 @@ def _compare(case, q_len, hint, workgroups, schedule=None, mask_dim=None, tol=TO
     ref = _oracle(case, qm)
     kw = {} if schedule is None else {"schedule": schedule}
     for n in workgroups:
-        ctx = mfa.mfa_decode_init(mfa.MfaConfig(max_batch=16, max_seq_len=32768, target_workgroups=n, **kw))
+        ctx = mfa.mfa_decode_init(mfa.MfaConfig(max_batch=max(16, case.B), max_seq_len=32768, target_workgroups=n, **kw))
         print(f"[case] {case.kv_dtype} {q_len} query tokens, {n} workgroups", flush=True)
         got = _run(ctx, case, qm, hint)
         err = U.row_normalised_error(got, ref)
@@ -76,6 +76,33 @@ def test_both_kernels_at_the_edges_of_tiles_and_stages(kv_dtype, q_len, paged):
 def test_both_kernels_under_the_fixed_schedule(kv_dtype):
     case = W.make_contiguous_case("lowbitfixed", 62, B=len(LENS), S=max(LENS), seq_lens=LENS, kv_dtype=kv_dtype, poison=True)
     _compare(case, 1, max(LENS), (256, 12), mfa.MFA_SCHEDULE_FIXED)
+
+
+@pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
+def test_long_chunks_of_the_fixed_schedule(kv_dtype):
+    """Two chunks of 55 tiles per sequence, enough for decode_lowbit_kernel: partial results by item, workgroups whose chunk lies past the
+    sequence's end, sequences that end just before, at and after the first chunk's end."""
+    lens = [7000, 100, 0, 3519, 3520, 3521, 3584, 1]
+    case = W.make_contiguous_case("lowbitchunks", 67, B=len(lens), S=7000, seq_lens=lens, kv_dtype=kv_dtype, poison=True)
+    _compare(case, 1, 7000, (16,), mfa.MFA_SCHEDULE_FIXED)
+
+
+@pytest.mark.parametrize("q_len", [1, 2])
+@pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
+@pytest.mark.parametrize("paged", [False, True])
+def test_more_sequences_than_one_wave_scans(kv_dtype, q_len, paged):
+    """Above 512 sequences the workgroup works the schedule out together; few workgroups, so decode_lowbit_kernel, and all of them
+    for the other kernel.  Empty sequences in front, in runs and at the end.  Tolerance: a row of a few tokens shows a weight's
+    rounding, 2^-8, in full, and where their values cancel twice of it."""
+    rng = np.random.default_rng(68)
+    lens = [0, 0] + [int(x) for x in rng.integers(1, 150, 636)] + [0, 0]
+    lens[100:170] = [0] * 70
+    lens[639 - 64:639] = [65] * 64
+    if paged:
+        case = W.make_paged_case("lowbit640", 68, seq_lens=lens, kv_dtype=kv_dtype)
+    else:
+        case = W.make_contiguous_case("lowbit640", 68, B=len(lens), S=150, seq_lens=lens, kv_dtype=kv_dtype, poison=True)
+    _compare(case, q_len, 150, (8, 256), tol=2 * 2.0 ** -8)
 
 
 @pytest.mark.parametrize("q_len", [1, 2])
