@@ -1,10 +1,11 @@
-// Device-side building blocks shared by the bf16 and fp8 decode attention kernels (gfx950).
+// Device-side building blocks of the decode attention kernels (gfx950).  Common to all of them: waits, direct loads, the schedule,
+// page lookup.  The kernels of four waves have shapes, matrix layouts and softmax rules of their own: mfa_lowbit.hpp
+// (decode_lowbit_kernel), mfa_multi.hpp (decode_bf16_multi_kernel), mfa_multi_short.hpp (short_bf16_multi_kernel, on this file's unit image).
 //
-// Workgroup shape common to both kernels: 8 waves; wave = 4*grp + wq.  wq selects 16 of the
-// 64 query heads, grp selects which 32-token unit of every 64-token tile the wave processes.
-// The two waves that share a SIMD (same wq, different grp) keep independent online-softmax
-// states which finish_item() merges through LDS, so one wave's MFMA work can overlap the
-// other's softmax.
+// Workgroup shape of decode_bf16_kernel (mfa_attn.hip) and short_lowbit_kernel (mfa_lowbit_short.hpp): 8 waves; wave = 4*grp + wq.
+// wq selects 16 of the 64 query heads, grp which 32-token unit of every 64-token tile the wave processes (with two query
+// tokens: which token).  The two waves that share a SIMD (same wq, different grp) keep independent online-softmax
+// states, which finish_segment() merges through LDS, so one wave's MFMA work can overlap the other's softmax.
 //
 // LDS image of one 32-token unit (what process_unit reads), bf16:
 //   K rows 0..31 then V rows 0..31, 512 B per row (256 bf16).

@@ -17,13 +17,17 @@
 // k = 32*hi + 16*h + lo, element j of lane half h of a 4-bit operand is k = 32*h + j.  Two 8-bit operands therefore match
 // byte for byte; where a 4-bit operand meets an 8-bit one the rows or dims are chosen to match.
 //
-// What bounds it.  8 bit, one token: memory (a 128-token stage in 4400 cycles, 64 KB per compute unit: 6.9 TB/s over the device).  4
-// bit: the matrix pipe, 2 x 16 instructions of 64 cycles per wave and stage, and what does not hide behind it (3070 cycles per
-// 128 tokens); two query tokens the same (3215 per 64 tokens).  About 9 us per launch go to the first segment's start (query
+// What bounds it.  8 bit, one token: memory (a 128-token stage, 64 KB per compute unit, in 4400 cycles of the about 1.8 GHz the device
+// holds in this kernel: 6.9 TB/s).  4 bit: the matrix pipe, 2 x 16 instructions of 64 cycles per wave and stage, and what does
+// not hide behind it (3070 cycles per 128 tokens); two query tokens the same (3215 per 64 tokens).  About 9 us per launch go to the first segment's start (query
 // conversion 5000 cycles, lengths and schedule 6000, first tile alone 4000) and end, which is why launches with little work have a kernel of
 // their own.  Alternatives measured at 128 x 8192 tokens, 8 bit / 4 bit / 8 bit two tokens: values expanded to bf16 (the other
 // kernel) 114 / 95 / 175 us, this one 102 / 79 / 154; eight waves of 16 columns on these instructions 108 / 85 / 162.
 // Error against 64 bits at 8192 tokens: 6.3e-4 of a row's largest element (bf16 weights: 1.7e-3).
+//
+// The accumulators are not rescaled (LowbitState): a segment in which a score outruns its first tile's by 2^40 is streamed twice, where the
+// other kernel moves its reference on.  128 x 8192 tokens, one token per sequence 400 times its score late in a segment, other
+// kernel / this one, 8 bit / 4 bit / 8 bit two tokens: 117/179, 100/135, 185/258 us; without such scores 121/108, 104/83, 188/162 on the same box.
 #pragma once
 #include "mfa_attn_core.hpp"
 
@@ -228,11 +232,12 @@ struct LowbitState {
 
 struct SplitWeights { i32x8 hi, lo; int e_hi, e_lo; };                 // value = hi * 2^(e_hi - 127) + lo * 2^(e_lo - 127)
 
-// The matrix instructions are written out: the query terms and the accumulators are only ever touched by them, so they live
-// in the accumulation half of the register file (as "a" operands) and everything the vector unit works on has the other
-// half; left to the compiler, scores and accumulators are copied between the halves every tile.  The hazard between a
+// The matrix instructions are written out: the accumulators are only ever touched by them, so they live in the accumulation
+// half of the register file (as "a" operands), and everything else -- query terms, scores, operands -- has the other half;
+// left to the compiler, scores and accumulators are copied between the halves every tile.  The hazard between a
 // matrix instruction and a vector instruction that reads its result is therefore covered by hand: 24 wait states
-// (mfma_results_ready), or two more matrix instructions issued in between (the pipe takes one every 16 passes).
+// (scores_ready, output_ready), or two more matrix instructions issued in between (the pipe takes one every 16 passes).  The
+// build checks the machine code for it (asm_check.py: check_matrix_hazards).
 template <int BITS> struct KeyOperand { typedef i32x8 type; };
 template <> struct KeyOperand<4> { typedef u32x4 type; };
 template <int BITS> using OperandA = typename KeyOperand<BITS>::type;                     // 32 bytes (8 bit) or 16 bytes per lane

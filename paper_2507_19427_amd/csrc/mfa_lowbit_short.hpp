@@ -1,8 +1,8 @@
-// decode attention over the 8-bit and the 4-bit cache for little work per workgroup (the rule is at launch_decode_attn).
+// Decode attention over the 8-bit and the 4-bit cache for little work per workgroup (the rule is short_lowbit_work() in mfa_attn.hip).
 //
 // Eight waves of 16 heads, 64-token tiles, scores on the 16x16x128 fp8/fp4 matrix instruction and the weighted sum on the
-// bf16 one from values converted once per tile.  Per tile it takes about 1.2 times what decode_lowbit_kernel takes, which is bound by memory, but a
-// segment begins and ends in less: its query fragments (64 values per lane) are converted straight from registers, two waves per SIMD
+// bf16 one from values converted once per tile.  Per tile it takes about 1.15 (8 bit) to 1.25 times (4 bit) what decode_lowbit_kernel takes,
+// but a segment begins and ends in less: its query fragments (64 values per lane) are converted straight from registers, two waves per SIMD
 // cover each other's waits, and there is no pipeline to fill.
 #pragma once
 #include "mfa_lowbit.hpp"

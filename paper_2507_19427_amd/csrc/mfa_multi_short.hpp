@@ -1,4 +1,4 @@
-// Three query tokens per sequence over a bf16 cache, for little work per workgroup (the rule is at launch_decode_attn).  Products, softmax and
+// Three query tokens per sequence over a bf16 cache, for little work per workgroup (the rule is short_multi_work() in mfa_attn.hip).  Products, softmax and
 // weighted sum of a unit follow one another, so a unit takes longer than in decode_bf16_multi_kernel, but a segment has no pipeline to
 // fill and all four waves compute.
 #pragma once
