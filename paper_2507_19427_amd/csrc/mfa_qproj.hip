@@ -223,7 +223,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_stream_kernel(const uint16_
     // stored row by row: whole 128-byte lines.  Stored straight from the accumulators (a lane has 4 columns of one
     // row, so 32 bytes of bf16 or 64 of fp32 to a line at a time) the query path of 128 rows took 45.1 us
     // instead of 44.4 and the output projection of 64 rows 53.8 instead of 53.3.
-    // Rows of the tile are 16 bytes apart modulo the banks, so 16 lanes on 16 rows do not collide.
+    // Rows of the tile are 16 bytes apart modulo the banks, so 16 lanes on 16 rows do not collide; what still does costs 256 cycles
+    // of a workgroup (SQ_LDS_BANK_CONFLICT 65,536 over 256 workgroups of the query path).
     __syncthreads();
     constexpr int kTileCols = kStripN * NS;
     constexpr int kTileStride = kTileCols * 4 + 16;
