@@ -21,7 +21,7 @@ Prints ONE JSON line: metric/value = KV tokens per second (from the wall time of
                 them (`frac_whole_call`: from the wall time of the timed steps where a step is exactly that call;
                 `frac_whole_call_by_events`: HIP events around the call on its stream, EVENT_SAMPLES samples, which
                 cost the call about 2 us)
-  cpu_baseline  the CPU oracle timed on this machine's host cores on a bounded sample of the same workload
+  cpu_baseline  the CPU oracle timed on this host's cores on a bounded sample of the same workload
 """
 import argparse
 import json
@@ -89,8 +89,7 @@ def build_workload(key, mfa, W, n_sets):
         # one prepared call per buffer set: the timed loop only crosses the C boundary
         w.steps = [mfa.PreparedDecodeAttn(w.ctx, q, ks[j], vs[j], lens, S, out) for j in range(n_sets)]
         w.read_pairs = list(zip(ks, vs))
-        w.desc = ("configs[%d]: B=%d, 64 q heads, 1 shared K/V head, head_dim 256, ctx %d, contiguous bf16 KV"
-                  % (1 if key == "cfg2" else 3, B, S))
+        w.desc = "B=%d, 64 q heads, 1 shared K/V head, head_dim 256, ctx %d, contiguous bf16 KV" % (B, S)
         w.metric = "KV tokens/s, MFA decode attention, B=%d, ctx %d, bf16, 1 GPU" % (B, S)
         w.dtype, w.kernel, w.kv_bytes_per_token = "bf16", "mfa::decode_bf16_kernel<false, 1>", 1024
         w.T, w.B, w.case = case.kv_tokens, B, case
@@ -107,7 +106,7 @@ def build_workload(key, mfa, W, n_sets):
         out = torch.empty(B, 64, 256, dtype=torch.float32, device="cuda")
         w.steps = [(lambda j=j: mfa.mfa_decode_attn_paged(w.ctx, q, ks[j], vs[j], table, lens, S, out=out))
                    for j in range(n_sets)]
-        w.desc = ("configs[2]: B=128, ctx uniform in [1024, 8192], 64-token pages behind a permuted block table, "
+        w.desc = ("B=128, ctx uniform in [1024, 8192], 64-token pages behind a permuted block table, "
                   "bf16 KV")
         w.metric = "KV tokens/s, MFA decode attention, B=128, ragged paged ctx 1K-8K, bf16, 1 GPU"
         w.dtype, w.kernel, w.kv_bytes_per_token = "bf16", "mfa::decode_bf16_kernel<true, 1>", 1024
@@ -134,7 +133,7 @@ def build_workload(key, mfa, W, n_sets):
             attn[j]()
         w.steps = [(lambda j=j: step(j)) for j in range(n_sets)]
         w.read_pairs = list(zip(ks, vs))
-        w.desc = ("configs[4]: B=128, query path 7168 -> 2048 -> RMSNorm -> 64x256, then attention over ctx 8192 of "
+        w.desc = ("B=128, query path 7168 -> 2048 -> RMSNorm -> 64x256, then attention over ctx 8192 of "
                   "fp8 e4m3 KV with per-token fp32 scales")
         w.metric = "KV tokens/s, MFA query path + decode attention, B=128, ctx 8192, fp8 KV, 1 GPU"
         w.dtype, w.kernel, w.kv_bytes_per_token = "bf16 (fp8 e4m3 KV storage)", "mfa::decode_lowbit_kernel<false, 1, 8>", 520
@@ -143,7 +142,7 @@ def build_workload(key, mfa, W, n_sets):
         w.extra_config = {"n_splits": mfa.mfa_decode_num_splits(w.ctx, B, S)}
         w.keep = [x, w_qa, w_qb]
     elif key in ("fp4", "fp4q2"):
-        # 4-bit cache (Section 5.2: 4-bit storage, 8-bit arithmetic): the cache shape of configs[4] in e2m1
+        # 4-bit cache (Section 5.2: 4-bit storage, 8-bit arithmetic): 128 x 8192 tokens in e2m1
         # codes, 264 bytes per token with the two fp32 scales.
         case = W.make_contiguous_case(key, 6, B=128, S=8192, kv_dtype="fp4", poison=False)
         B, S = case.B, case.k.shape[1]
@@ -171,7 +170,7 @@ def build_workload(key, mfa, W, n_sets):
         w.extra_config = {"query_tokens_per_sequence": q_len}
     elif key in ("cfg2q2", "cfg2q3", "cfg2q4", "fp8q2"):
         # Several new tokens per sequence in one pass over the cache (the multi-token step of Section 5.2):
-        # same cache shapes as configs[1] / the cache of configs[4], q_len times the arithmetic per byte.
+        # 64 x 4096 tokens in bf16, 128 x 8192 in fp8, q_len times the arithmetic per byte.
         fp8 = key == "fp8q2"
         q_len = int(key[-1])
         case = (W.make_contiguous_case(key, 6, B=128, S=8192, kv_dtype="fp8", poison=False) if fp8

@@ -355,7 +355,7 @@ bool short_multi_work(const AttnArgs& a) { return a.q_len == 3 && tiles_per_work
 //   8 bit, two tokens   56.9/53.4  52.6/55.5    96.3/85.0  73.3/74.0    138.4/120.4 94.5/88.8    175.6/154.5  121.2/111.8
 //   4 bit, one token    33.5/32.2  38.1/40.7    52.8/46.3  48.1/50.0     74.5/63.1  57.8/56.6     95.0/78.8    73.6/73.1
 //   4 bit, two tokens   50.4/48.2  48.2/52.2    82.9/73.5  65.4/68.8    118.2/105.3 84.6/82.4    154.0/132.5  107.3/103.7
-// and on another box
+// and on another device
 //                                20 tiles                  28 tiles                  36 tiles                    40 tiles
 //   8 bit, one token    47.7/43.0  42.6/43.2    58.9/53.7  47.3/47.7     71.7/63.1  52.8/53.3     78.8/69.5    60.9/60.9
 //   8 bit, two tokens   70.1/60.3  58.6/59.1    90.8/76.8  65.7/67.0    109.8/93.8  75.4/72.6    119.3/103.1   77.6/75.5

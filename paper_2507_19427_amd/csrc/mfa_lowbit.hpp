@@ -27,7 +27,7 @@
 //
 // The accumulators are not rescaled (LowbitState): a segment in which a score outruns its first tile's by 2^40 is streamed twice, where the
 // other kernel moves its reference on.  128 x 8192 tokens, one token per sequence 400 times its score late in a segment, other
-// kernel / this one, 8 bit / 4 bit / 8 bit two tokens: 117/179, 100/135, 185/258 us; without such scores 121/108, 104/83, 188/162 on the same box.
+// kernel / this one, 8 bit / 4 bit / 8 bit two tokens: 117/179, 100/135, 185/258 us; without such scores 121/108, 104/83, 188/162 on the same device.
 #pragma once
 #include "mfa_attn_core.hpp"
 

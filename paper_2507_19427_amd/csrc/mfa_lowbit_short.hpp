@@ -435,7 +435,7 @@ __global__ __launch_bounds__(kAttnThreads) void short_lowbit_kernel(AttnArgs a)
             const int scales = kLbScaleBase + P * 512;
             // The score products of this wave's (first) unit are issued ahead of the conversion of the next tile's
             // values: the MFMA pipe and the LDS work while the vector ALU converts (4 % on the 8-bit workload,
-            // compared on one box).
+            // compared on one device).
             const int u0 = QL == 2 ? 0 : grp;
             const RawScores raw0 = few::qk_unit<BITS>(q, lds_base, kb + u0 * kUnitTokens * kRowBytes, n, g);
             store_tile(regs[P ^ 1], P ^ 1);                                 // values of tile t+1

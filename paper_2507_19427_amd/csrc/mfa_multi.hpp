@@ -13,7 +13,7 @@
 // written out: the scores of unit s + 1 are taken beside the softmax of the second block of unit s, the weighted sum of unit s
 // beside the softmax of the first block of unit s + 1.
 // 64 x 4096 tokens, four query tokens, one product after the other (16 heads of all tokens per wave): 113.4 us a call, kernel 99.8; now
-// 92.9 .. 99 by box, kernel 77 .. 82.  Of the kernel, without its matrix instructions, softmax and loads 32 remain (start, operand reads, 67 MB of
+// 92.9 .. 99 by device, kernel 77 .. 82.  Of the kernel, without its matrix instructions, softmax and loads 32 remain (start, operand reads, 67 MB of
 // partial results written); the merge that reads those takes 14.  Three units in flight instead of two: 1 % slower on average.
 //
 // The reference exponent of a column is set by its first unit and then stays: weights may grow to 2^kFixedReferenceLag relative to

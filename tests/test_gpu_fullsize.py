@@ -36,7 +36,7 @@ def test_config2_b64_ctx4096():
     assert mfa.mfa_decode_num_splits(ctx, 64, 4096) == 4
     got = U.run_gpu(ctx, case)
     assert np.isfinite(got).all()
-    # every one of the 64 x 64 rows against the oracle (a few seconds on the machine's host cores)
+    # every one of the 64 x 64 rows against the oracle (a few seconds on the host's cores)
     err = U.row_normalised_error(got, U.run_oracle(case))
     print(f"[{case.name}] all {64 * 64} rows: row-normalised max error {err:.3e}", flush=True)
     assert err <= U.TOL_BF16
