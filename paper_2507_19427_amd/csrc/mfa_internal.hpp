@@ -80,22 +80,22 @@ struct QProjArgs {
     const void* w_qb;     // bf16 [q_rank,n_out]
     void* q_out;          // bf16 [B,n_out]
     float* ws_c;          // fp32 [split_k][B_pad][q_rank] partial sums of the first product
-    void* ws_chat;        // bf16, k-step-major: element (m, k) at ((k/32)*B_pad + m)*32 + k%32
+    void* ws_chat;        // bf16 in the order the second product's waves load it
     int32_t B, d_model, q_rank, n_out;
     int32_t split_k;
-    int32_t k_per_split;  // multiple of 32
+    int32_t k_per_split;  // multiple of 64
     float eps;
 };
 constexpr int kQProjRows = 128;   // rows of x one workgroup covers
 struct QProjPlan {
     int32_t split_k;      // K splits of a product whose fp32 partials go through the workspace
     int32_t k_per_split;
-    int32_t strips_per_wg;   // adjacent 64-column strips a workgroup owns: 1, or 2 / 4 (output projection with at most 128 / 64 rows)
+    int32_t strips_per_wg;   // adjacent 64-column strips a workgroup owns: 1, or 4 (output projection)
 };
 // Split of the k range of y = x.W ([K] -> [N]) that fills the device: N/64 column strips times split_k
 // workgroups, about one per compute unit, at most 32 splits.
 QProjPlan plan_linear(int32_t K, int32_t N, int32_t strips_per_wg = 1);
-QProjPlan plan_out_proj(int32_t K, int32_t N, int32_t B);
+QProjPlan plan_out_proj(int32_t K, int32_t N);
 inline QProjPlan plan_qproj(int32_t d_model, int32_t q_rank) { return plan_linear(d_model, q_rank); }
 hipError_t prepare_query_proj_kernels();   // one-time function attributes (dynamic LDS size)
 hipError_t launch_query_proj(const QProjArgs& a, hipStream_t stream);
@@ -128,7 +128,7 @@ struct OutProjArgs {
     const void* w_o;               // bf16 [n_in, d_model]
     void* y;                       // bf16 [B, d_model]
     float* ws_c;                   // fp32 [split_k][B_pad][d_model]
-    void* ws_act;                  // bf16 k-step-major copy of attn
+    void* ws_act;                  // bf16 copy of attn in the order the product's waves load it (more than 64 rows)
     int32_t B, n_in, d_model;
     QProjPlan plan;
 };

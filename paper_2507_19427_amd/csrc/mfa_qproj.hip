@@ -3,30 +3,95 @@
 //   1. split-K bf16 MFMA GEMM, fp32 partial sums of c into the workspace;
 //   2. reduce the partials, normalise, apply the gain, round to bf16;
 //   3. bf16 MFMA GEMM writing q in bf16.
-// With at most a few hundred rows of x both products are bound by streaming the weights
-// once, so the GEMM is built like the attention kernel's value product: a workgroup owns a
-// strip of 64 output columns and all (up to 128) rows of x, streams its [K, 64] slice of W
-// through LDS with global->LDS direct loads (128 B per row, two stages of 512 rows = 64 KB each,
-// one in flight while the other is multiplied), and feeds v_mfma_f32_16x16x32_bf16 with
-//   A = W^T  (16 columns x 32 k) read with the LDS transposing read,
-//   B = x^T  (32 k x 16 rows)    loaded from global memory (L2-resident) one stage ahead,
-// giving C^T[column, row]; a lane ends up with 4 consecutive columns of one row.  The eight
-// waves are 4 row groups x 2 interleaved halves of the k steps, so every x element is fetched
-// by one wave only; the two halves are added through LDS at the end.  64-column strips give the
-// second product (16384 columns) 256 workgroups, one per compute unit, each with 64 KB in flight.
+// The key/value projection and the output projection of the same layer are built from the same products.
+//
+// With at most a few hundred rows of x a product is bound by streaming the weights once: a workgroup owns a strip of
+// output columns and all (up to 128) rows of x, and what decides its speed is how the two streams, W from HBM and x from L2,
+// share a compute unit's way to memory (measured on MI355X, W of 67 MB, 256 workgroups):
+//   * A compute unit is served best with 16 .. 32 KB of W in flight: a stream alone takes 12.9 us with 16, 13.2 with 32, 14.7 with
+//     64 and 15.3 with 128 KB (a matrix of 235 MB: 36.4 us with 32, 38.9 with 64).  More only waits longer.
+//   * Loads of one wave come back in order.  x asked for behind W waits as long as W does: 256 KB of W and 512 KB of x per compute
+//     unit take 22 us when the same waves load both, the sum of either alone, and 15.0 when different waves do.
+//   * Rows of 512 bytes of W side by side stream faster than rows of 256 or 128 (235 MB: 34.8 / 36.4 / 37 us).
+//   * x is fast only as whole 128-byte lines per load instruction (row-major fragments of 64 bytes: 26 against 60 .. 80 GB/s).
+// gemm_loader_kernel follows from that, for any number of rows.
 #include "mfa_attn_core.hpp"
 
 namespace mfa {
 
 namespace {
 
-constexpr int kStripN = 64;                  // output columns per workgroup
-constexpr int kRowBytes = kStripN * 2;       // 128 B of W per k row
-constexpr int kStageRows = 512;              // k rows per stage
-constexpr int kStageBytes = kStageRows * kRowBytes;   // 64 KB
-constexpr int kGemmLdsBytes = 2 * kStageBytes;
-constexpr int kGemmThreads = 512;
-constexpr int kColBlocks = kStripN / 16;
+constexpr int kStripN = 64;                  // columns of a strip
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// How a product finds x:
+//   kRows   bf16, row-major [M, K]
+//   kTiled  bf16 in the order a wave loads it: element (m, k) at ((k/32)*rows_pad + (m & ~15))*32 + ((k%32)/8)*128 + (m%16)*8 + k%8, so that
+//           16 rows x 32 k are one KB in lane order
+//   kFloat  fp32, row-major [M, K], rounded to bf16 on the way
+enum class XKind { kRows, kTiled, kFloat };
+__device__ __forceinline__ size_t tiled_index(int m, int k, int rows_pad)
+{
+    return ((size_t)(k >> 5) * rows_pad + (m & ~15)) * 32 + ((k & 31) >> 3) * 128 + (m & 15) * 8 + (k & 7);
+}
+
+// Buffer resource for `base`: loads through it at offsets below 2 GiB read memory, all others (kOutside) and, with !valid, every
+// load return zeros without touching it.
+constexpr uint32_t kOutside = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const unsigned char* base, bool valid)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0, valid ? 0x7FFFFFFF : 0, 0x00020000);
+}
+constexpr int kNonTemporal = 2;              // cache policy operand of a buffer load
+
+// Row-major x reaches the lanes by way of a small image of the wave's own in LDS: it is loaded in whole 128-byte lines, written row
+// by row and read back as fragments.  bf16, 64 k of a row = 128 bytes: 16-byte chunk c of row r at c ^ ((r >> 1) & 7).  From fp32, 32 k of a
+// row = 64 bytes of bf16: chunk c of row r at c ^ ((r >> 2) & 3).  Either way 16 rows x one chunk touch every bank once.
+__device__ __forceinline__ int image64_at(int row, int chunk) { return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); }
+__device__ __forceinline__ int image32_at(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
+
+// ---- The product.  Four waves only load W, with direct loads into a ring of stages in LDS (128 B rows, XOR-swizzled on the global side so
+// that the transposing reads are conflict-free), each keeping a fixed number of loads in flight: as the oldest lands, the next is asked for.
+// Eight waves multiply: A = W^T (16 columns x 32 k) from the LDS transposing read, one unit ahead of its MFMAs, B = x^T (32 k x 16 rows) from
+// global memory two stages ahead, v_mfma_f32_16x16x32_bf16 giving C^T[column, row].  One barrier per stage, which waits for
+// LDS reads but for nobody's global loads.  The eight waves are 4 row groups x 2: alternate k steps (the two sums are added
+// through LDS) or, where the sums of both would not fit the registers, the halves of the columns.
+// OUT_BF16 = false: fp32 partial sums to out[(kz*rows_pad + m)*N + n];  true: bf16 result to out[m*N + n] (requires gridDim.z == 1).
+// MB = 1 or 2: 16-row blocks per wave; a workgroup covers 64 * MB rows of x.
+// NS = 1 or 4: 64-column strips per workgroup.  NS = 4 (the output projection) reads rows of 512 bytes and x once per 256 columns.
+// us per product at 4 / 64 / 128 rows, a kernel whose eight waves loaded 64 KB stages of W, loaded x and multiplied in turn -> this one:
+//   7168 -> 512     5.2 / 6.8 / 10.2  ->  4.2 / 5.6 / 7.7        7168 -> 2048   9.5 / 12.4 / 17.3  ->  7.7 / 9.3 / 12.4
+//   2048 -> 16384  16.1 / 18.3 / 22.6 -> 13.3 / 15.4 / 18.0     16384 -> 7168  42.8 / 43.9 / 59.9  -> 38.7 / 42.6 / 47.5 (up to 64 rows from fp32)
+// In flight: 16 KB with NS = 1 (32: 14.5 / 16.3 / 19.1 for the third), 32 KB with NS = 4 (64: 39.2 / 43.4 / 48.6, 16: 43.7 at 64 rows).  Two loading
+// waves instead of four: 16.6 / 16.8 / 18.9 for the third; eight: the same within 1 %.  x three stages ahead: 1 .. 2 % slower.
+constexpr int kLoaders = 4;
+constexpr int kMultipliers = 8;
+constexpr int kLoaderThreads = (kMultipliers + kLoaders) * 64;
+
+template <XKind X_KIND, int MB, int NS>
+struct LoaderShape {
+    static constexpr bool kSplitK = NS == 1 || MB == 1;
+    static constexpr int kStageBytes = NS == 4 && MB == 1 ? 32768 : 16384;
+    static constexpr int kStageRows = kStageBytes / (128 * NS);
+    static constexpr int kSubBytes = kStageBytes / NS;                  // one strip's part of a stage
+    static constexpr int kMySteps = kStageRows / 32 / (kSplitK ? 2 : 1);   // k steps of a multiplying wave per stage
+    static constexpr int kMyStrips = kSplitK ? NS : NS / 2;
+    static constexpr int kLoads = kStageBytes / 1024 / kLoaders;       // direct loads of a loading wave per stage
+    static constexpr int kAhead = (NS == 1 ? 16384 : 32768) / kStageBytes;   // stages in flight
+    static constexpr int kSlots = kAhead + 2;                          // (one being multiplied, one complete)
+    static constexpr int kImageBytes = X_KIND == XKind::kRows ? MB * 2048 : X_KIND == XKind::kFloat ? MB * 1024 : 0;
+    static constexpr int kImageBase = kSlots * kStageBytes;
+    static constexpr int kCols = kStripN * NS;
+    static constexpr int kRows = 64 * MB;
+    static constexpr int kTileStride = kCols * 4 + 16;                  // rows of the result tile 16 bytes apart modulo the banks
+    static constexpr int kRingBytes = kImageBase + kMultipliers * kImageBytes;
+    static constexpr int kLdsBytes = kRingBytes > kRows * kTileStride ? kRingBytes : kRows * kTileStride;
+    static_assert(kLdsBytes <= 160 * 1024, "LDS of a compute unit");
+    static_assert(NS == 1 || NS == 4, "one strip, k steps shared out; or four, columns shared out");
+    static_assert(X_KIND != XKind::kRows || kMySteps == 2, "an image of row-major bf16 holds 64 k");
+    static_assert(X_KIND != XKind::kFloat || kMySteps == 1, "an image of row-major fp32 holds 32 k");
+};
 
 // Swizzle key of a W row in LDS: its 32-byte chunk c is stored at position c ^ key.  A transposing
 // read touches rows 8g + 4t + i (g = 0..3, i = 0..3) at one chunk each.  Rows are 128 bytes, so rows
@@ -34,255 +99,233 @@ constexpr int kColBlocks = kStripN / 16;
 // by each half of the wave (g = 0, 1 or g = 2, 3) take the four chunk positions once each.
 __device__ __forceinline__ int w_key(int row) { return (((row >> 3) & 1) << 1) | ((row >> 1) & 1); }
 
-// OUT_BF16 = false: fp32 partial sums to out[(kz*rows_pad + m)*N + n] for every row of the tile.
-// OUT_BF16 = true : bf16 result to out[m*N + n] for m < M (requires gridDim.z == 1).
-// X_TILED = false: x is row-major [M, K].
-// X_TILED = true : x is stored k-step-major, element (m, k) at ((k/32)*rows_pad + m)*32 + k%32, so
-//                  that the 16 rows x 64 B a wave loads per k step are contiguous.
-// MB = 2 or 1: 16-row blocks per wave; a workgroup covers 64 * MB rows of x (MB = 1 when there are
-//                  no more than 64 rows: half the x traffic and MFMA work).
-// NS = 1, 2 or 4: adjacent 64-column strips per workgroup.  A stage holds 512 / NS k rows of each; the x
-//                  fragments of a k step are multiplied into all NS strips, so x is fetched once per
-//                  64 * NS columns (for products whose x is as large as a workgroup's share of W: the
-//                  output projection).
-template <bool OUT_BF16, bool X_TILED, int MB, int NS>
-__global__ __launch_bounds__(kGemmThreads) void gemm_stream_kernel(const uint16_t* __restrict__ X,
-                                                                   const uint16_t* __restrict__ W,
-                                                                   void* __restrict__ out, int M, int K, int N,
-                                                                   int k_per_split, int rows_pad)
+// Workgroup barrier that leaves this wave's global loads in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <bool OUT_BF16, XKind X_KIND, int MB, int NS>
+__global__ __launch_bounds__(kLoaderThreads) void gemm_loader_kernel(const void* __restrict__ X, const uint16_t* __restrict__ W,
+                                                                     void* __restrict__ out, int M, int K, int N, int k_per_split, int rows_pad)
 {
+    using S = LoaderShape<X_KIND, MB, NS>;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const lds_ptr_t lds_base = (lds_ptr_t)smem;
     const uint32_t lds_addr0 = (uint32_t)(uintptr_t)lds_base;
-
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int mp = wave & 3;                  // rows 16*MB*mp .. of the workgroup's tile
-    const int kh = wave >> 2;                 // takes the k steps of every stage with (step & 1) == kh
-    const int n = lane & 15;
-    const int g = lane >> 4;
+    const int n = lane & 15, g = lane >> 4;
 
-    constexpr int kSubRows = kStageRows / NS;            // k rows of one stage
-    constexpr int kSubBytes = kSubRows * kRowBytes;       // one strip's part of a stage buffer
-    constexpr int kStepsPerStage = kSubRows / 32;
-    constexpr int kCols = kColBlocks * NS;                // 16-column blocks of the workgroup
-    // Groups of strips (the output projection): the workgroups are numbered die by die (workgroup i runs on die i % 8; nothing but speed depends on it): a die's
-    // workgroups then share one or two slices of x, and its lines of W lie side by side (16384 -> 7168: 53.3 -> 50.9 us a call at 64
-    // rows, 70.7 -> 67.1 at 128).  Single strips over a k split (2048 or 512 columns) lose 0.2 .. 0.7 us by it.
-    int strip_group = blockIdx.x, kz = blockIdx.z;
-    const int n_groups = gridDim.x;
-    constexpr bool by_die = NS > 1;
-    if (by_die) {
-        const int n_wgs = n_groups * gridDim.z, id = blockIdx.x + n_groups * blockIdx.z, die = id & 7, rest = n_wgs & 7;
+    // Groups of strips (the output projection): the workgroups are numbered die by die (workgroup i runs on die i % 8; nothing but speed
+    // depends on it): a die's workgroups then share one or two slices of x, and its lines of W lie side by side.
+    int group = blockIdx.x, kz = blockIdx.z;
+    if (NS > 1) {
+        const int n_groups = gridDim.x, n_wgs = n_groups * gridDim.z, id = blockIdx.x + n_groups * blockIdx.z, die = id & 7, rest = n_wgs & 7;
         const int place = die * (n_wgs >> 3) + (die < rest ? die : rest) + (id >> 3);
         kz = __builtin_amdgcn_readfirstlane(place / n_groups);
-        strip_group = place - kz * n_groups;
+        group = place - kz * n_groups;
     }
-    const int n0 = strip_group * kStripN * NS;
-    const int m0 = blockIdx.y * 64 * MB;
+    const int n0 = group * S::kCols;
+    const int m0 = blockIdx.y * S::kRows;
     const int k_begin = kz * k_per_split;
-    const int k_end = (k_begin + k_per_split < K) ? k_begin + k_per_split : K;
-    const int n_stages = (k_end - k_begin + kSubRows - 1) / kSubRows;
+    const int k_end = k_begin + k_per_split < K ? k_begin + k_per_split : K;
+    const int n_stages = (k_end - k_begin + S::kStageRows - 1) / S::kStageRows;
+    // Workgroups walk the stages of their k range starting at different points and wrapping round: at any moment
+    // those that share an L2 then ask it for different parts of x instead of all for the same lines.
+    const int phase = (int)((unsigned)(NS > 1 ? group : group >> 3) % (unsigned)n_stages);   // (without a k split, workgroups 8 apart share an L2)
+    auto stage_k0 = [&](int it) { const int s = it + phase; return k_begin + (s < n_stages ? s : s - n_stages) * S::kStageRows; };
 
-    // Direct load of one stage of W: 64 loads of 8 rows; wave w issues loads 8w .. 8w+7.  Load l brings rows
-    // 8*(l % (64/NS)) .. of strip l / (64/NS).
-    auto issue_stage = [&](int stage, int slot) {
-        const int k0 = k_begin + stage * kSubRows;
-        const int rows_valid = (k_end - k0 < kSubRows) ? k_end - k0 : kSubRows;       // multiple of 32
-        const int p8 = lane & 7;                                       // 16-byte position in the 128-byte row
-        const unsigned char* w_stage = (const unsigned char*)W + ((size_t)k0 * N + n0) * 2;   // wave-uniform
+    f32x4 acc[MB][4 * S::kMyStrips];
+    const int mp = wave & 3, half = (wave >> 2) & 1;
+    const int kh = S::kSplitK ? half : 0, nh = S::kSplitK ? 0 : half;
+    const int my_row0 = 16 * MB * mp;
+    if (wave >= kMultipliers) {
+        const int lw = wave - kMultipliers;
+        constexpr int L = S::kLoads, A = S::kAhead;
+        // load i of a stage: 8 rows of one strip.  (A half stage at the end of the k range: its first rows again, never multiplied.)
+        auto request = [&](int it, int slot, int i) {
+            const int k0 = stage_k0(it);
+            const unsigned char* w_stage = (const unsigned char*)W + ((size_t)k0 * N + n0) * 2;   // wave-uniform
+            const int l = L * lw + i;
+            constexpr int kGroups = S::kStageRows / 8;
+            const int strip = l / kGroups, first_row = 8 * (l % kGroups);
+            const int in_stage = first_row + (lane >> 3);
+            const int row = k0 + first_row < k_end ? in_stage : lane >> 3;
+            const int p8 = lane & 7;                                   // 16-byte position in the 128-byte row
+            const int c16 = (((p8 >> 1) ^ w_key(in_stage)) << 1) | (p8 & 1);
+            load_to_lds_16B(w_stage, (uint32_t)row * (uint32_t)N * 2u + (uint32_t)(strip * 128 + c16 * 16),
+                            lds_addr0 + slot * S::kStageBytes + strip * S::kSubBytes + first_row * 128);
+        };
+        int slot = 0;
+        for (; slot < A && slot < n_stages; ++slot)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int l = 8 * wave + i;                                // wave-uniform
-            const int strip = l / (64 / NS);
-            const int first_row = 8 * (l % (64 / NS));
-            if (first_row < rows_valid) {
-                const int row = first_row + (lane >> 3);
-                const int c16 = ((((p8 >> 1) ^ w_key(row)) << 1) | (p8 & 1));
-                load_to_lds_16B(w_stage, (uint32_t)(row * N * 2 + strip * kRowBytes + c16 * 16),
-                                lds_addr0 + slot * kStageBytes + strip * kSubBytes + first_row * kRowBytes);
-            }
+            for (int i = 0; i < L; ++i) request(slot, slot, i);
+        for (int it = 0; it < n_stages; ++it) {
+            // stage `it` is complete when no more than the A - 1 stages behind it are in flight.  The slot that stage it + A goes to was
+            // multiplied before the last barrier but one.
+            if (it + A < n_stages) {
+#pragma unroll
+                for (int i = 0; i < L; ++i) { wait_vmem_but<A * L - 1>(); request(it + A, slot, i); }
+            } else if (A == 2 && it + 1 < n_stages) wait_vmem_but<L>();
+            else wait_vmem_but<0>();
+            slot = slot + 1 == S::kSlots ? 0 : slot + 1;
+            lds_barrier();
         }
-    };
-
-    // x fragments of this wave's k steps of one stage: lane (row n of a 16-row block, k group g)
-    // holds x[row][k0 + 32*(2j + kh) + 8g .. +7].  Every x element is loaded by exactly one wave.
-    // Two sets: the next stage's fragments are requested right after its W, a whole stage ahead.
-    constexpr int kMySteps = kStepsPerStage / 2;
-    bf16x8 xf[2][MB][kMySteps];               // [buffer][row block][own k step]
-    int xrow[MB];
+        static_assert(A <= 2, "waits at the end of the k range");
+    } else {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        const int r = m0 + 16 * MB * mp + 16 * mb + n;
-        xrow[mb] = r < M ? r : M - 1;         // rows past M repeat the last one; their results are not stored
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < 4 * S::kMyStrips; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        // Loads of x per stage: row-major in groups of 8 rows x 128 bytes, else one per 16-row block and k step.  Every element is
+        // loaded by one wave (by two with NS = 4).  Rows past M, and stages past the last, read nothing.
+        constexpr int kXLoads = X_KIND == XKind::kTiled ? MB * S::kMySteps : 2 * MB;
+        struct XRegs { u32x4 v[kXLoads]; };
+        uint32_t x_off[kXLoads];
+#pragma unroll
+        for (int i = 0; i < kXLoads; ++i) {
+            if (X_KIND == XKind::kTiled) x_off[i] = m0 + my_row0 + 16 * (i % MB) < M ? (uint32_t)(16 * lane + 1024 * (i % MB)) : kOutside;
+            else                         x_off[i] = m0 + my_row0 + 8 * i + (lane >> 3) < M ? (uint32_t)(lane >> 3) * (uint32_t)K * (X_KIND == XKind::kFloat ? 4 : 2) + (lane & 7) * 16 : kOutside;
+        }
+        constexpr int kBytes = X_KIND == XKind::kFloat ? 4 : 2;
+        const size_t x_step = X_KIND == XKind::kTiled ? (size_t)rows_pad * 64 : (size_t)32 * kBytes;     // bytes from a k step to the next
+        const unsigned char* const x0 = (const unsigned char*)X + (X_KIND == XKind::kTiled ? (size_t)(m0 + my_row0) * 64 : (size_t)(m0 + my_row0) * K * kBytes);
+        auto request_x = [&](XRegs& b, int it) {
+            const int k0 = stage_k0(it < n_stages ? it : 0) + 32 * kh * S::kMySteps;
+            const __amdgpu_buffer_rsrc_t xr = buffer_at(x0 + (size_t)(unsigned)(k0 >> 5) * x_step, it < n_stages && k0 < k_end);
+#pragma unroll
+            for (int i = 0; i < kXLoads; ++i)
+                b.v[i] = __builtin_amdgcn_raw_buffer_load_b128(xr, x_off[i], X_KIND == XKind::kTiled ? (i / MB) * rows_pad * 64 : 8 * i * K * kBytes, 0);
+        };
+        const int a_lane_off = (8 * g + (n >> 2)) * 128 + ((n & 3) << 3);         // row 8g + i, 8 bytes per lane
+        const int a_key = ((g & 1) << 1) | ((n >> 3) & 1);                        // w_key of rows 8g + 4t + i
+        // A operands of one k step and strip: for each 16-column block the two transposing reads that make W^T
+        union AFrag { bf16x8 v; s16x4 h[2]; };
+        auto read_a = [&](AFrag (&f)[4], int base, int ks) {
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    f[nb].h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_AT(s16x4, lds_base, base + (32 * ks + 4 * t) * 128 + a_lane_off + ((nb ^ a_key) << 5)));
+        };
+        const int image = S::kImageBase + wave * S::kImageBytes;
+        auto multiply = [&](const XRegs& b, int it, int slot) {
+            if (m0 + my_row0 >= M || stage_k0(it) + 32 * kh * S::kMySteps >= k_end) return;   // no rows; half a stage at the end of the k range
+            bf16x8 xf[MB * S::kMySteps];                                          // [own k step][row block]
+            if constexpr (X_KIND == XKind::kTiled) {
+#pragma unroll
+                for (int i = 0; i < kXLoads; ++i) xf[i] = __builtin_bit_cast(bf16x8, b.v[i]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kXLoads; ++i) {
+                    const int r = 8 * i + (lane >> 3);
+                    if constexpr (X_KIND == XKind::kRows) *LDS_AT(u32x4, lds_base, image + image64_at(r, lane & 7)) = b.v[i];
+                    else {
+                        const f32x4 f = __builtin_bit_cast(f32x4, b.v[i]);
+                        bf16x4 h;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) h[c] = (__bf16)f[c];
+                        *LDS_AT(bf16x4, lds_base, image + image32_at(r, (lane & 7) >> 1) + (lane & 1) * 8) = h;
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < S::kMySteps; ++j)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+                        xf[j * MB + mb] = *LDS_AT(bf16x8, lds_base, image + (X_KIND == XKind::kRows ? image64_at(16 * mb + n, 4 * j + g) : image32_at(16 * mb + n, g)));
+            }
+            // units (own k step, strip): the operands of the next one are read from LDS while the current one is multiplied
+            constexpr int T = S::kMyStrips, kUnits = S::kMySteps * T;
+            const int base = slot * S::kStageBytes + nh * T * S::kSubBytes;
+            AFrag f[2][4];
+            read_a(f[0], base, kh * S::kMySteps);
+#pragma unroll
+            for (int u = 0; u < kUnits; ++u) {
+                if (u + 1 < kUnits) read_a(f[(u + 1) & 1], base + ((u + 1) % T) * S::kSubBytes, kh * S::kMySteps + (u + 1) / T);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+                        acc[mb][(u % T) * 4 + nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[u & 1][nb].v, xf[(u / T) * MB + mb], acc[mb][(u % T) * 4 + nb], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        constexpr int kXAhead = 2;
+        XRegs x[kXAhead];
+#pragma unroll
+        for (int d = 0; d < kXAhead; ++d) request_x(x[d], d);
+        int slot = 0;
+        for (int it = 0; it < n_stages; it += kXAhead)
+#pragma unroll
+            for (int d = 0; d < kXAhead; ++d) {
+                if (it + d < n_stages) {
+                    lds_barrier();
+                    multiply(x[d], it + d, slot);
+                }
+                slot = slot + 1 == S::kSlots ? 0 : slot + 1;
+                __builtin_amdgcn_sched_barrier(0);
+                request_x(x[d], it + d + kXAhead);
+                __builtin_amdgcn_sched_barrier(0);
+            }
     }
-    auto load_x_stage = [&](int stage, int buf) {
-        const int k0 = k_begin + stage * kSubRows;
-#pragma unroll
-        for (int j = 0; j < kMySteps; ++j) {
-            int k = k0 + 32 * (2 * j + kh) + 8 * g;
-            k = k + 8 <= K ? k : K - 8;       // steps past k_end are never used; keep the address inside x
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const size_t idx = X_TILED ? ((size_t)(k >> 5) * rows_pad + xrow[mb]) * 32 + (k & 31)
-                                           : (size_t)xrow[mb] * K + k;
-                xf[buf][mb][j] = *(const bf16x8*)(X + idx);
-            }
-        }
-    };
 
-    f32x4 acc[MB][kCols];
+    // The result tile meets in LDS (the ring is dead, no direct load is in flight), always as (kh 0 part) + (kh 1 part), and is
+    // stored row by row: whole 128-byte lines.
+    __syncthreads();
+    const int own = (my_row0 + n) * S::kTileStride + 16 * g + nh * S::kMyStrips * kStripN * 4;
+    if (wave < kMultipliers && (!S::kSplitK || kh == 1)) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int j = 0; j < kCols; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-    const int a_lane_off = (8 * g + (n >> 2)) * kRowBytes + ((n & 3) << 3);   // row 8g + i, 8 bytes per lane
-    const int a_key = ((g & 1) << 1) | ((n >> 3) & 1);                        // w_key of rows 8g + 4t + i
-
-    // A operands of one k step: for each 16-column block the two transposing reads that make W^T.
-    struct AFrag { union { bf16x8 v; s16x4 h[2]; } nb[kColBlocks]; };
-    auto read_a = [&](AFrag& f, int base, int ks) {
-#pragma unroll
-        for (int nb = 0; nb < kColBlocks; ++nb)
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int off = base + (32 * ks + 4 * t) * kRowBytes + a_lane_off + ((nb ^ a_key) << 5);
-                f.nb[nb].h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_AT(s16x4, lds_base, off));
-            }
-    };
-    auto multiply = [&](const AFrag& f, int buf, int j, int strip) {
-#pragma unroll
-        for (int nb = 0; nb < kColBlocks; ++nb)
+            for (int j = 0; j < 4 * S::kMyStrips; ++j) *LDS_AT(f32x4, lds_base, own + 16 * mb * S::kTileStride + 64 * j) = acc[mb][j];
+    }
+    __syncthreads();
+    if (S::kSplitK) {
+        if (wave < kMultipliers && kh == 0) {
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
-                acc[mb][strip * kColBlocks + nb] =
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.nb[nb].v, xf[buf][mb][j], acc[mb][strip * kColBlocks + nb], 0, 0, 0);
-    };
-    // A stage is worked off in units (own k step j, strip): unit u = j * NS + strip.  The A operands of
-    // the next unit are read from LDS while the current one is multiplied, so that the LDS latency
-    // hides behind the MFMAs instead of stalling each pair.
-    constexpr int kUnits = kMySteps * NS;
-    static_assert(kUnits % 2 == 0, "units are taken in pairs");
-    auto compute_stage = [&](int stage, int slot, int buf) {
-        const int k0 = k_begin + stage * kSubRows;
-        const int steps = ((k_end - k0 < kSubRows) ? k_end - k0 : kSubRows) / 32;
-        const int base = slot * kStageBytes;
-        auto unit_base = [&](int u) { return base + (u % NS) * kSubBytes; };
-        auto unit_step = [&](int u) { return 2 * (u / NS) + kh; };
-        AFrag fa, fb;
-        if (steps == kStepsPerStage) {                 // full stage: straight-line code
-            // (the scheduling fences keep the compiler from sinking the reads back to their uses)
-            read_a(fa, unit_base(0), unit_step(0));
 #pragma unroll
-            for (int u = 0; u < kUnits; u += 2) {
-                read_a(fb, unit_base(u + 1), unit_step(u + 1));
-                __builtin_amdgcn_sched_barrier(0);
-                multiply(fa, buf, u / NS, u % NS);
-                __builtin_amdgcn_sched_barrier(0);
-                if (u + 2 < kUnits) read_a(fa, unit_base(u + 2), unit_step(u + 2));
-                __builtin_amdgcn_sched_barrier(0);
-                multiply(fb, buf, (u + 1) / NS, (u + 1) % NS);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < kUnits; ++u)
-                if (unit_step(u) < steps) {
-                    read_a(fa, unit_base(u), unit_step(u));
-                    multiply(fa, buf, u / NS, u % NS);
+                for (int j = 0; j < 4 * S::kMyStrips; ++j) {
+                    const int at = own + 16 * mb * S::kTileStride + 64 * j;
+                    *LDS_AT(f32x4, lds_base, at) = acc[mb][j] + *LDS_AT(f32x4, lds_base, at);
                 }
         }
-    };
-
-    // While a stage is multiplied the next one (W by direct loads, x into the other register set) is
-    // in flight; everything requested is awaited at the barrier that opens a stage.
-    // Workgroups walk the stages of their k range starting at different points (strip index modulo
-    // the stage count) and wrapping round: at any moment the strips that share an L2 then ask it for
-    // different parts of x instead of all for the same lines.
-    const int phase = (int)((unsigned)(by_die ? strip_group : strip_group >> 3) % (unsigned)n_stages);   // (without a k split, workgroups 8 apart share an L2)
-    auto stage_of = [&](int it) { const int s = it + phase; return s < n_stages ? s : s - n_stages; };
-    issue_stage(stage_of(0), 0);
-    load_x_stage(stage_of(0), 0);
-    for (int st = 0; st < n_stages; st += 2) {
-        // even step: slot 0, x buffer 0
-        wait_vmem_all();
         __syncthreads();
-        if (st + 1 < n_stages) { issue_stage(stage_of(st + 1), 1); load_x_stage(stage_of(st + 1), 1); }
-        compute_stage(stage_of(st), 0, 0);
-        if (st + 1 >= n_stages) break;
-        // odd step: slot 1, x buffer 1
-        wait_vmem_all();
-        __syncthreads();
-        if (st + 2 < n_stages) { issue_stage(stage_of(st + 2), 0); load_x_stage(stage_of(st + 2), 0); }
-        compute_stage(stage_of(st + 1), 1, 1);
     }
-
-    // The two waves that share their rows (kh = 0, 1) hold sums over disjoint k steps.  They meet in one fp32 tile in LDS (the stage
-    // buffers are dead, no direct load is in flight), always as (kh 0 part) + (kh 1 part), and the tile is
-    // stored row by row: whole 128-byte lines.  Stored straight from the accumulators (a lane has 4 columns of one
-    // row, so 32 bytes of bf16 or 64 of fp32 to a line at a time) the query path of 128 rows took 45.1 us
-    // instead of 44.4 and the output projection of 64 rows 53.8 instead of 53.3.
-    // Rows of the tile are 16 bytes apart modulo the banks, so 16 lanes on 16 rows do not collide; what still does costs 256 cycles
-    // of a workgroup (SQ_LDS_BANK_CONFLICT 65,536 over 256 workgroups of the query path).
-    __syncthreads();
-    constexpr int kTileCols = kStripN * NS;
-    constexpr int kTileStride = kTileCols * 4 + 16;
-    static_assert(64 * MB * kTileStride <= kGemmLdsBytes, "the result tile fits the stage buffers");
-    const int own = (16 * MB * mp + n) * kTileStride + 16 * g;
-    if (kh == 1) {
+    constexpr int kPiece = OUT_BF16 ? 8 : 4;                            // columns a thread stores at a time: 16 bytes
+    constexpr int kLanesPerRow = S::kCols / kPiece, kPieces = S::kRows * kLanesPerRow;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int j = 0; j < kCols; ++j) *LDS_AT(f32x4, lds_base, own + 16 * mb * kTileStride + 64 * j) = acc[mb][j];
-    }
-    __syncthreads();
-    if (kh == 0) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int j = 0; j < kCols; ++j) {
-                const int at = own + 16 * mb * kTileStride + 64 * j;
-                *LDS_AT(f32x4, lds_base, at) = acc[mb][j] + *LDS_AT(f32x4, lds_base, at);
-            }
-    }
-    __syncthreads();
-    if constexpr (OUT_BF16) {
-        constexpr int kLanesPerRow = kTileCols / 8;
-#pragma unroll
-        for (int i = 0; i < 64 * MB * kLanesPerRow / kGemmThreads; ++i) {
-            const int piece = i * kGemmThreads + threadIdx.x, row = piece / kLanesPerRow, col = piece % kLanesPerRow * 8;
-            const f32x4 lo = *LDS_AT(f32x4, lds_base, row * kTileStride + col * 4), hi = *LDS_AT(f32x4, lds_base, row * kTileStride + col * 4 + 16);
+    for (int i = 0; i < (kPieces + kLoaderThreads - 1) / kLoaderThreads; ++i) {
+        const int piece = i * kLoaderThreads + threadIdx.x, row = piece / kLanesPerRow, col = piece % kLanesPerRow * kPiece;
+        if (piece >= kPieces || m0 + row >= M) break;
+        const f32x4 lo = *LDS_AT(f32x4, lds_base, row * S::kTileStride + col * 4);
+        if constexpr (OUT_BF16) {
+            const f32x4 hi = *LDS_AT(f32x4, lds_base, row * S::kTileStride + col * 4 + 16);
             bf16x8 o;
 #pragma unroll
             for (int c = 0; c < 4; ++c) { o[c] = (__bf16)lo[c]; o[4 + c] = (__bf16)hi[c]; }
-            if (m0 + row < M) *(bf16x8*)((__bf16*)out + (size_t)(m0 + row) * N + n0 + col) = o;
-        }
-    } else {
-        constexpr int kLanesPerRow = kTileCols / 4;
-        float* dst = (float*)out + ((size_t)kz * rows_pad + m0) * N + n0;
-#pragma unroll
-        for (int i = 0; i < 64 * MB * kLanesPerRow / kGemmThreads; ++i) {
-            const int piece = i * kGemmThreads + threadIdx.x, row = piece / kLanesPerRow, col = piece % kLanesPerRow * 4;
-            *(f32x4*)(dst + (size_t)row * N + col) = *LDS_AT(f32x4, lds_base, row * kTileStride + col * 4);
+            *(bf16x8*)((__bf16*)out + (size_t)(m0 + row) * N + n0 + col) = o;
+        } else {
+            *(f32x4*)((float*)out + ((size_t)kz * rows_pad + m0 + row) * N + n0 + col) = lo;
         }
     }
 }
 
 // One workgroup per row of x: c = sum of the split-K partials (in split order),
 // c_hat = c / sqrt(mean(c^2) + eps) * gain.  A thread owns float4 pieces of the row; the partials
-// of a piece are loaded eight splits at a time so that the loads are in flight together.
-__global__ __launch_bounds__(256) void rmsnorm_reduce_kernel(const float* __restrict__ ws_c, const float* __restrict__ gain,
+// of a piece are loaded eight splits at a time so that the loads are in flight together: eight splits and a rank
+// of 2048 are one round trip.
+constexpr int kNormThreads = 512;
+__global__ __launch_bounds__(kNormThreads) void rmsnorm_reduce_kernel(const float* __restrict__ ws_c, const float* __restrict__ gain,
                                                              __bf16* __restrict__ chat, int r, int split_k, int rows_pad,
                                                              float eps)
 {
-    __shared__ float red[4];
+    __shared__ float red[kNormThreads / 64];
     extern __shared__ float crow[];           // r floats: the reduced row, kept between the two passes
     const int m = blockIdx.x;
     const int tid = threadIdx.x;
     const size_t split_stride = (size_t)rows_pad * r;
     float ss = 0.f;
-    for (int j = 4 * tid; j < r; j += 1024) {
+    for (int j = 4 * tid; j < r; j += 4 * kNormThreads) {
         const float* p = ws_c + (size_t)m * r + j;
         f32x4 c = {0.f, 0.f, 0.f, 0.f};
         for (int z0 = 0; z0 < split_k; z0 += 8) {
@@ -302,14 +345,16 @@ __global__ __launch_bounds__(256) void rmsnorm_reduce_kernel(const float* __rest
     for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
     if ((tid & 63) == 0) red[tid >> 6] = ss;
     __syncthreads();
-    const float total = red[0] + red[1] + red[2] + red[3];
+    float total = 0.f;
+#pragma unroll
+    for (int i = 0; i < kNormThreads / 64; ++i) total += red[i];
     const float inv = 1.0f / sqrtf(total / (float)r + eps);
-    for (int j = 4 * tid; j < r; j += 1024) {
+    for (int j = 4 * tid; j < r; j += 4 * kNormThreads) {
         const f32x4 c = *(const f32x4*)(crow + j);
         union { __bf16 h[4]; uint2 u; } o;
 #pragma unroll
         for (int i = 0; i < 4; ++i) o.h[i] = (__bf16)(c[i] * inv * (gain ? gain[j + i] : 1.0f));
-        *(uint2*)(chat + ((size_t)(j >> 5) * rows_pad + m) * 32 + (j & 31)) = o.u;   // k-step-major for the second product
+        *(uint2*)(chat + tiled_index(m, j, rows_pad)) = o.u;
     }
 }
 
@@ -390,10 +435,8 @@ __global__ __launch_bounds__(kHeadDim) void kv_record_kernel(const float* __rest
 }
 static_assert(kHeadDim == 256, "kv_record_kernel reduces over four waves");
 
-// fp32 [M, K] -> bf16, k-step-major: element (m, k) at ((k/32)*rows_pad + m)*32 + k%32.  A wave takes 16 rows of one k step: reads
-// whole 128-byte lines, writes one contiguous KB.  (A thread per four elements, with a 64-bit division each and 8-byte
-// stores: with the like change to
-// reduce_partials_bf16_kernel a call of 1 .. 16 rows takes 1.3 us less; 64 rows the same.)
+// fp32 [M, K] -> bf16 in the tiled order, for output projections of more than 64 rows (up to 64 the product converts by itself).  A wave takes
+// 16 rows of one k step: reads whole 128-byte lines, writes one contiguous KB.
 __global__ __launch_bounds__(256) void to_bf16_tiled_kernel(const float* __restrict__ src, __bf16* __restrict__ dst, int M, int K,
                                                             int rows_pad)
 {
@@ -407,7 +450,7 @@ __global__ __launch_bounds__(256) void to_bf16_tiled_kernel(const float* __restr
     bf16x8 o;
 #pragma unroll
     for (int j = 0; j < 4; ++j) { o[j] = (__bf16)lo[j]; o[4 + j] = (__bf16)hi[j]; }
-    *(bf16x8*)(dst + ((size_t)ks * rows_pad + m) * 32 + k) = o;
+    *(bf16x8*)(dst + tiled_index(m, 32 * ks + k, rows_pad)) = o;
 }
 
 // y[m][n] = bf16(sum over splits, in split order, of the fp32 partials); eight splits' loads in flight together.
@@ -441,35 +484,37 @@ __global__ __launch_bounds__(256) void reduce_partials_bf16_kernel(const float* 
 
 namespace {
 
-// One streaming product: rows of x in tiles of 128 (64 when there are no more), strips of 64 columns (groups of
-// two or four strips when the plan says so: fp32 partial output, k-step-major x, at most 128 rows), k splits.
-template <bool OUT_BF16, bool X_TILED>
-hipError_t launch_gemm(const void* X, const void* Wt, void* out, int M, int K, int N, const QProjPlan& plan, int split_k,
+// The kernel of one streaming product and what it covers.
+struct GemmForm { const void* fn; unsigned threads, lds_bytes; int rows, cols; };
+
+template <bool OUT_BF16, XKind X_KIND, int MB, int NS>
+GemmForm loader_form()
+{
+    using S = LoaderShape<X_KIND, MB, NS>;
+    return {(const void*)gemm_loader_kernel<OUT_BF16, X_KIND, MB, NS>, kLoaderThreads, S::kLdsBytes, S::kRows, S::kCols};
+}
+// Products over single strips: up to 64 rows, or tiles of 128.
+template <bool OUT_BF16, XKind X_KIND>
+GemmForm strip_form(int M)
+{
+    return M <= 64 ? loader_form<OUT_BF16, X_KIND, 1, 1>() : loader_form<OUT_BF16, X_KIND, 2, 1>();
+}
+// The output projection over groups of four strips: up to 64 rows straight from the fp32 activations (64 rows: 42.6 us where the product over a
+// converted copy takes 41.5, and the launch that converts 4 or 5), with more rows, where x is as large as a workgroup's share of W, from
+// the converted copy (128 rows: 55.0 and 47.5 + 5).
+bool converts_itself(int M, int strips_per_wg) { return strips_per_wg == 4 && M <= 64; }
+GemmForm out_form(int M, int strips_per_wg)
+{
+    if (strips_per_wg == 4) return M <= 64 ? loader_form<false, XKind::kFloat, 1, 4>() : loader_form<false, XKind::kTiled, 2, 4>();
+    return M <= 64 ? loader_form<false, XKind::kTiled, 1, 1>() : loader_form<false, XKind::kTiled, 2, 1>();
+}
+
+hipError_t launch_gemm(const GemmForm& f, const void* X, const void* W, void* out, int M, int K, int N, int k_per_split, int split_k,
                        int rows_pad, hipStream_t stream)
 {
-    if (plan.strips_per_wg > 1) {
-        if constexpr (!OUT_BF16 && X_TILED) {
-            const int ns = plan.strips_per_wg;
-            if (M > 128 || (ns != 2 && ns != 4) || (ns == 4 && M > 64) || N % (ns * kStripN) != 0) return hipErrorInvalidValue;
-            const dim3 grid(N / (ns * kStripN), 1, split_k);
-            const void* kernel = M <= 64 ? (ns == 2 ? (const void*)gemm_stream_kernel<false, true, 1, 2> : (const void*)gemm_stream_kernel<false, true, 1, 4>)
-                                         : (const void*)gemm_stream_kernel<false, true, 2, 2>;
-            const uint16_t* xp = (const uint16_t*)X;
-            const uint16_t* wp = (const uint16_t*)Wt;
-            int k_per_split = plan.k_per_split;
-            void* params[] = {&xp, &wp, &out, &M, &K, &N, &k_per_split, &rows_pad};
-            return hipLaunchKernel(kernel, grid, dim3(kGemmThreads), params, kGemmLdsBytes, stream);
-        } else {
-            return hipErrorInvalidValue;
-        }
-    }
-    if (M <= 64)
-        hipLaunchKernelGGL((gemm_stream_kernel<OUT_BF16, X_TILED, 1, 1>), dim3(N / kStripN, 1, split_k), dim3(kGemmThreads), kGemmLdsBytes,
-                           stream, (const uint16_t*)X, (const uint16_t*)Wt, out, M, K, N, plan.k_per_split, rows_pad);
-    else
-        hipLaunchKernelGGL((gemm_stream_kernel<OUT_BF16, X_TILED, 2, 1>), dim3(N / kStripN, (M + 127) / 128, split_k), dim3(kGemmThreads),
-                           kGemmLdsBytes, stream, (const uint16_t*)X, (const uint16_t*)Wt, out, M, K, N, plan.k_per_split, rows_pad);
-    return hipGetLastError();
+    const uint16_t* wp = (const uint16_t*)W;
+    void* params[] = {&X, &wp, &out, &M, &K, &N, &k_per_split, &rows_pad};
+    return hipLaunchKernel(f.fn, dim3(N / f.cols, (M + f.rows - 1) / f.rows, split_k), dim3(f.threads), params, f.lds_bytes, stream);
 }
 
 }  // namespace
@@ -480,37 +525,29 @@ QProjPlan plan_linear(int32_t K, int32_t N, int32_t strips_per_wg)
     int32_t want = 256 / (strips > 0 ? strips : 1);
     if (want < 1) want = 1;
     if (want > 32) want = 32;
-    const int32_t ksteps = K / 32;
-    const int32_t per = (ksteps + want - 1) / want;
+    const int32_t units = K / 64;                // a split is whole 64 k: what a wave takes at a time (every K here is a multiple of 64)
+    const int32_t per = (units + want - 1) / want;
     QProjPlan p;
-    p.k_per_split = per * 32;
-    p.split_k = (ksteps + per - 1) / per;
+    p.k_per_split = per * 64;
+    p.split_k = (units + per - 1) / per;
     p.strips_per_wg = strips_per_wg;
     return p;
 }
 
-// Output projection: with at most 64 rows a workgroup's share of the activations is as large as its share
-// of W, so groups of four strips (activations fetched once per 256 columns) pay for the fourfold k split
-// (16384 -> 7168 on MI355X: 66.6 us with single strips, 54.8 with pairs, 48.6 with fours).  With 65 to 128
-// rows: pairs (whole call 105 -> 82 us).
-QProjPlan plan_out_proj(int32_t K, int32_t N, int32_t B)
+// Output projection: groups of four strips (x once per 256 columns, W in rows of 512 bytes) pay for the fourfold k split.
+QProjPlan plan_out_proj(int32_t K, int32_t N)
 {
-    int32_t ns = 1;
-    if (B <= 64) ns = N % (4 * kStripN) == 0 ? 4 : (N % (2 * kStripN) == 0 ? 2 : 1);
-    else if (B <= 128) ns = N % (2 * kStripN) == 0 ? 2 : 1;      // (four strips of 128 rows do not fit the registers)
-    return plan_linear(K, N, ns);
+    return plan_linear(K, N, N % (4 * kStripN) == 0 ? 4 : 1);
 }
 
 hipError_t prepare_query_proj_kernels()
 {
-    const void* kernels[] = {(const void*)gemm_stream_kernel<false, false, 1, 1>, (const void*)gemm_stream_kernel<false, false, 2, 1>,
-                             (const void*)gemm_stream_kernel<true, true, 1, 1>, (const void*)gemm_stream_kernel<true, true, 2, 1>,
-                             (const void*)gemm_stream_kernel<false, true, 1, 1>, (const void*)gemm_stream_kernel<false, true, 2, 1>,
-                             (const void*)gemm_stream_kernel<false, true, 1, 2>, (const void*)gemm_stream_kernel<false, true, 1, 4>,
-                             (const void*)gemm_stream_kernel<false, true, 2, 2>};
-    for (const void* k : kernels) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLdsBytes);
-        if (e != hipSuccess) return e;
+    for (const int rows : {64, 128}) {
+        const GemmForm forms[] = {strip_form<false, XKind::kRows>(rows), strip_form<true, XKind::kTiled>(rows), out_form(rows, 1), out_form(rows, 4)};
+        for (const GemmForm& f : forms) {
+            const hipError_t e = hipFuncSetAttribute(f.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f.lds_bytes);
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }
@@ -519,19 +556,14 @@ hipError_t launch_query_proj(const QProjArgs& a, hipStream_t stream)
 {
     const int m_blocks = (a.B + kQProjRows - 1) / kQProjRows;
     const int rows_pad = m_blocks * kQProjRows;
-    QProjPlan plan;
-    plan.split_k = a.split_k;
-    plan.k_per_split = a.k_per_split;
-    plan.strips_per_wg = 1;
-    hipError_t e = launch_gemm<false, false>(a.x, a.w_qa, a.ws_c, a.B, a.d_model, a.q_rank, plan, a.split_k, rows_pad, stream);
+    hipError_t e = launch_gemm(strip_form<false, XKind::kRows>(a.B), a.x, a.w_qa, a.ws_c, a.B, a.d_model, a.q_rank, a.k_per_split, a.split_k,
+                               rows_pad, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rmsnorm_reduce_kernel, dim3(a.B), dim3(256), a.q_rank * sizeof(float), stream,
+    hipLaunchKernelGGL(rmsnorm_reduce_kernel, dim3(a.B), dim3(kNormThreads), a.q_rank * sizeof(float), stream,
                        (const float*)a.ws_c, a.gain, (__bf16*)a.ws_chat, a.q_rank, a.split_k, rows_pad, a.eps);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    plan.split_k = 1;
-    plan.k_per_split = a.q_rank;
-    return launch_gemm<true, true>(a.ws_chat, a.w_qb, a.q_out, a.B, a.q_rank, a.n_out, plan, 1, rows_pad, stream);
+    return launch_gemm(strip_form<true, XKind::kTiled>(a.B), a.ws_chat, a.w_qb, a.q_out, a.B, a.q_rank, a.n_out, a.q_rank, 1, rows_pad, stream);
 }
 
 namespace {
@@ -562,7 +594,8 @@ hipError_t launch_kv_append(const KvAppendArgs& a, mfa_kv_dtype kv_dtype, hipStr
 {
     const int m_blocks = (a.B + kQProjRows - 1) / kQProjRows;
     const int rows_pad = m_blocks * kQProjRows;
-    const hipError_t e = launch_gemm<false, false>(a.x, a.w_kv, a.ws_c, a.B, a.d_model, kKvWidth, a.plan, a.plan.split_k, rows_pad, stream);
+    const hipError_t e = launch_gemm(strip_form<false, XKind::kRows>(a.B), a.x, a.w_kv, a.ws_c, a.B, a.d_model, kKvWidth, a.plan.k_per_split,
+                                     a.plan.split_k, rows_pad, stream);
     if (e != hipSuccess) return e;
     return launch_record(a, kv_dtype, a.ws_c, a.plan.split_k, rows_pad, stream);
 }
@@ -571,11 +604,16 @@ hipError_t launch_out_proj(const OutProjArgs& a, hipStream_t stream)
 {
     const int m_blocks = (a.B + kQProjRows - 1) / kQProjRows;
     const int rows_pad = m_blocks * kQProjRows;
-    hipLaunchKernelGGL(to_bf16_tiled_kernel, dim3((a.n_in / 32 + 3) / 4, (a.B + 15) / 16), dim3(256), 0, stream, a.attn, (__bf16*)a.ws_act,
-                       a.B, a.n_in, rows_pad);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = launch_gemm<false, true>(a.ws_act, a.w_o, a.ws_c, a.B, a.n_in, a.d_model, a.plan, a.plan.split_k, rows_pad, stream);
+    const bool fused = converts_itself(a.B, a.plan.strips_per_wg);
+    hipError_t e = hipSuccess;
+    if (!fused) {
+        hipLaunchKernelGGL(to_bf16_tiled_kernel, dim3((a.n_in / 32 + 3) / 4, (a.B + 15) / 16), dim3(256), 0, stream, a.attn, (__bf16*)a.ws_act,
+                           a.B, a.n_in, rows_pad);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    e = launch_gemm(out_form(a.B, a.plan.strips_per_wg), fused ? (const void*)a.attn : a.ws_act, a.w_o, a.ws_c, a.B, a.n_in, a.d_model,
+                    a.plan.k_per_split, a.plan.split_k, rows_pad, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reduce_partials_bf16_kernel, dim3((a.d_model / 4 + 255) / 256, a.B), dim3(256), 0, stream, (const float*)a.ws_c,
                        (__bf16*)a.y, a.d_model, a.plan.split_k, rows_pad);
