@@ -142,22 +142,27 @@ def _check(status, where):
         raise MfaError(status, where)
 
 
+# The smallest calls take about as long to enqueue as to run (attention over 2 x 256 tokens: two launches, 10.5 us on the device), so what
+# is done per call is kept short: addresses and the stream go over as plain integers (the declared argument types convert them), shapes
+# are compared as they are.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current device's current stream, as torch.cuda.current_stream().cuda_stream (without building the Stream object)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+# (uint8: e2m1 codes, two per byte, last dimension head_dim / 2)
+_KV_DTYPES = {torch.bfloat16: MFA_KV_BF16, torch.float8_e4m3fn: MFA_KV_FP8_E4M3, torch.uint8: MFA_KV_FP4_E2M1}
 
 
 def _kv_dtype(t):
-    if t.dtype == torch.bfloat16:
-        return MFA_KV_BF16
-    if t.dtype == torch.float8_e4m3fn:
-        return MFA_KV_FP8_E4M3
-    if t.dtype == torch.uint8:                       # e2m1 codes, two per byte: last dimension head_dim / 2
-        return MFA_KV_FP4_E2M1
-    raise TypeError(f"unsupported cache dtype {t.dtype}")
+    kvd = _KV_DTYPES.get(t.dtype)
+    if kvd is None:
+        raise TypeError(f"unsupported cache dtype {t.dtype}")
+    return kvd
 
 
 def _cache_width(cfg, kvd):
@@ -166,7 +171,7 @@ def _cache_width(cfg, kvd):
 
 
 def _want(t, dtype, name):
-    if t.dtype != dtype or not t.is_cuda or not t.is_contiguous():
+    if t.dtype is not dtype or not t.is_cuda or not t.is_contiguous():
         raise TypeError(f"{name}: expected contiguous device tensor of {dtype}, got {t.dtype} on {t.device}")
 
 
@@ -217,12 +222,12 @@ def mfa_query_proj(ctx: MfaContext, x, w_qa, w_qb, rms_gain=None, q_out=None):
     for t, nm in ((x, "x"), (w_qa, "w_qa"), (w_qb, "w_qb")):
         _want(t, torch.bfloat16, nm)
     B = x.shape[0]
-    if tuple(x.shape) != (B, cfg.d_model) or tuple(w_qa.shape) != (cfg.d_model, cfg.q_rank) or \
-            tuple(w_qb.shape) != (cfg.q_rank, cfg.n_q_heads * cfg.head_dim):
+    if x.shape != (B, cfg.d_model) or w_qa.shape != (cfg.d_model, cfg.q_rank) or \
+            w_qb.shape != (cfg.q_rank, cfg.n_q_heads * cfg.head_dim):
         raise ValueError("query path shapes do not match the context configuration")
     if rms_gain is not None:
         _want(rms_gain, torch.float32, "rms_gain")
-        if tuple(rms_gain.shape) != (cfg.q_rank,):
+        if rms_gain.shape != (cfg.q_rank,):
             raise ValueError("rms_gain shape")
     if q_out is None:
         q_out = torch.empty(B, cfg.n_q_heads, cfg.head_dim, dtype=torch.bfloat16, device=x.device)
@@ -245,19 +250,19 @@ def mfa_decode_attn(ctx: MfaContext, q, k_cache, v_cache, seq_lens, max_seq_len_
         raise TypeError("k_cache / v_cache must be contiguous and of one dtype")
     S = k_cache.shape[1]
     width = _cache_width(cfg, kvd)
-    if tuple(q.shape) != (B, cfg.n_q_heads, cfg.head_dim) or tuple(k_cache.shape) != (B, S, width) or \
-            tuple(v_cache.shape) != (B, S, width) or tuple(seq_lens.shape) != (B,):
+    if q.shape != (B, cfg.n_q_heads, cfg.head_dim) or k_cache.shape != (B, S, width) or \
+            v_cache.shape != (B, S, width) or seq_lens.shape != (B,):
         raise ValueError("attention shapes do not match")
     for t, nm in ((k_scale, "k_scale"), (v_scale, "v_scale")):
         if t is not None:
             _want(t, torch.float32, nm)
-            if tuple(t.shape) != (B, S):
+            if t.shape != (B, S):
                 raise ValueError(nm + " shape")
     if out is None:
         out = torch.empty(B, cfg.n_q_heads, cfg.head_dim, dtype=torch.float32, device=q.device)
     else:
         _want(out, torch.float32, "out")
-        if tuple(out.shape) != (B, cfg.n_q_heads, cfg.head_dim):
+        if out.shape != (B, cfg.n_q_heads, cfg.head_dim):
             raise ValueError("out shape")
     _check(getattr(lib(), _entry)(ctx.handle, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_scale), _ptr(v_scale),
                                   kvd, S, _ptr(seq_lens), int(max_seq_len_hint), B, _ptr(out), _stream()), _entry)
@@ -286,20 +291,20 @@ def mfa_decode_attn_paged(ctx: MfaContext, q, k_pool, v_pool, block_table, seq_l
     if v_pool.dtype != k_pool.dtype or not k_pool.is_contiguous() or not v_pool.is_contiguous():
         raise TypeError("k_pool / v_pool must be contiguous and of one dtype")
     n_pages = k_pool.shape[0]
-    if tuple(k_pool.shape) != (n_pages, cfg.page_size, _cache_width(cfg, kvd)) or tuple(v_pool.shape) != tuple(k_pool.shape) \
-            or block_table.shape[0] != B or tuple(seq_lens.shape) != (B,) or \
-            tuple(q.shape) != (B, cfg.n_q_heads, cfg.head_dim):
+    if k_pool.shape != (n_pages, cfg.page_size, _cache_width(cfg, kvd)) or v_pool.shape != k_pool.shape \
+            or block_table.shape[0] != B or seq_lens.shape != (B,) or \
+            q.shape != (B, cfg.n_q_heads, cfg.head_dim):
         raise ValueError("paged attention shapes do not match")
     for t, nm in ((k_scale_pool, "k_scale_pool"), (v_scale_pool, "v_scale_pool")):
         if t is not None:
             _want(t, torch.float32, nm)
-            if tuple(t.shape) != (n_pages, cfg.page_size):
+            if t.shape != (n_pages, cfg.page_size):
                 raise ValueError(nm + " shape")
     if out is None:
         out = torch.empty(B, cfg.n_q_heads, cfg.head_dim, dtype=torch.float32, device=q.device)
     else:
         _want(out, torch.float32, "out")
-        if tuple(out.shape) != (B, cfg.n_q_heads, cfg.head_dim):
+        if out.shape != (B, cfg.n_q_heads, cfg.head_dim):
             raise ValueError("out shape")
     _check(lib().mfa_decode_attn_paged(ctx.handle, _ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(k_scale_pool),
                                        _ptr(v_scale_pool), kvd, n_pages, _ptr(block_table), block_table.shape[1],
@@ -322,19 +327,19 @@ def mfa_decode_attn_multi(ctx: MfaContext, q, k_cache, v_cache, seq_lens, max_se
         raise TypeError("k_cache / v_cache must be contiguous and of one dtype")
     S = k_cache.shape[1]
     width = _cache_width(cfg, kvd)
-    if tuple(q.shape) != (B, q_len, cfg.n_q_heads, cfg.head_dim) or tuple(k_cache.shape) != (B, S, width) or \
-            tuple(v_cache.shape) != (B, S, width) or tuple(seq_lens.shape) != (B,):
+    if q.shape != (B, q_len, cfg.n_q_heads, cfg.head_dim) or k_cache.shape != (B, S, width) or \
+            v_cache.shape != (B, S, width) or seq_lens.shape != (B,):
         raise ValueError("attention shapes do not match")
     for t, nm in ((k_scale, "k_scale"), (v_scale, "v_scale")):
         if t is not None:
             _want(t, torch.float32, nm)
-            if tuple(t.shape) != (B, S):
+            if t.shape != (B, S):
                 raise ValueError(nm + " shape")
     if out is None:
         out = torch.empty(B, q_len, cfg.n_q_heads, cfg.head_dim, dtype=torch.float32, device=q.device)
     else:
         _want(out, torch.float32, "out")
-        if tuple(out.shape) != tuple(q.shape):
+        if out.shape != q.shape:
             raise ValueError("out shape")
     _check(lib().mfa_decode_attn_multi(ctx.handle, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_scale),
                                        _ptr(v_scale), kvd, S, _ptr(seq_lens), int(max_seq_len_hint), B, q_len,
@@ -356,20 +361,20 @@ def mfa_decode_attn_paged_multi(ctx: MfaContext, q, k_pool, v_pool, block_table,
     if v_pool.dtype != k_pool.dtype or not k_pool.is_contiguous() or not v_pool.is_contiguous():
         raise TypeError("k_pool / v_pool must be contiguous and of one dtype")
     n_pages = k_pool.shape[0]
-    if tuple(k_pool.shape) != (n_pages, cfg.page_size, _cache_width(cfg, kvd)) or tuple(v_pool.shape) != tuple(k_pool.shape) \
-            or block_table.shape[0] != B or tuple(seq_lens.shape) != (B,) or \
-            tuple(q.shape) != (B, q_len, cfg.n_q_heads, cfg.head_dim):
+    if k_pool.shape != (n_pages, cfg.page_size, _cache_width(cfg, kvd)) or v_pool.shape != k_pool.shape \
+            or block_table.shape[0] != B or seq_lens.shape != (B,) or \
+            q.shape != (B, q_len, cfg.n_q_heads, cfg.head_dim):
         raise ValueError("paged attention shapes do not match")
     for t, nm in ((k_scale_pool, "k_scale_pool"), (v_scale_pool, "v_scale_pool")):
         if t is not None:
             _want(t, torch.float32, nm)
-            if tuple(t.shape) != (n_pages, cfg.page_size):
+            if t.shape != (n_pages, cfg.page_size):
                 raise ValueError(nm + " shape")
     if out is None:
         out = torch.empty(B, q_len, cfg.n_q_heads, cfg.head_dim, dtype=torch.float32, device=q.device)
     else:
         _want(out, torch.float32, "out")
-        if tuple(out.shape) != tuple(q.shape):
+        if out.shape != q.shape:
             raise ValueError("out shape")
     _check(lib().mfa_decode_attn_paged_multi(ctx.handle, _ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(k_scale_pool),
                                              _ptr(v_scale_pool), kvd, n_pages, _ptr(block_table),
@@ -406,7 +411,7 @@ def mfa_debug_stream_read(ctx: MfaContext, a, b):
 
 def _check_cache_pair(k, v, ks, vs, rows_shape):
     kvd = _kv_dtype(k)
-    if v.dtype != k.dtype or not k.is_contiguous() or not v.is_contiguous() or tuple(v.shape) != tuple(k.shape):
+    if v.dtype != k.dtype or not k.is_contiguous() or not v.is_contiguous() or v.shape != k.shape:
         raise TypeError("key and value caches must be contiguous, of one dtype and one shape")
     for t, nm in ((ks, "k_scale"), (vs, "v_scale")):
         if t is not None:
@@ -423,9 +428,9 @@ def mfa_kv_append(ctx: MfaContext, x, w_kv, k_cache, v_cache, seq_lens, k_scale=
     _want(w_kv, torch.bfloat16, "w_kv")
     _want(seq_lens, torch.int32, "seq_lens")
     B = x.shape[0]
-    if tuple(x.shape) != (B, cfg.d_model) or tuple(w_kv.shape) != (cfg.d_model, 2 * cfg.head_dim) or \
+    if x.shape != (B, cfg.d_model) or w_kv.shape != (cfg.d_model, 2 * cfg.head_dim) or \
             k_cache.dim() != 3 or k_cache.shape[0] != B or k_cache.shape[2] != _cache_width(cfg, _kv_dtype(k_cache)) or \
-            tuple(seq_lens.shape) != (B,):
+            seq_lens.shape != (B,):
         raise ValueError("kv append shapes do not match")
     kvd = _check_cache_pair(k_cache, v_cache, k_scale, v_scale, k_cache.shape[:2])
     _check(lib().mfa_kv_append(ctx.handle, _ptr(x), _ptr(w_kv), kvd, _ptr(k_cache), _ptr(v_cache), _ptr(k_scale),
@@ -442,9 +447,9 @@ def mfa_kv_append_paged(ctx: MfaContext, x, w_kv, k_pool, v_pool, block_table, s
     _want(block_table, torch.int32, "block_table")
     B = x.shape[0]
     n_pages = k_pool.shape[0]
-    if tuple(x.shape) != (B, cfg.d_model) or tuple(w_kv.shape) != (cfg.d_model, 2 * cfg.head_dim) or \
-            tuple(k_pool.shape) != (n_pages, cfg.page_size, _cache_width(cfg, _kv_dtype(k_pool))) or \
-            block_table.shape[0] != B or tuple(seq_lens.shape) != (B,):
+    if x.shape != (B, cfg.d_model) or w_kv.shape != (cfg.d_model, 2 * cfg.head_dim) or \
+            k_pool.shape != (n_pages, cfg.page_size, _cache_width(cfg, _kv_dtype(k_pool))) or \
+            block_table.shape[0] != B or seq_lens.shape != (B,):
         raise ValueError("paged kv append shapes do not match")
     kvd = _check_cache_pair(k_pool, v_pool, k_scale_pool, v_scale_pool, k_pool.shape[:2])
     _check(lib().mfa_kv_append_paged(ctx.handle, _ptr(x), _ptr(w_kv), kvd, _ptr(k_pool), _ptr(v_pool), _ptr(k_scale_pool),
@@ -471,7 +476,7 @@ def mfa_out_proj(ctx: MfaContext, attn_out, w_o, y=None):
     _want(w_o, torch.bfloat16, "w_o")
     B = attn_out.shape[0]
     n_in = cfg.n_q_heads * cfg.head_dim
-    if attn_out.numel() != B * n_in or tuple(w_o.shape) != (n_in, cfg.d_model):
+    if attn_out.numel() != B * n_in or w_o.shape != (n_in, cfg.d_model):
         raise ValueError("output projection shapes do not match")
     if y is None:
         y = torch.empty(B, cfg.d_model, dtype=torch.bfloat16, device=attn_out.device)
