@@ -89,15 +89,14 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
     // disagrees (ragged lengths), the right tile goes into the other slot and the guessed one is never looked
     // at; the guess only ever names whole tiles below the hint, i.e. memory the caller has vouched for.
     stage_lengths(a, lds_base, kBf16SchedOffset);
-    const FirstTileGuess guess = guess_first_tile(a);
+    const FirstTileGuess guess = guess_first_tile(a, kBf16Switch);
     if (guess.valid) {
         Segment gs;
         gs.b = guess.b; gs.t0 = guess.t0; gs.t1 = guess.t0 + kTile;
         issue_tile(gs, 0, 0, lookup_page<PAGED>(a, guess.b, guess.t0), true);   // kLoadsPerTileAndWave loads
     }
-    Lengths lens;
-    staged_lengths<kLoadsPerTileAndWave>(a, lds_base, kBf16SchedOffset, guess.valid, lens);
-    Schedule sched = schedule_begin<kAttnThreads>(a, lds_base, kBf16SchedOffset, lens);
+    await_lengths<kLoadsPerTileAndWave>(a, guess.valid);
+    Schedule sched = schedule_begin<kAttnThreads>(a, lds_base, kBf16SchedOffset, kBf16Switch);
     Segment r, r_next;
     if (!schedule_next<kAttnThreads>(a, sched, r)) {
         wait_vmem_all();                              // nothing may still be writing into this workgroup's LDS when it ends
@@ -111,6 +110,7 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
         issue_tile(r, 0, slot0, lookup_page<PAGED>(a, r.b, r.t0));
     }
     for (bool more = true; more;) {
+        schedule_record(a, sched, r);
         const int end_mine = r.len - (a.q_len - 1 - a.q0 - grp);      // QL == 2: grp = query token of the pair
         const int t1_mine = QL == 2 ? (r.t1 < end_mine ? r.t1 : end_mine) : r.t1;
         WaveState st;

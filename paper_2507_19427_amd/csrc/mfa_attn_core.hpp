@@ -312,6 +312,7 @@ struct Segment {
     int b, t0, t1, n_tiles, slot;
     int len;              // the sequence's (clamped) length
     bool final_result;
+    int seq_end;          // balanced schedule: the tiles up to the end of its sequence if it holds the sequence's first, else 0
 };
 
 // Every field of a segment is the same in all threads; saying so keeps the branches on them scalar.
@@ -324,6 +325,7 @@ __device__ __forceinline__ void make_uniform(Segment& r)
     r.slot = __builtin_amdgcn_readfirstlane(r.slot);
     r.len = __builtin_amdgcn_readfirstlane(r.len);
     r.final_result = __builtin_amdgcn_readfirstlane((int)r.final_result) != 0;
+    r.seq_end = __builtin_amdgcn_readfirstlane(r.seq_end);
 }
 
 // xbase: LDS byte offset of the 64 KB the exchange may use (tile memory nobody reads any more).
@@ -392,7 +394,8 @@ __device__ __forceinline__ int clamped_len(const AttnArgs& a, int b)
 // Fixed splits (n_wgs == 0): workgroup = (sequence, split), one segment of chunk_tokens tokens;
 // the partial slot is the workgroup index; the first split of an empty sequence writes the zeros.
 //
-// Balanced (n_wgs > 0): with T_b = ceil(L_b / 64) tiles per sequence and P the exclusive prefix
+// Balanced (n_wgs > 0): with T_b = ceil(L_b / 64) tiles per sequence (and, where sequences begin in mid-range, the pad that
+// stands for the cost of a switch ahead of them: batches of up to 512 sequences) and P the exclusive prefix
 // sums of T, workgroup w takes the tile range [w*N/G, (w+1)*N/G) of the N = P[B] tiles laid end to
 // end (G = min(n_wgs, N), so that no workgroup below G is idle) and cuts it at sequence boundaries.  The workgroups touching sequence b are
 // consecutive, first(b)..last(b) with wg_of(t) = ((t+1)*G - 1) / N; the segment of workgroup w on
@@ -414,7 +417,18 @@ constexpr int kSlotBytes = 2 * kUnitBytes;            // one 64-token tile: two 
 constexpr int kBf16SchedOffset = 2 * kSlotBytes + 1024;
 constexpr int kBf16LdsBytes = kBf16SchedOffset + kSchedLdsBytes;
 
+// What starting on another sequence costs a workgroup, in tiles' worth of time (end of a segment, its result, and the start of the next
+// with nothing in flight; decode_bf16_kernel has the next tile on its way already).  The schedule lays that many tiles ahead of every sequence's
+// own, so that a range which holds a boundary holds fewer tiles: without them the few workgroups with two segments decide the time.  us per
+// call without / with, lengths drawn from 1 .. the longest: 8 bit 40 x 9000 42.3 / 31.7, 100 x 5000 52.8 / 43.7, 60 x 12000 60.3 / 50.5,
+// 23 x 20011 44.4 / 39.5; 4 bit 40 x 9000 38.6 / 28.6; 8 bit, two tokens, 60 x 6000 59.6 / 49.5; bf16, three tokens 16 x 4096 46.1 / 37.3, four
+// 30 x 3000 53.7 / 41.9; bf16 128 x 8192 paged 123.0 / 121.2.  Half or one and a half times as many: within 3 %.
+constexpr int kBf16Switch = 2;
+constexpr int kShortLowbitSwitch = 6;
+constexpr int kLowbitSwitch = 8;
+constexpr int kMultiSwitch = 3;
 struct Schedule {
+    int pad;            // tiles laid ahead of every sequence's own (what a switch costs), or 0
     int lo, hi;         // balanced: my tile range (lo moves on as segments are handed out); fixed: hi > lo while my one segment is still to do
     int n_tiles_all;    // N
     int n_wgs;          // G: workgroups that have a range (min of the grid size and N)
@@ -433,15 +447,20 @@ __device__ __forceinline__ unsigned div_floor_u32(unsigned a, unsigned d)
     else if (prod + d <= a) ++q;
     return q;
 }
-// floor(x * N / G) and the workgroup of a tile, in 32 bits when the products fit.
+// floor(x * N / G), in 32 bits when the products fit.  The common cases are no division: fewer tiles than workgroups (G = N), and
+// a workgroup per compute unit (G = 256).
 __device__ __forceinline__ int scaled_floor(int x, int N, int G)
 {
-    if (N < (1 << 20) && x <= (1 << 11)) return (int)div_floor_u32((unsigned)x * (unsigned)N, (unsigned)G);
+    if (G == N) return x;
+    const bool small = N < (1 << 20) && x <= (1 << 11);
+    if (small && (G & (G - 1)) == 0) return (int)(((unsigned)x * (unsigned)N) >> __builtin_ctz(G));
+    if (small) return (int)div_floor_u32((unsigned)x * (unsigned)N, (unsigned)G);
     return (int)((unsigned long long)x * (unsigned long long)N / (unsigned long long)G);
 }
 // ((t + 1) * G - 1) / N: at most G <= 4096, so a double-precision estimate is off by at most one whatever the size of the product.
 __device__ __forceinline__ int wg_of_tile(int t, int G, int N)
 {
+    if (G == N) return t;
     asm volatile("" : "+s"(N));                       // (formed where it is used, once per sequence, not ahead of the segment loop)
     const unsigned long long a = ((unsigned long long)t + 1ull) * (unsigned)G - 1ull;
     unsigned q = (unsigned)((double)a * __builtin_amdgcn_rcp((double)N));
@@ -476,18 +495,26 @@ __device__ __forceinline__ int range_index()
     return (g & 7) == 0 ? (i & 7) * (g >> 3) + (i >> 3) : i;
 }
 
+// Sequences of one length: do they all start where a range does?  (Then nobody switches in mid-range.)
+__device__ __forceinline__ bool boundaries_on_edges(int B, int n_wgs) { return (B & (B - 1)) == 0 && (n_wgs & (n_wgs - 1)) == 0; }
+
 // All threads of the workgroup call this; the values returned are the same in every thread.
 //
-// Batches of up to 512 sequences: every wave scans the whole batch by itself (eight lengths per lane at most), so the way
+// Batches of up to 512 sequences: every wave scans the whole batch by itself (64 lengths at a time), so the way
 // to a workgroup's first segment crosses no barrier.  Larger batches: one cooperative scan, a run of consecutive
 // sequences per thread.  Only the first sequence of a range is searched for; from there the lengths are read on as the segments
 // are handed out.
+//
+// All of this runs once per workgroup, ahead of its first load of cache rows, and comes cold from the instruction cache (about 100
+// cycles per 64 bytes): what it costs is its length in instructions.  Hence loops that are not unrolled, no division in the common
+// cases, and the merge's record written later (schedule_record).  From the lengths' arrival to the first segment, 128 sequences: 2.1 us
+// unrolled over eight groups of 64 with the lengths in registers and the record in between, 1.4 us now.
 constexpr int kWaveScanChunks = 8;
 // The lengths of such a batch reach the waves through LDS: every wave copies seq_lens[0 .. B) there with direct
 // loads (all waves write the same bytes to the same place, so a wave that has waited for its own loads has the
 // lengths without a barrier).  Direct loads are counted like every vector-memory operation but wait for nothing
 // themselves, so a kernel can ask for the lengths, then for its first tile, and work the schedule out as soon as
-// the lengths -- the older loads -- are there: stage_lengths(), further loads, staged_lengths(.., loads issued
+// the lengths -- the older loads -- are there: stage_lengths(), further loads, await_lengths(.., loads issued
 // since).
 static_assert(kWaveScanChunks * 256 <= kSchedTotals, "staged lengths");
 __device__ __forceinline__ bool lengths_are_staged(const AttnArgs& a) { return a.n_wgs != 0 && a.B <= kWaveScanChunks * 64; }
@@ -495,77 +522,81 @@ __device__ __forceinline__ void stage_lengths(const AttnArgs& a, lds_ptr_t lds_b
 {
     if (!lengths_are_staged(a)) return;
     const int lane = threadIdx.x & 63;
-    const uint32_t dst = (uint32_t)(uintptr_t)lds_base + base;
-#pragma unroll
-    for (int c = 0; c < kWaveScanChunks; ++c)
-        if (c * 64 < a.B) {
-            const int i = c * 64 + lane < a.B ? c * 64 + lane : a.B - 1;      // lanes past the batch repeat its last entry
-            load_to_lds_4B(a.seq_lens, (uint32_t)i * 4u, dst + c * 256);
-        }
+    uint32_t dst = (uint32_t)(uintptr_t)lds_base + base;
+#pragma unroll 1
+    for (int c0 = 0; c0 < a.B; c0 += 64, dst += 256) {
+        const int i = c0 + lane < a.B ? c0 + lane : a.B - 1;              // lanes past the batch repeat its last entry
+        load_to_lds_4B(a.seq_lens, (uint32_t)i * 4u, dst);
+    }
 }
-// The same lengths in registers: lane l of a wave holds those of sequences 64c + l.
-struct Lengths { int v[kWaveScanChunks]; };
 // LATER: vector-memory operations this wave has issued since stage_lengths when `later` (a tile asked for ahead)
 template <int LATER>
-__device__ __forceinline__ void staged_lengths(const AttnArgs& a, lds_ptr_t lds_base, int base, bool later, Lengths& lens)
+__device__ __forceinline__ void await_lengths(const AttnArgs& a, bool later)
 {
     if (!lengths_are_staged(a)) return;
     // the staged lengths have landed once only the loads issued after them are outstanding
     if (later) wait_vmem_but<LATER>();
     else       wait_vmem_but<0>();
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int c = 0; c < kWaveScanChunks; ++c) {
-        lens.v[c] = 0;
-        if (c * 64 < a.B) lens.v[c] = *LDS_AT(int, lds_base, base + (c * 64 + lane) * 4);
-    }
 }
 template <int THREADS>
-__device__ __forceinline__ Schedule schedule_begin(const AttnArgs& a, lds_ptr_t lds_base, int base, const Lengths& lens)
+__device__ __forceinline__ Schedule schedule_begin(const AttnArgs& a, lds_ptr_t lds_base, int base, int switch_tiles)
 {
     Schedule s;
-    s.b = s.seq0 = s.len = s.n_tiles_all = s.n_wgs = s.lo = s.my_lo = 0;
+    s.b = s.seq0 = s.len = s.n_tiles_all = s.n_wgs = s.lo = s.my_lo = s.pad = 0;
     s.hi = 1;
     if (a.n_wgs == 0) return s;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
 
     if (a.B <= kWaveScanChunks * 64) {
-        int len[kWaveScanChunks], p1[kWaveScanChunks];
-#pragma unroll
-        for (int c = 0; c < kWaveScanChunks; ++c) {
-            const int i = c * 64 + lane;
-            const int L = i < a.B ? lens.v[c] : 0;
-            len[c] = L < 0 ? 0 : (L > a.max_seq_len_hint ? a.max_seq_len_hint : L);
+        // lanes of the group of 64 sequences from c0 on: length, its tiles, and sums within the group up to and including the lane's
+        int len, x, incl, incl_seqs;
+        unsigned long long with_tiles;
+        auto scan = [&](int c0) {
+            const int i = c0 + lane;
+            const int L = *LDS_AT(int, lds_base, base + i * 4);
+            len = i >= a.B || L < 0 ? 0 : (L > a.max_seq_len_hint ? a.max_seq_len_hint : L);
+            x = (len + kTile - 1) / kTile;
+            incl = wave_inclusive_scan(x);
+            with_tiles = __ballot(x != 0);
+            incl_seqs = __builtin_amdgcn_mbcnt_hi((unsigned)(with_tiles >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)with_tiles, 0)) + (x != 0);
+        };
+        int c0 = 0, before = 0, before_seqs = 0, N = 0, n_seqs = 0;       // ahead of the group, and up to its end
+        int x_first = 0;
+        bool equal = true;
+#pragma unroll 1
+        for (;; c0 += 64) {
+            scan(c0);
+            if (c0 == 0) x_first = __builtin_amdgcn_readfirstlane(x);
+            equal &= !__ballot(x != x_first && c0 + lane < a.B);
+            before = N;
+            before_seqs = n_seqs;
+            N += __builtin_amdgcn_readlane(incl, 63);
+            n_seqs += __builtin_popcountll(with_tiles);
+            if (c0 + 64 >= a.B) break;
         }
-        int N = 0;
-#pragma unroll
-        for (int c = 0; c < kWaveScanChunks; ++c) {
-            p1[c] = N;
-            if (c * 64 < a.B) {
-                const int incl = wave_inclusive_scan((len[c] + kTile - 1) / kTile);
-                p1[c] = N + incl;                                      // P[i + 1]
-                N += __builtin_amdgcn_readlane(incl, 63);
-            }
-        }
+        const int w = range_index();
+        if (N > a.n_wgs && !(equal && boundaries_on_edges(a.B, a.n_wgs))) s.pad = switch_tiles;   // (up to a tile per workgroup nobody switches)
+        N += s.pad * n_seqs;
+        before += s.pad * before_seqs;
         const int G = a.n_wgs < N ? a.n_wgs : N;      // with fewer tiles than workgroups the last ones idle
         s.n_tiles_all = N;
         s.n_wgs = G;
-        if (range_index() >= G) { s.lo = s.hi = 0; return s; }
-        s.lo = s.my_lo = __builtin_amdgcn_readfirstlane(scaled_floor(range_index(), N, G));
-        s.hi = __builtin_amdgcn_readfirstlane(scaled_floor(range_index() + 1, N, G));
-#pragma unroll
-        for (int c = 0; c < kWaveScanChunks; ++c) {
-            if (c * 64 >= a.B) break;
-            const int x = (len[c] + kTile - 1) / kTile;
-            const unsigned long long hit = __ballot(p1[c] - x <= s.lo && s.lo < p1[c]);   // at most one lane of one chunk
-            if (hit) {
-                const int src = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
-                s.b = c * 64 + src;
-                s.seq0 = __builtin_amdgcn_readlane(p1[c], src) - __builtin_amdgcn_readlane(x, src);
-                s.len = __builtin_amdgcn_readlane(len[c], src);
-            }
+        if (w >= G) { s.lo = s.hi = 0; return s; }
+        s.lo = s.my_lo = __builtin_amdgcn_readfirstlane(scaled_floor(w, N, G));
+        s.hi = __builtin_amdgcn_readfirstlane(scaled_floor(w + 1, N, G));
+        // the one sequence with P[b] <= lo < P[b + 1], from the last group (still in registers) back
+#pragma unroll 1
+        while (before > s.lo) {
+            c0 -= 64;
+            scan(c0);
+            before -= __builtin_amdgcn_readlane(incl, 63) + s.pad * __builtin_popcountll(with_tiles);
         }
+        incl += s.pad * incl_seqs;
+        const int src = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(__ballot(before + incl > s.lo)));
+        s.b = c0 + src;
+        s.len = __builtin_amdgcn_readlane(len, src);
+        s.seq0 = before + __builtin_amdgcn_readlane(incl, src) - __builtin_amdgcn_readlane(x, src) - s.pad;
         return s;
     }
 
@@ -613,24 +644,40 @@ __device__ __forceinline__ Schedule schedule_begin(const AttnArgs& a, lds_ptr_t 
 // to the hint stays inside memory the caller has vouched for (rows below max_seq_len_hint of a sequence below B;
 // paged: a table entry below ceil(hint / 64), clamped into the pool like every other).
 struct FirstTileGuess { int b, t0; bool valid; };
-__device__ __forceinline__ FirstTileGuess guess_first_tile(const AttnArgs& a)
+__device__ __forceinline__ FirstTileGuess guess_first_tile(const AttnArgs& a, int switch_tiles)
 {
     FirstTileGuess gs;
     gs.b = gs.t0 = 0;
     gs.valid = false;
     if (!lengths_are_staged(a)) return gs;            // (the guess rides on the staged lengths' head start)
-    const int T = (a.max_seq_len_hint + kTile - 1) / kTile;
+    int T = (a.max_seq_len_hint + kTile - 1) / kTile;
+    const int pad = a.B * T > a.n_wgs && !boundaries_on_edges(a.B, a.n_wgs) ? switch_tiles : 0;
+    T += pad;
     const int N = a.B * T;
     const int G = a.n_wgs < N ? a.n_wgs : N;
     const int w = range_index();
     if (w >= G) return gs;
     const int lo = scaled_floor(w, N, G);
     gs.b = (int)div_floor_u32((unsigned)lo, (unsigned)T);
-    gs.t0 = (lo - gs.b * T) * kTile;
+    const int tile = lo - gs.b * T - pad;
+    gs.t0 = tile > 0 ? tile * kTile : 0;
     gs.b = __builtin_amdgcn_readfirstlane(gs.b);
     gs.t0 = __builtin_amdgcn_readfirstlane(gs.t0);
     gs.valid = gs.b < a.B && gs.t0 + kTile <= a.max_seq_len_hint;     // whole tiles only
     return gs;
+}
+
+// The holder of a sequence's first tile tells the merge which partial results there are.  Not needed before the segment's end: called
+// once its loads are on their way.
+__device__ __forceinline__ void schedule_record(const AttnArgs& a, const Schedule& s, const Segment& r)
+{
+    if (r.seq_end == 0) return;
+    const int first = range_index();
+    const int last = r.final_result ? first : wg_of_tile(r.seq_end - 1, s.n_wgs, s.n_tiles_all);
+    if (threadIdx.x == 0) {
+        a.ws_seg[2 * r.b] = first + r.b;
+        a.ws_seg[2 * r.b + 1] = last - first + 1;
+    }
 }
 
 // The next segment of this workgroup, or false when it has none left.  A false return for the very
@@ -651,6 +698,7 @@ __device__ __forceinline__ bool schedule_next(const AttnArgs& a, Schedule& s, Se
         r.len = L;
         r.slot = item;
         r.final_result = a.n_splits == 1;
+        r.seq_end = 0;
         if (r.t0 >= r.t1) {
             if (split == 0) {
                 float4* o = (float4*)(a.out + (size_t)r.b * kHeads * kHeadDim);
@@ -670,8 +718,10 @@ __device__ __forceinline__ bool schedule_next(const AttnArgs& a, Schedule& s, Se
         b = __builtin_amdgcn_readfirstlane(b + 1 + src);
         L = __builtin_amdgcn_readlane(ahead, __builtin_amdgcn_readfirstlane(src));
     }
-    const int seq0 = s.seq0, seq1 = seq0 + (L + kTile - 1) / kTile;
+    const int seq0 = s.seq0 + s.pad, seq1 = seq0 + (L + kTile - 1) / kTile;
     const int end = s.hi < seq1 ? s.hi : seq1;
+    if (s.lo < seq0) s.lo = seq0;
+    if (s.lo >= end) { s.lo = s.hi; return false; }                  // the range ends in what is laid ahead of the sequence
     r.b = b;
     r.t0 = (s.lo - seq0) * kTile;
     r.t1 = (end - seq0) * kTile < L ? (end - seq0) * kTile : L;
@@ -679,13 +729,7 @@ __device__ __forceinline__ bool schedule_next(const AttnArgs& a, Schedule& s, Se
     r.len = L;
     r.final_result = seq0 >= s.my_lo && seq1 <= s.hi;                // the whole sequence lies in my range
     r.slot = range_index() + b;
-    if (s.lo == seq0) {                                               // I hold its first tile: tell the merge
-        const int last = r.final_result ? range_index() : wg_of_tile(seq1 - 1, s.n_wgs, s.n_tiles_all);
-        if (threadIdx.x == 0) {
-            a.ws_seg[2 * b] = range_index() + b;
-            a.ws_seg[2 * b + 1] = last - range_index() + 1;
-        }
-    }
+    r.seq_end = s.lo == seq0 ? seq1 : 0;
     s.lo = end;
     s.seq0 = seq1;
     s.b = b + 1;

@@ -673,9 +673,8 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
     // changes nothing when they do -- 56.1 against 56.3 us, 64 x 8192 tokens at 8 bits -- and costs 1 .. 2.5 us
     // when they do not: the wrong 96 KB per workgroup come first.)
     stage_lengths(a, lds, S::kSchedBase);
-    Lengths lens;
-    staged_lengths<0>(a, lds, S::kSchedBase, false, lens);
-    Schedule sched = schedule_begin<kLowbitThreads>(a, lds, S::kSchedBase, lens);
+    await_lengths<0>(a, false);
+    Schedule sched = schedule_begin<kLowbitThreads>(a, lds, S::kSchedBase, kLowbitSwitch);
     Segment r;
     while (schedule_next<kLowbitThreads>(a, sched, r)) {
         const Span span = {r.b, r.t0, r.t1, r.n_tiles};
@@ -698,6 +697,7 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
         // Prologue: the start of the segment (the query is converted while its tiles are on their way), then the keys of one stage more.
         if (threadIdx.x == 0) *LDS_AT(int, lds, S::kFlag) = 0;
         request_start(span);
+        if (!retried) schedule_record(a, sched, r);
         wait_vmem_but<S::kDepth * S::kOps>();
         {
             int lane_now = lane;

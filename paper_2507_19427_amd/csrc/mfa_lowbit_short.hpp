@@ -304,9 +304,8 @@ __global__ __launch_bounds__(kAttnThreads) void short_lowbit_kernel(AttnArgs a)
     const int g = lane >> 4;
 
     stage_lengths(a, lds_base, kBf16SchedOffset);
-    Lengths lens;
-    staged_lengths<0>(a, lds_base, kBf16SchedOffset, false, lens);
-    Schedule sched = schedule_begin<kAttnThreads>(a, lds_base, kBf16SchedOffset, lens);
+    await_lengths<0>(a, false);
+    Schedule sched = schedule_begin<kAttnThreads>(a, lds_base, kBf16SchedOffset, kShortLowbitSwitch);
     Segment r;
     bool first_segment = true;
     while (schedule_next<kAttnThreads>(a, sched, r)) {
@@ -424,6 +423,7 @@ __global__ __launch_bounds__(kAttnThreads) void short_lowbit_kernel(AttnArgs a)
         store_tile(regs[0], 0);
         load_tile(regs[0], 2);
         issue_keys(1, 1);
+        schedule_record(a, sched, r);
 
         int kslot = 0;                                                     // t % 3
         auto step = [&](auto parity_c, int t) {

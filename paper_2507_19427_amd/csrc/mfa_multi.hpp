@@ -164,9 +164,8 @@ __global__ __launch_bounds__(kMultiThreads) __attribute__((amdgpu_waves_per_eu(1
     };
 
     stage_lengths(a, lds, kMultiSchedBase);
-    Lengths lens;
-    staged_lengths<0>(a, lds, kMultiSchedBase, false, lens);
-    Schedule sched = schedule_begin<kMultiThreads>(a, lds, kMultiSchedBase, lens);
+    await_lengths<0>(a, false);
+    Schedule sched = schedule_begin<kMultiThreads>(a, lds, kMultiSchedBase, kMultiSwitch);
     Segment r;
     while (schedule_next<kMultiThreads>(a, sched, r)) {
         // Every segment leaves a partial result, also one that covers its whole sequence; the merge kernel normalises
@@ -206,6 +205,7 @@ __global__ __launch_bounds__(kMultiThreads) __attribute__((amdgpu_waves_per_eu(1
                 load_unit(false, span, d, o, d);
                 load_unit(true, span, d, o, d);
             }
+            if (!retried) schedule_record(a, sched, r);
             wait_vmem_but<0>();
             __syncthreads();
 #pragma unroll

@@ -170,9 +170,8 @@ __global__ __launch_bounds__(kMultiThreads) void short_bf16_multi_kernel(AttnArg
     // A word of LDS behind the schedule's tables: set by a wave whose unit was refused (a score more than
     // 2^kFixedReferenceLag above its head's reference exponent), seen by all waves after the next barrier.
     stage_lengths(a, lds_base, kBf16SchedOffset);
-    Lengths lens;
-    staged_lengths<0>(a, lds_base, kBf16SchedOffset, false, lens);
-    Schedule sched = schedule_begin<kMultiThreads>(a, lds_base, kBf16SchedOffset, lens);
+    await_lengths<0>(a, false);
+    Schedule sched = schedule_begin<kMultiThreads>(a, lds_base, kBf16SchedOffset, kMultiSwitch);
     Segment r;
     bool first_segment = true;
     while (schedule_next<kMultiThreads>(a, sched, r)) {
@@ -183,6 +182,7 @@ __global__ __launch_bounds__(kMultiThreads) void short_bf16_multi_kernel(AttnArg
         // ordinary registers to be normalised.  The merge kernel normalises (AttnArgs::n_here >= 3).
         r.final_result = false;
         load_q(r);
+        schedule_record(a, sched, r);
         int t1_mine[kThree];
         float m_floor[kThree];                            // reference exponents handed to the next attempt (-inf: none)
 #pragma unroll
