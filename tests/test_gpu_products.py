@@ -62,3 +62,17 @@ def test_a_row_that_is_not_finite_stays_alone(B):
     assert torch.isnan(got[B // 2]).all()
     others = [i for i in range(B) if i != B // 2]
     assert torch.equal(got[others].view(torch.int16), clean[others].view(torch.int16))
+
+
+def test_rank_beyond_a_thread_group():
+    """A rank above four columns for each of 512 threads: the rows' further columns pass through LDS."""
+    B, d_model, rank = 3, 128, 2176
+    ctx = U.get_ctx(max_batch=256, max_seq_len=1024, d_model=d_model, q_rank=rank)
+    g = torch.Generator().manual_seed(5)
+    x = torch.randn(B, d_model, generator=g).to(torch.bfloat16)
+    w_qa, w_qb = ((torch.randn(k, n, generator=g) * 0.05).to(torch.bfloat16) for k, n in ((d_model, rank), (rank, 16384)))
+    gain = 1.0 + 0.1 * torch.randn(rank, generator=g)
+    q = mfa.mfa_query_proj(ctx, x.cuda(), w_qa.cuda(), w_qb.cuda(), rms_gain=gain.cuda()).float().cpu().numpy()
+    b = O.bits_of
+    _, q64, _ = O.query_proj(b(x), b(w_qa), b(w_qb), 1e-6, gain=gain.numpy(), want_f64=True)
+    assert U.row_normalised_error(q.reshape(-1, 256), np.asarray(q64).reshape(-1, 256)) <= TOL
