@@ -55,7 +55,8 @@ struct LowbitShape {
     static constexpr int kScaleStage = kTiles * kTile * 4;                // fp32 scales of one tensor of a stage (they come with the keys)
     static constexpr int kKScaleBase = kVBase + kSlots * kStageBytes;
     static constexpr int kVScaleBase = kKScaleBase + kSlots * kScaleStage;
-    static constexpr int kFlag = kVScaleBase + kSlots * kScaleStage;      // restart flag
+    static constexpr int kKcBase = kVScaleBase + kSlots * kScaleStage;    // key scales of the tile a wave is at, times the softmax scale: 256 bytes per wave
+    static constexpr int kFlag = kKcBase + 4 * kTile * 4;                 // restart flag
     static constexpr int kSchedBase = kFlag + 16;
     // Four areas of 32 query rows (16 KB; only used before the first tile): the slots no stage of the prologue lands in, then memory
     // of their own.
@@ -76,7 +77,7 @@ struct LowbitShape {
 // The query of one column, split into two e4m3 terms: q * 2^e = hi + lo with e chosen per head so that the largest |q|
 // of the head lands in [128, 256): hi is the nearest e4m3 value and lo the remainder, which e4m3 holds exactly (the 8
 // significant bits of bf16 are 4 + 4) down to 2^-9, i.e. to 2^-17 of the head's largest element.
-struct SplitQuery { i32x8 hi[4]; i32x8 lo[4]; float inv_scale; };        // [64-dim chunk]; inv_scale = 2^-e
+struct SplitQuery { i32x8 hi[4]; i32x8 lo[4]; int scale; };              // [64-dim chunk]; scale: 2^-e as the matrix instruction's scale operand takes it
 
 // max over the two lanes {n, n + 32} that hold one column
 __device__ __forceinline__ float half_max(float x)
@@ -135,7 +136,8 @@ __device__ __forceinline__ void split_query(SplitQuery& q, lds_ptr_t lds, int in
     const float amax = half_max(__uint_as_float((uint32_t)(top[0] > top[1] ? top[0] : top[1]) << 16));
     int e = (int)((__float_as_uint(amax) >> 23) & 0xFFu);          // biased exponent of the largest element
     e = e < 24 ? 24 : e;                                           // (all-zero or vanishing heads: any scale will do)
-    q.inv_scale = __uint_as_float((uint32_t)(e - 7) << 23);        // amax / inv_scale in [128, 256)
+    q.scale = e - 7;
+    const float inv_scale = __uint_as_float((uint32_t)(e - 7) << 23);   // 2^-e: amax / inv_scale in [128, 256)
 #pragma unroll 1
     for (int c = QL == 1 ? 2 * grp : 0; c < (QL == 1 ? 2 * grp + 2 : 4); ++c) {
         u32x4 hi4[2], lo4[2];
@@ -145,15 +147,15 @@ __device__ __forceinline__ void split_query(SplitQuery& q, lds_ptr_t lds, int in
 #pragma unroll
             for (int w = 0; w < 2; ++w) {
                 const uint32_t u0 = x[2 * w], u1 = x[2 * w + 1];
-                s16x2 hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16((s16x2){0, 0}, __builtin_bit_cast(bf16x2, u0), q.inv_scale, false);
-                hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(hi, __builtin_bit_cast(bf16x2, u1), q.inv_scale, true);
+                s16x2 hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16((s16x2){0, 0}, __builtin_bit_cast(bf16x2, u0), inv_scale, false);
+                hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(hi, __builtin_bit_cast(bf16x2, u1), inv_scale, true);
                 const int hi_bits = __builtin_bit_cast(int, hi);
-                const f32x2 b01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi_bits, q.inv_scale, false);
-                const f32x2 b23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi_bits, q.inv_scale, true);
+                const f32x2 b01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi_bits, inv_scale, false);
+                const f32x2 b23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi_bits, inv_scale, true);
                 s16x2 lo = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32((s16x2){0, 0}, __uint_as_float(u0 << 16) - b01[0],
-                                                                    __uint_as_float(u0 & 0xFFFF0000u) - b01[1], q.inv_scale, false);
+                                                                    __uint_as_float(u0 & 0xFFFF0000u) - b01[1], inv_scale, false);
                 lo = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(lo, __uint_as_float(u1 << 16) - b23[0],
-                                                              __uint_as_float(u1 & 0xFFFF0000u) - b23[1], q.inv_scale, true);
+                                                              __uint_as_float(u1 & 0xFFFF0000u) - b23[1], inv_scale, true);
                 hi4[i >> 1][2 * (i & 1) + w] = (uint32_t)hi_bits;
                 lo4[i >> 1][2 * (i & 1) + w] = __builtin_bit_cast(uint32_t, lo);
             }
@@ -222,10 +224,15 @@ __device__ __forceinline__ LowbitLanes<BITS> lowbit_lanes(int lane)
 // where on sums could leave fp32, and a lower reference is to blame: 2^24 tokens times the largest code, 448, stay finite
 // below 2^95.
 constexpr float kLargeWeight = 1.2089258e24f;        // 2^80
+// The true maximum is tracked from the reference on (an exponent is one fused multiply-add), so a reference far below the scores that count would
+// hide them in its own rounding: a first tile below kLowestReference leaves none (-inf: exponents from 0 on), and the restart
+// takes the maximum as it is.  Below kLowestScore a score is no more than -inf (differences between such scores are rounding).
+constexpr float kLowestReference = -16777216.0f;     // -2^24: rounded to at most 1
+constexpr float kLowestScore = -1.2676506e30f;       // -2^100
 struct LowbitState {
     f32x16 acc[8];       // [32-dim block]; element i: d = 32*db + 8*(i/4) + 4*h + i%4
     float m;             // reference exponent, log2 domain (-inf: the column has no token here)
-    float s_max;         // this lane's largest score so far, key scale applied (not yet c)
+    float s_max;         // this lane's largest score so far, log2 domain, from the reference on (from 0 on while that is -inf)
     float w_top;         // this lane's largest weight times value scale so far (magnitude)
     float l;             // this lane's share of the sum of weights
 };
@@ -241,19 +248,23 @@ struct SplitWeights { i32x8 hi, lo; int e_hi, e_lo; };                 // value 
 template <int BITS> struct KeyOperand { typedef i32x8 type; };
 template <> struct KeyOperand<4> { typedef u32x4 type; };
 template <int BITS> using OperandA = typename KeyOperand<BITS>::type;                     // 32 bytes (8 bit) or 16 bytes per lane
+// (the scale operand of A is the unit scale, E8M0 127; the query's is its head's 2^-e, so that all columns' scores come in one unit)
 template <int BITS>
-__device__ __forceinline__ void mfma_scores_first(f32x16& d, const OperandA<BITS>& a, const i32x8& b)
+__device__ __forceinline__ void mfma_scores_first(f32x16& d, const OperandA<BITS>& a, const i32x8& b, int one, int b_scale)
 {
-    if constexpr (BITS == 8) asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
-    else                     asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0 cbsz:4" : "=&v"(d) : "v"(a), "v"(b));
+    if constexpr (BITS == 8)
+        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, 0, %3, %4 op_sel_hi:[0,0,0]" : "=&v"(d) : "v"(a), "v"(b), "v"(one), "v"(b_scale));
+    else
+        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, 0, %3, %4 op_sel_hi:[0,0,0] cbsz:4" : "=&v"(d) : "v"(a), "v"(b), "v"(one), "v"(b_scale));
 }
 template <int BITS>
-__device__ __forceinline__ void mfma_scores(f32x16& d, const OperandA<BITS>& a, const i32x8& b)
+__device__ __forceinline__ void mfma_scores(f32x16& d, const OperandA<BITS>& a, const i32x8& b, int one, int b_scale)
 {
-    if constexpr (BITS == 8) asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
-    else                     asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0 cbsz:4" : "+v"(d) : "v"(a), "v"(b));
+    if constexpr (BITS == 8)
+        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(d) : "v"(a), "v"(b), "v"(one), "v"(b_scale));
+    else
+        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0] cbsz:4" : "+v"(d) : "v"(a), "v"(b), "v"(one), "v"(b_scale));
 }
-// (the scale operand of A is the unit scale, E8M0 127)
 template <int BITS>
 __device__ __forceinline__ void mfma_output(f32x16& d, const OperandA<BITS>& a, const i32x8& b, int one, int b_scale)
 {
@@ -324,15 +335,16 @@ struct ValueReader {
 template <int BITS, class F>
 __device__ __forceinline__ void qk_tile(f32x16 (&s)[2], const SplitQuery& q, KeyReader<BITS>& keys, F&& beside)
 {
+    const int one = 0x7F;
     for_slots([&](auto k) {
         constexpr int f = k.value >> 1;
         __builtin_amdgcn_sched_barrier(0);
         if constexpr ((k.value & 1) == 0) {
-            if constexpr (f < 2) mfma_scores_first<BITS>(s[f & 1], keys.f[f % 3], q.lo[f >> 1]);
-            else                 mfma_scores<BITS>(s[f & 1], keys.f[f % 3], q.lo[f >> 1]);
+            if constexpr (f < 2) mfma_scores_first<BITS>(s[f & 1], keys.f[f % 3], q.lo[f >> 1], one, q.scale);
+            else                 mfma_scores<BITS>(s[f & 1], keys.f[f % 3], q.lo[f >> 1], one, q.scale);
             if constexpr (f + 2 < 8) keys.read(f + 2);
         } else {
-            mfma_scores<BITS>(s[f & 1], keys.f[f % 3], q.hi[f >> 1]);
+            mfma_scores<BITS>(s[f & 1], keys.f[f % 3], q.hi[f >> 1], one, q.scale);
         }
         beside(k);
     }, std::make_integer_sequence<int, 16>{});
@@ -368,10 +380,9 @@ struct ScoresToWeights {
     f32x16 (&s)[2];
     float (&out)[32];
     LowbitState& st;
-    float c;                 // softmax scale * log2(e) * 2^-e of the head's query
     float m_safe;            // reference exponent, 0 for a column without tokens
     lds_ptr_t lds;
-    int ks_off, vs_off;      // LDS offsets of the tile's scales, this lane's half (+ 16*h) included
+    int ks_off, vs_off;      // LDS offsets of the tile's scales (the keys' times the softmax scale), this lane's half (+ 16*h) included
     int tok_left;            // t1 - tok0 - 4*h
     f32x4 ksc[3], vsc[3];    // of tokens 8i + 4h .. (values 4i ..) at [i % 3]: read two groups ahead
     float w_max, psum[2];
@@ -388,32 +399,31 @@ struct ScoresToWeights {
         w_max = psum[0] = psum[1] = 0.f;
     }
     __device__ __forceinline__ float masked(float x, int v) const { return MASKED && 8 * (v >> 2) + (v & 3) >= tok_left ? -INFINITY : x; }
-    __device__ __forceinline__ void weigh(float x0, float x1, int v)
+    __device__ __forceinline__ void weigh(float x0, float x1, int v)      // scores from the reference on
     {
-        const float p0 = fast_exp2(__builtin_fmaf(x0, c, -m_safe));
-        const float p1 = fast_exp2(__builtin_fmaf(x1, c, -m_safe));
-        psum[0] += p0;
-        psum[1] += p1;
+        const float p0 = fast_exp2(x0);
+        const float p1 = fast_exp2(x1);
         float y0 = p0 * vsc[(v >> 2) % 3][v & 3];
         float y1 = p1 * vsc[(v >> 2) % 3][(v & 3) + 1];
         pin(y0);
         pin(y1);
+        // (the sums stand between the pinned weights and their first reader: the compiler puts a wait state where an instruction reads what the
+        // one before it, an assembly block, has written)
+        psum[0] += p0;
+        psum[1] += p1;
+        pin(psum[0]);
+        pin(psum[1]);
         w_max = fmaxf(fmaxf(w_max, fabsf(y0)), fabsf(y1));
         out[v] = y0;
         out[v + 1] = y1;
         pin(w_max);
-        pin(psum[0]);
-        pin(psum[1]);
     }
     template <int K> __device__ __forceinline__ void step(Slot<K>)
     {
         constexpr int v = 2 * K;
         if constexpr ((K & 1) == 0 && K / 2 + 2 < 8) read(K / 2 + 2);
-        float x0 = s[v >> 4][v & 15], x1 = s[v >> 4][(v & 15) + 1];
-        pin(x0);
-        pin(x1);
-        x0 = masked(x0 * ksc[(v >> 2) % 3][v & 3], v);
-        x1 = masked(x1 * ksc[(v >> 2) % 3][(v & 3) + 1], v + 1);
+        const float x0 = masked(__builtin_fmaf(s[v >> 4][v & 15], ksc[(v >> 2) % 3][v & 3], -m_safe), v);
+        const float x1 = masked(__builtin_fmaf(s[v >> 4][(v & 15) + 1], ksc[(v >> 2) % 3][(v & 3) + 1], -m_safe), v + 1);
         st.s_max = fmaxf(fmaxf(st.s_max, x0), x1);
         pin(st.s_max);
         weigh(x0, x1, v);
@@ -442,12 +452,16 @@ struct ScoresToWeights {
         }
 #pragma unroll
         for (int v = 0; v < 32; ++v) st.s_max = fmaxf(st.s_max, out[v]);
-        if (st.m == -INFINITY) st.m = half_max(st.s_max) * c;                  // (c > 0)
+        if (st.m == -INFINITY) {
+            const float top = half_max(st.s_max);
+            st.m = top < kLowestReference ? -INFINITY : top;
+        }
         m_safe = st.m == -INFINITY ? 0.f : st.m;
+        st.s_max -= m_safe;
 #pragma unroll
         for (int v = 0; v < 32; v += 2) {
             if ((v & 3) == 0) vsc[(v >> 2) % 3] = *LDS_AT(f32x4, lds, vs_off + (v >> 2) * 32);
-            weigh(out[v], out[v + 1], v);
+            weigh(out[v] - m_safe, out[v + 1] - m_safe, v);
         }
         sum_up();
     }
@@ -458,7 +472,7 @@ struct ScoresToWeights {
 // hi keeps 4 significant bits, the remainder (at most half a step of hi) 4 more and its sign: at least the 8 bits of a bf16
 // weight down to 2^-13 of the tile's largest (where hi becomes subnormal), below that an error of at most 2^-22 of the
 // largest (half a subnormal step of lo).  A bf16 weight would keep its 8 bits there too; it shows only in dims where the heavy
-// tokens' codes are 0 (test_light_tokens_beside_a_heavy_one).  scale() picks k, step(i), i = 0 .. 7, converts four values.
+// tokens' codes are 0 (test_light_tokens_beside_a_heavy_one).  scale() picks k, steps i = 0 .. 7 convert the 32 values.
 struct WeightsToOperands {
     float (&p)[32];
     SplitWeights& w;
@@ -473,26 +487,40 @@ struct WeightsToOperands {
         s_hi = __uint_as_float((uint32_t)(e - 7) << 23);
         s_lo = __uint_as_float((uint32_t)(e - 12) << 23);
     }
-    // (one block: left to the compiler, every conversion comes with a cleared destination and a wait state of its own; the
-    // s_nop covers the half-register write ahead of its first reader)
+    // Two steps take eight values: the even one their first terms and what those stand for, the odd one the remainders.  Eight, so that
+    // each conversion has two others between the half-register write of its operand and itself (four at a time take wait states
+    // there; with those ahead of the first readers of pinned values, 4 bit, 128 x 8192 tokens: 80.1 us, without 78.1).  (One block: left to the compiler, every conversion comes with a cleared
+    // destination and a wait state of its own.)
+    f32x2 t[4];
     template <int I> __device__ __forceinline__ void step(Slot<I>)
     {
-        constexpr int i = 4 * I;
-        int hi, lo;
-        f32x2 t0, t1;
-        asm volatile("v_cvt_scalef32_pk_fp8_f32 %0, %3, %4, %7\n\t"
-                     "v_cvt_scalef32_pk_fp8_f32 %0, %5, %6, %7 op_sel:[0,0,0,1]\n\t"
-                     "s_nop 1\n\t"
-                     "v_cvt_scalef32_pk_f32_fp8 %1, %0, %7\n\t"
-                     "v_cvt_scalef32_pk_f32_fp8 %2, %0, %7 op_sel:[1,0,0]"
-                     : "=&v"(hi), "=&v"(t0), "=&v"(t1)
-                     : "v"(p[i]), "v"(p[i + 1]), "v"(p[i + 2]), "v"(p[i + 3]), "v"(s_hi));
-        float r0 = p[i] - t0[0], r1 = p[i + 1] - t0[1], r2 = p[i + 2] - t1[0], r3 = p[i + 3] - t1[1];
-        asm volatile("v_cvt_scalef32_pk_fp8_f32 %0, %1, %2, %5\n\t"
-                     "v_cvt_scalef32_pk_fp8_f32 %0, %3, %4, %5 op_sel:[0,0,0,1]"
-                     : "=&v"(lo) : "v"(r0), "v"(r1), "v"(r2), "v"(r3), "v"(s_lo));
-        w.hi[I] = hi;
-        w.lo[I] = lo;
+        constexpr int i = 8 * (I / 2);
+        if constexpr ((I & 1) == 0) {
+            int hi0, hi1;
+            asm volatile("v_cvt_scalef32_pk_fp8_f32 %0, %6, %7, %14\n\t"
+                         "v_cvt_scalef32_pk_fp8_f32 %0, %8, %9, %14 op_sel:[0,0,0,1]\n\t"
+                         "v_cvt_scalef32_pk_fp8_f32 %1, %10, %11, %14\n\t"
+                         "v_cvt_scalef32_pk_fp8_f32 %1, %12, %13, %14 op_sel:[0,0,0,1]\n\t"
+                         "v_cvt_scalef32_pk_f32_fp8 %2, %0, %14\n\t"
+                         "v_cvt_scalef32_pk_f32_fp8 %3, %0, %14 op_sel:[1,0,0]\n\t"
+                         "v_cvt_scalef32_pk_f32_fp8 %4, %1, %14\n\t"
+                         "v_cvt_scalef32_pk_f32_fp8 %5, %1, %14 op_sel:[1,0,0]"
+                         : "=&v"(hi0), "=&v"(hi1), "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3])
+                         : "v"(p[i]), "v"(p[i + 1]), "v"(p[i + 2]), "v"(p[i + 3]), "v"(p[i + 4]), "v"(p[i + 5]), "v"(p[i + 6]), "v"(p[i + 7]), "v"(s_hi));
+            w.hi[I] = hi0;
+            w.hi[I + 1] = hi1;
+        } else {
+            int lo0, lo1;
+            const float r0 = p[i] - t[0][0], r1 = p[i + 1] - t[0][1], r2 = p[i + 2] - t[1][0], r3 = p[i + 3] - t[1][1];
+            const float r4 = p[i + 4] - t[2][0], r5 = p[i + 5] - t[2][1], r6 = p[i + 6] - t[3][0], r7 = p[i + 7] - t[3][1];
+            asm volatile("v_cvt_scalef32_pk_fp8_f32 %0, %2, %3, %10\n\t"
+                         "v_cvt_scalef32_pk_fp8_f32 %0, %4, %5, %10 op_sel:[0,0,0,1]\n\t"
+                         "v_cvt_scalef32_pk_fp8_f32 %1, %6, %7, %10\n\t"
+                         "v_cvt_scalef32_pk_fp8_f32 %1, %8, %9, %10 op_sel:[0,0,0,1]"
+                         : "=&v"(lo0), "=&v"(lo1) : "v"(r0), "v"(r1), "v"(r2), "v"(r3), "v"(r4), "v"(r5), "v"(r6), "v"(r7), "v"(s_lo));
+            w.lo[I - 1] = lo0;
+            w.lo[I] = lo1;
+        }
     }
 };
 
@@ -686,7 +714,11 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
         auto tok_left = [&](int stage) { return t1_mine - (r.t0 + (S::kTiles * stage + my_tile) * kTile) - 4 * h; };
         auto k_of = [&](int slot) { return slot * S::kStageBytes + my_tile * S::kTileBytes; };
         auto v_of = [&](int slot) { return S::kVBase + slot * S::kStageBytes + my_tile * S::kTileBytes; };
-        auto ks_of = [&](int slot) { return S::kKScaleBase + slot * S::kScaleStage + my_tile * kTile * 4 + 16 * h; };
+        // Key scales of this wave's tile, times softmax scale * log2(e) (the query's 2^-e is in the scores already): a token's for every lane, so
+        // that a score becomes an exponent in one fused multiply-add.  Written and read by the wave itself: LDS keeps the order.
+        auto take_key_scale = [&](int slot) { return *LDS_AT(float, lds, S::kKScaleBase + slot * S::kScaleStage + my_tile * kTile * 4 + lane * 4); };
+        auto put_key_scale = [&](float ks) { *LDS_AT(float, lds, S::kKcBase + wave * kTile * 4 + lane * 4) = ks * a.scale_log2e; };
+        const int kc = S::kKcBase + wave * kTile * 4 + 16 * h;
         auto vs_of = [&](int slot) { return S::kVScaleBase + slot * S::kScaleStage + my_tile * kTile * 4 + 16 * h; };
 
         LowbitState st;
@@ -704,7 +736,6 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
             asm volatile("" : "+v"(lane_now));
             split_query<QL, BITS>(q, lds, q_in, q_out, grp, lane_now);
         }
-        const float c = a.scale_log2e * q.inv_scale;
         wait_vmem_but<0>();
         __syncthreads();
         StageOrigin o[2];                                              // of stages s + kDepth (values) and s + 1 + kDepth (keys)
@@ -726,9 +757,10 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
         keys.begin(k_of(0));
         {
             f32x16 sc[2];
+            put_key_scale(take_key_scale(0));
             qk_tile<BITS>(sc, q, keys, [](auto) {});
             scores_ready(sc);
-            ScoresToWeights<true> f{sc, wt, st, c, 0.f, lds, ks_of(0), vs_of(0), tok_left(0)};
+            ScoresToWeights<true> f{sc, wt, st, 0.f, lds, kc, vs_of(0), tok_left(0)};
             f.first();
             w_max = f.w_max;
             m_safe = f.m_safe;
@@ -750,12 +782,14 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
             constexpr bool STEADY = decltype(steady)::value;
             constexpr int kLoads = 2 * S::kTiles * S::kLoadsPerTile, kPerSlot = 2, kLoadSlots = STEADY ? kLoads / kPerSlot : 0;
             constexpr int kConvert = STEADY ? 7 : 2;                   // first slot of the conversion
+            constexpr int kKeyScale = 4;
             keys.begin(k_of(slot_next));
             f32x16 sc[2];
             SplitWeights w;
             WeightsToOperands f2{wt, w};
             ValueReader<BITS> values{ln, lds};
-            ScoresToWeights<!STEADY> f1{sc, wt, st, c, m_safe, lds, ks_of(slot_next), vs_of(slot_next), STEADY ? 0 : tok_left(s + 1)};
+            ScoresToWeights<!STEADY> f1{sc, wt, st, m_safe, lds, kc, vs_of(slot_next), STEADY ? 0 : tok_left(s + 1)};
+            float key_scale;
             const uint32_t k_dst = k_dst_of(slot), v_dst = v_dst_of(slot_prev);      // keys s + 1 + kDepth take the slot of keys s
             qk_tile<BITS>(sc, q, keys, [&](auto k) {
                 if constexpr (k.value < kLoadSlots)
@@ -763,6 +797,8 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
                 if constexpr (STEADY && k.value == kLoadSlots) load_scales(o[1], slot, (uint32_t)(4 * lane));
                 if constexpr (k.value == 0) f2.scale(w_max);
                 if constexpr (k.value >= kConvert && k.value < kConvert + 8) f2.step(Slot<k.value - kConvert>{});
+                if constexpr (k.value == kKeyScale) key_scale = take_key_scale(slot_next);
+                if constexpr (k.value == kKeyScale + 2) put_key_scale(key_scale);
                 if constexpr (k.value == 14) values.begin(v_of(slot));
                 if constexpr (k.value == 15) f1.begin();
             });
@@ -806,7 +842,8 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
         // A column whose largest score has outrun its reference too far: the workgroup streams the segment once more, the
         // maxima as references.  (A reference of -inf, left by a first tile of nothing but -inf, is outrun by any finite score;
         // a column without tokens has s_max = -inf too and keeps it.)
-        const float m_true = half_max(st.s_max) * c;
+        const float top = half_max(st.s_max) + m_safe;
+        const float m_true = top < kLowestScore ? -INFINITY : top;
         const bool outrun = !retried && (m_true > st.m + kFixedReferenceLag || (m_true > st.m && half_max(st.w_top) > kLargeWeight));
         if (outrun) *LDS_AT(int, lds, S::kFlag) = 1;
         __syncthreads();                              // every wave is done reading the tile memory

@@ -142,6 +142,22 @@ def test_scores_of_minus_infinity_ahead_of_finite_ones(kv_dtype, q_len, n_masked
 
 @pytest.mark.parametrize("q_len", [1, 2])
 @pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
+@pytest.mark.parametrize("k_scale", [1e3, 3e5, 3e7])
+@pytest.mark.parametrize("n_low", [64, 200, 4000])
+def test_far_lower_scores_ahead(kv_dtype, q_len, k_scale, n_low):
+    """Finite scores far below the rest begin every segment, to either side of 2^24 (where the rounding of an exponent reaches 1): their size
+    must not show in what follows.  Tolerance: as for scores of -inf."""
+    lens = [4100, 900, 300, 2000, 65]
+    case = W.make_contiguous_case("lowbitlow", 69, B=len(lens), S=max(lens), seq_lens=lens, kv_dtype=kv_dtype, poison=True)
+    for b, n in enumerate(lens):
+        n_here = min(n_low, n - 40)
+        _mask_tokens(case, b, n_here)
+        case.k_scale[b, :n_here] = k_scale if kv_dtype == "fp4" else k_scale / 64
+    _compare(case, q_len, 4100, (256, 7, 1), mask_dim=0, tol=2 * 2.0 ** -8)
+
+
+@pytest.mark.parametrize("q_len", [1, 2])
+@pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
 @pytest.mark.parametrize("vscale_log2", [40, 100, 110])
 def test_large_values_under_scores_that_grow(kv_dtype, q_len, vscale_log2):
     """Value scales far above 1 and a late token whose score lies some 2^36 above the first ones, which the reference exponent allows: the
