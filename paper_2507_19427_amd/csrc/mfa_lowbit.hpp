@@ -232,7 +232,7 @@ constexpr float kLowestScore = -1.2676506e30f;       // -2^100
 struct LowbitState {
     f32x16 acc[8];       // [32-dim block]; element i: d = 32*db + 8*(i/4) + 4*h + i%4
     float m;             // reference exponent, log2 domain (-inf: the column has no token here)
-    float s_max;         // this lane's largest score so far, log2 domain, from the reference on (from 0 on while that is -inf)
+    float s_max;         // this lane's largest score so far, log2 domain, from the reference on (from 0 on while that is -inf); decode_bf16_multi_kernel: the raw score
     float w_top;         // this lane's largest weight times value scale so far (magnitude)
     float l;             // this lane's share of the sum of weights
 };

@@ -89,17 +89,13 @@ struct MultiSoftmax {
     __device__ __forceinline__ float masked(float x, int i) const { return MASKED && 8 * (i >> 2) + (i & 3) >= tok_left ? -INFINITY : x; }
     template <int K> __device__ __forceinline__ void step(Slot<K>)
     {
-        float x0 = s[2 * K], x1 = s[2 * K + 1];
-        pin(x0);
-        pin(x1);
-        x0 = masked(x0, 2 * K);
-        x1 = masked(x1, 2 * K + 1);
-        st.s_max = fmaxf(fmaxf(st.s_max, x0), x1);
-        pin(st.s_max);
+        const float x0 = masked(s[2 * K], 2 * K), x1 = masked(s[2 * K + 1], 2 * K + 1);
         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
         const bf16x2 pb = {(__bf16)fast_exp2(__builtin_fmaf(x0, c, -m_safe)), (__bf16)fast_exp2(__builtin_fmaf(x1, c, -m_safe))};
         int bits = __builtin_bit_cast(int, pb);
         pin(bits);
+        st.s_max = fmaxf(fmaxf(st.s_max, x0), x1);    // (between the pinned weights and their first reader, which takes a wait state right behind them)
+        pin(st.s_max);
         st.l += __uint_as_float((uint32_t)bits << 16);
         st.l += __uint_as_float((uint32_t)bits & 0xFFFF0000u);
         pin(st.l);
