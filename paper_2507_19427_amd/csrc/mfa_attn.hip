@@ -158,25 +158,35 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
 //   out = sum_s 2^(m_s - m*) acc_s / sum_s 2^(m_s - m*) l_s,  m* = max_s m_s,
 // summed in split order (m* is reached batch by batch, rescaling what has been summed).  One thread per float4 of the partial's lane-order layout; splits are
 // taken four at a time so that their loads are independent and in flight together.
+//
+// merge_by_die: whether the blocks of a die take the sequences of that die (below).  Not with less than a tile for every compute unit, where a
+// sequence's many one-tile pieces lie on several dies anyway (5 x 1500 ragged: 16.7 us, in order 16.2), unless the batch divides evenly.
+__host__ __device__ __forceinline__ bool merge_by_die(int B, int n_wgs) { return n_wgs > 0 && (n_wgs & 7) == 0 && (n_wgs >= 256 || (B & 7) == 0); }
+// The first sequence of a die (die 8: the batch)
+__device__ __forceinline__ int first_of_die(int die, int B) { return (int)((2u * (unsigned)die * (unsigned)B + 7u) >> 4); }
 __global__ __launch_bounds__(256) void merge_splits_kernel(AttnArgs a)
 {
     const int n_here = a.n_here;                                      // query tokens of this launch
     // 16 blocks per (sequence, query token).  Consecutive block indices go to consecutive dies; the streaming kernel
     // has numbered its ranges so that a die holds consecutive ranges (range_index), i.e. with lengths that are about
-    // equal the partial results of row r of B * n_here were written on die r * 8 / (B * n_here): the blocks of a
-    // die take the rows of that die.
-    const unsigned rows = (unsigned)(a.B * n_here);
-    unsigned block = blockIdx.x;
-    if ((rows & 7u) == 0 && a.n_wgs > 0 && (a.n_wgs & 7) == 0 && gridDim.x == rows * 16u) {
-        const unsigned die = block & 7u, j = block >> 3;
-        block = (die * (rows >> 3) + (j >> 4)) * 16u + (j & 15u);
+    // equal the middle of sequence b was worked off on die (b + 1/2) * 8 / B: the blocks of a die take the sequences of that die.  us per
+    // call so, against rows in order unless the batch is a multiple of 8: 9 x 8000 27.3 / 31.9, 23 x 4096 28.4 / 33.0, 30 x 6000 ragged 31.9 / 36.0, 8 bit 9 x 12000
+    // ragged 23.8 / 28.8, 23 x 20011 ragged 35.3 / 39.2, 127 x 4000 ragged 44.0 / 45.1.  (Looked up in the records instead, which is exact for ragged
+    // lengths, with what a die has beyond its share given to others: the same for these, but 122.2 against 120.5 at 128 x 8192 ragged and 24.8
+    // against 22.6 at 128 x 400.)
+    int b, qtok, p;                                                   // query token of the launch; position in the partial's lane-order layout
+    if (merge_by_die(a.B, a.n_wgs)) {
+        const int die = blockIdx.x & 7, j = blockIdx.x >> 3, idx = j / (16 * n_here), rest = j - idx * 16 * n_here;
+        b = first_of_die(die, a.B) + idx;
+        if (b >= first_of_die(die + 1, a.B)) return;
+        qtok = rest >> 4;
+        p = (rest & 15) * 256 + threadIdx.x;
+    } else {
+        const int bq = (int)(blockIdx.x >> 4);                        // sequence * n_here + query token of the launch
+        b = bq / n_here;
+        qtok = bq - b * n_here;
+        p = (int)(blockIdx.x & 15) * 256 + threadIdx.x;
     }
-    const size_t idx = (size_t)block * 256 + threadIdx.x;             // over B * n_here * 4096 float4
-    const int p = (int)(idx & 4095);                                  // position in the partial's lane-order layout
-    const int bq = (int)(idx >> 12);                                  // sequence * n_here + query token of the launch
-    if (bq >= a.B * n_here) return;
-    const int b = bq / n_here;
-    const int qtok = bq - b * n_here;
     const int lane = p & 63;
     const int db = (p >> 6) & 15;
     const int wq = p >> 10;
@@ -398,7 +408,8 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
     // times at which that kernel starts and ends on the device, with no launch gap inside the interval.
     // (With more than two query tokens: the first pair's.)
     if (!(ev_before && ev_after)) ev_before = ev_after = nullptr;
-    const unsigned merge_blocks_per_token = (unsigned)(((size_t)a.B * kHeads * (kHeadDim / 4) + 255) / 256);
+    static_assert(kHeads * kHeadDim / 4 == 16 * 256, "sixteen blocks per row");
+    const unsigned merge_blocks_per_token = 16u * (unsigned)(merge_by_die(a.B, a.n_wgs) ? (a.B + 7) / 8 * 8 : a.B);
     // Three and four query tokens over a bf16 cache, batches the per-wave schedule covers: one pass over the cache
     // by the kernel that keeps all of a sequence's query tokens in one wave.
     if (a.q_len >= 3 && kv_dtype == MFA_KV_BF16 && a.B <= kWaveScanChunks * 64) {
