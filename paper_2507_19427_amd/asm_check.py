@@ -24,7 +24,7 @@ import re
 
 # decode_lowbit_kernel, by (cache bits, query tokens): vector-memory operations of a wave per stage (direct loads of keys and values and
 # one of scales: LowbitShape::kOps), and stages in flight beside the one awaited (kDepth - 1).
-LOWBIT_STEADY = {(8, 1): (17, 0), (4, 1): (9, 1), (8, 2): (9, 1), (4, 2): (5, 3)}
+LOWBIT_STEADY = {(8, 1): (17, 0), (4, 1): (9, 0), (8, 2): (9, 0), (4, 2): (5, 1)}
 # decode_bf16_multi_kernel: kMultiOps, kMultiDepth - 1
 MULTI_STEADY = (8, 1)
 # short_lowbit_kernel loads to registers in two unrolled steps, each of which waits for all but the youngest step's loads.

@@ -41,15 +41,17 @@ constexpr int kLowbitThreads = 256;
 
 // LDS of a workgroup.  A stage is the tiles the workgroup works on at a time (two for one query token, a tile per wave
 // pair; one for two).  Keys are used one iteration ahead of the values of the same tile: iteration s reads the keys of
-// stage s + 1 and the values of stage s, and requests keys s + 1 + kDepth and values s + kDepth; kDepth stages (64 KB of keys and
-// values per compute unit) are in flight.
+// stage s + 1 and the values of stage s, and requests keys s + 1 + kDepth and values s + kDepth.  kDepth stages are in
+// flight: 32 KB of keys and values per compute unit, 64 KB where one stage is as large (8 bit, one token).  64 KB everywhere,
+// against this, in us: 4 bit 60 x 12000 ragged 42.6 / 41.8, 100 x 5000 ragged 37.8 / 37.1, two tokens 40 x 7000 ragged 36.7 / 35.5;
+// 8 bit, two tokens 60 x 6000 ragged 45.3 / 44.6; equal lengths 0.3 .. 1 % slower.
 template <int QL, int BITS>
 struct LowbitShape {
     static constexpr int kTiles = QL == 1 ? 2 : 1;
     static constexpr int kRowBytes = BITS == 8 ? 256 : 128;              // one cached row of K or V
     static constexpr int kTileBytes = kTile * kRowBytes;
     static constexpr int kStageBytes = kTiles * kTileBytes;               // of K or of V
-    static constexpr int kDepth = 32768 / kStageBytes;
+    static constexpr int kDepth = kStageBytes >= 16384 ? 1 : 16384 / kStageBytes;
     static constexpr int kSlots = kDepth + 1;                             // (a stage in use beside those in flight)
     static constexpr int kVBase = kSlots * kStageBytes;
     static constexpr int kScaleStage = kTiles * kTile * 4;                // fp32 scales of one tensor of a stage (they come with the keys)
@@ -72,6 +74,7 @@ struct LowbitShape {
     static constexpr int kLoadsPerTile = kTileBytes / (4 * 1024);         // 1 KB direct loads of a wave per tile of K or V
     static constexpr int kOps = 2 * kTiles * kLoadsPerTile + 1;           // vector-memory operations of a wave per stage
     static_assert(kLdsBytes <= 160 * 1024, "LDS of a compute unit");
+    static_assert(QL == 2 || 4 * 16384 + 4 * 256 <= kKcBase, "the exchange at a segment's end fits the tiles and their scales");
 };
 
 // The query of one column, split into two e4m3 terms: q * 2^e = hi + lo with e chosen per head so that the largest |q|
@@ -525,7 +528,8 @@ struct WeightsToOperands {
 };
 
 // End of a segment, one query token: the two waves that share 32 columns (tp = 0, 1: the even and the odd tiles) exchange
-// halves of their accumulators through 64 KB of dead tile memory; tp 0 finishes dims 0..127, tp 1 the rest.
+// halves of their accumulators through 64 KB of dead tile memory (and 1 KB behind it: tiles or their scales, dead as
+// well); tp 0 finishes dims 0..127, tp 1 the rest.
 // Partials keep the lane-order layout of the other kernels (float4 index (head/16*16 + d/16)*64 + d/4%4*16 + head%16).
 __device__ __forceinline__ size_t partial_index(int head, int dq)           // dq = d / 4
 {
@@ -684,7 +688,7 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
     // (one query token: from area hh to area 2 + hh; two: area `wave`)
     const int q_in = QL == 1 ? (hh ? S::query_area(1) : S::query_area(0)) : wave == 0 ? S::query_area(0) : wave == 1 ? S::query_area(1) : wave == 2 ? S::query_area(2) : S::query_area(3);
     const int q_out = QL == 1 ? (hh ? S::query_area(3) : S::query_area(2)) : q_in;
-    // Everything a segment starts with: the query, then keys and values of the first kDepth stages (64 KB)
+    // Everything a segment starts with: the query, then keys and values of the first kDepth stages
     auto request_start = [&](const Span& g) {
         int lane_now = lane;
         asm volatile("" : "+v"(lane_now));
