@@ -17,12 +17,13 @@
 // k = 32*hi + 16*h + lo, element j of lane half h of a 4-bit operand is k = 32*h + j.  Two 8-bit operands therefore match
 // byte for byte; where a 4-bit operand meets an 8-bit one the rows or dims are chosen to match.
 //
-// What bounds it.  8 bit, one token: memory (a 128-token stage, 64 KB per compute unit, in 4400 cycles of the about 1.8 GHz the device
-// holds in this kernel: 6.9 TB/s).  4 bit: the matrix pipe, 2 x 16 instructions of 64 cycles per wave and stage, and what does
-// not hide behind it (3070 cycles per 128 tokens); two query tokens the same (3215 per 64 tokens).  About 9 us per launch go to the first segment's start (query
-// conversion 5000 cycles, lengths and schedule 6000, first tile alone 4000) and end, which is why launches with little work have a kernel of
+// What bounds it.  8 bit, one token: memory (6.9 TB/s in the steady stream).  4 bit, and two query tokens: the matrix pipe, 2 x 16
+// instructions of 64 cycles per wave and stage, and what does not hide behind it.  About 9 us per launch go to the first segment's
+// start and the end (8 bit, 128 x 8192 tokens, us from the first workgroup's start: first segment known 2.05, everything requested 4.0, query converted
+// 6.2, first tile done 8.4, last product 80.7, result stored 82.6), which is why launches with little work have a kernel of
 // their own.  Alternatives measured at 128 x 8192 tokens, 8 bit / 4 bit / 8 bit two tokens: values expanded to bf16 (the other
-// kernel) 114 / 95 / 175 us, this one 102 / 79 / 154; eight waves of 16 columns on these instructions 108 / 85 / 162.
+// kernel) 114 / 95 / 175 us, this one 102 / 79 / 154 and, with fewer wait states and the scales folded, 100 / 75 / 148;
+// eight waves of 16 columns on these instructions 108 / 85 / 162.
 // Error against 64 bits at 8192 tokens: 6.3e-4 of a row's largest element (bf16 weights: 1.7e-3).
 //
 // The accumulators are not rescaled (LowbitState): a segment in which a score outruns its first tile's by 2^40 is streamed twice, where the
