@@ -437,25 +437,24 @@ struct ScoresToWeights {
         st.l += psum[0] + psum[1];
         st.w_top = fmaxf(st.w_top, w_max);
     }
-    // The segment's first tile, in one go: sets the reference.
+    // The segment's first tile, in one go: sets the reference.  (Tokens past the end have a key scale of 1 here.)  The exponents are formed as in
+    // step(), one fused multiply-add from score and scale: a product rounded ahead of the subtraction would set tokens of this tile apart from
+    // equal ones of the next by the rounding of a large score.
     __device__ __forceinline__ void first()
     {
         w_max = psum[0] = psum[1] = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const f32x4 k4 = *LDS_AT(f32x4, lds, ks_off + i * 32);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                out[4 * i + j] = s[i >> 2][4 * (i & 3) + j] * k4[j];
-            }
-        }
         if (tok_left < kTile) {                       // (a real branch, and no comparison made ahead of it)
             asm volatile("" : "+v"(tok_left));
 #pragma unroll
-            for (int v = 0; v < 32; ++v) out[v] = masked(out[v], v);
+            for (int v = 0; v < 32; ++v) s[v >> 4][v & 15] = masked(s[v >> 4][v & 15], v);
         }
+        f32x4 k4[8];
 #pragma unroll
-        for (int v = 0; v < 32; ++v) st.s_max = fmaxf(st.s_max, out[v]);
+        for (int i = 0; i < 8; ++i) {
+            k4[i] = *LDS_AT(f32x4, lds, ks_off + i * 32);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) st.s_max = fmaxf(st.s_max, s[i >> 2][4 * (i & 3) + j] * k4[i][j]);
+        }
         if (st.m == -INFINITY) {
             const float top = half_max(st.s_max);
             st.m = top < kLowestReference ? -INFINITY : top;
@@ -465,7 +464,7 @@ struct ScoresToWeights {
 #pragma unroll
         for (int v = 0; v < 32; v += 2) {
             if ((v & 3) == 0) vsc[(v >> 2) % 3] = *LDS_AT(f32x4, lds, vs_off + (v >> 2) * 32);
-            weigh(out[v] - m_safe, out[v + 1] - m_safe, v);
+            weigh(__builtin_fmaf(s[v >> 4][v & 15], k4[v >> 2][v & 3], -m_safe), __builtin_fmaf(s[v >> 4][(v & 15) + 1], k4[v >> 2][(v & 3) + 1], -m_safe), v);
         }
         sum_up();
     }
@@ -762,7 +761,7 @@ __global__ __launch_bounds__(kLowbitThreads) __attribute__((amdgpu_waves_per_eu(
         keys.begin(k_of(0));
         {
             f32x16 sc[2];
-            put_key_scale(take_key_scale(0));
+            put_key_scale(lane < tok_left(0) + 4 * h ? take_key_scale(0) : 1.f);
             qk_tile<BITS>(sc, q, keys, [](auto) {});
             scores_ready(sc);
             ScoresToWeights<true> f{sc, wt, st, 0.f, lds, kc, vs_of(0), tok_left(0)};

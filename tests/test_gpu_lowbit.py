@@ -158,6 +158,29 @@ def test_far_lower_scores_ahead(kv_dtype, q_len, k_scale, n_low):
 
 @pytest.mark.parametrize("q_len", [1, 2])
 @pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
+@pytest.mark.parametrize("size_log2", [10, 20, 25, 28])
+def test_equal_scores_of_any_size_weigh_the_same(kv_dtype, q_len, size_log2):
+    """One key for all tokens, scores of either sign up to about 2^size: the result is the mean of the values, as it is for scores of 0, whether
+    a token's weight comes from the first tile of a segment or from a later one.  Tolerance: TOL, since a weight's rounding is that of all others."""
+    lens = [4100, 900, 300, 65]
+    case = W.make_contiguous_case("lowbitequal", 70, B=len(lens), S=max(lens), seq_lens=lens, kv_dtype=kv_dtype, poison=True)
+    for b, n in enumerate(lens):
+        case.k.view(torch.uint8)[b, :n] = 0x38 if kv_dtype == "fp8" else 0x22               # codes of 1
+        case.k_scale[b, :n] = 0.0
+    qm = W.make_multi_query(case, q_len, 41) if q_len > 1 else case.q.unsqueeze(1).contiguous()
+    ref = _oracle(case, qm)
+    for b, n in enumerate(lens):
+        case.k_scale[b, :n] = 1.1 * 2.0 ** size_log2 / 4                 # (the elements of a query sum to about 16, the softmax scale is 1/16)
+    for n_wgs in (7, 3, 1):
+        ctx = mfa.mfa_decode_init(mfa.MfaConfig(max_batch=16, max_seq_len=32768, target_workgroups=n_wgs))
+        err = U.row_normalised_error(_run(ctx, case, qm, max(lens)), ref)
+        print(f"[case] {kv_dtype} {q_len} query tokens, 2^{size_log2}, {n_wgs} workgroups: {err:.3e}", flush=True)
+        assert err <= TOL
+        ctx.close()
+
+
+@pytest.mark.parametrize("q_len", [1, 2])
+@pytest.mark.parametrize("kv_dtype", ["fp8", "fp4"])
 @pytest.mark.parametrize("vscale_log2", [40, 100, 110])
 def test_large_values_under_scores_that_grow(kv_dtype, q_len, vscale_log2):
     """Value scales far above 1 and a late token whose score lies some 2^36 above the first ones, which the reference exponent allows: the
