@@ -21,6 +21,7 @@
 #include <hip/hip_ext.h>
 
 #include "mfa_lowbit_short.hpp"
+#include "mfa_merge_place.hpp"
 #include "mfa_multi_short.hpp"
 
 namespace mfa {
@@ -159,34 +160,30 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
 // summed in split order (m* is reached batch by batch, rescaling what has been summed).  One thread per float4 of the partial's lane-order layout; splits are
 // taken four at a time so that their loads are independent and in flight together.
 //
-// merge_by_die: whether the blocks of a die take the sequences of that die (below).  Not with less than a tile for every compute unit, where a
-// sequence's many one-tile pieces lie on several dies anyway (5 x 1500 ragged: 16.7 us, in order 16.2), unless the batch divides evenly.
+// merge_by_die: whether the blocks of a die take the rows of that die (mfa_merge_place.hpp).  us per call so / with rows in order:
+//   one token    1 x 32768 45.2/49.3   2 x 32768 36.8/41.4   4 x 32768 39.2/43.9   9 x 8000 27.3/31.9   23 x 4096 28.4/33.0   30 x 6000 ragged 31.9/36.0
+//     8 bit, ragged   9 x 12000 23.8/28.8   23 x 20011 35.3/39.2   bf16   127 x 4000 44.0/45.1
+//   four tokens  1 x 32768 59.4/61.7   2 x 32768 54.3/55.2   4 x 25000 54.0/55.5   7 x 14285 54.1/55.0
+// With all tokens of a sequence on the die of its middle instead, four tokens took 81.6 at 1 x 32768, 63.7 at 2 x 32768, 57.9 at 4 x 25000 and 58.8 (now 55.1) at 9 x 11111 (up to three rows
+// of 16 blocks wait for one L2 while others idle).  Looked up in the records, which is exact for ragged lengths, with what a die has
+// beyond its share given to others: the same for most, but 122.2 against 120.5 at 128 x 8192 ragged and 24.8 against 22.6 at 128 x 400.
+// Not by die with less than a tile for every compute unit, where a sequence's many one-tile pieces lie on several dies anyway (5 x 1500
+// ragged: 16.7, in order 16.2), unless the batch divides evenly.
 __host__ __device__ __forceinline__ bool merge_by_die(int B, int n_wgs) { return n_wgs > 0 && (n_wgs & 7) == 0 && (n_wgs >= 256 || (B & 7) == 0); }
-// The first sequence of a die (die 8: the batch)
-__device__ __forceinline__ int first_of_die(int die, int B) { return (int)((2u * (unsigned)die * (unsigned)B + 7u) >> 4); }
 __global__ __launch_bounds__(256) void merge_splits_kernel(AttnArgs a)
 {
     const int n_here = a.n_here;                                      // query tokens of this launch
-    // 16 blocks per (sequence, query token).  Consecutive block indices go to consecutive dies; the streaming kernel
-    // has numbered its ranges so that a die holds consecutive ranges (range_index), i.e. with lengths that are about
-    // equal the middle of sequence b was worked off on die (b + 1/2) * 8 / B: the blocks of a die take the sequences of that die.  us per
-    // call so, against rows in order unless the batch is a multiple of 8: 9 x 8000 27.3 / 31.9, 23 x 4096 28.4 / 33.0, 30 x 6000 ragged 31.9 / 36.0, 8 bit 9 x 12000
-    // ragged 23.8 / 28.8, 23 x 20011 ragged 35.3 / 39.2, 127 x 4000 ragged 44.0 / 45.1.  (Looked up in the records instead, which is exact for ragged
-    // lengths, with what a die has beyond its share given to others: the same for these, but 122.2 against 120.5 at 128 x 8192 ragged and 24.8
-    // against 22.6 at 128 x 400.)
-    int b, qtok, p;                                                   // query token of the launch; position in the partial's lane-order layout
+    int row, p;                                                       // sequence * n_here + query token of the launch; position in the partial's lane-order layout
     if (merge_by_die(a.B, a.n_wgs)) {
-        const int die = blockIdx.x & 7, j = blockIdx.x >> 3, idx = j / (16 * n_here), rest = j - idx * 16 * n_here;
-        b = first_of_die(die, a.B) + idx;
-        if (b >= first_of_die(die + 1, a.B)) return;
-        qtok = rest >> 4;
-        p = (rest & 15) * 256 + threadIdx.x;
+        row = merge_row(blockIdx.x, a.B * n_here);
+        if (row < 0) return;
+        p = (int)((blockIdx.x >> 3) & 15) * 256 + threadIdx.x;
     } else {
-        const int bq = (int)(blockIdx.x >> 4);                        // sequence * n_here + query token of the launch
-        b = bq / n_here;
-        qtok = bq - b * n_here;
+        row = (int)(blockIdx.x >> 4);
         p = (int)(blockIdx.x & 15) * 256 + threadIdx.x;
     }
+    const int b = row / n_here;
+    const int qtok = row - b * n_here;
     const int lane = p & 63;
     const int db = (p >> 6) & 15;
     const int wq = p >> 10;
@@ -408,8 +405,8 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
     // times at which that kernel starts and ends on the device, with no launch gap inside the interval.
     // (With more than two query tokens: the first pair's.)
     if (!(ev_before && ev_after)) ev_before = ev_after = nullptr;
-    static_assert(kHeads * kHeadDim / 4 == 16 * 256, "sixteen blocks per row");
-    const unsigned merge_blocks_per_token = 16u * (unsigned)(merge_by_die(a.B, a.n_wgs) ? (a.B + 7) / 8 * 8 : a.B);
+    static_assert(kHeads * kHeadDim / 4 == kMergeBlocksPerRow * 256, "sixteen blocks per row");
+    auto merge_blocks = [&](int n_here) { return merge_by_die(a.B, a.n_wgs) ? merge_blocks_by_die(a.B * n_here) : (unsigned)(kMergeBlocksPerRow * a.B * n_here); };
     // Three and four query tokens over a bf16 cache, batches the per-wave schedule covers: one pass over the cache
     // by the kernel that keeps all of a sequence's query tokens in one wave.
     if (a.q_len >= 3 && kv_dtype == MFA_KV_BF16 && a.B <= kWaveScanChunks * 64) {
@@ -422,7 +419,7 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
         if (e != hipSuccess) return e;
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(merge_splits_kernel, dim3(merge_blocks_per_token * a.q_len), dim3(256), 0, stream, args);
+        hipLaunchKernelGGL(merge_splits_kernel, dim3(merge_blocks(a.q_len)), dim3(256), 0, stream, args);
         return hipGetLastError();
     }
     const bool short_work = kv_dtype != MFA_KV_BF16 && short_lowbit_work(a, kv_dtype);
@@ -442,7 +439,7 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (a.n_wgs > 0 || a.n_splits > 1) {
-            hipLaunchKernelGGL(merge_splits_kernel, dim3(merge_blocks_per_token * n_here), dim3(256), 0, stream, args);
+            hipLaunchKernelGGL(merge_splits_kernel, dim3(merge_blocks(n_here)), dim3(256), 0, stream, args);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
