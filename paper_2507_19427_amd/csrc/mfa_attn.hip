@@ -169,12 +169,19 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
 // beyond its share given to others: the same for most, but 122.2 against 120.5 at 128 x 8192 ragged and 24.8 against 22.6 at 128 x 400.
 // Not by die with less than a tile for every compute unit, where a sequence's many one-tile pieces lie on several dies anyway (5 x 1500
 // ragged: 16.7, in order 16.2), unless the batch divides evenly.
-__host__ __device__ __forceinline__ bool merge_by_die(int B, int n_wgs) { return n_wgs > 0 && (n_wgs & 7) == 0 && (n_wgs >= 256 || (B & 7) == 0); }
+bool merge_by_die(int B, int n_wgs) { return n_wgs > 0 && (n_wgs & 7) == 0 && (n_wgs >= 256 || (B & 7) == 0); }
+
+// With many short sequences nearly every block only finds that a workgroup has written its row's result, and what counts is the way there:
+// the rule is a template argument, the division by 1 .. 4 a shift or a multiplication, length and record one round trip.  us of the kernel
+// at 4000 / 512 sequences of one tile: 44.7 / 6.6 without these, 27.6 / 4.8 now.
+template <bool BY_DIE>                                                // (only under the balanced schedule)
 __global__ __launch_bounds__(256) void merge_splits_kernel(AttnArgs a)
 {
-    const int n_here = a.n_here;                                      // query tokens of this launch
+    const int n_here = a.n_here;                                      // query tokens of this launch, 1 .. 4
+    static_assert(kMaxQueryTokens == 4, "the division by n_here");
+    const bool balanced = BY_DIE || a.n_wgs > 0;
     int row, p;                                                       // sequence * n_here + query token of the launch; position in the partial's lane-order layout
-    if (merge_by_die(a.B, a.n_wgs)) {
+    if (BY_DIE) {
         row = merge_row(blockIdx.x, a.B * n_here);
         if (row < 0) return;
         p = (int)((blockIdx.x >> 3) & 15) * 256 + threadIdx.x;
@@ -182,7 +189,7 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(AttnArgs a)
         row = (int)(blockIdx.x >> 4);
         p = (int)(blockIdx.x & 15) * 256 + threadIdx.x;
     }
-    const int b = row / n_here;
+    const int b = n_here == 3 ? (int)((unsigned)row / 3u) : row >> (n_here >> 1);
     const int qtok = row - b * n_here;
     const int lane = p & 63;
     const int db = (p >> 6) & 15;
@@ -192,17 +199,16 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(AttnArgs a)
     // (the length and the sequence's slot record are asked for together: one round trip, not two; the record of
     // a sequence without tokens holds whatever the workspace held and is not used)
     int L = a.seq_lens[b];
-    const int rec_first = a.n_wgs > 0 ? a.ws_seg[2 * b] : 0;
-    const int rec_count = a.n_wgs > 0 ? a.ws_seg[2 * b + 1] : 0;
+    const int2 rec = balanced ? ((const int2*)a.ws_seg)[b] : make_int2(0, 0);      // first slot, number of partials
     L = L < 0 ? 0 : (L > a.max_seq_len_hint ? a.max_seq_len_hint : L);
     float4* const o = (float4*)(a.out + (((size_t)b * a.q_len + a.q0 + qtok) * kHeads + h) * kHeadDim + d);
     const int L_mine = L - (a.q_len - 1 - a.q0 - qtok);               // tokens this query token attends to
     int n_valid;
     size_t item0;
-    if (a.n_wgs > 0) {                                                // balanced schedule
+    if (balanced) {
         if (L == 0) { *o = make_float4(0.f, 0.f, 0.f, 0.f); return; }
-        item0 = (size_t)rec_first;
-        n_valid = rec_count;
+        item0 = (size_t)rec.x;
+        n_valid = rec.y;
         if (n_valid == 1 && n_here < 3) return;                       // one workgroup held it all and wrote the result
                                                                       // (the one-pass kernel for 3 / 4 tokens never does)
     } else {
@@ -406,7 +412,12 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
     // (With more than two query tokens: the first pair's.)
     if (!(ev_before && ev_after)) ev_before = ev_after = nullptr;
     static_assert(kHeads * kHeadDim / 4 == kMergeBlocksPerRow * 256, "sixteen blocks per row");
-    auto merge_blocks = [&](int n_here) { return merge_by_die(a.B, a.n_wgs) ? merge_blocks_by_die(a.B * n_here) : (unsigned)(kMergeBlocksPerRow * a.B * n_here); };
+    auto launch_merge = [&](const AttnArgs& args) {
+        const int rows = args.B * args.n_here;
+        if (merge_by_die(args.B, args.n_wgs)) hipLaunchKernelGGL(merge_splits_kernel<true>, dim3(merge_blocks_by_die(rows)), dim3(256), 0, stream, args);
+        else                                  hipLaunchKernelGGL(merge_splits_kernel<false>, dim3((unsigned)(kMergeBlocksPerRow * rows)), dim3(256), 0, stream, args);
+        return hipGetLastError();
+    };
     // Three and four query tokens over a bf16 cache, batches the per-wave schedule covers: one pass over the cache
     // by the kernel that keeps all of a sequence's query tokens in one wave.
     if (a.q_len >= 3 && kv_dtype == MFA_KV_BF16 && a.B <= kWaveScanChunks * 64) {
@@ -419,8 +430,7 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
         if (e != hipSuccess) return e;
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(merge_splits_kernel, dim3(merge_blocks(a.q_len)), dim3(256), 0, stream, args);
-        return hipGetLastError();
+        return launch_merge(args);
     }
     const bool short_work = kv_dtype != MFA_KV_BF16 && short_lowbit_work(a, kv_dtype);
     const AttnKernel kernel = a.q_len >= 2 ? attn_kernel<2>(kv_dtype, a.block_table != nullptr, short_work) : attn_kernel<1>(kv_dtype, a.block_table != nullptr, short_work);
@@ -439,8 +449,7 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (a.n_wgs > 0 || a.n_splits > 1) {
-            hipLaunchKernelGGL(merge_splits_kernel, dim3(merge_blocks(n_here)), dim3(256), 0, stream, args);
-            e = hipGetLastError();
+            e = launch_merge(args);
             if (e != hipSuccess) return e;
         }
     }
