@@ -202,7 +202,8 @@ MFA_API mfa_status mfa_out_proj(mfa_ctx* ctx, const float* attn_out, const void*
  *   max_seq_len_hint  host-side upper bound of seq_lens; 1 <= hint <= cfg.max_seq_len.  It
  *            sizes the launch and, with B, selects the kernel: results for different
  *            hints may differ in rounding, and a hint far above the lengths costs time
- *            (up to a fifth where the real work is a few tiles per workgroup)
+ *            (up to a fifth where the real work is a few tiles per workgroup, a few
+ *            percent under a hint of twice the longest length)
  *   out      fp32 [B, n_q_heads, head_dim]      (written)
  * Scores and sums are accumulated in fp32.  Attention weights are rounded where they
  * multiply V:

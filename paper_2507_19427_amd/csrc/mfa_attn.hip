@@ -20,6 +20,7 @@
 // on the attention weight of its token.
 #include <hip/hip_ext.h>
 
+#include "mfa_kernel_choice.hpp"
 #include "mfa_lowbit_short.hpp"
 #include "mfa_merge_place.hpp"
 #include "mfa_multi_short.hpp"
@@ -347,11 +348,8 @@ AttnKernel multi_kernel(int q_len, bool paged, bool short_work)
 }
 
 // 64-token tiles per workgroup at the length of the hint (the host knows no other).
-int64_t tiles_per_workgroup(const AttnArgs& a)
-{
-    const int64_t tiles_per_seq = (a.max_seq_len_hint + kTile - 1) / kTile;
-    return a.n_wgs > 0 ? a.B * tiles_per_seq / a.n_wgs : a.chunk_tokens / kTile;
-}
+int64_t tiles_per_sequence(const AttnArgs& a) { return (a.max_seq_len_hint + kTile - 1) / kTile; }
+int64_t tiles_per_workgroup(const AttnArgs& a) { return a.n_wgs > 0 ? a.B * tiles_per_sequence(a) / a.n_wgs : a.chunk_tokens / kTile; }
 // Three query tokens over a bf16 cache: short_bf16_multi_kernel below 4 tiles per workgroup.  us per call, short / decode, 20 and 128 sequences of the
 // length of the hint and drawn from 1 .. hint:
 //   1 tile  30.4/31.7 31.5/32.6  33.3/34.8 34.2/34.8     3 tiles  40.3/38.2 36.1/36.2  42.3/41.2 43.7/42.8     5 tiles  49.1/44.0 39.5/39.0  50.7/46.9 49.0/45.3
@@ -359,26 +357,10 @@ int64_t tiles_per_workgroup(const AttnArgs& a)
 //   1 tile  37.7/37.4  37.8/37.6     2 tiles  43.3/42.2  48.9/48.6     4 tiles  54.1/49.1  56.1/54.0     16 tiles  122.7/97.3  90.0/77.8
 bool short_multi_work(const AttnArgs& a) { return a.q_len == 3 && tiles_per_workgroup(a) < 4; }
 
-// Which of its two kernels a low-bit cache takes: short_lowbit_kernel below so many 64-token tiles per workgroup, counted at the length of
-// the hint.  The lines lie where lengths drawn from 1 .. hint, half the hint on average, no longer lose more than 1 %; equal ones
-// would have them lower.  us per call, short / decode, 50 sequences of the length of the hint and drawn:
-//                                12 tiles                16 tiles                20 tiles                24 tiles                30 tiles
-//   8 bit, one token    40.2/37.8  30.9/30.2    42.8/41.7  33.6/34.4    48.9/46.9  37.1/37.7    53.9/52.2  38.2/38.4    64.2/59.9  43.5/42.0
-//   4 bit, one token    35.8/34.8  28.1/28.3    41.0/40.0  32.6/31.9    44.5/43.0  34.9/35.0    49.3/46.5  36.5/36.3    56.8/50.5  41.6/40.2
-//   8 bit, two tokens   52.1/47.2  39.8/37.9    62.1/54.5  45.6/42.2    71.7/63.9  50.9/45.9    80.6/72.4  53.3/48.3    94.6/84.5  63.1/55.8
-//   4 bit, two tokens   46.7/44.9  35.5/36.4    53.8/50.0  40.8/40.2    61.9/56.3  45.0/43.4    69.2/62.3  46.4/45.1    82.3/72.3  54.5/51.2
-// and 8 bit, one token, 23 and 100 sequences at 24 tiles 51.6/50.9 35.9/35.4 54.4/53.7 39.2/39.9, at 30 59.8/58.0 46.6/46.1 63.3/62.2 43.4/43.3; two tokens at 8
-// tiles 43.5/40.4 33.0/34.1 (8 bit), 39.8/39.4 31.9/34.3 (4 bit).
-// The host knows no lengths: with a hint far above them short work takes decode_lowbit_kernel too.  Hint 32768, 64 sequences of 32 .. 64,
-// 512 .. 1024 and 2048 .. 4096 tokens, short / decode:
-//   8 bit, one token  15.4/16.7  26.0/27.3  40.5/40.1     8 bit, two tokens  18.0/21.1  36.9/37.7  57.8/54.3
-//   4 bit, one token  15.0/16.8  25.6/27.5  35.8/36.3     4 bit, two tokens  17.7/20.9  33.8/36.5  49.9/50.5
-// (three tokens over bf16 27.8/28.8  52.4/50.4  91.8/81.4).  Asking only for the stages that a short segment has, instead of its last one again,
-// changes none of these.
+// Which of its two kernels a low-bit cache takes (mfa_kernel_choice.hpp)
 bool short_lowbit_work(const AttnArgs& a, mfa_kv_dtype kv_dtype)
 {
-    const bool four_bit = kv_dtype == MFA_KV_FP4_E2M1;
-    return tiles_per_workgroup(a) < (a.q_len == 1 ? (four_bit ? 20 : 30) : (four_bit ? 16 : 12));
+    return takes_short_lowbit_kernel(kv_dtype == MFA_KV_FP4_E2M1, a.q_len == 1, tiles_per_workgroup(a), tiles_per_sequence(a));
 }
 }  // namespace
 
