@@ -36,12 +36,12 @@ __device__ __forceinline__ size_t tiled_index(int m, int k, int rows_pad)
     return ((size_t)(k >> 5) * rows_pad + (m & ~15)) * 32 + ((k & 31) >> 3) * 128 + (m & 15) * 8 + (k & 7);
 }
 
-// Buffer resource for `base`: loads through it at offsets below 2 GiB read memory, all others (kOutside) and, with !valid, every
+// Buffer resource for `base`: loads through it at offsets below kReach read memory, all others (kOutside) and, with !valid, every
 // load return zeros without touching it.
-constexpr uint32_t kOutside = 0x80000000u;
+constexpr uint32_t kReach = 0x7FFFFFFFu, kOutside = 0x80000000u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const unsigned char* base, bool valid)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0, valid ? 0x7FFFFFFF : 0, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0, valid ? (int)kReach : 0, 0x00020000);
 }
 constexpr int kNonTemporal = 2;              // cache policy operand of a buffer load
 
@@ -190,10 +190,14 @@ __global__ __launch_bounds__(kLoaderThreads) void gemm_loader_kernel(const void*
         const unsigned char* const x0 = (const unsigned char*)X + (X_KIND == XKind::kTiled ? (size_t)(m0 + my_row0) * 64 : (size_t)(m0 + my_row0) * K * kBytes);
         auto request_x = [&](XRegs& b, int it) {
             const int k0 = stage_k0(it < n_stages ? it : 0) + 32 * kh * S::kMySteps;
-            const __amdgpu_buffer_rsrc_t xr = buffer_at(x0 + (size_t)(unsigned)(k0 >> 5) * x_step, it < n_stages && k0 < k_end);
+            const unsigned char* const x_stage = x0 + (size_t)(unsigned)(k0 >> 5) * x_step;
+            const bool valid = it < n_stages && k0 < k_end;
+            // (row-major: a resource per group of eight rows, whose distance is not an offset: 24 rows of 45 million k are 2 GiB)
 #pragma unroll
-            for (int i = 0; i < kXLoads; ++i)
-                b.v[i] = __builtin_amdgcn_raw_buffer_load_b128(xr, x_off[i], X_KIND == XKind::kTiled ? (i / MB) * rows_pad * 64 : 8 * i * K * kBytes, 0);
+            for (int i = 0; i < kXLoads; ++i) {
+                if (X_KIND == XKind::kTiled) b.v[i] = __builtin_amdgcn_raw_buffer_load_b128(buffer_at(x_stage, valid), x_off[i], (i / MB) * rows_pad * 64, 0);
+                else                         b.v[i] = __builtin_amdgcn_raw_buffer_load_b128(buffer_at(x_stage + (size_t)(8 * i) * K * kBytes, valid), x_off[i], 0, 0);
+            }
         };
         const int a_lane_off = (8 * g + (n >> 2)) * 128 + ((n & 3) << 3);         // row 8g + i, 8 bytes per lane
         const int a_key = ((g & 1) << 1) | ((n >> 3) & 1);                        // w_key of rows 8g + 4t + i
@@ -487,13 +491,13 @@ __global__ __launch_bounds__(256) void reduce_partials_bf16_kernel(const float* 
 namespace {
 
 // The kernel of one streaming product and what it covers.
-struct GemmForm { const void* fn; unsigned threads, lds_bytes; int rows, cols; };
+struct GemmForm { const void* fn; unsigned threads, lds_bytes; int rows, cols; bool row_major_bf16; };
 
 template <bool OUT_BF16, XKind X_KIND, int MB, int NS>
 GemmForm loader_form()
 {
     using S = LoaderShape<X_KIND, MB, NS>;
-    return {(const void*)gemm_loader_kernel<OUT_BF16, X_KIND, MB, NS>, kLoaderThreads, S::kLdsBytes, S::kRows, S::kCols};
+    return {(const void*)gemm_loader_kernel<OUT_BF16, X_KIND, MB, NS>, kLoaderThreads, S::kLdsBytes, S::kRows, S::kCols, X_KIND == XKind::kRows};
 }
 // Products over single strips: up to 64 rows, or tiles of 128.
 template <bool OUT_BF16, XKind X_KIND>
@@ -515,8 +519,17 @@ hipError_t launch_gemm(const GemmForm& f, const void* X, const void* W, void* ou
                        int rows_pad, hipStream_t stream)
 {
     const uint16_t* wp = (const uint16_t*)W;
-    void* params[] = {&X, &wp, &out, &M, &K, &N, &k_per_split, &rows_pad};
-    return hipLaunchKernel(f.fn, dim3(N / f.cols, (M + f.rows - 1) / f.rows, split_k), dim3(f.threads), params, f.lds_bytes, stream);
+    // The kernel reaches eight rows of row-major bf16 through one resource: from 153 million k on, a launch per row (fp32 partial sums).
+    const int rows = f.row_major_bf16 && (int64_t)7 * K * 2 + 128 > (int64_t)kReach ? 1 : M;
+    for (int m = 0; m < M; m += rows) {
+        const void* x_here = f.row_major_bf16 ? (const uint16_t*)X + (size_t)m * K : X;
+        void* out_here = f.row_major_bf16 ? (float*)out + (size_t)m * N : out;
+        int rows_here = rows;
+        void* params[] = {&x_here, &wp, &out_here, &rows_here, &K, &N, &k_per_split, &rows_pad};
+        const hipError_t e = hipLaunchKernel(f.fn, dim3(N / f.cols, (rows + f.rows - 1) / f.rows, split_k), dim3(f.threads), params, f.lds_bytes, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace

@@ -76,3 +76,25 @@ def test_rank_beyond_a_thread_group():
     b = O.bits_of
     _, q64, _ = O.query_proj(b(x), b(w_qa), b(w_qb), 1e-6, gain=gain.numpy(), want_f64=True)
     assert U.row_normalised_error(q.reshape(-1, 256), np.asarray(q64).reshape(-1, 256)) <= TOL
+
+
+def test_rows_more_than_two_gib_apart():
+    """32 rows of x that lie more than 2 GiB apart from first to last, as one wave reads them; all of x and w_qa but five k are zeros."""
+    B, d_model, rank = 65, 35 << 20, 128
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("takes 33 GB of device memory")
+    ctx = mfa.mfa_decode_init(mfa.MfaConfig(max_batch=B, max_seq_len=1024, d_model=d_model, q_rank=rank))
+    g = torch.Generator().manual_seed(6)
+    ks = torch.tensor([0, 1003, d_model // 2 + 70, d_model - 64, d_model - 1])
+    some_x = torch.randn(B, 5, generator=g).to(torch.bfloat16)
+    some_w, w_qb = ((torch.randn(k, n, generator=g) * 0.05).to(torch.bfloat16) for k, n in ((5, rank), (rank, 16384)))
+    x = torch.zeros(B, d_model, dtype=torch.bfloat16, device="cuda")
+    w_qa = torch.zeros(d_model, rank, dtype=torch.bfloat16, device="cuda")
+    x[:, ks.cuda()], w_qa[ks.cuda()] = some_x.cuda(), some_w.cuda()
+    q = mfa.mfa_query_proj(ctx, x, w_qa, w_qb.cuda()).float().cpu().numpy()
+    ctx.close()
+    del x, w_qa, ctx
+    torch.cuda.empty_cache()
+    c = some_x.double() @ some_w.double()
+    c = c / torch.sqrt(c.square().mean(-1, keepdim=True) + 1e-6)
+    assert U.row_normalised_error(q.reshape(-1, 256), (c @ w_qb.double()).numpy().reshape(-1, 256)) <= TOL
