@@ -1,4 +1,4 @@
-"""Host-side checks of the compiled attention kernels (no GPU needed).
+"""Host-side checks of the compiled attention kernels and linear products (no GPU needed).
 
 The attention kernels load cache data with inline-assembly loads (to LDS; short_lowbit_kernel also to registers) and wait for them
 with inline-assembly s_waitcnt, counted where several stages are in flight (left to the compiler the wait would drain the
@@ -14,10 +14,13 @@ build checks the machine code it has just produced:
   * no compiler-made vector-memory wait inside a pipeline loop: it would wait for the pipeline's own loads;
   * no instruction reads or writes a matrix instruction's result, and no matrix instruction reads a vector instruction's, before it is
     there (check_matrix_hazards);
-  * the kernels use no scratch memory -- for every attention kernel, since scratch also costs every wave its set-up,
+  * the loading waves of gemm_loader_kernel ask for a load each time the oldest has landed (check_loading_loop): on every way through
+    their loop there is one barrier and either a stage's loads, each behind a wait that leaves what is in flight but one, or, towards the
+    end of the k range, one wait and no load; nothing else touches vector memory, and no wait is compiler-made;
+  * the kernels use no scratch memory -- for every attention kernel and product, since scratch also costs every wave its set-up,
     and a reload inside a pipeline loop waits for everything in flight.
 
-build.py runs check_attention_asm() on the assembly of every build and fails the build on a violation;
+build.py runs check_attention_asm() and check_products_asm() on the assembly of every build and fails the build on a violation;
 tests/test_build_asm.py runs the same functions, and the checkers themselves against planted mistakes.
 """
 import re
@@ -29,6 +32,9 @@ LOWBIT_STEADY = {(8, 1): (17, 0), (4, 1): (9, 0), (8, 2): (9, 0), (4, 2): (5, 1)
 MULTI_STEADY = (8, 1)
 # short_lowbit_kernel loads to registers in two unrolled steps, each of which waits for all but the youngest step's loads.
 SHORT_OPS_PER_STEP = {8: 5, 4: 3}
+
+# gemm_loader_kernel, by (16-row blocks of a wave, strips): loads of a loading wave per stage and stages in flight (LoaderShape::kLoads, kAhead).
+LOADING = {(1, 1): (4, 1), (2, 1): (4, 1), (1, 4): (8, 1), (2, 4): (4, 2)}
 
 _REG = re.compile(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b")
 
@@ -411,3 +417,51 @@ def check_attention_asm(text):
     assert len(short) == 10, f"expected 10 attention kernels for little work, found {sorted(short)}"
     for name, nbytes in {**decode, **short}.items():
         assert nbytes == 0, f"{name} uses {nbytes} bytes of scratch per lane (register spills)"
+
+
+def check_loading_loop(lines, loads, stages):
+    """Raises AssertionError unless the kernel's loading waves keep `stages` stages of `loads` direct loads in flight, asking for the next
+    load whenever the oldest has landed."""
+    blocks, successors = basic_blocks(lines)
+    loading = [i for i, b in enumerate(blocks) if any(x.op.startswith("global_load_lds") for x in b) and any(x.vector_memory_wait is not None for x in b)]
+    assert len(loading) == 1, f"{len(loading)} loading blocks"
+    loop = innermost_loop(successors, loading[0])
+    assert loop is not None, "the loading block is in no loop"
+    header, body = loop
+    left = stages * loads - 1
+    closed, todo = set(), [(header, (), frozenset())]
+    while todo:
+        b, way, flags = todo.pop()
+        for x in blocks[b]:
+            if x.is_vector_memory:
+                assert x.in_asm and x.op.startswith("global_load_lds"), f"a vector-memory operation that is no load of the pipeline: {x.text}"
+                way += ("load",)
+            elif x.vector_memory_wait is not None:
+                assert x.in_asm, f"compiler-made vector-memory wait in a loading loop: {x.text}"
+                way += (x.vector_memory_wait,)
+            elif x.op == "s_barrier":
+                way += ("barrier",)
+            assert len(way) <= 2 * loads + 1, f"more than a stage on a way through the loop: {way}"
+        flags = flags_after(blocks[b], flags)
+        for t in ways_on(blocks, successors, b, flags) & body:
+            if t == header:
+                closed.add(way)
+            else:
+                todo.append((t, way, flags))
+    steady = (left, "load") * loads + ("barrier",)
+    ends = {(0, "barrier")} | ({((stages - 1) * loads, "barrier")} if stages > 1 else set())
+    assert steady in closed and closed <= {steady} | ends, f"ways through the loop: {sorted(map(str, closed - {steady} - ends))} beside {steady in closed}"
+
+
+def check_products_asm(text):
+    """All checks on the assembly text of mfa_qproj.hip.  Raises AssertionError naming the first violation."""
+    names = re.findall(r"^(_ZN3mfa\w*gemm_loader_kernelI\w+):", text, re.M)
+    assert len(names) == 8, f"expected 8 forms of the product, found {names}"
+    scratch = scratch_bytes(text)
+    for name in names:
+        row_blocks, strips = (int(x) for x in re.search(r"Li(\d)ELi(\d)EEEv", name).groups())
+        try:
+            check_loading_loop(kernel_body(text, name), *LOADING[row_blocks, strips])
+        except AssertionError as e:
+            raise AssertionError(f"{name}: {e}") from None
+        assert scratch[name] == 0, f"{name} uses {scratch[name]} bytes of scratch per lane (register spills)"

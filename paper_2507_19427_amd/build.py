@@ -1,5 +1,5 @@
 """Compile the HIP sources under csrc/ into paper_2507_19427_amd/libmfa.so for gfx950, and check the machine
-code of the attention kernels (asm_check.py) before the library is put in place."""
+code of the attention kernels and the linear products (asm_check.py) before the library is put in place."""
 import glob
 import os
 import shutil
@@ -52,14 +52,15 @@ def build(force: bool = True, verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed:\n" + out)
         if verbose and out.strip():
             print(out)
-        asm = glob.glob(os.path.join(tmp, "mfa_attn-hip-amdgcn-amd-amdhsa-gfx950.s"))
-        if len(asm) != 1:
-            raise RuntimeError("the device assembly of mfa_attn.hip was not produced; cannot check it")
-        try:
-            with open(asm[0]) as f:
-                asm_check.check_attention_asm(f.read())
-        except AssertionError as e:
-            raise RuntimeError(f"the compiled attention kernels fail the machine-code check, library not installed: {e}")
+        for name, check in (("mfa_attn", asm_check.check_attention_asm), ("mfa_qproj", asm_check.check_products_asm)):
+            asm = glob.glob(os.path.join(tmp, f"{name}-hip-amdgcn-amd-amdhsa-gfx950.s"))
+            if len(asm) != 1:
+                raise RuntimeError(f"the device assembly of {name}.hip was not produced; cannot check it")
+            try:
+                with open(asm[0]) as f:
+                    check(f.read())
+            except AssertionError as e:
+                raise RuntimeError(f"the compiled kernels of {name}.hip fail the machine-code check, library not installed: {e}")
         shutil.move(out_lib, LIB + ".tmp")
         os.replace(LIB + ".tmp", LIB)
     finally:

@@ -1,6 +1,6 @@
-"""Host-side check of the compiled attention kernels (the checker is paper_2507_19427_amd/asm_check.py, which
+"""Host-side check of the compiled attention kernels and linear products (the checker is paper_2507_19427_amd/asm_check.py, which
 the build itself runs on every library it produces).  Here: the same checks on a fresh compilation of
-mfa_attn.hip, kernel by kernel, and the checker against planted mistakes."""
+mfa_attn.hip, kernel by kernel, and of mfa_qproj.hip, and the checker against planted mistakes."""
 import os
 import shutil
 import subprocess
@@ -10,20 +10,29 @@ import pytest
 from paper_2507_19427_amd import asm_check as A
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SRC = os.path.join(ROOT, "paper_2507_19427_amd", "csrc", "mfa_attn.hip")
+CSRC = os.path.join(ROOT, "paper_2507_19427_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+def _assembly(tmp_path_factory, name):
+    if not (os.path.exists(HIPCC) or shutil.which(HIPCC)):
+        pytest.skip("hipcc not available")
+    out = tmp_path_factory.mktemp("asm") / f"{name}.s"
+    cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", "--cuda-device-only", "-S", "-o", str(out), os.path.join(CSRC, f"{name}.hip")]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert res.returncode == 0, res.stdout
+    return out.read_text()
 
 
 @pytest.fixture(scope="module")
 def asm_text(tmp_path_factory):
-    if not (os.path.exists(HIPCC) or shutil.which(HIPCC)):
-        pytest.skip("hipcc not available")
-    out = tmp_path_factory.mktemp("asm") / "mfa_attn.s"
-    cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
-           "-packed-fp32-ops", "--cuda-device-only", "-S", "-o", str(out), SRC]
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    assert res.returncode == 0, res.stdout
-    return out.read_text()
+    return _assembly(tmp_path_factory, "mfa_attn")
+
+
+@pytest.fixture(scope="module")
+def products_text(tmp_path_factory):
+    return _assembly(tmp_path_factory, "mfa_qproj")
 
 
 LOWBIT = [(paged, q_len, bits) for bits in (8, 4) for q_len in (1, 2) for paged in (0, 1)]
@@ -62,6 +71,10 @@ def test_no_attention_kernel_uses_scratch_memory(asm_text):
 
 def test_everything_the_build_checks(asm_text):
     A.check_attention_asm(asm_text)
+
+
+def test_loading_waves_of_the_products(products_text):
+    A.check_products_asm(products_text)
 
 
 def _snippet(between):
@@ -123,6 +136,27 @@ def test_the_steady_loop_check_catches_planted_mistakes():
     for flag in ([], ["s_mov_b64 s[8:9], 0", "s_mov_b32 s9, s10"]):
         with pytest.raises(AssertionError, match="operations"):
             check(["s_mov_b32 s0, 0"] + sides(flag))
+
+
+def test_the_loading_loop_check_catches_planted_mistakes():
+    asm = lambda *t: [";;#ASMSTART", *t, ";;#ASMEND"]
+    load = asm("s_mov_b32 m0, s4", "s_nop 0", "global_load_lds_dwordx4 v1, s[2:3] nt")
+
+    def loop(pairs, end_wait="s_waitcnt vmcnt(0)", barrier="s_waitcnt lgkmcnt(0)\ns_barrier", extra=()):
+        end = asm(end_wait) if end_wait else []
+        return load * 2 + [".LBB0_1:", "s_cbranch_scc0 .LBB0_2", *pairs, *extra, "s_branch .LBB0_3", ".LBB0_2:", *end, ".LBB0_3:", *asm(*barrier.split("\n")),
+                           "s_add_i32 s0, s0, 1", "s_cmp_lt_i32 s0, s1", "s_cbranch_scc1 .LBB0_1", "s_endpgm"]
+
+    pair = asm("s_waitcnt vmcnt(1)") + load
+    A.check_loading_loop(loop(pair * 2), 2, 1)
+    A.check_loading_loop(loop((asm("s_waitcnt vmcnt(3)") + load) * 2, end_wait="s_waitcnt vmcnt(2)"), 2, 2)
+    for bad in (loop(pair + load), loop(pair), loop(pair * 3), loop((asm("s_waitcnt vmcnt(2)") + load) * 2),       # a wait or a load too few or too many, counted wrongly
+                loop(pair * 2, end_wait=None), loop(pair * 2, end_wait="s_waitcnt vmcnt(1)"),                          # the last stages not awaited
+                loop(pair * 2, barrier="s_nop 0"),
+                loop(pair * 2, extra=["s_waitcnt vmcnt(0)"]), loop(pair * 2, extra=["scratch_load_dword v20, off, off offset:16"]),
+                loop(pair * 2, extra=["global_store_dword v1, v20, s[2:3]"]), loop(pair * 2)[:-2] + ["s_endpgm"]):
+        with pytest.raises(AssertionError):
+            A.check_loading_loop(bad, 2, 1)
 
 
 def test_the_compiler_wait_check_catches_planted_mistakes():
