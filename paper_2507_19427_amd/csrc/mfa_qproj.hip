@@ -23,7 +23,6 @@ namespace {
 
 constexpr int kStripN = 64;                  // columns of a strip
 constexpr int kMaxSplits = 32;               // k splits of a product, at most
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 // How a product finds x:
@@ -44,7 +43,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const unsigned char*
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0, valid ? (int)kReach : 0, 0x00020000);
 }
-constexpr int kNonTemporal = 2;              // cache policy operand of a buffer load
 
 // Row-major x reaches the lanes by way of a small image of the wave's own in LDS: it is loaded in whole 128-byte lines, written row
 // by row and read back as fragments.  bf16, 64 k of a row = 128 bytes: 16-byte chunk c of row r at c ^ ((r >> 1) & 7).  From fp32, 32 k of a
@@ -56,7 +54,7 @@ __device__ __forceinline__ int image32_at(int row, int chunk) { return row * 64 
 // that the transposing reads are conflict-free), each keeping a fixed number of loads in flight: as the oldest lands, the next is asked for.
 // Eight waves multiply: A = W^T (16 columns x 32 k) from the LDS transposing read, one unit ahead of its MFMAs, B = x^T (32 k x 16 rows) from
 // global memory two stages ahead, v_mfma_f32_16x16x32_bf16 giving C^T[column, row].  One barrier per stage, which waits for
-// LDS reads but for nobody's global loads.  The eight waves are 4 row groups x 2: alternate k steps (the two sums are added
+// LDS reads but for nobody's global loads.  The eight waves are 4 row groups x 2: halves of a stage's k steps (the two sums are added
 // through LDS) or, where the sums of both would not fit the registers, the halves of the columns.
 // OUT_BF16 = false: fp32 partial sums to out[(kz*rows_pad + m)*N + n];  true: bf16 result to out[m*N + n] (requires gridDim.z == 1).
 // MB = 1 or 2: 16-row blocks per wave; a workgroup covers 64 * MB rows of x.
@@ -177,7 +175,7 @@ __global__ __launch_bounds__(kLoaderThreads) void gemm_loader_kernel(const void*
 #pragma unroll
             for (int j = 0; j < 4 * S::kMyStrips; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
         // Loads of x per stage: row-major in groups of 8 rows x 128 bytes, else one per 16-row block and k step.  Every element is
-        // loaded by one wave (by two with NS = 4).  Rows past M, and stages past the last, read nothing.
+        // loaded by one wave, or by two where they share its k steps (!kSplitK).  Rows past M, and stages past the last, read nothing.
         constexpr int kXLoads = X_KIND == XKind::kTiled ? MB * S::kMySteps : 2 * MB;
         struct XRegs { u32x4 v[kXLoads]; };
         uint32_t x_off[kXLoads];
@@ -325,7 +323,7 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_reduce_kernel(const floa
                                                              float eps)
 {
     __shared__ float red[kNormThreads / 64];
-    extern __shared__ float crow[];           // r floats: the reduced row, kept between the two passes
+    extern __shared__ float crow[];           // the reduced row's columns from 4 * kNormThreads on, kept between the two passes
     const int m = blockIdx.x;
     const int tid = threadIdx.x;
     const size_t split_stride = (size_t)rows_pad * r;
@@ -356,7 +354,7 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_reduce_kernel(const floa
     float ss = square(c0);
     for (int j = j0 + 4 * kNormThreads; j < r; j += 4 * kNormThreads) {
         const f32x4 c = sum_splits(j);
-        *(f32x4*)(crow + j) = c;
+        *(f32x4*)(crow + j - 4 * kNormThreads) = c;
         ss += square(c);
     }
     for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
@@ -367,7 +365,7 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_reduce_kernel(const floa
     for (int i = 0; i < kNormThreads / 64; ++i) total += red[i];
     const float inv = 1.0f / sqrtf(total / (float)r + eps);
     for (int j = j0; j < r; j += 4 * kNormThreads) {
-        const f32x4 c = j == j0 ? c0 : *(const f32x4*)(crow + j);
+        const f32x4 c = j == j0 ? c0 : *(const f32x4*)(crow + j - 4 * kNormThreads);
         const f32x4 g = j == j0 || !gain ? g0 : *(const f32x4*)(gain + j);
         bf16x4 o;
 #pragma unroll
@@ -551,7 +549,11 @@ QProjPlan plan_linear(int32_t K, int32_t N, int32_t strips_per_wg)
     return p;
 }
 
-// Output projection: groups of four strips (x once per 256 columns, W in rows of 512 bytes) pay for the fourfold k split.
+// Output projection: groups of four strips (x once per 256 columns, W in rows of 512 bytes) pay for the fourfold k split, with more than 128 rows
+// as well, and single strips do where the columns do not divide.  us per call, a plan of four strips up to 64 rows, pairs up to 128 and single ones beyond
+// (on the kernel whose waves loaded and multiplied in turn) -> this one:  7168 columns, 256 / 512 / 1024 rows 163.7 / 322.0 / 576.3 -> 127.5 / 214.8 / 409.1;
+// 1152 columns (pairs, now single strips), 4 / 64 / 128 / 256 rows 17.5 / 22.0 / 25.7 / 46.1 -> 14.6 / 20.6 / 25.3 / 39.3;
+// 2176 columns 21.8 / 27.2 / 32.4 / 64.2 -> 20.3 / 27.4 / 32.1 / 53.2.
 QProjPlan plan_out_proj(int32_t K, int32_t N)
 {
     return plan_linear(K, N, N % (4 * kStripN) == 0 ? 4 : 1);
@@ -569,6 +571,10 @@ hipError_t prepare_query_proj_kernels()
     return hipSuccess;
 }
 
+namespace {
+size_t norm_lds_bytes(int q_rank) { return q_rank > 4 * kNormThreads ? (q_rank - 4 * kNormThreads) * sizeof(float) : 0; }
+}  // namespace
+
 hipError_t launch_query_proj(const QProjArgs& a, hipStream_t stream)
 {
     const int m_blocks = (a.B + kQProjRows - 1) / kQProjRows;
@@ -576,7 +582,7 @@ hipError_t launch_query_proj(const QProjArgs& a, hipStream_t stream)
     hipError_t e = launch_gemm(strip_form<false, XKind::kRows>(a.B), a.x, a.w_qa, a.ws_c, a.B, a.d_model, a.q_rank, a.k_per_split, a.split_k,
                                rows_pad, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rmsnorm_reduce_kernel, dim3(a.B), dim3(kNormThreads), a.q_rank * sizeof(float), stream,
+    hipLaunchKernelGGL(rmsnorm_reduce_kernel, dim3(a.B), dim3(kNormThreads), norm_lds_bytes(a.q_rank), stream,
                        (const float*)a.ws_c, a.gain, (__bf16*)a.ws_chat, a.q_rank, a.split_k, rows_pad, a.eps);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
