@@ -149,9 +149,16 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-def _stream():
-    """The current device's current stream, as torch.cuda.current_stream().cuda_stream (without building the Stream object)."""
+def _public_stream():
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _raw_stream():
+    """The same address without building the Stream object (0.2 us instead of 2.8), by two functions that torch does not document."""
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+_stream = _raw_stream if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice") else _public_stream
 
 
 # (uint8: e2m1 codes, two per byte, last dimension head_dim / 2)

@@ -212,3 +212,31 @@ def test_scores_of_minus_infinity_ahead_of_finite_ones(workgroups, n_masked):
     ctx = mfa.mfa_decode_init(mfa.MfaConfig(max_batch=8, max_seq_len=8192, target_workgroups=workgroups))
     assert U.row_normalised_error(U.run_gpu(ctx, case), U.run_oracle(case)) <= U.TOL_BF16
     ctx.close()
+
+
+def test_the_stream_of_a_call_is_the_current_one(monkeypatch):
+    """By torch's undocumented functions and by its public one alike: on the default stream, a stream of the caller's and a stream under capture."""
+    from paper_2507_19427_amd import binding as B
+    case = W.make_contiguous_case("stream", 28, B=2, S=300, seq_lens=[300, 65])
+    ctx = U.get_ctx()
+    args = [U.to_dev(t) for t in (case.q, case.k, case.v, case.seq_lens)]
+    want = mfa.mfa_decode_attn(ctx, *args, 300)
+    assert B._stream() == B._public_stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for stream_of in (B._stream, B._public_stream):
+        monkeypatch.setattr(B, "_stream", stream_of)
+        with torch.cuda.stream(side):
+            assert stream_of() == side.cuda_stream
+            out = torch.zeros_like(want)
+            mfa.mfa_decode_attn(ctx, *args, 300, out=out)
+        side.synchronize()
+        assert torch.equal(out, want)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            mfa.mfa_decode_attn(ctx, *args, 300, out=out)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
