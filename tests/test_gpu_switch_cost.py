@@ -40,9 +40,11 @@ def test_against_the_oracle(kind, kv, q_len):
     got = mfa.mfa_decode_attn_paged_multi(ctx, qm.cuda(), *dev, max(lens), *scales).cpu().numpy()
     again = mfa.mfa_decode_attn_paged_multi(ctx, qm.cuda(), *dev, max(lens), *scales).cpu().numpy()
     assert (got.view("uint32") == again.view("uint32")).all()
+    assert torch.isfinite(torch.from_numpy(got)).all()
+    # every sequence, by one head or another; more heads of the longest and of a few others
     longest = sorted(range(len(lens)), key=lambda b: -lens[b])[:2]
-    picks = sorted(set(longest + [0, 1, len(lens) // 2, len(lens) - 1]))
-    rows = [(b, h) for b in picks for h in (0, 17, 63)]
+    picks = set(longest + [0, 1, len(lens) // 2, len(lens) - 1])
+    rows = sorted({(b, (5 * b + 3) % 64) for b in range(len(lens))} | {(b, h) for b in picks for h in (0, 17, 63)})
     b_ = O.bits_of
     kd = {"bf16": O.KV_BF16, "fp8": O.KV_E4M3, "fp4": O.KV_E2M1}[kv]
     opt = lambda t: None if t is None else b_(t)
