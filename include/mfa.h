@@ -205,7 +205,8 @@ MFA_API mfa_status mfa_out_proj(mfa_ctx* ctx, const float* attn_out, const void*
  *            (up to a fifth where the real work is a few tiles per workgroup, a few
  *            percent under a hint of twice the longest length)
  *   out      fp32 [B, n_q_heads, head_dim]      (written)
- * Scores and sums are accumulated in fp32.  Attention weights are rounded where they
+ * Scores and sums are accumulated in fp32 (long 8-bit and 4-bit caches: query times codes, ahead
+ * of a key's scale, which leaves fp32 from query elements of about 2^100 on).  Attention weights are rounded where they
  * multiply V:
  *   bf16 caches, and 8-bit and 4-bit ones with little work per workgroup at the length of
  *     the hint: to bf16 (8 significant bits; the value scale of a token multiplied in before);

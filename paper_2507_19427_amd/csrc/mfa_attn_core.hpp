@@ -422,7 +422,9 @@ constexpr int kBf16LdsBytes = kBf16SchedOffset + kSchedLdsBytes;
 // own, so that a range which holds a boundary holds fewer tiles: without them the few workgroups with two segments decide the time.  us per
 // call without / with, lengths drawn from 1 .. the longest: 8 bit 40 x 9000 42.3 / 31.7, 100 x 5000 52.8 / 43.7, 60 x 12000 60.3 / 50.5,
 // 23 x 20011 44.4 / 39.5; 4 bit 40 x 9000 38.6 / 28.6; 8 bit, two tokens, 60 x 6000 59.6 / 49.5; bf16, three tokens 16 x 4096 46.1 / 37.3, four
-// 30 x 3000 53.7 / 41.9; bf16 128 x 8192 paged 123.0 / 121.2.  Half or one and a half times as many: within 3 %.
+// 30 x 3000 53.7 / 41.9; bf16, one token, three draws each: 100 x 3000 45.3 .. 49.4 / 41.1 .. 45.7, 33 x 12000 45.6 .. 53.4 / 43.3 .. 50.9, two tokens 40 x 6000
+// 48.4 .. 51.0 / 42.0 .. 45.0, but 128 x 1024..8192 within what two runs of one side differ by (121.7, 114.4, 112.8 / 120.4, 115.0, 111.3): its 38 tiles per
+// workgroup leave little to balance.  Half or one and a half times as many: within 3 %.  Batches of more than 512 sequences have no pad.
 constexpr int kBf16Switch = 2;
 constexpr int kShortLowbitSwitch = 6;
 constexpr int kLowbitSwitch = 8;
@@ -495,7 +497,7 @@ __device__ __forceinline__ int range_index()
     return (g & 7) == 0 ? (i & 7) * (g >> 3) + (i >> 3) : i;
 }
 
-// Sequences of one length: do they all start where a range does?  (Then nobody switches in mid-range.)
+// Sequences of one length: are all ranges alike, a part of one sequence or the same number of whole ones?  (Then a switch costs all of them the same.)
 __device__ __forceinline__ bool boundaries_on_edges(int B, int n_wgs) { return (B & (B - 1)) == 0 && (n_wgs & (n_wgs - 1)) == 0; }
 
 // All threads of the workgroup call this; the values returned are the same in every thread.
