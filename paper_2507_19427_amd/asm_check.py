@@ -456,7 +456,7 @@ def check_loading_loop(lines, loads, stages):
 def check_products_asm(text):
     """All checks on the assembly text of mfa_qproj.hip.  Raises AssertionError naming the first violation."""
     names = re.findall(r"^(_ZN3mfa\w*gemm_loader_kernelI\w+):", text, re.M)
-    assert len(names) == 8, f"expected 8 forms of the product, found {names}"
+    assert len(names) == 10, f"expected 10 forms of the product, found {names}"
     scratch = scratch_bytes(text)
     for name in names:
         row_blocks, strips = (int(x) for x in re.search(r"Li(\d)ELi(\d)EEEv", name).groups())

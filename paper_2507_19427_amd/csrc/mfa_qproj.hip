@@ -30,7 +30,9 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 //   kTiled  bf16 in the order a wave loads it: element (m, k) at ((k/32)*rows_pad + (m & ~15))*32 + ((k%32)/8)*128 + (m%16)*8 + k%8, so that
 //           16 rows x 32 k are one KB in lane order
 //   kFloat  fp32, row-major [M, K], rounded to bf16 on the way
-enum class XKind { kRows, kTiled, kFloat };
+//   kFarRows  as kRows, for rows so long that those of a wave are more than kReach apart
+enum class XKind { kRows, kTiled, kFloat, kFarRows };
+constexpr bool bf16_rows(XKind k) { return k == XKind::kRows || k == XKind::kFarRows; }
 __device__ __forceinline__ size_t tiled_index(int m, int k, int rows_pad)
 {
     return ((size_t)(k >> 5) * rows_pad + (m & ~15)) * 32 + ((k & 31) >> 3) * 128 + (m & 15) * 8 + (k & 7);
@@ -79,7 +81,7 @@ struct LoaderShape {
     static constexpr int kLoads = kStageBytes / 1024 / kLoaders;       // direct loads of a loading wave per stage
     static constexpr int kAhead = (NS == 1 ? 16384 : 32768) / kStageBytes;   // stages in flight
     static constexpr int kSlots = kAhead + 2;                          // (one being multiplied, one complete)
-    static constexpr int kImageBytes = X_KIND == XKind::kRows ? MB * 2048 : X_KIND == XKind::kFloat ? MB * 1024 : 0;
+    static constexpr int kImageBytes = bf16_rows(X_KIND) ? MB * 2048 : X_KIND == XKind::kFloat ? MB * 1024 : 0;
     static constexpr int kImageBase = kSlots * kStageBytes;
     static constexpr int kCols = kStripN * NS;
     static constexpr int kRows = 64 * MB;
@@ -88,7 +90,7 @@ struct LoaderShape {
     static constexpr int kLdsBytes = kRingBytes > kRows * kTileStride ? kRingBytes : kRows * kTileStride;
     static_assert(kLdsBytes <= 160 * 1024, "LDS of a compute unit");
     static_assert(NS == 1 || NS == 4, "one strip, k steps shared out; or four, columns shared out");
-    static_assert(X_KIND != XKind::kRows || kMySteps == 2, "an image of row-major bf16 holds 64 k");
+    static_assert(!bf16_rows(X_KIND) || kMySteps == 2, "an image of row-major bf16 holds 64 k");
     static_assert(X_KIND != XKind::kFloat || kMySteps == 1, "an image of row-major fp32 holds 32 k");
 };
 
@@ -191,11 +193,12 @@ __global__ __launch_bounds__(kLoaderThreads) void gemm_loader_kernel(const void*
             const int k0 = stage_k0(it < n_stages ? it : 0) + 32 * kh * S::kMySteps;
             const unsigned char* const x_stage = x0 + (size_t)(unsigned)(k0 >> 5) * x_step;
             const bool valid = it < n_stages && k0 < k_end;
-            // (row-major: a resource per group of eight rows, whose distance is not an offset: 24 rows of 45 million k are 2 GiB)
+            const __amdgpu_buffer_rsrc_t xr = buffer_at(x_stage, valid);
 #pragma unroll
             for (int i = 0; i < kXLoads; ++i) {
-                if (X_KIND == XKind::kTiled) b.v[i] = __builtin_amdgcn_raw_buffer_load_b128(buffer_at(x_stage, valid), x_off[i], (i / MB) * rows_pad * 64, 0);
-                else                         b.v[i] = __builtin_amdgcn_raw_buffer_load_b128(buffer_at(x_stage + (size_t)(8 * i) * K * kBytes, valid), x_off[i], 0, 0);
+                // (far rows: a resource per group of eight, at 0.05 .. 0.2 us a call)
+                if (X_KIND == XKind::kFarRows) b.v[i] = __builtin_amdgcn_raw_buffer_load_b128(buffer_at(x_stage + (size_t)(8 * i) * K * kBytes, valid), x_off[i], 0, 0);
+                else                           b.v[i] = __builtin_amdgcn_raw_buffer_load_b128(xr, x_off[i], X_KIND == XKind::kTiled ? (i / MB) * rows_pad * 64 : 8 * i * K * kBytes, 0);
             }
         };
         const int a_lane_off = (8 * g + (n >> 2)) * 128 + ((n & 3) << 3);         // row 8g + i, 8 bytes per lane
@@ -220,7 +223,7 @@ __global__ __launch_bounds__(kLoaderThreads) void gemm_loader_kernel(const void*
 #pragma unroll
                 for (int i = 0; i < kXLoads; ++i) {
                     const int r = 8 * i + (lane >> 3);
-                    if constexpr (X_KIND == XKind::kRows) *LDS_AT(u32x4, lds_base, image + image64_at(r, lane & 7)) = b.v[i];
+                    if constexpr (bf16_rows(X_KIND)) *LDS_AT(u32x4, lds_base, image + image64_at(r, lane & 7)) = b.v[i];
                     else {
                         const f32x4 f = __builtin_bit_cast(f32x4, b.v[i]);
                         bf16x4 h;
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(kLoaderThreads) void gemm_loader_kernel(const void*
                 for (int j = 0; j < S::kMySteps; ++j)
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb)
-                        xf[j * MB + mb] = *LDS_AT(bf16x8, lds_base, image + (X_KIND == XKind::kRows ? image64_at(16 * mb + n, 4 * j + g) : image32_at(16 * mb + n, g)));
+                        xf[j * MB + mb] = *LDS_AT(bf16x8, lds_base, image + (bf16_rows(X_KIND) ? image64_at(16 * mb + n, 4 * j + g) : image32_at(16 * mb + n, g)));
             }
             // units (own k step, strip): the operands of the next one are read from LDS while the current one is multiplied
             constexpr int T = S::kMyStrips, kUnits = S::kMySteps * T;
@@ -497,7 +500,7 @@ template <bool OUT_BF16, XKind X_KIND, int MB, int NS>
 GemmForm loader_form()
 {
     using S = LoaderShape<X_KIND, MB, NS>;
-    return {(const void*)gemm_loader_kernel<OUT_BF16, X_KIND, MB, NS>, kLoaderThreads, S::kLdsBytes, S::kRows, S::kCols, X_KIND == XKind::kRows};
+    return {(const void*)gemm_loader_kernel<OUT_BF16, X_KIND, MB, NS>, kLoaderThreads, S::kLdsBytes, S::kRows, S::kCols, bf16_rows(X_KIND)};
 }
 // Products over single strips: up to 64 rows, or tiles of 128.
 template <bool OUT_BF16, XKind X_KIND>
@@ -505,6 +508,10 @@ GemmForm strip_form(int M)
 {
     return M <= 64 ? loader_form<OUT_BF16, X_KIND, 1, 1>() : loader_form<OUT_BF16, X_KIND, 2, 1>();
 }
+// Products whose x is row-major bf16.  A wave's rows are reached by offsets into one resource, or, from 34.6 million k on, where 32 rows leave its reach, by a
+// resource per eight rows.
+constexpr bool within_reach(int rows, int K) { return (int64_t)(rows - 1) * K * 2 + 128 <= (int64_t)kReach; }
+GemmForm rows_form(int M, int K) { return within_reach(32, K) ? strip_form<false, XKind::kRows>(M) : strip_form<false, XKind::kFarRows>(M); }
 // The output projection over groups of four strips: up to 64 rows straight from the fp32 activations (64 rows: 42.6 us where the product over a
 // converted copy takes 41.5, and the launch that converts 4 or 5), with more rows, where x is as large as a workgroup's share of W, from
 // the converted copy (128 rows: 55.0 and 47.5 + 5).
@@ -519,8 +526,8 @@ hipError_t launch_gemm(const GemmForm& f, const void* X, const void* W, void* ou
                        int rows_pad, hipStream_t stream)
 {
     const uint16_t* wp = (const uint16_t*)W;
-    // The kernel reaches eight rows of row-major bf16 through one resource: from 153 million k on, a launch per row (fp32 partial sums).
-    const int rows = f.row_major_bf16 && (int64_t)7 * K * 2 + 128 > (int64_t)kReach ? 1 : M;
+    // Where not even eight rows are within reach, from 153 million k on, a launch per row (fp32 partial sums).
+    const int rows = f.row_major_bf16 && !within_reach(8, K) ? 1 : M;
     for (int m = 0; m < M; m += rows) {
         const void* x_here = f.row_major_bf16 ? (const uint16_t*)X + (size_t)m * K : X;
         void* out_here = f.row_major_bf16 ? (float*)out + (size_t)m * N : out;
@@ -562,7 +569,7 @@ QProjPlan plan_out_proj(int32_t K, int32_t N)
 hipError_t prepare_query_proj_kernels()
 {
     for (const int rows : {64, 128}) {
-        const GemmForm forms[] = {strip_form<false, XKind::kRows>(rows), strip_form<true, XKind::kTiled>(rows), out_form(rows, 1), out_form(rows, 4)};
+        const GemmForm forms[] = {strip_form<false, XKind::kRows>(rows), strip_form<false, XKind::kFarRows>(rows), strip_form<true, XKind::kTiled>(rows), out_form(rows, 1), out_form(rows, 4)};
         for (const GemmForm& f : forms) {
             const hipError_t e = hipFuncSetAttribute(f.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f.lds_bytes);
             if (e != hipSuccess) return e;
@@ -579,7 +586,7 @@ hipError_t launch_query_proj(const QProjArgs& a, hipStream_t stream)
 {
     const int m_blocks = (a.B + kQProjRows - 1) / kQProjRows;
     const int rows_pad = m_blocks * kQProjRows;
-    hipError_t e = launch_gemm(strip_form<false, XKind::kRows>(a.B), a.x, a.w_qa, a.ws_c, a.B, a.d_model, a.q_rank, a.k_per_split, a.split_k,
+    hipError_t e = launch_gemm(rows_form(a.B, a.d_model), a.x, a.w_qa, a.ws_c, a.B, a.d_model, a.q_rank, a.k_per_split, a.split_k,
                                rows_pad, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(rmsnorm_reduce_kernel, dim3(a.B), dim3(kNormThreads), norm_lds_bytes(a.q_rank), stream,
@@ -617,7 +624,7 @@ hipError_t launch_kv_append(const KvAppendArgs& a, mfa_kv_dtype kv_dtype, hipStr
 {
     const int m_blocks = (a.B + kQProjRows - 1) / kQProjRows;
     const int rows_pad = m_blocks * kQProjRows;
-    const hipError_t e = launch_gemm(strip_form<false, XKind::kRows>(a.B), a.x, a.w_kv, a.ws_c, a.B, a.d_model, kKvWidth, a.plan.k_per_split,
+    const hipError_t e = launch_gemm(rows_form(a.B, a.d_model), a.x, a.w_kv, a.ws_c, a.B, a.d_model, kKvWidth, a.plan.k_per_split,
                                      a.plan.split_k, rows_pad, stream);
     if (e != hipSuccess) return e;
     return launch_record(a, kv_dtype, a.ws_c, a.plan.split_k, rows_pad, stream);
