@@ -13,6 +13,7 @@ using namespace mfa;
 struct mfa_ctx {
     mfa_config cfg;
     int32_t target_items;      // workgroups the planner aims for (one per compute unit by default)
+    bool may_be_brief;         // AttnArgs::may_be_brief
     bool fixed_splits;         // MFA_SCHEDULE_FIXED: every sequence cut into the same number of equal chunks
     size_t max_items;          // bound on B * n_splits over all admissible calls
     float* ws_acc;
@@ -69,7 +70,7 @@ hipError_t static_scratch_for_device(int device, unsigned char** out)
 
 // Workgroups an attention call aims for: the configuration's figure, else (test override) the
 // environment's, else one per compute unit.
-int32_t target_items_of(const mfa_config* c)
+int32_t asked_target_items(const mfa_config* c)           // 0: none
 {
     if (c->target_workgroups >= 1 && c->target_workgroups <= 4096) return c->target_workgroups;
     const char* s = std::getenv("MFA_TARGET_ITEMS");
@@ -77,7 +78,12 @@ int32_t target_items_of(const mfa_config* c)
         const long v = std::strtol(s, nullptr, 10);
         if (v >= 1 && v <= 4096) return (int32_t)v;
     }
-    return kDefaultTargetItems;
+    return 0;
+}
+int32_t target_items_of(const mfa_config* c)
+{
+    const int32_t asked = asked_target_items(c);
+    return asked ? asked : kDefaultTargetItems;
 }
 
 bool fixed_schedule_of(const mfa_config* c)
@@ -192,6 +198,7 @@ void fill_common(const mfa_ctx* ctx, AttnArgs& a, int32_t B, int32_t hint)
     a.ws_ml = ctx->ws_ml;
     a.ws_seg = ctx->ws_seg;
     a.n_wgs = ctx->fixed_splits ? 0 : balanced_workgroups(B, hint, ctx->target_items);
+    a.may_be_brief = ctx->may_be_brief;
     a.scale_log2e = ctx->cfg.softmax_scale * 1.44269504088896340736f;
 }
 
@@ -233,6 +240,7 @@ mfa_status mfa_decode_init(const mfa_config* cfg, void* d_workspace, size_t work
     ctx->cfg = *cfg;
     ctx->target_items = target;
     ctx->fixed_splits = fixed_schedule_of(cfg);
+    ctx->may_be_brief = !ctx->fixed_splits && asked_target_items(cfg) == 0;
     ctx->max_items = w.max_items;
     unsigned char* base = static_cast<unsigned char*>(d_workspace);
     ctx->ws_acc = reinterpret_cast<float*>(base + w.acc);

@@ -16,10 +16,12 @@
 //
 // 8-bit and 4-bit caches (e4m3 / e2m1 codes, one fp32 scale per token per
 // tensor): mfa_lowbit.hpp and, for little work per workgroup, mfa_lowbit_short.hpp.
+// Short contexts of any cache type: mfa_brief.hpp, one launch and nothing to merge.
 // The key scale multiplies the score column of its token, the value scale rides
 // on the attention weight of its token.
 #include <hip/hip_ext.h>
 
+#include "mfa_brief.hpp"
 #include "mfa_kernel_choice.hpp"
 #include "mfa_lowbit_short.hpp"
 #include "mfa_merge_place.hpp"
@@ -347,6 +349,28 @@ AttnKernel multi_kernel(int q_len, bool paged, bool short_work)
     return {paged ? (const void*)decode_bf16_multi_kernel<true, 4> : (const void*)decode_bf16_multi_kernel<false, 4>, kMultiThreads, kMultiLdsBytes};
 }
 
+template <int BITS, int NH, int DS>
+AttnKernel brief_form(bool paged)
+{
+    using S = BriefShape<BITS, NH, DS>;
+    return {paged ? (const void*)brief_attn_kernel<true, BITS, NH, DS> : (const void*)brief_attn_kernel<false, BITS, NH, DS>, S::kThreads, S::kLdsBytes};
+}
+template <int BITS>
+AttnKernel brief_kernel(bool paged, int parts)
+{
+    return parts == 16 ? brief_form<BITS, 1, 4>(paged) : parts == 8 ? brief_form<BITS, 1, 2>(paged) : parts == 4 ? brief_form<BITS, 1, 1>(paged) : brief_form<BITS, 2, 1>(paged);
+}
+AttnKernel brief_kernel(mfa_kv_dtype kv_dtype, bool paged, int parts)
+{
+    return kv_dtype == MFA_KV_BF16 ? brief_kernel<16>(paged, parts) : kv_dtype == MFA_KV_FP8_E4M3 ? brief_kernel<8>(paged, parts) : brief_kernel<4>(paged, parts);
+}
+// Workgroups per row of brief_attn_kernel, 0 where another kernel takes the call (mfa_kernel_choice.hpp)
+int brief_cut(const AttnArgs& a, mfa_kv_dtype kv_dtype)
+{
+    if (!a.may_be_brief) return 0;
+    return brief_parts(kv_dtype == MFA_KV_BF16 ? 16 : kv_dtype == MFA_KV_FP8_E4M3 ? 8 : 4, a.q_len, (int64_t)a.B * a.q_len, a.max_seq_len_hint);
+}
+
 // 64-token tiles per workgroup at the length of the hint (the host knows no other).
 int64_t tiles_per_sequence(const AttnArgs& a) { return (a.max_seq_len_hint + kTile - 1) / kTile; }
 int64_t tiles_per_workgroup(const AttnArgs& a) { return a.n_wgs > 0 ? a.B * tiles_per_sequence(a) / a.n_wgs : a.chunk_tokens / kTile; }
@@ -366,6 +390,12 @@ bool short_lowbit_work(const AttnArgs& a, mfa_kv_dtype kv_dtype)
 
 hipError_t prepare_decode_attn_kernels()
 {
+    for (const int parts : {2, 4, 8, 16})
+        for (int form = 0; form < 6; ++form) {
+            const AttnKernel k = brief_kernel(form < 2 ? MFA_KV_BF16 : form < 4 ? MFA_KV_FP8_E4M3 : MFA_KV_FP4_E2M1, (form & 1) != 0, parts);
+            const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds_bytes);
+            if (e != hipSuccess) return e;
+        }
     for (int form = 0; form < 6; ++form) {            // three and four tokens, three tokens for little work; paged or not
         const AttnKernel k = multi_kernel(form / 2 == 1 ? 4 : 3, (form & 1) != 0, form / 2 == 2);
         const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds_bytes);
@@ -400,6 +430,14 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
         else                                  hipLaunchKernelGGL(merge_splits_kernel<false>, dim3((unsigned)(kMergeBlocksPerRow * rows)), dim3(256), 0, stream, args);
         return hipGetLastError();
     };
+    if (const int parts = brief_cut(a, kv_dtype)) {
+        AttnArgs args = a;
+        void* params[] = {&args};
+        const AttnKernel k = brief_kernel(kv_dtype, a.block_table != nullptr, parts);
+        const unsigned rows = (unsigned)(a.B * a.q_len);
+        const hipError_t e = hipExtLaunchKernel(k.fn, dim3(8u * (unsigned)parts * ((rows + 7) / 8)), dim3(k.threads), params, k.lds_bytes, stream, ev_before, ev_after, 0);
+        return e != hipSuccess ? e : hipGetLastError();
+    }
     // Three and four query tokens over a bf16 cache, batches the per-wave schedule covers: one pass over the cache
     // by the kernel that keeps all of a sequence's query tokens in one wave.
     if (a.q_len >= 3 && kv_dtype == MFA_KV_BF16 && a.B <= kWaveScanChunks * 64) {

@@ -1,0 +1,79 @@
+"""Short contexts, which one launch works off without cutting them: every form of that kernel (by the number of rows) at the edges of its
+units of 32 tokens and rounds of waves, for every cache type, layout and number of query tokens.  The same weights rounded to bf16 and sums in
+single precision as elsewhere: the tolerances of the other attention tests."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_19427_amd as mfa
+from paper_2507_19427_amd import workloads as W
+
+import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [0, 1, 2, 3, 31, 32, 33, 64, 65, 127, 160, 161, 255, 256, 257, 320]
+# (sequences, query tokens, longest): 1 .. 16, 17 .. 32, 33 .. 64 and more rows; a hint of less than a unit; several rounds of every wave
+CASES = [(1, 1, 20), (5, 3, 700), (7, 4, 321), (16, 1, 1500), (30, 1, 600), (21, 2, 330), (20, 3, 90), (60, 1, 1000), (90, 1, 512), (35, 2, 257)]
+
+
+def _attend(ctx, case, q, hint):
+    d = U.to_dev
+    f = mfa.mfa_decode_attn_paged_multi if case.paged else mfa.mfa_decode_attn_multi
+    cache = (case.k_pool, case.v_pool, case.block_table) if case.paged else (case.k, case.v)
+    scales = (case.k_scale_pool, case.v_scale_pool) if case.paged else (case.k_scale, case.v_scale)
+    out = f(ctx, d(q), *[d(t) for t in cache], d(case.seq_lens), hint, *[d(t) for t in scales])
+    torch.cuda.synchronize()
+    return out.cpu()
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8", "fp4"])
+@pytest.mark.parametrize("B,q_len,longest", CASES)
+def test_short_contexts(B, q_len, longest, kv):
+    print(f"\n[case] short contexts {B} x {longest}, {q_len} query tokens, {kv}", flush=True)
+    lens = [min(EDGES[(3 * b + 1) % len(EDGES)], longest) for b in range(B)]
+    lens[-1] = longest
+    ctx = U.get_ctx()
+    paged = W.make_paged_case("brief", 40 + B, lens, kv_dtype=kv, spare_pages=3, poison=True)
+    case = W.paged_to_contiguous(paged, longest)
+    q = W.make_multi_query(case, q_len, 7) if q_len > 1 else case.q.view(B, 1, 64, 256)
+    got = _attend(ctx, case, q, longest)
+    assert torch.equal(got, _attend(ctx, paged, q, longest))
+    # the kernels that cut the cache, which have tests of their own
+    tol = U.TOL_BF16 if kv == "bf16" else U.TOL_FP8
+    assert U.row_normalised_error(got.numpy(), _attend(U.get_ctx(target_workgroups=256), case, q, longest).numpy()) <= tol
+    # the oracle on some rows: query token j attends to the first L - (q_len - 1 - j) tokens
+    full, worst = case.seq_lens, 0.0
+    for j in range(q_len):
+        case.q, case.seq_lens = q[:, j].contiguous(), (full - (q_len - 1 - j)).clamp(min=0).to(torch.int32)
+        rows = U.sample_rows(case, 12, seed=j)
+        worst = max(worst, U.row_normalised_error(np.stack([got[b, j, h].numpy() for b, h in rows]), U.run_oracle(case, rows=rows)))
+    print(f"   error {worst:.2e}", flush=True)
+    assert worst <= tol
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8", "fp4"])
+@pytest.mark.parametrize("B", [2, 20, 40, 70])
+def test_scores_of_minus_infinity_and_growing_ones(B, kv):
+    """Tokens 0 .. 39 (a unit and part of one) have scores of -inf and count for nothing; later scores grow by hundreds, so that every wave's reference
+    moves.  The rows are those of the same cache without its first 40 tokens."""
+    S, skip = 300, 40
+    case = W.make_contiguous_case("brief inf", 90 + B, B=B, S=S, kv_dtype=kv, poison=False)
+    case.q[..., 0] = 1.0
+    if kv == "bf16":
+        case.k[:, skip:] *= (1 + torch.arange(S - skip) / 20).to(torch.bfloat16)[None, :, None]
+        case.k[:, :skip, 0] = float("-inf")
+    else:
+        case.k_scale[:, skip:] *= 1 + torch.arange(S - skip)[None, :] / 20
+        case.k.view(torch.uint8)[:, :skip] = 0
+        case.k.view(torch.uint8)[:, :skip, 0] = 0xB8 if kv == "fp8" else 0x0A            # -1 in dim 0, 0 elsewhere
+        case.k_scale[:, :skip] = float("inf")
+    got = _attend(U.get_ctx(), case, case.q.view(B, 1, 64, 256), S)
+    for name in ("k", "v", "k_scale", "v_scale"):
+        t = getattr(case, name)
+        setattr(case, name, None if t is None else t[:, skip:].contiguous())
+    case.seq_lens = case.seq_lens - skip
+    rows = U.sample_rows(case, 16)
+    err = U.row_normalised_error(np.stack([got[b, 0, h].numpy() for b, h in rows]), U.run_oracle(case, rows=rows))
+    print(f"\n[case] -inf and growing scores, {B} sequences, {kv}: error {err:.2e}", flush=True)
+    assert err <= (U.TOL_BF16 if kv == "bf16" else U.TOL_FP8)

@@ -44,3 +44,23 @@ def test_choice(takes_short, four_bit, q_len):
     for hint in (64, 500, 704, 705, 5000, 32768):
         seen = [takes_short(four_bit, q_len, B, hint) for B in range(1, 4097, 7)]
         assert seen == sorted(seen, reverse=True)
+
+
+def test_short_contexts(tmp_path):
+    """Which calls go uncut, and into how many parts: by rows, cache bits, query tokens and hint alone."""
+    (tmp_path / "shim.cpp").write_text('#include "mfa_kernel_choice.hpp"\nextern "C" int parts(int bits, int q_len, long rows, long hint) { return mfa::brief_parts(bits, q_len, rows, hint); }\n')
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", str(tmp_path / "shim.so"), str(tmp_path / "shim.cpp")], check=True)
+    f = ctypes.CDLL(str(tmp_path / "shim.so")).parts
+
+    def parts(bits, q_len, rows, hint):
+        return f(bits, q_len, ctypes.c_long(rows), ctypes.c_long(hint))
+    for bits in (16, 8, 4):
+        for q_len in (1, 2, 3, 4):
+            for rows in list(range(1, 600)) + [4096, 65536]:
+                # at most a workgroup per compute unit up to 128 rows, and what is cut at one hint is cut at every longer one
+                p = parts(bits, q_len, rows, 64)
+                assert p in (0, 2, 4, 8, 16) and (p > 0 or rows > 128) and (rows > 128 or p * rows <= 256)
+                hints = [parts(bits, q_len, rows, hint) for hint in range(32, 8192, 96)]
+                assert hints == sorted(hints, reverse=True) and set(hints) <= {0, p}
+            assert parts(bits, q_len, 64, 8192) == 0 and parts(bits, q_len, 400, 64) == 0
+    assert parts(16, 1, 2, 256) == 16 and parts(16, 1, 64, 4096) == 0 and parts(8, 4, 64, 6144) == 4 and parts(8, 2, 64, 6144) == 0
