@@ -163,34 +163,54 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
 // summed in split order (m* is reached batch by batch, rescaling what has been summed).  One thread per float4 of the partial's lane-order layout; splits are
 // taken four at a time so that their loads are independent and in flight together.
 //
+// merge_waves: few rows have many partial results each, and a thread that takes them four at a time is a chain of round trips (1 x 32768: 256 of them, 29 us); then a
+// block takes a quarter as many positions, and each of its waves a run of the partial results, eight at a time.  us per call, one wave / this: 1 x 32768 43.8/21.8,
+// 2 x 8000 28.3/16.9, 4 x 4096 21.5/16.8, 6 x 6000 ragged 25.4/22.0, 8 bit, two tokens 2 x 8000 30.9/21.8, four tokens 1 x 16000 53.6/34.4, 3 x 8000 ragged 40.3/32.6;
+// 12 x 8000 ragged 25.8/24.3, two tokens 8 x 4000 25.5/24.6; from there on one wave is ahead (16 x 4096 24.7/25.1, 20 x 8000 38.9/40, 32 x 4096 33.9/36.3, 128 x 8192 ragged 110/119), and with few
+// partial results per row (16 x 256, four 10.3/12.0; 2 x 512, eight 10.5/11.1; 4 x 1024, sixteen 13.0/12.4).
+int merge_waves(const AttnArgs& a)
+{
+    const int rows = a.B * a.n_here, pieces = a.n_wgs > 0 ? a.n_wgs / a.B : a.n_splits;
+    return rows > 16 || pieces < (rows <= 8 ? 12 : 17) ? 1 : rows <= 8 ? 8 : 4;
+}
 // merge_by_die: whether the blocks of a die take the rows of that die (mfa_merge_place.hpp).  us per call so / with rows in order:
-//   one token    1 x 32768 45.2/49.3   2 x 32768 36.8/41.4   4 x 32768 39.2/43.9   9 x 8000 27.3/31.9   23 x 4096 28.4/33.0   30 x 6000 ragged 31.9/36.0
-//     8 bit, ragged   9 x 12000 23.8/28.8   23 x 20011 35.3/39.2   bf16   127 x 4000 44.0/45.1
-//   four tokens  1 x 32768 59.4/61.7   2 x 32768 54.3/55.2   4 x 25000 54.0/55.5   7 x 14285 54.1/55.0
-// With all tokens of a sequence on the die of its middle instead, four tokens took 81.6 at 1 x 32768, 63.7 at 2 x 32768, 57.9 at 4 x 25000 and 58.8 (now 55.1) at 9 x 11111 (up to three rows
-// of 16 blocks wait for one L2 while others idle).  Looked up in the records, which is exact for ragged lengths, with what a die has
+//   one token   23 x 4096 28.4/33.0   30 x 6000 ragged 31.9/36.0   8 bit, ragged 23 x 20011 35.3/39.2   bf16 127 x 4000 44.0/45.1
+//   several waves a block  5 x 8000 21.3/21.5   6 x 3000 ragged 17.9/19.1   8 bit, two tokens, 4 x 8000 24.4/24.7   16 x 4096 24.7/25.2
+// Not where it would leave dies idle or give some of them twice the rows of others: 1 x 32768 30.2/21.7, 3 x 8000 20.8/19.1, 4 x 16000 ragged 25.9/23.5, 12 x 8000 ragged 24.7/24.1, four
+// tokens 3 x 8000 ragged 38.1/32.4.  Looked up in the records, which is exact for ragged lengths, with what a die has
 // beyond its share given to others: the same for most, but 122.2 against 120.5 at 128 x 8192 ragged and 24.8 against 22.6 at 128 x 400.
 // Not by die with less than a tile for every compute unit, where a sequence's many one-tile pieces lie on several dies anyway (5 x 1500
 // ragged: 16.7, in order 16.2), unless the batch divides evenly.
-bool merge_by_die(int B, int n_wgs) { return n_wgs > 0 && (n_wgs & 7) == 0 && (n_wgs >= 256 || (B & 7) == 0); }
+bool merge_by_die(const AttnArgs& a, int waves)
+{
+    const int rows = a.B * a.n_here;
+    if (waves > 1 && (rows <= 4 || (rows > 8 && (a.B & 7) != 0))) return false;
+    return a.n_wgs > 0 && (a.n_wgs & 7) == 0 && (a.n_wgs >= 256 || (a.B & 7) == 0);
+}
 
 // With many short sequences nearly every block only finds that a workgroup has written its row's result, and what counts is the way there:
 // the rule is a template argument, the division by 1 .. 4 a shift or a multiplication, length and record one round trip.  us of the kernel
 // at 4000 / 512 sequences of one tile: 44.7 / 6.6 without these, 27.6 / 4.8 now.
-template <bool BY_DIE>                                                // (only under the balanced schedule)
-__global__ __launch_bounds__(256) void merge_splits_kernel(AttnArgs a)
+//
+// WAVES > 1: a block takes 64 float4 of a row, each of its waves a run of consecutive partial results, and the
+// waves' sums are added in order through LDS.
+template <bool BY_DIE, int WAVES>                                     // (BY_DIE: only under the balanced schedule)
+__global__ __launch_bounds__(WAVES == 1 ? 256 : 64 * WAVES) void merge_splits_kernel(AttnArgs a)
 {
+    constexpr int kThreads = WAVES == 1 ? 256 : 64;                   // positions of a block
+    constexpr int kBlocksPerRow = kHeads * kHeadDim / 4 / kThreads;
     const int n_here = a.n_here;                                      // query tokens of this launch, 1 .. 4
     static_assert(kMaxQueryTokens == 4, "the division by n_here");
     const bool balanced = BY_DIE || a.n_wgs > 0;
+    const int thread = WAVES == 1 ? threadIdx.x : threadIdx.x & 63;
     int row, p;                                                       // sequence * n_here + query token of the launch; position in the partial's lane-order layout
     if (BY_DIE) {
-        row = merge_row(blockIdx.x, a.B * n_here);
+        row = merge_row(blockIdx.x, a.B * n_here, kBlocksPerRow);
         if (row < 0) return;
-        p = (int)((blockIdx.x >> 3) & 15) * 256 + threadIdx.x;
+        p = (int)((blockIdx.x >> 3) % kBlocksPerRow) * kThreads + thread;
     } else {
-        row = (int)(blockIdx.x >> 4);
-        p = (int)(blockIdx.x & 15) * 256 + threadIdx.x;
+        row = (int)(blockIdx.x / kBlocksPerRow);
+        p = (int)(blockIdx.x % kBlocksPerRow) * kThreads + thread;
     }
     const int b = n_here == 3 ? (int)((unsigned)row / 3u) : row >> (n_here >> 1);
     const int qtok = row - b * n_here;
@@ -227,32 +247,56 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(AttnArgs a)
 
     // One pass with a running reference exponent: a batch's (m, l) pairs and accumulator pieces are loaded
     // together, so the weights do not wait for a first round trip that only fetches the maxima.
+    constexpr int kBatch = WAVES == 1 ? 4 : 8;
     float m = -INFINITY;
     float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
     float l = 0.f;
-    for (int s0 = 0; s0 < n_valid; s0 += 4) {
-        float2 ml[4];
-        float4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int s = s0 + u < n_valid ? s0 + u : n_valid - 1;
-            ml[u] = ml_base[(size_t)s * slot_step * kHeads];
-            v[u] = acc_base[(size_t)s * slot_step * (kHeads * kHeadDim / 4)];
-        }
+    auto add = [&](const float2* ml, const float4* v, int n) {        // pieces 0 .. n - 1 of a batch (the others repeat the last)
         float m_new = m;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) m_new = fmaxf(m_new, ml[u].x);   // (a repeated last piece changes nothing)
+        for (int u = 0; u < kBatch; ++u) m_new = fmaxf(m_new, ml[u].x);
         const float m_safe = m_new == -INFINITY ? 0.f : m_new;       // pieces without tokens have m = -inf
         const float keep = fast_exp2(m - m_safe);                    // 0 while nothing has been summed
         sum.x *= keep; sum.y *= keep; sum.z *= keep; sum.w *= keep;
         l *= keep;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float w = s0 + u < n_valid ? fast_exp2(ml[u].x - m_safe) : 0.f;
+        for (int u = 0; u < kBatch; ++u) {
+            const float w = u < n ? fast_exp2(ml[u].x - m_safe) : 0.f;
             sum.x += w * v[u].x; sum.y += w * v[u].y; sum.z += w * v[u].z; sum.w += w * v[u].w;
             l += w * ml[u].y;
         }
         m = m_new;
+    };
+    const int wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int first = n_valid * wave / WAVES, end = n_valid * (wave + 1) / WAVES;
+    for (int s0 = first; s0 < end; s0 += kBatch) {
+        float2 ml[kBatch];
+        float4 v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int s = s0 + u < end ? s0 + u : end - 1;
+            ml[u] = ml_base[(size_t)s * slot_step * kHeads];
+            v[u] = acc_base[(size_t)s * slot_step * (kHeads * kHeadDim / 4)];
+        }
+        add(ml, v, end - s0);
+    }
+    if constexpr (WAVES > 1) {
+        __shared__ float4 part[WAVES][64];
+        __shared__ float2 part_ml[WAVES][64];
+        part[wave][thread] = sum;
+        part_ml[wave][thread] = make_float2(m, l);
+        __syncthreads();
+        if (wave != 0) return;
+        m = -INFINITY;
+        sum = make_float4(0.f, 0.f, 0.f, 0.f);
+        l = 0.f;
+        for (int s0 = 0; s0 < WAVES; s0 += kBatch) {
+            float2 ml[kBatch];
+            float4 v[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) { const int s = s0 + u < WAVES ? s0 + u : WAVES - 1; ml[u] = part_ml[s][thread]; v[u] = part[s][thread]; }
+            add(ml, v, WAVES - s0);
+        }
     }
     const float inv = 1.0f / l;
     *o = make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv);
@@ -423,12 +467,18 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
     // times at which that kernel starts and ends on the device, with no launch gap inside the interval.
     // (With more than two query tokens: the first pair's.)
     if (!(ev_before && ev_after)) ev_before = ev_after = nullptr;
-    static_assert(kHeads * kHeadDim / 4 == kMergeBlocksPerRow * 256, "sixteen blocks per row");
     auto launch_merge = [&](const AttnArgs& args) {
         const int rows = args.B * args.n_here;
-        if (merge_by_die(args.B, args.n_wgs)) hipLaunchKernelGGL(merge_splits_kernel<true>, dim3(merge_blocks_by_die(rows)), dim3(256), 0, stream, args);
-        else                                  hipLaunchKernelGGL(merge_splits_kernel<false>, dim3((unsigned)(kMergeBlocksPerRow * rows)), dim3(256), 0, stream, args);
-        return hipGetLastError();
+        const int waves = merge_waves(args);
+        const bool by_die = merge_by_die(args, waves);
+        const int per_row = waves == 1 ? kMergeBlocksPerRow : kHeads * kHeadDim / 4 / 64;
+        const void* fn = waves == 8 ? (by_die ? (const void*)merge_splits_kernel<true, 8> : (const void*)merge_splits_kernel<false, 8>)
+                       : waves == 4 ? (by_die ? (const void*)merge_splits_kernel<true, 4> : (const void*)merge_splits_kernel<false, 4>)
+                                     : (by_die ? (const void*)merge_splits_kernel<true, 1> : (const void*)merge_splits_kernel<false, 1>);
+        AttnArgs copy = args;
+        void* params[] = {&copy};
+        const hipError_t e = hipLaunchKernel(fn, dim3(by_die ? merge_blocks_by_die(rows, per_row) : (unsigned)(per_row * rows)), dim3(waves == 1 ? 256 : 64 * waves), params, 0, stream);
+        return e != hipSuccess ? e : hipGetLastError();
     };
     if (const int parts = brief_cut(a, kv_dtype)) {
         AttnArgs args = a;

@@ -10,35 +10,31 @@ namespace mfa {
 //
 // The lines, in tokens of the hint, lie where neither equal lengths nor lengths drawn from 1 .. hint lose.  us per call, the other kernels (streaming
 // kernel and merge) / this one, equal and drawn lengths; in brackets what lies beyond a line:
-//   bf16, one token    2 x 256  9.8/6.6     2 x 1024  11.9/11.0 12.0/10.9    (2 x 1536  13.3/13.5 13.2/13.4)    16 x 1536  18.3/16.5 19.1/14.1    (16 x 2048  19.9/20.1 20.2/17.8)
+//   bf16, one token    2 x 256  9.8/6.6     2 x 1024  11.6/11.0 11.7/10.9    (3 x 1280  12.4/12.6 12.2/12.3)    6 x 1536  17.2/13.8 15.9/13.5    16 x 1536  18.3/16.5 19.1/14.1    (16 x 2048  19.9/20.1 20.2/17.8)
 //                      18 x 1536  19.2/17.9 18.9/16.9    (18 x 2048  21.0/20.9 20.2/20.2)    34 x 1280  22.1/20.7 20.2/19.7    (34 x 1536  24.1/22.8 20.7/21.7)    48 x 1536  28.7/23.1 22.7/21.9
 //                      66 x 512  21.1/18.0 20.0/18.6    (66 x 640  23.0/20.0 20.8/21.0)    100 x 768  30.3/23.5 24.8/23.8    128 x 768  32.7/24.7 27.6/24.6
-//   8 bit, one token   2 x 256  10.9/6.2    2 x 1536  14.4/12.9 14.0/12.8    (2 x 2048  15.6/15.7 15.5/15.4)    16 x 2048  19.1/17.6 19.2/15.9    18 x 2048  20.3/18.3 18.0/17.4
+//   8 bit, one token   2 x 256  10.9/6.2    1 x 1280  12.3/11.6     (1 x 1536  12.5/12.9)    6 x 2048  20.4/15.6 16.4/15.4    16 x 2048  19.1/17.6 19.2/15.9    18 x 2048  20.3/18.3 18.0/17.4
 //                      34 x 1536  22.3/18.8 18.2/17.5    (34 x 2048  24.4/22.2 19.0/20.6)    64 x 2048  30.2/24.3 23.8/22.6    (48 x 2048  28.4/22.5 22.0/22.1)
 //                      66 x 512  20.9/17.1 17.8/17.5    (66 x 640  21.3/19.2 19.5/19.8)    100 x 640  25.4/19.8 22.0/20.4    128 x 640  26.4/20.5 23.7/21.0
-//   4 bit, one token   1 x 2048  14.5/14.5 14.6/14.5    16 x 2048  18.1/15.9 19.4/14.9    32 x 2048  20.5/17.9 17.6/16.1    34 x 1536  20.2/17.0 17.0/15.4    48 x 2048  25.2/20.8 20.7/20.0
+//   4 bit, one token   1 x 1536  12.3/11.9    (1 x 1792  12.3/13.1)    6 x 2048  20.7/14.6 15.7/14.2    16 x 2048  18.1/15.9 19.4/14.9    32 x 2048  20.5/17.9 17.6/16.1    34 x 1536  20.2/17.0 17.0/15.4    48 x 2048  25.2/20.8 20.7/20.0
 //                      66 x 640  20.1/17.9 18.8/18.3    100 x 768  24.5/20.5 21.2/20.6    128 x 768  25.3/21.0 23.5/21.2
 //   two tokens within 1 us of twice the sequences
 // Three and four tokens: the other kernels have more to merge (bf16) or take two passes (8 and 4 bit).  (With weights rounded to bf16 and rolled loads, up to a tenth slower
 // than now:)
-//   bf16, four   1 x 2048  22.9/18.0    8 x 2048  34.8/22.7 31.7/22.1    16 x 1536  36.3/25.9 33.4/25.0    64 x 256  36.9/29.0 31.8/26.7      three  33 x 768  31.7/25.6 28.1/25.3
-//   8 bit, four  1 x 6144  53.0/39.3    8 x 6144  52.4/43.9 50.5/43.2    16 x 6144  66.0/54.8 55.5/53.1    32 x 2048  58.3/45.2 45.8/44.1    64 x 1024  60.6/53.7 54.7/48.2
-//   4 bit, four  1 x 6144  51.8/32.6    8 x 6144  49.2/39.8 49.2/39.3    16 x 6144  60.6/47.1 52.1/46.3    32 x 2048  54.2/39.9 42.9/38.8    (64 x 2048  72.4/76.8 60.9/68.6)
+//   bf16, four   1 x 2048  20.7/17.9    8 x 2048  34.8/22.7 31.7/22.1    16 x 1536  36.3/25.9 33.4/25.0    64 x 256  36.9/29.0 31.8/26.7      three  33 x 768  31.7/25.6 28.1/25.3
+//   8 bit, four  1 x 4096  31.7/27.5    (1 x 6144  36.9/38.7)    4 x 6144  46.7/41.0 48.9/38.6    8 x 6144  52.4/43.9 50.5/43.2    16 x 6144  66.0/54.8 55.5/53.1    32 x 2048  58.3/45.2 45.8/44.1    64 x 1024  60.6/53.7 54.7/48.2
+//   4 bit, four  1 x 4096  30.9/24.6    4 x 6144  45.4/38.1 47.9/36.7    8 x 6144  49.2/39.8 49.2/39.3    16 x 6144  60.6/47.1 52.1/46.3    32 x 2048  54.2/39.9 42.9/38.8    (64 x 2048  72.4/76.8 60.9/68.6)
 //   8 bit, three  128 x 256  53.6/37.1 54.1/35.9
-constexpr int kBriefBands = 8;
-constexpr int kBriefRows[kBriefBands] = {16, 32, 47, 64, 99, 128, 256, 384};
-constexpr int kBriefParts[kBriefBands] = {16, 8, 4, 4, 2, 2, 2, 2};
+constexpr int kBriefBands = 9;
+constexpr int kBriefRows[kBriefBands] = {4, 16, 32, 47, 64, 99, 128, 256, 384};
+constexpr int kBriefParts[kBriefBands] = {16, 16, 8, 4, 4, 2, 2, 2, 2};
 constexpr int kBriefLines[2][3][kBriefBands] = {                        // [three or four tokens][16, 8, 4 bits]
-    {{1536, 1536, 1280, 1536, 512, 768, 0, 0}, {2048, 2048, 1536, 1792, 512, 640, 0, 0}, {2048, 2048, 1536, 2048, 640, 768, 0, 0}},
-    {{2048, 2048, 1536, 1536, 768, 768, 256, 0}, {6144, 6144, 6144, 6144, 2048, 2048, 1024, 256}, {6144, 6144, 6144, 6144, 2048, 2048, 1024, 256}}};
+    {{960, 1536, 1536, 1280, 1536, 512, 768, 0, 0}, {1280, 2048, 2048, 1536, 1792, 512, 640, 0, 0}, {1536, 2048, 2048, 1536, 2048, 640, 768, 0, 0}},
+    {{2048, 2048, 2048, 1536, 1536, 768, 768, 256, 0}, {4096, 6144, 6144, 6144, 6144, 2048, 2048, 1024, 256}, {4096, 6144, 6144, 6144, 6144, 2048, 2048, 1024, 256}}};
 constexpr int brief_parts(int bits, int q_len, int64_t rows, int64_t hint)
 {
     for (int band = 0; band < kBriefBands; ++band)
-        if (rows <= kBriefRows[band]) {
-            int line = kBriefLines[q_len >= 3][bits == 16 ? 0 : bits == 8 ? 1 : 2][band];
-            if (q_len < 3 && rows < 4 && bits != 4) line -= 512;        // (1 .. 3 rows leave most of the device idle)
-            return hint <= line ? kBriefParts[band] : 0;
-        }
+        if (rows <= kBriefRows[band]) return hint <= kBriefLines[q_len >= 3][bits == 16 ? 0 : bits == 8 ? 1 : 2][band] ? kBriefParts[band] : 0;
     return 0;
 }
 

@@ -15,12 +15,12 @@ constexpr int kMergeBlocksPerRow = 16;
 constexpr int first_row_of_die(int die, int rows) { return (int)((2u * (unsigned)die * (unsigned)rows + 7u) >> 4); }
 
 // The row of a block, or -1: a die has room for ceil(rows / 8) rows and may have one less.  The block's place among the row's sixteen: (block >> 3) & 15.
-constexpr int merge_row(unsigned block, int rows)
+constexpr int merge_row(unsigned block, int rows, int blocks_per_row = kMergeBlocksPerRow)
 {
-    const int die = (int)(block & 7u), row = first_row_of_die(die, rows) + (int)(block >> 7);
+    const int die = (int)(block & 7u), row = first_row_of_die(die, rows) + (int)((block >> 3) / (unsigned)blocks_per_row);
     return row < first_row_of_die(die + 1, rows) ? row : -1;
 }
 
-constexpr unsigned merge_blocks_by_die(int rows) { return (unsigned)kMergeBlocksPerRow * (unsigned)((rows + 7) / 8 * 8); }
+constexpr unsigned merge_blocks_by_die(int rows, int blocks_per_row = kMergeBlocksPerRow) { return (unsigned)blocks_per_row * (unsigned)((rows + 7) / 8 * 8); }
 
 }  // namespace mfa
