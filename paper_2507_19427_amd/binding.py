@@ -142,9 +142,9 @@ def _check(status, where):
         raise MfaError(status, where)
 
 
-# The smallest calls take about as long to enqueue as to run (attention over 2 x 256 tokens: two launches, 10.5 us on the device), so what
-# is done per call is kept short: addresses and the stream go over as plain integers (the declared argument types convert them), shapes
-# are compared as they are.
+# The smallest calls take longer to enqueue than to run (a cache record of few rows: two launches, 7.4 us on the device), so what
+# is done per call is kept short: addresses and the stream go over as plain integers (the declared argument types convert them) and are taken in
+# place, shapes are compared as they are, types by identity (torch has one object of each).
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -240,7 +240,7 @@ def mfa_query_proj(ctx: MfaContext, x, w_qa, w_qb, rms_gain=None, q_out=None):
         q_out = torch.empty(B, cfg.n_q_heads, cfg.head_dim, dtype=torch.bfloat16, device=x.device)
     else:
         _want(q_out, torch.bfloat16, "q_out")
-    _check(lib().mfa_query_proj(ctx.handle, _ptr(x), _ptr(w_qa), _ptr(rms_gain), _ptr(w_qb), _ptr(q_out), B,
+    _check((_lib or lib()).mfa_query_proj(ctx.handle, x.data_ptr(), w_qa.data_ptr(), _ptr(rms_gain), w_qb.data_ptr(), q_out.data_ptr(), B,
                                 _stream()), "mfa_query_proj")
     return q_out
 
@@ -253,7 +253,7 @@ def mfa_decode_attn(ctx: MfaContext, q, k_cache, v_cache, seq_lens, max_seq_len_
     _want(seq_lens, torch.int32, "seq_lens")
     B = q.shape[0]
     kvd = _kv_dtype(k_cache)
-    if v_cache.dtype != k_cache.dtype or not k_cache.is_contiguous() or not v_cache.is_contiguous():
+    if v_cache.dtype is not k_cache.dtype or not k_cache.is_contiguous() or not v_cache.is_contiguous():
         raise TypeError("k_cache / v_cache must be contiguous and of one dtype")
     S = k_cache.shape[1]
     width = _cache_width(cfg, kvd)
@@ -271,8 +271,8 @@ def mfa_decode_attn(ctx: MfaContext, q, k_cache, v_cache, seq_lens, max_seq_len_
         _want(out, torch.float32, "out")
         if out.shape != (B, cfg.n_q_heads, cfg.head_dim):
             raise ValueError("out shape")
-    _check(getattr(lib(), _entry)(ctx.handle, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_scale), _ptr(v_scale),
-                                  kvd, S, _ptr(seq_lens), int(max_seq_len_hint), B, _ptr(out), _stream()), _entry)
+    _check(getattr(_lib or lib(), _entry)(ctx.handle, q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), _ptr(k_scale), _ptr(v_scale),
+                                  kvd, S, seq_lens.data_ptr(), int(max_seq_len_hint), B, out.data_ptr(), _stream()), _entry)
     return out
 
 
@@ -295,7 +295,7 @@ def mfa_decode_attn_paged(ctx: MfaContext, q, k_pool, v_pool, block_table, seq_l
     _want(block_table, torch.int32, "block_table")
     B = q.shape[0]
     kvd = _kv_dtype(k_pool)
-    if v_pool.dtype != k_pool.dtype or not k_pool.is_contiguous() or not v_pool.is_contiguous():
+    if v_pool.dtype is not k_pool.dtype or not k_pool.is_contiguous() or not v_pool.is_contiguous():
         raise TypeError("k_pool / v_pool must be contiguous and of one dtype")
     n_pages = k_pool.shape[0]
     if k_pool.shape != (n_pages, cfg.page_size, _cache_width(cfg, kvd)) or v_pool.shape != k_pool.shape \
@@ -313,9 +313,9 @@ def mfa_decode_attn_paged(ctx: MfaContext, q, k_pool, v_pool, block_table, seq_l
         _want(out, torch.float32, "out")
         if out.shape != (B, cfg.n_q_heads, cfg.head_dim):
             raise ValueError("out shape")
-    _check(lib().mfa_decode_attn_paged(ctx.handle, _ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(k_scale_pool),
-                                       _ptr(v_scale_pool), kvd, n_pages, _ptr(block_table), block_table.shape[1],
-                                       _ptr(seq_lens), int(max_seq_len_hint), B, _ptr(out), _stream()),
+    _check((_lib or lib()).mfa_decode_attn_paged(ctx.handle, q.data_ptr(), k_pool.data_ptr(), v_pool.data_ptr(), _ptr(k_scale_pool),
+                                       _ptr(v_scale_pool), kvd, n_pages, block_table.data_ptr(), block_table.shape[1],
+                                       seq_lens.data_ptr(), int(max_seq_len_hint), B, out.data_ptr(), _stream()),
            "mfa_decode_attn_paged")
     return out
 
@@ -330,7 +330,7 @@ def mfa_decode_attn_multi(ctx: MfaContext, q, k_cache, v_cache, seq_lens, max_se
         raise ValueError("q must be [B, q_len, H, D]")
     B, q_len = q.shape[0], q.shape[1]
     kvd = _kv_dtype(k_cache)
-    if v_cache.dtype != k_cache.dtype or not k_cache.is_contiguous() or not v_cache.is_contiguous():
+    if v_cache.dtype is not k_cache.dtype or not k_cache.is_contiguous() or not v_cache.is_contiguous():
         raise TypeError("k_cache / v_cache must be contiguous and of one dtype")
     S = k_cache.shape[1]
     width = _cache_width(cfg, kvd)
@@ -348,9 +348,9 @@ def mfa_decode_attn_multi(ctx: MfaContext, q, k_cache, v_cache, seq_lens, max_se
         _want(out, torch.float32, "out")
         if out.shape != q.shape:
             raise ValueError("out shape")
-    _check(lib().mfa_decode_attn_multi(ctx.handle, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_scale),
-                                       _ptr(v_scale), kvd, S, _ptr(seq_lens), int(max_seq_len_hint), B, q_len,
-                                       _ptr(out), _stream()), "mfa_decode_attn_multi")
+    _check((_lib or lib()).mfa_decode_attn_multi(ctx.handle, q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), _ptr(k_scale),
+                                       _ptr(v_scale), kvd, S, seq_lens.data_ptr(), int(max_seq_len_hint), B, q_len,
+                                       out.data_ptr(), _stream()), "mfa_decode_attn_multi")
     return out
 
 
@@ -365,7 +365,7 @@ def mfa_decode_attn_paged_multi(ctx: MfaContext, q, k_pool, v_pool, block_table,
         raise ValueError("q must be [B, q_len, H, D]")
     B, q_len = q.shape[0], q.shape[1]
     kvd = _kv_dtype(k_pool)
-    if v_pool.dtype != k_pool.dtype or not k_pool.is_contiguous() or not v_pool.is_contiguous():
+    if v_pool.dtype is not k_pool.dtype or not k_pool.is_contiguous() or not v_pool.is_contiguous():
         raise TypeError("k_pool / v_pool must be contiguous and of one dtype")
     n_pages = k_pool.shape[0]
     if k_pool.shape != (n_pages, cfg.page_size, _cache_width(cfg, kvd)) or v_pool.shape != k_pool.shape \
@@ -383,10 +383,10 @@ def mfa_decode_attn_paged_multi(ctx: MfaContext, q, k_pool, v_pool, block_table,
         _want(out, torch.float32, "out")
         if out.shape != q.shape:
             raise ValueError("out shape")
-    _check(lib().mfa_decode_attn_paged_multi(ctx.handle, _ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(k_scale_pool),
-                                             _ptr(v_scale_pool), kvd, n_pages, _ptr(block_table),
-                                             block_table.shape[1], _ptr(seq_lens), int(max_seq_len_hint), B, q_len,
-                                             _ptr(out), _stream()), "mfa_decode_attn_paged_multi")
+    _check((_lib or lib()).mfa_decode_attn_paged_multi(ctx.handle, q.data_ptr(), k_pool.data_ptr(), v_pool.data_ptr(), _ptr(k_scale_pool),
+                                             _ptr(v_scale_pool), kvd, n_pages, block_table.data_ptr(),
+                                             block_table.shape[1], seq_lens.data_ptr(), int(max_seq_len_hint), B, q_len,
+                                             out.data_ptr(), _stream()), "mfa_decode_attn_paged_multi")
     return out
 
 
@@ -416,16 +416,15 @@ def mfa_debug_stream_read(ctx: MfaContext, a, b):
     _check(lib().mfa_debug_stream_read(ctx.handle, _ptr(a), _ptr(b), nbytes, _stream()), "mfa_debug_stream_read")
 
 
-def _check_cache_pair(k, v, ks, vs, rows_shape):
-    kvd = _kv_dtype(k)
-    if v.dtype != k.dtype or not k.is_contiguous() or not v.is_contiguous() or v.shape != k.shape:
+def _check_cache_pair(k, v, ks, vs):
+    rows_shape = k.shape[:2]
+    if v.dtype is not k.dtype or not k.is_contiguous() or not v.is_contiguous() or v.shape != k.shape:
         raise TypeError("key and value caches must be contiguous, of one dtype and one shape")
     for t, nm in ((ks, "k_scale"), (vs, "v_scale")):
         if t is not None:
             _want(t, torch.float32, nm)
-            if tuple(t.shape) != tuple(rows_shape):
+            if t.shape != rows_shape:
                 raise ValueError(nm + " shape")
-    return kvd
 
 
 def mfa_kv_append(ctx: MfaContext, x, w_kv, k_cache, v_cache, seq_lens, k_scale=None, v_scale=None):
@@ -435,13 +434,14 @@ def mfa_kv_append(ctx: MfaContext, x, w_kv, k_cache, v_cache, seq_lens, k_scale=
     _want(w_kv, torch.bfloat16, "w_kv")
     _want(seq_lens, torch.int32, "seq_lens")
     B = x.shape[0]
+    kvd = _kv_dtype(k_cache)
+    S = k_cache.shape[1] if k_cache.dim() == 3 else 0
     if x.shape != (B, cfg.d_model) or w_kv.shape != (cfg.d_model, 2 * cfg.head_dim) or \
-            k_cache.dim() != 3 or k_cache.shape[0] != B or k_cache.shape[2] != _cache_width(cfg, _kv_dtype(k_cache)) or \
-            seq_lens.shape != (B,):
+            k_cache.shape != (B, S, _cache_width(cfg, kvd)) or seq_lens.shape != (B,):
         raise ValueError("kv append shapes do not match")
-    kvd = _check_cache_pair(k_cache, v_cache, k_scale, v_scale, k_cache.shape[:2])
-    _check(lib().mfa_kv_append(ctx.handle, _ptr(x), _ptr(w_kv), kvd, _ptr(k_cache), _ptr(v_cache), _ptr(k_scale),
-                               _ptr(v_scale), k_cache.shape[1], _ptr(seq_lens), B, _stream()), "mfa_kv_append")
+    _check_cache_pair(k_cache, v_cache, k_scale, v_scale)
+    _check((_lib or lib()).mfa_kv_append(ctx.handle, x.data_ptr(), w_kv.data_ptr(), kvd, k_cache.data_ptr(), v_cache.data_ptr(), _ptr(k_scale),
+                               _ptr(v_scale), S, seq_lens.data_ptr(), B, _stream()), "mfa_kv_append")
 
 
 def mfa_kv_append_paged(ctx: MfaContext, x, w_kv, k_pool, v_pool, block_table, seq_lens, k_scale_pool=None,
@@ -454,13 +454,14 @@ def mfa_kv_append_paged(ctx: MfaContext, x, w_kv, k_pool, v_pool, block_table, s
     _want(block_table, torch.int32, "block_table")
     B = x.shape[0]
     n_pages = k_pool.shape[0]
+    kvd = _kv_dtype(k_pool)
     if x.shape != (B, cfg.d_model) or w_kv.shape != (cfg.d_model, 2 * cfg.head_dim) or \
-            k_pool.shape != (n_pages, cfg.page_size, _cache_width(cfg, _kv_dtype(k_pool))) or \
+            k_pool.shape != (n_pages, cfg.page_size, _cache_width(cfg, kvd)) or \
             block_table.shape[0] != B or seq_lens.shape != (B,):
         raise ValueError("paged kv append shapes do not match")
-    kvd = _check_cache_pair(k_pool, v_pool, k_scale_pool, v_scale_pool, k_pool.shape[:2])
-    _check(lib().mfa_kv_append_paged(ctx.handle, _ptr(x), _ptr(w_kv), kvd, _ptr(k_pool), _ptr(v_pool), _ptr(k_scale_pool),
-                                     _ptr(v_scale_pool), n_pages, _ptr(block_table), block_table.shape[1], _ptr(seq_lens),
+    _check_cache_pair(k_pool, v_pool, k_scale_pool, v_scale_pool)
+    _check((_lib or lib()).mfa_kv_append_paged(ctx.handle, x.data_ptr(), w_kv.data_ptr(), kvd, k_pool.data_ptr(), v_pool.data_ptr(), _ptr(k_scale_pool),
+                                     _ptr(v_scale_pool), n_pages, block_table.data_ptr(), block_table.shape[1], seq_lens.data_ptr(),
                                      B, _stream()), "mfa_kv_append_paged")
 
 
@@ -469,7 +470,8 @@ def mfa_debug_kv_record(ctx: MfaContext, kv, k_cache, v_cache, seq_lens, k_scale
     _want(kv, torch.float32, "kv")
     _want(seq_lens, torch.int32, "seq_lens")
     B = kv.shape[0]
-    kvd = _check_cache_pair(k_cache, v_cache, k_scale, v_scale, k_cache.shape[:2])
+    kvd = _kv_dtype(k_cache)
+    _check_cache_pair(k_cache, v_cache, k_scale, v_scale)
     stride = 0 if block_table is not None else k_cache.shape[1]
     width = block_table.shape[1] if block_table is not None else 0
     _check(lib().mfa_debug_kv_record(ctx.handle, _ptr(kv), kvd, _ptr(k_cache), _ptr(v_cache), _ptr(k_scale), _ptr(v_scale),
@@ -489,7 +491,7 @@ def mfa_out_proj(ctx: MfaContext, attn_out, w_o, y=None):
         y = torch.empty(B, cfg.d_model, dtype=torch.bfloat16, device=attn_out.device)
     else:
         _want(y, torch.bfloat16, "y")
-    _check(lib().mfa_out_proj(ctx.handle, _ptr(attn_out), _ptr(w_o), _ptr(y), B, _stream()), "mfa_out_proj")
+    _check((_lib or lib()).mfa_out_proj(ctx.handle, attn_out.data_ptr(), w_o.data_ptr(), y.data_ptr(), B, _stream()), "mfa_out_proj")
     return y
 
 
