@@ -91,7 +91,7 @@ typedef struct {
     int32_t max_seq_len;    /* largest max_seq_len_hint of any later call                  */
     int32_t device;         /* HIP device ordinal                                          */
     int32_t target_workgroups; /* workgroups an attention call aims for; 0 = the default, one per
-                                  compute unit of MI355X (256), short contexts apart; 1..4096     */
+                                  compute unit of MI355X (256), little work apart; 1..4096        */
     int32_t schedule;       /* mfa_schedule; MFA_SCHEDULE_BALANCED (0) is the default; batches
                                above 4096 sequences always take MFA_SCHEDULE_FIXED                 */
 } mfa_config;
@@ -208,8 +208,8 @@ MFA_API mfa_status mfa_out_proj(mfa_ctx* ctx, const float* attn_out, const void*
  * Scores and sums are accumulated in fp32 (long 8-bit and 4-bit caches: query times codes, ahead
  * of a key's scale, which leaves fp32 from query elements of about 2^100 on).  Attention weights are rounded where they
  * multiply V:
- *   short contexts that are not cut (below): to two bf16 terms (16 significant bits; the value
- *     scale of a token multiplied in before);
+ *   little work (below): to two bf16 terms (16 significant bits; the value scale of a token
+ *     multiplied in before);
  *   other bf16 caches, and 8-bit and 4-bit ones with little work per workgroup at the length of
  *     the hint: to bf16 (8 significant bits; the value scale multiplied in before);
  *   long 8-bit and 4-bit caches: weight times value scale to two e4m3 terms with one power
@@ -227,11 +227,14 @@ MFA_API mfa_status mfa_out_proj(mfa_ctx* ctx, const float* attn_out, const void*
  * individual lengths are (they are read on the device); larger batches, or a
  * context created with schedule = MFA_SCHEDULE_FIXED, cut every sequence
  * into the same number of equal chunks of max_seq_len_hint instead.  Pieces of a
- * sequence are merged in order of position by the library.  Short contexts (by the
- * hint: up to 512 .. 2048 tokens with up to 128 sequences, and further with three or
- * four query tokens) are not cut: workgroups share the heads and output dims of a
- * sequence, and a single launch writes the result.  So it is unless the context was
- * created with target_workgroups or a schedule of its own.
+ * sequence are merged in order of position by the library.  Little work (by the hint) is
+ * distributed otherwise: short contexts (up to 512 .. 2048 tokens with up to 128 sequences,
+ * and further with three or four query tokens) are not cut: workgroups share the heads and
+ * output dims of a sequence, and a single launch writes the result; longer ones of few
+ * sequences (up to 21, up to about 65536 tokens in all, more with three or four query
+ * tokens) are dealt out in units of 32 tokens to at most 64 pieces, merged in a fixed
+ * order.  So it is unless the context was created with target_workgroups or a schedule of
+ * its own.
  */
 MFA_API mfa_status mfa_decode_attn(mfa_ctx* ctx, const void* q, const void* k_cache, const void* v_cache,
                            const float* k_scale, const float* v_scale, mfa_kv_dtype kv_dtype,
@@ -341,8 +344,8 @@ MFA_API mfa_status mfa_debug_stream_read(mfa_ctx* ctx, const void* a, const void
 /* Number of pieces into which the next mfa_decode_attn* call with these host
  * arguments cuts a sequence of the full length max_seq_len_hint when every
  * sequence has that length (shorter sequences get proportionally fewer; each
- * piece's partial result is merged by the library).  Calls over contexts short
- * enough not to be cut (mfa_decode_attn) have one piece whatever it returns.  Pure
+ * piece's partial result is merged by the library).  Calls with little work
+ * (mfa_decode_attn) have pieces of their own, 64 at most, whatever it returns.  Pure
  * host function; 0 on invalid arguments. */
 MFA_API int32_t mfa_decode_num_splits(const mfa_ctx* ctx, int32_t B, int32_t max_seq_len_hint);
 

@@ -168,9 +168,12 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
 // 2 x 8000 28.3/16.9, 4 x 4096 21.5/16.8, 6 x 6000 ragged 25.4/22.0, 8 bit, two tokens 2 x 8000 30.9/21.8, four tokens 1 x 16000 53.6/34.4, 3 x 8000 ragged 40.3/32.6;
 // 12 x 8000 ragged 25.8/24.3, two tokens 8 x 4000 25.5/24.6; from there on one wave is ahead (16 x 4096 24.7/25.1, 20 x 8000 38.9/40, 32 x 4096 33.9/36.3, 128 x 8192 ragged 110/119), and with few
 // partial results per row (16 x 256, four 10.3/12.0; 2 x 512, eight 10.5/11.1; 4 x 1024, sixteen 13.0/12.4).
+// The runs of brief_attn_kernel, 64 at most, one / four / eight waves: 1 x 4096, 64 of them 16.3/11.2/10.8, 24 13.0/11.1/11.7; 4 x 1536, sixteen 11.8/10.8/11.4;
+// 5 x 1536, nine 12.2/12.4/13.2; 8 x 4096, eight 16.2/16.6/17.6.
 int merge_waves(const AttnArgs& a)
 {
     const int rows = a.B * a.n_here, pieces = a.n_wgs > 0 ? a.n_wgs / a.B : a.n_splits;
+    if (a.n_wgs == 0 && a.chunk_tokens == kUnitTokens) return pieces < 12 ? 1 : pieces < 48 ? 4 : 8;     // (runs: brief_cut_runs)
     return rows > 16 || pieces < (rows <= 8 ? 12 : 17) ? 1 : rows <= 8 ? 8 : 4;
 }
 // merge_by_die: whether the blocks of a die take the rows of that die (mfa_merge_place.hpp).  us per call so / with rows in order:
@@ -236,7 +239,8 @@ __global__ __launch_bounds__(WAVES == 1 ? 256 : 64 * WAVES) void merge_splits_ke
                                                                       // (the one-pass kernel for 3 / 4 tokens never does)
     } else {
         if (L == 0) return;                                           // zeros were written by the first split
-        n_valid = (L + a.chunk_tokens - 1) / a.chunk_tokens;          // <= n_splits
+        n_valid = (L + a.chunk_tokens - 1) / a.chunk_tokens;
+        if (n_valid > a.n_splits) n_valid = a.n_splits;               // (brief_attn_kernel's runs: they have several units each)
         item0 = (size_t)b * a.n_splits;
     }
     if (L_mine <= 0) { *o = make_float4(0.f, 0.f, 0.f, 0.f); return; }   // (only with several query tokens and L < q_len)
@@ -393,26 +397,36 @@ AttnKernel multi_kernel(int q_len, bool paged, bool short_work)
     return {paged ? (const void*)decode_bf16_multi_kernel<true, 4> : (const void*)decode_bf16_multi_kernel<false, 4>, kMultiThreads, kMultiLdsBytes};
 }
 
-template <int BITS, int NH, int DS>
+template <int BITS, int NH, int DS, bool CUT = false>
 AttnKernel brief_form(bool paged)
 {
     using S = BriefShape<BITS, NH, DS>;
-    return {paged ? (const void*)brief_attn_kernel<true, BITS, NH, DS> : (const void*)brief_attn_kernel<false, BITS, NH, DS>, S::kThreads, S::kLdsBytes};
+    return {paged ? (const void*)brief_attn_kernel<true, BITS, NH, DS, CUT> : (const void*)brief_attn_kernel<false, BITS, NH, DS, CUT>, S::kThreads, S::kLdsBytes};
 }
 template <int BITS>
-AttnKernel brief_kernel(bool paged, int parts)
+AttnKernel brief_kernel(bool paged, int parts, bool cut)
 {
+    static_assert(BriefShape<BITS, 1, 1>::kParts == kBriefCutParts, "workgroups per run");
+    if (cut) return brief_form<BITS, 1, 1, true>(paged);
     return parts == 16 ? brief_form<BITS, 1, 4>(paged) : parts == 8 ? brief_form<BITS, 1, 2>(paged) : parts == 4 ? brief_form<BITS, 1, 1>(paged) : brief_form<BITS, 2, 1>(paged);
 }
-AttnKernel brief_kernel(mfa_kv_dtype kv_dtype, bool paged, int parts)
+AttnKernel brief_kernel(mfa_kv_dtype kv_dtype, bool paged, int parts, bool cut)
 {
-    return kv_dtype == MFA_KV_BF16 ? brief_kernel<16>(paged, parts) : kv_dtype == MFA_KV_FP8_E4M3 ? brief_kernel<8>(paged, parts) : brief_kernel<4>(paged, parts);
+    return kv_dtype == MFA_KV_BF16 ? brief_kernel<16>(paged, parts, cut) : kv_dtype == MFA_KV_FP8_E4M3 ? brief_kernel<8>(paged, parts, cut) : brief_kernel<4>(paged, parts, cut);
 }
+int cache_bits(mfa_kv_dtype kv_dtype) { return kv_dtype == MFA_KV_BF16 ? 16 : kv_dtype == MFA_KV_FP8_E4M3 ? 8 : 4; }
 // Workgroups per row of brief_attn_kernel, 0 where another kernel takes the call (mfa_kernel_choice.hpp)
 int brief_cut(const AttnArgs& a, mfa_kv_dtype kv_dtype)
 {
     if (!a.may_be_brief) return 0;
-    return brief_parts(kv_dtype == MFA_KV_BF16 ? 16 : kv_dtype == MFA_KV_FP8_E4M3 ? 8 : 4, a.q_len, (int64_t)a.B * a.q_len, a.max_seq_len_hint);
+    return brief_parts(cache_bits(kv_dtype), a.q_len, (int64_t)a.B * a.q_len, a.max_seq_len_hint);
+}
+
+// ... and else into how many runs it cuts a row, 0 likewise
+int brief_cut_runs(const AttnArgs& a, mfa_kv_dtype kv_dtype)
+{
+    if (!a.may_be_brief) return 0;
+    return brief_runs(cache_bits(kv_dtype), a.q_len, (int64_t)a.B * a.q_len, a.max_seq_len_hint);
 }
 
 // 64-token tiles per workgroup at the length of the hint (the host knows no other).
@@ -434,9 +448,9 @@ bool short_lowbit_work(const AttnArgs& a, mfa_kv_dtype kv_dtype)
 
 hipError_t prepare_decode_attn_kernels()
 {
-    for (const int parts : {2, 4, 8, 16})
+    for (const int parts : {2, 4, 8, 16, 0})          // (0: runs)
         for (int form = 0; form < 6; ++form) {
-            const AttnKernel k = brief_kernel(form < 2 ? MFA_KV_BF16 : form < 4 ? MFA_KV_FP8_E4M3 : MFA_KV_FP4_E2M1, (form & 1) != 0, parts);
+            const AttnKernel k = brief_kernel(form < 2 ? MFA_KV_BF16 : form < 4 ? MFA_KV_FP8_E4M3 : MFA_KV_FP4_E2M1, (form & 1) != 0, parts, parts == 0);
             const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds_bytes);
             if (e != hipSuccess) return e;
         }
@@ -483,10 +497,23 @@ hipError_t launch_decode_attn(const AttnArgs& a, mfa_kv_dtype kv_dtype, hipStrea
     if (const int parts = brief_cut(a, kv_dtype)) {
         AttnArgs args = a;
         void* params[] = {&args};
-        const AttnKernel k = brief_kernel(kv_dtype, a.block_table != nullptr, parts);
+        const AttnKernel k = brief_kernel(kv_dtype, a.block_table != nullptr, parts, false);
         const unsigned rows = (unsigned)(a.B * a.q_len);
         const hipError_t e = hipExtLaunchKernel(k.fn, dim3(8u * (unsigned)parts * ((rows + 7) / 8)), dim3(k.threads), params, k.lds_bytes, stream, ev_before, ev_after, 0);
         return e != hipSuccess ? e : hipGetLastError();
+    }
+    if (const int runs = brief_cut_runs(a, kv_dtype)) {
+        AttnArgs args = a;
+        args.n_wgs = 0;                                                 // (partial results: at most kMostBriefRuns slots, fewer than any workspace with the default work distribution has)
+        args.n_splits = runs;
+        args.chunk_tokens = kUnitTokens;                                // (units are dealt out: as many runs have some as the length has units)
+        args.n_here = a.q_len;
+        void* params[] = {&args};
+        const AttnKernel k = brief_kernel(kv_dtype, a.block_table != nullptr, 0, true);
+        const unsigned items = (unsigned)(a.B * a.q_len * runs);
+        hipError_t e = hipExtLaunchKernel(k.fn, dim3(8u * kBriefCutParts * ((items + 7) / 8)), dim3(k.threads), params, k.lds_bytes, stream, ev_before, ev_after, 0);
+        if (e == hipSuccess) e = hipGetLastError();
+        return e != hipSuccess ? e : launch_merge(args);
     }
     // Three and four query tokens over a bf16 cache, batches the per-wave schedule covers: one pass over the cache
     // by the kernel that keeps all of a sequence's query tokens in one wave.

@@ -1,4 +1,4 @@
-// Decode attention over short contexts (any cache type, gfx950): final results by one launch, no partial results and no merge.
+// Decode attention with little work (any cache type, gfx950).  Short contexts: final results by one launch, no partial results and no merge.
 //
 // What bounds a call over short contexts is not its bytes but what has to happen in turn: lengths, schedule, tiles, partial results, the end of a
 // kernel, the start of the next, merge; about 10 us before anything counts.  So a workgroup computes 16 * NH heads and 256 / DS output dims of one
@@ -57,7 +57,13 @@ struct BriefShape {
     }
 };
 
-template <bool PAGED, int BITS, int NH, int DS>
+// CUT: few rows of longer contexts leave most of the chip idle so.  Then a row's units are dealt out to a.n_splits runs (of kParts workgroups; run s has units
+// s, s + n_splits, ..: as even as it can be for every length, and the first units still lie where the hint alone says), which leave partial results;
+// merge_splits_kernel adds those up in the order of the runs.  Against the streaming kernels, where a compute unit takes all heads of a
+// range: a quarter as many ranges, so a quarter of the partial results to write and merge, and eight waves with 16 heads each where there are four with all.  us per call, 64 runs of
+// 1 x 32768 bf16 22.0 -> 16.5, 8 bit 22.3 -> 15.0; 12 of 5 x 4096 bf16 18.6 -> 14.8; 16 of four tokens, 1 x 8192 8 bit 41.0 -> 15.5 (two passes before).  Runs of
+// consecutive tokens, cut by the hint: the same at its length, up to 5 us slower where lengths fall short of it.
+template <bool PAGED, int BITS, int NH, int DS, bool CUT>
 __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__((amdgpu_waves_per_eu(NH == 2 ? 1 : 2, NH == 2 ? 1 : 2))) void brief_attn_kernel(AttnArgs a)
 {
     using S = BriefShape<BITS, NH, DS>;
@@ -68,11 +74,12 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
 
-    // workgroup i runs on die i % 8 (only speed depends on it): the workgroups of a row follow each other on one die
-    const int rows = a.B * a.q_len;
+    // workgroup i runs on die i % 8 (only speed depends on it): the workgroups of a row (of a run of it) follow each other on one die
+    const int rows = a.B * a.q_len, runs = CUT ? a.n_splits : 1;
     const int place = (int)(blockIdx.x >> 3);
-    const int row = place / S::kParts * 8 + (int)(blockIdx.x & 7);
-    if (row >= rows) return;
+    const int item = place / S::kParts * 8 + (int)(blockIdx.x & 7);
+    if (item >= rows * runs) return;
+    const int row = CUT ? item / runs : item, run = CUT ? item - row * runs : 0;
     const int part = place % S::kParts;
     const int head0 = part / DS * 16 * NH, block0 = part % DS * S::kDimBlocks;
     static_assert(kMaxQueryTokens == 4, "the division by q_len");
@@ -115,7 +122,8 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
         }
     };
 
-    int unit = wave;
+    int unit = run + runs * wave;
+    const int stride = runs * S::kWaves;
     if (unit * kUnitTokens < a.max_seq_len_hint) {
         const int64_t row0 = row_of(unit);
         request(row0, a.max_seq_len_hint - unit * kUnitTokens, std::false_type{});
@@ -130,7 +138,11 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) q[j][ks] = src[BITS == 16 ? 4 * ks + g : BITS == 8 ? 8 * (ks >> 1) + 2 * g + (ks & 1) : 16 * (ks >> 2) + 4 * g + (ks & 3)];
     }
-    const int end = clamped_len(a, b) - (a.q_len - 1 - qtok);           // tokens this row attends to
+    const int len = clamped_len(a, b), end = len - (a.q_len - 1 - qtok);   // tokens this row attends to
+    if (CUT && run > 0 && run * kUnitTokens >= len) {                   // no partial result is expected of this run
+        wait_vmem_but<0>();                                             // (no load may still be on its way into LDS that others get next)
+        return;
+    }
 
     f32x4 acc[NH][S::kDimBlocks];
     float m[NH], l[NH];
@@ -162,11 +174,11 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
     };
 
     const float c = BITS == 16 ? a.scale_log2e : 1.0f;
-    for (; unit * kUnitTokens < end; unit += S::kWaves) {
+    for (; unit * kUnitTokens < end; unit += stride) {
         const int left = end - unit * kUnitTokens;                      // tokens of this unit that count
         const bool whole = left >= kUnitTokens;
-        const int left_next = left - S::kWaves * kUnitTokens;           // of the unit that takes this one's place
-        const int64_t row_next = left_next > 0 ? row_of(unit + S::kWaves) : 0;
+        const int left_next = left - stride * kUnitTokens;              // of the unit that takes this one's place
+        const int64_t row_next = left_next > 0 ? row_of(unit + stride) : 0;
         wait_vmem_but<0>();
         // ---- scores
         f32x4 s[NH][2];
@@ -291,7 +303,10 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
 
     // ---- the waves' results added up
     wait_vmem_but<0>();                                                 // (a unit asked for ahead of a shorter length)
-    const int units = (end + kUnitTokens - 1) / kUnitTokens, n_active = units < S::kWaves ? units : S::kWaves;
+    const int units = end > 0 ? (end + kUnitTokens - 1) / kUnitTokens : 0;
+    const int mine = CUT ? (units - run + runs - 1) / runs : units, n_active = mine < S::kWaves ? mine : S::kWaves;   // (below 1: no tokens)
+    const bool partial = CUT && len > 0;                                // (an empty sequence: zeros by its first run, and nothing is merged)
+    const size_t slot_out = CUT ? ((size_t)b * runs + run) * a.q_len + qtok : 0;
 #pragma unroll
     for (int j = 0; j < NH; ++j) {
         __syncthreads();                                                // nobody reads a unit, or the results of the heads before, any more
@@ -319,11 +334,14 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
             }
         }
         // (a row without tokens is zero; one of nothing but -inf scores is not)
-        const float inv = 1.0f / l_sum;
+        const float inv = partial ? 1.0f : 1.0f / l_sum;
+        if (partial && wave == 0 && block0 == 0 && g == 0) *(float2*)(a.ws_ml + (slot_out * kHeads + head0 + 16 * j + n) * 2) = make_float2(top * c, l_sum);
 #pragma unroll
         for (int i = 0, block = wave; i * S::kWaves < S::kDimBlocks; ++i, block += S::kWaves) {
             if (block >= S::kDimBlocks) break;
-            *(f32x4*)(a.out + ((size_t)row * kHeads + head0 + 16 * j + n) * kHeadDim + 16 * (block0 + block) + 4 * g) = end > 0 ? sum[i] * inv : (f32x4){0.f, 0.f, 0.f, 0.f};
+            const f32x4 result = n_active > 0 ? sum[i] * inv : (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (partial) ((f32x4*)a.ws_acc)[(slot_out * (kHeads / 16) + (head0 / 16 + j)) * 1024 + (block0 + block) * 64 + lane] = result;
+            else *(f32x4*)(a.out + ((size_t)row * kHeads + head0 + 16 * j + n) * kHeadDim + 16 * (block0 + block) + 4 * g) = result;
         }
     }
 }

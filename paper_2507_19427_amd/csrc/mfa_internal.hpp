@@ -62,7 +62,7 @@ struct AttnArgs {
     int32_t n_splits;
     int32_t chunk_tokens;
     int32_t max_seq_len_hint;
-    bool may_be_brief;             // no work distribution was asked for: short contexts may go to brief_attn_kernel
+    bool may_be_brief;             // no work distribution was asked for: little work may go to brief_attn_kernel
     float scale_log2e;             // softmax_scale * log2(e)
 };
 

@@ -25,17 +25,42 @@ namespace mfa {
 //   8 bit, four  1 x 4096  31.7/27.5    (1 x 6144  36.9/38.7)    4 x 6144  46.7/41.0 48.9/38.6    8 x 6144  52.4/43.9 50.5/43.2    16 x 6144  66.0/54.8 55.5/53.1    32 x 2048  58.3/45.2 45.8/44.1    64 x 1024  60.6/53.7 54.7/48.2
 //   4 bit, four  1 x 4096  30.9/24.6    4 x 6144  45.4/38.1 47.9/36.7    8 x 6144  49.2/39.8 49.2/39.3    16 x 6144  60.6/47.1 52.1/46.3    32 x 2048  54.2/39.9 42.9/38.8    (64 x 2048  72.4/76.8 60.9/68.6)
 //   8 bit, three  128 x 256  53.6/37.1 54.1/35.9
-constexpr int kBriefBands = 9;
-constexpr int kBriefRows[kBriefBands] = {4, 16, 32, 47, 64, 99, 128, 256, 384};
-constexpr int kBriefParts[kBriefBands] = {16, 16, 8, 4, 4, 2, 2, 2, 2};
+// Up to 32 rows the lines lie lower than these figures would have them, where brief_runs (below) has something better.
+constexpr int kBriefBands = 10;
+constexpr int kBriefRows[kBriefBands] = {4, 16, 21, 32, 47, 64, 99, 128, 256, 384};
+constexpr int kBriefParts[kBriefBands] = {16, 16, 8, 8, 4, 4, 2, 2, 2, 2};
 constexpr int kBriefLines[2][3][kBriefBands] = {                        // [three or four tokens][16, 8, 4 bits]
-    {{960, 1536, 1536, 1280, 1536, 512, 768, 0, 0}, {1280, 2048, 2048, 1536, 1792, 512, 640, 0, 0}, {1536, 2048, 2048, 1536, 2048, 640, 768, 0, 0}},
-    {{2048, 2048, 2048, 1536, 1536, 768, 768, 256, 0}, {4096, 6144, 6144, 6144, 6144, 2048, 2048, 1024, 256}, {4096, 6144, 6144, 6144, 6144, 2048, 2048, 1024, 256}}};
+    {{768, 1152, 1280, 1536, 1280, 1536, 512, 768, 0, 0}, {896, 1280, 1536, 2048, 1536, 1792, 512, 640, 0, 0}, {1024, 1280, 1536, 2048, 1536, 2048, 640, 768, 0, 0}},
+    {{768, 1152, 1280, 2048, 1536, 1536, 768, 768, 256, 0}, {896, 1280, 1536, 2048, 6144, 6144, 2048, 2048, 1024, 256}, {1024, 1280, 1536, 2048, 6144, 6144, 2048, 2048, 1024, 256}}};
 constexpr int brief_parts(int bits, int q_len, int64_t rows, int64_t hint)
 {
     for (int band = 0; band < kBriefBands; ++band)
         if (rows <= kBriefRows[band]) return hint <= kBriefLines[q_len >= 3][bits == 16 ? 0 : bits == 8 ? 1 : 2][band] ? kBriefParts[band] : 0;
     return 0;
+}
+
+// Beyond those lines, up to 32 rows (21 with one or two tokens): into how many runs brief_attn_kernel cuts a row, or 0 where the other kernels are ahead.  A run takes
+// kBriefCutParts workgroups; the runs of all rows fill the compute units once (a second round is a loss: 2 x 8192 with 32 runs 13.2, with 48 19.2), but with no
+// less than 64 tokens each, 128 from three rows on (5 x 1536, of 12/9/6 runs 12.9/12.3/11.9 us).  Each compute unit reads rows * hint / 64 tokens' keys and values
+// whole, through its own 107 GB/s: that is what the limits on rows * hint are.  us per call, uncut / the other kernels / runs, equal and drawn lengths:
+//   bf16, one token    1 x 512 8.2/10.5/8.5   1 x 1024 10.9/11.4/9.2   1 x 1536 13.5/11.5/9.0   1 x 4096 -/12.7/10.8   1 x 32768 -/22.0/16.5   2 x 8192 -/18.1/13.7 -/18.9/13.7   4 x 768 10.1/12.4/10.2
+//                      4 x 16384 -/25.1/22.3 -/22.5/21.9   (4 x 32768 -/34.6/37.2 -/27.7/32.5)   5 x 1536 13.9/16.2/11.9 13.4/14.1/12.0   8 x 8192 -/25.4/22.1 -/22.2/21.5   (8 x 16384 -/35.2/37.0)
+//                      12 x 1024 12.6/17.1/13.2 11.2/15.8/12.8   12 x 2048 19.3/18.9/15.3 17.7/18.3/14.9   (16 x 4096 -/25.0/21.7 -/21.5/21.1, 16 x 8192 -/34.5/37.7 -/26.1/31.7)   20 x 2048 21.9/21.3/18.6
+//                      20.5/19.8/17.6   (drawn: 10 x 6500 -/21.3/21.6   19 x 3400 -/21.3/22.6)   (24 x 2048, two runs 21.8/23.3/21.5 20.7/20.6/20.9)
+//   8 bit, one token   1 x 32768 -/22.3/15.0   4 x 2048 16.0/17.2/11.7 15.5/14.4/11.3   16 x 2048 17.6/20.2/14.7 15.9/19.2/14.5   16 x 4096 -/22.2/18.5 -/20.1/18.3   (16 x 8192 -/27.9/26.3 -/22.9/25.9)
+//   two tokens         bf16 2 x 8192 -/22.8/16.4 -/22.0/16.2   8 x 4096 -/24.2/22.0 -/24.7/21.2   8 bit 8 x 4096 -/24.5/18.4 -/23.7/18.4
+//   four tokens        bf16 1 x 32768 -/39.8/32.4   2 x 16384 -/38.9/32.3 -/37.5/32.2   4 x 8192 -/40.0/32.3 -/35.6/31.6   (4 x 16384 -/46.4/55.0)   (8 x 4096 -/38.7/33.0 -/39.3/32.2)   three (10 x 4300, drawn -/32.0/33.5)
+//                      8 bit 1 x 8192 -/41.0/15.5   2 x 32768 -/64.6/41.6 -/60.1/41.0   4 x 16384 -/57.2/41.3 -/55.9/40.4   8 x 8192 -/55.4/42.3 -/55.8/40.9
+// The units of a row are dealt out to its runs, so shorter lengths than the hint cost less: 1 x 4096 under a hint of 32768 15.9/11.9, 16 x 512 under 4096 18.0/11.5.
+constexpr int kBriefCutParts = 4;
+constexpr int kMostBriefRuns = 64;                                      // of all rows: 256 compute units
+constexpr int brief_runs(int bits, int q_len, int64_t rows, int64_t hint)
+{
+    const bool many = q_len >= 3;                                       // (the other kernels have more to merge, or take two passes)
+    const int64_t most = bits != 16 ? (many ? 262144 : 65536) : rows > 16 ? (many ? 114688 : 49152) : rows > 8 && !many ? 57344 : many ? 131072 : 65536;
+    if (rows > (many ? 32 : 21) || rows * hint > most) return 0;
+    const int64_t fill = kMostBriefRuns / rows, by_length = hint / (rows <= 2 ? 64 : 128);
+    return (int)(by_length < fill ? by_length : fill);
 }
 
 // short_lowbit_kernel below so many 64-token tiles per workgroup, counted at the length of the hint, else decode_lowbit_kernel.  The lines lie where lengths

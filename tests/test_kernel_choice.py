@@ -64,3 +64,23 @@ def test_short_contexts(tmp_path):
                 assert hints == sorted(hints, reverse=True) and set(hints) <= {0, p}
             assert parts(bits, q_len, 64, 8192) == 0 and parts(bits, q_len, 400, 64) == 0
     assert parts(16, 1, 2, 256) == 16 and parts(16, 1, 64, 4096) == 0 and parts(8, 4, 64, 6144) == 4 and parts(8, 2, 64, 6144) == 0
+
+
+def test_runs_of_few_rows(tmp_path):
+    """Into how many runs a row of a longer context is cut: what the launch and the scratch memory rely on, over all rows, hints, cache bits and query tokens."""
+    (tmp_path / "shim.cpp").write_text('#include "mfa_kernel_choice.hpp"\nextern "C" int runs(int bits, int q_len, long rows, long hint) { return mfa::brief_parts(bits, q_len, rows, hint) ? -1 : mfa::brief_runs(bits, q_len, rows, hint); }\n')
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", str(tmp_path / "shim.so"), str(tmp_path / "shim.cpp")], check=True)
+    f = ctypes.CDLL(str(tmp_path / "shim.so")).runs
+
+    def runs(bits, q_len, rows, hint):
+        return f(bits, q_len, ctypes.c_long(rows), ctypes.c_long(hint))
+    for bits in (16, 8, 4):
+        for q_len in (1, 2, 3, 4):
+            for rows in list(range(q_len, 40, q_len)) + [4096, 65536]:
+                seen = [runs(bits, q_len, rows, hint) for hint in list(range(1, 4500)) + [8192, 16384, 32768, 65536, 131072, 262144, 1 << 20, (1 << 31) - 1]]
+                # uncut, then runs (two at least, a workgroup per compute unit at most, never fewer for a longer hint), then the other kernels
+                cut = [r for r in seen if r > 0]
+                assert all(2 <= r and r * rows <= 64 for r in cut) and cut == sorted(cut)
+                assert [min(r, 1) for r in seen] == [-1] * seen.count(-1) + [1] * len(cut) + [0] * seen.count(0)
+                assert seen[-1] == 0 and (rows <= 32 or not cut)
+    assert runs(16, 1, 1, 4096) == 64 and runs(16, 1, 5, 1500) == 11 and runs(8, 4, 16, 16384) == 4 and runs(8, 1, 22, 3000) == 0
