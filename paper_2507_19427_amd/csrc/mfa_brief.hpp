@@ -62,7 +62,7 @@ struct BriefShape {
 // merge_splits_kernel adds those up in the order of the runs.  Against the streaming kernels, where a compute unit takes all heads of a
 // range: a quarter as many ranges, so a quarter of the partial results to write and merge, and eight waves with 16 heads each where there are four with all.  us per call, 64 runs of
 // 1 x 32768 bf16 22.0 -> 16.5, 8 bit 22.3 -> 15.0; 12 of 5 x 4096 bf16 18.6 -> 14.8; 16 of four tokens, 1 x 8192 8 bit 41.0 -> 15.5 (two passes before).  Runs of
-// consecutive tokens, cut by the hint: the same at its length, up to 5 us slower where lengths fall short of it.
+// consecutive tokens, cut by the hint, take the same at its length, but no less wherever a length fills the first of them.
 template <bool PAGED, int BITS, int NH, int DS, bool CUT>
 __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__((amdgpu_waves_per_eu(NH == 2 ? 1 : 2, NH == 2 ? 1 : 2))) void brief_attn_kernel(AttnArgs a)
 {
