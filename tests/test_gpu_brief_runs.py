@@ -68,3 +68,27 @@ def test_runs_replayed(kv):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out.cpu(), eager), lens
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_runs_of_minus_infinity(kv):
+    """Tokens 0 .. 199 have scores of -inf: all that some of the runs have under a length of 230, and the first units of every run under 1500.  The rows are
+    those of the same cache without them."""
+    S, skip = 1500, 200
+    case = W.make_contiguous_case("runs inf", 93, B=2, S=S, kv_dtype=kv, seq_lens=[S, 230], poison=False)
+    case.q[..., 0] = 1.0
+    if kv == "bf16":
+        case.k[:, :skip, 0] = float("-inf")
+    else:
+        case.k.view(torch.uint8)[:, :skip] = 0
+        case.k.view(torch.uint8)[:, :skip, 0] = 0xB8                    # -1 in dim 0, 0 elsewhere
+        case.k_scale[:, :skip] = float("inf")
+    got = _attend(U.get_ctx(), case, case.q.view(2, 1, 64, 256), S)
+    for name in ("k", "v", "k_scale", "v_scale"):
+        t = getattr(case, name)
+        setattr(case, name, None if t is None else t[:, skip:].contiguous())
+    case.seq_lens = case.seq_lens - skip
+    rows = U.sample_rows(case, 16)
+    err = U.row_normalised_error(np.stack([got[b, 0, h].numpy() for b, h in rows]), U.run_oracle(case, rows=rows))
+    print(f"\n[case] runs of -inf, {kv}: error {err:.2e}", flush=True)
+    assert err <= (U.TOL_BF16 if kv == "bf16" else U.TOL_FP8)
