@@ -39,7 +39,7 @@ constexpr int brief_parts(int bits, int q_len, int64_t rows, int64_t hint)
     return 0;
 }
 
-// Beyond those lines, up to 32 rows (21 with one or two tokens): into how many runs brief_attn_kernel cuts a row, or 0 where the other kernels are ahead.  A run takes
+// Beyond those lines, up to 32 rows (21 with one token, or two of longer contexts): into how many runs brief_attn_kernel cuts a row, or 0 where the other kernels are ahead.  A run takes
 // kBriefCutParts workgroups; the runs of all rows fill the compute units once (a second round is a loss: 2 x 8192 with 32 runs 13.2, with 48 19.2), but with no
 // less than 64 tokens each, 128 from three rows on (5 x 1536, of 12/9/6 runs 12.9/12.3/11.9 us).  Each compute unit reads rows * hint / 64 tokens' keys and values
 // whole, through its own 107 GB/s: that is what the limits on rows * hint are.  us per call, uncut / the other kernels / runs, equal and drawn lengths:
@@ -48,7 +48,8 @@ constexpr int brief_parts(int bits, int q_len, int64_t rows, int64_t hint)
 //                      12 x 1024 12.6/17.1/13.2 11.2/15.8/12.8   12 x 2048 19.3/18.9/15.3 17.7/18.3/14.9   (16 x 4096 -/25.0/21.7 -/21.5/21.1, 16 x 8192 -/34.5/37.7 -/26.1/31.7)   20 x 2048 21.9/21.3/18.6
 //                      20.5/19.8/17.6   (drawn: 10 x 6500 -/21.3/21.6   19 x 3400 -/21.3/22.6)   (24 x 2048, two runs 21.8/23.3/21.5 20.7/20.6/20.9)
 //   8 bit, one token   1 x 32768 -/22.3/15.0   4 x 2048 16.0/17.2/11.7 15.5/14.4/11.3   16 x 2048 17.6/20.2/14.7 15.9/19.2/14.5   16 x 4096 -/22.2/18.5 -/20.1/18.3   (16 x 8192 -/27.9/26.3 -/22.9/25.9)
-//   two tokens         bf16 2 x 8192 -/22.8/16.4 -/22.0/16.2   8 x 4096 -/24.2/22.0 -/24.7/21.2   8 bit 8 x 4096 -/24.5/18.4 -/23.7/18.4
+//   two tokens         bf16 2 x 8192 -/22.8/16.4 -/22.0/16.2   8 x 4096 -/24.2/22.0 -/24.7/21.2   8 bit 8 x 4096 -/24.5/18.4 -/23.7/18.4   11 x 2700 -/25.3/20.6 -/23.3/20.2   16 x 2700 -/26.0/21.8 -/22.7/20.7
+//                      (12 x 3400 -/25.4/24.7 -/22.7/24.0)   bf16 16 x 2048 22.9/25.8/23.4 21.2/24.2/21.5   (16 x 3072 -/27.8/29.2 -/25.0/26.6)
 //   four tokens        bf16 1 x 32768 -/39.8/32.4   2 x 16384 -/38.9/32.3 -/37.5/32.2   4 x 8192 -/40.0/32.3 -/35.6/31.6   (4 x 16384 -/46.4/55.0)   (8 x 4096 -/38.7/33.0 -/39.3/32.2)   three (10 x 4300, drawn -/32.0/33.5)
 //                      8 bit 1 x 8192 -/41.0/15.5   2 x 32768 -/64.6/41.6 -/60.1/41.0   4 x 16384 -/57.2/41.3 -/55.9/40.4   8 x 8192 -/55.4/42.3 -/55.8/40.9
 // The units of a row are dealt out to its runs, so shorter lengths than the hint cost less: 1 x 4096 under a hint of 32768 15.9/11.9, 16 x 512 under 4096 18.0/11.5.
@@ -58,7 +59,8 @@ constexpr int brief_runs(int bits, int q_len, int64_t rows, int64_t hint)
 {
     const bool many = q_len >= 3;                                       // (the other kernels have more to merge, or take two passes)
     const int64_t most = bits != 16 ? (many ? 262144 : 65536) : rows > 16 ? (many ? 114688 : 49152) : rows > 8 && !many ? 57344 : many ? 131072 : 65536;
-    if (rows > (many ? 32 : 21) || rows * hint > most) return 0;
+    const bool two = q_len == 2 && rows > 21 && hint <= (bits == 16 ? 2048 : 2816);
+    if (rows > (many || two ? 32 : 21) || (!two && rows * hint > most)) return 0;
     const int64_t fill = kMostBriefRuns / rows, by_length = hint / (rows <= 2 ? 64 : 128);
     return (int)(by_length < fill ? by_length : fill);
 }

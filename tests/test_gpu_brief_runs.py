@@ -23,10 +23,10 @@ def _attend(ctx, case, q, hint):
 
 
 # (lengths, query tokens, hint): 16 to 64 runs of one row, 32 of two, 9 of five (a hint that is no multiple of anything), 4 of sixteen, 3 of twenty; more runs than
-# units, lengths of 0, 1 and less than the query tokens; 16, 4, 2 runs with several tokens
+# units, lengths of 0, 1 and less than the query tokens; 16, 4, 2 runs with several tokens, 2 of 24 rows with two
 @pytest.mark.parametrize("lens,q_len,hint", [
     ([1025], 1, 1025), ([8200], 1, 8200), ([33], 1, 5000), ([4096, 2047], 1, 4096), ([1300, 0, 1, 289, 1057], 1, 1301), ([0, 31, 32, 2000] * 4, 1, 2000),
-    ([1600, 1, 513] * 6 + [96, 97], 1, 1600), ([3000, 2], 2, 3000), ([2100], 4, 2100), ([1, 2, 3, 2500], 4, 2500), ([4, 0, 2049, 33, 700, 2500, 65, 1], 4, 2500), ([1500, 700, 2, 64, 1499], 3, 1500)])
+    ([1600, 1, 513] * 6 + [96, 97], 1, 1600), ([3000, 2], 2, 3000), ([2048, 1, 33, 700] * 3, 2, 2048), ([2100], 4, 2100), ([1, 2, 3, 2500], 4, 2500), ([4, 0, 2049, 33, 700, 2500, 65, 1], 4, 2500), ([1500, 700, 2, 64, 1499], 3, 1500)])
 @pytest.mark.parametrize("kv", ["bf16", "fp8", "fp4"])
 def test_runs(lens, q_len, hint, kv):
     print(f"\n[case] runs {len(lens)} x {max(lens)} under {hint}, {q_len} query tokens, {kv}", flush=True)

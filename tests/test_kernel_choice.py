@@ -84,3 +84,4 @@ def test_runs_of_few_rows(tmp_path):
                 assert [min(r, 1) for r in seen] == [-1] * seen.count(-1) + [1] * len(cut) + [0] * seen.count(0)
                 assert seen[-1] == 0 and (rows <= 32 or not cut)
     assert runs(16, 1, 1, 4096) == 64 and runs(16, 1, 5, 1500) == 11 and runs(8, 4, 16, 16384) == 4 and runs(8, 1, 22, 3000) == 0
+    assert runs(8, 2, 32, 2816) == 2 and runs(8, 2, 32, 2817) == 0 and runs(16, 2, 22, 2048) == 2 and runs(16, 2, 22, 2049) == 0
