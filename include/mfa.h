@@ -219,8 +219,11 @@ MFA_API mfa_status mfa_out_proj(mfa_ctx* ctx, const float* attn_out, const void*
  * value scales are alike (6e-4 against 1.7e-3 of it at 8192 tokens).  It is the larger one in a
  * single element to which the heaviest tokens of a tile contribute nothing (codes of 0) while
  * the tokens that make it up are more than 2^13 lighter, by attention or by value scale: such
- * an element is itself that much smaller than its row.  A value scale that is inf or NaN makes
- * its sequence's rows non-finite in either form (inf or NaN in the first, NaN in the second).
+ * an element is itself that much smaller than its row.  An infinite element of a bf16 value row
+ * makes the elements of the result that it meets infinite with little work (NaN where infinities
+ * of both signs meet, as in the plain sum), and infinite or NaN otherwise.  A value scale that is inf
+ * or NaN makes its sequence's rows non-finite in every form (inf or NaN in the first and second,
+ * NaN in the third).
  * For a given build, device and arguments the result is bitwise reproducible from call to call.
  * Work distribution: for B <= 4096 the 64-token tiles of all sequences, laid end
  * to end, are cut into equal ranges over at most 256 workgroups, whatever the

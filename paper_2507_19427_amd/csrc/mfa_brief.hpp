@@ -15,6 +15,8 @@
 //
 // Weights (times value scales) meet the values as two bf16 terms, 16 significant bits: the error against 64 bits is 2e-6 of a result, where weights
 // rounded once leave 1.2 .. 1.7e-3.  It costs up to 8 %: 64 x 1024 bf16 19.7 -> 21.7 us, now, with the loads unrolled by eight, 18.3.
+// The second term may be negative or zero, which an infinite value (or value scale) would turn into NaN.  So where a sum is not finite the workgroup
+// works its tokens off once more, with terms that are both positive (two_terms); every other call pays a vote of the waves at its end.
 //
 // MFMA shapes as in mfa_attn_core.hpp (v_mfma_f32_16x16x32_bf16; lane = 16*g + n): scores S^T[token, head], two blocks of 16 tokens; a lane's eight weights,
 // tokens 16*tb + 4*g + i, are its operand of O^T[d, head] += V^T . P^T.  8-bit and 4-bit codes are expanded to bf16 (exactly) between LDS and the matrix
@@ -43,7 +45,8 @@ struct BriefShape {
     static constexpr int kThreads = 64 * kWaves;
     static constexpr int kAccBytes = kDimBlocks * 1024;                 // a wave's result for 16 heads ...
     static constexpr int kMlBase = kWaves * kAccBytes;                  // ... and (m, l) per head, over the dead units
-    static constexpr int kMergeBytes = kMlBase + kWaves * 128;
+    static constexpr int kVote = kMlBase + kWaves * 128;                // whether a sum is not finite
+    static constexpr int kMergeBytes = kVote + 16;
     static constexpr int kLdsBytes = kWaves * kSlotBytes > kMergeBytes ? kWaves * kSlotBytes : kMergeBytes;
     static_assert(kLdsBytes <= kLds, "LDS of a compute unit");
     // Where 16-byte chunk c of row r of a unit lies within its row.  Keys: operand reads (16 rows x one chunk) touch every bank once.  Values: the
@@ -57,28 +60,43 @@ struct BriefShape {
     }
 };
 
+// A weight as the sum of two bf16 terms.  The nearest one and what it leaves: 2^-17 of the weight at most is lost.  Or (BOTH_POSITIVE) the largest one
+// below the weight and what that leaves, 2^-16: of a weight above zero neither term is zero or negative then, so infinite values stay infinite.
+template <bool BOTH_POSITIVE>
+__device__ __forceinline__ void two_terms(float w, __bf16& first, __bf16& rest)
+{
+    if constexpr (BOTH_POSITIVE) {
+        const uint32_t bits = __float_as_uint(w);
+        first = __builtin_bit_cast(__bf16, (uint16_t)((bits - ((bits << 1) != 0 ? 1u : 0u)) >> 16));
+    } else {
+        first = (__bf16)w;
+    }
+    rest = (__bf16)(w - (float)first);
+}
+
 // CUT: few rows of longer contexts leave most of the chip idle so.  Then a row's units are dealt out to a.n_splits runs (of kParts workgroups; run s has units
 // s, s + n_splits, ..: as even as it can be for every length, and the first units still lie where the hint alone says), which leave partial results;
 // merge_splits_kernel adds those up in the order of the runs.  Against the streaming kernels, where a compute unit takes all heads of a
 // range: a quarter as many ranges, so a quarter of the partial results to write and merge, and eight waves with 16 heads each where there are four with all.  us per call, 64 runs of
 // 1 x 32768 bf16 22.0 -> 16.5, 8 bit 22.3 -> 15.0; 12 of 5 x 4096 bf16 18.6 -> 14.8; 16 of four tokens, 1 x 8192 8 bit 41.0 -> 15.5 (two passes before).  Runs of
 // consecutive tokens, cut by the hint, take the same at its length, but no less wherever a length fills the first of them.
-template <bool PAGED, int BITS, int NH, int DS, bool CUT>
-__global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__((amdgpu_waves_per_eu(NH == 2 ? 1 : 2, NH == 2 ? 1 : 2))) void brief_attn_kernel(AttnArgs a)
+//
+// Returns whether a sum is not finite (never with BOTH_POSITIVE).
+template <bool PAGED, int BITS, int NH, int DS, bool CUT, bool BOTH_POSITIVE>
+__device__ __forceinline__ bool brief_attn(const AttnArgs& a, lds_ptr_t lds_base)
 {
     using S = BriefShape<BITS, NH, DS>;
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    const lds_ptr_t lds_base = (lds_ptr_t)smem;
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int thread = threadIdx.x;
+    asm volatile("" : "+v"(thread));                                    // (nothing computed from it is kept for the second time)
+    const int lane = thread & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(thread >> 6);
     const int n = lane & 15, g = lane >> 4;
 
     // workgroup i runs on die i % 8 (only speed depends on it): the workgroups of a row (of a run of it) follow each other on one die
     const int rows = a.B * a.q_len, runs = CUT ? a.n_splits : 1;
     const int place = (int)(blockIdx.x >> 3);
     const int item = place / S::kParts * 8 + (int)(blockIdx.x & 7);
-    if (item >= rows * runs) return;
+    if (item >= rows * runs) return false;
     const int row = CUT ? item / runs : item, run = CUT ? item - row * runs : 0;
     const int part = place % S::kParts;
     const int head0 = part / DS * 16 * NH, block0 = part % DS * S::kDimBlocks;
@@ -141,7 +159,7 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
     const int len = clamped_len(a, b), end = len - (a.q_len - 1 - qtok);   // tokens this row attends to
     if (CUT && run > 0 && run * kUnitTokens >= len) {                   // no partial result is expected of this run
         wait_vmem_but<0>();                                             // (no load may still be on its way into LDS that others get next)
-        return;
+        return false;
     }
 
     f32x4 acc[NH][S::kDimBlocks];
@@ -228,7 +246,7 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
 #pragma unroll
         for (int j = 0; j < NH; ++j) {
             // Reference and exponents, in units of c: raw scores (bf16; their differences are exact where it matters, and a sequence of one token is its
-            // value row to the bit) or scores in the log2 domain (codes)
+            // value row to the bit, infinities included) or scores in the log2 domain (codes)
             float factor[8], top = -INFINITY;
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
@@ -251,9 +269,10 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
             for (int t = 0; t < 8; ++t) {
                 const float w = fast_exp2(BITS == 16 ? (s[j][t >> 2][t & 3] - m_safe) * c : __builtin_fmaf(s[j][t >> 2][t & 3], factor[t], -m_safe));
                 l[j] += w;
-                const float y = BITS == 16 ? w : w * vs[t >> 2][t & 3];
-                p[j][t] = (__bf16)y;
-                p_rest[j][t] = (__bf16)(y - (float)p[j][t]);
+                __bf16 first, rest;
+                two_terms<BOTH_POSITIVE>(BITS == 16 ? w : w * vs[t >> 2][t & 3], first, rest);
+                p[j][t] = first;
+                p_rest[j][t] = rest;
             }
         }
         // ---- weighted sum
@@ -307,10 +326,12 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
     const int mine = CUT ? (units - run + runs - 1) / runs : units, n_active = mine < S::kWaves ? mine : S::kWaves;   // (below 1: no tokens)
     const bool partial = CUT && len > 0;                                // (an empty sequence: zeros by its first run, and nothing is merged)
     const size_t slot_out = CUT ? ((size_t)b * runs + run) * a.q_len + qtok : 0;
+    float finite = 0.f;                                                 // NaN once a sum is not
 #pragma unroll
     for (int j = 0; j < NH; ++j) {
         __syncthreads();                                                // nobody reads a unit, or the results of the heads before, any more
         l[j] = head_sum(l[j]);
+        if (!BOTH_POSITIVE && j == 0 && thread == 0) *LDS_AT(int, lds_base, S::kVote) = 0;
 #pragma unroll
         for (int i = 0; i < S::kDimBlocks; ++i) *LDS_AT(f32x4, lds_base, wave * S::kAccBytes + i * 1024 + lane * 16) = acc[j][i];
         const int ml = S::kMlBase + n * 4;
@@ -339,11 +360,28 @@ __global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__
 #pragma unroll
         for (int i = 0, block = wave; i * S::kWaves < S::kDimBlocks; ++i, block += S::kWaves) {
             if (block >= S::kDimBlocks) break;
+            if (!BOTH_POSITIVE && n_active > 0)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) finite = __builtin_fmaf(sum[i][k], 0.f, finite);
             const f32x4 result = n_active > 0 ? sum[i] * inv : (f32x4){0.f, 0.f, 0.f, 0.f};
             if (partial) ((f32x4*)a.ws_acc)[(slot_out * (kHeads / 16) + (head0 / 16 + j)) * 1024 + (block0 + block) * 64 + lane] = result;
             else *(f32x4*)(a.out + ((size_t)row * kHeads + head0 + 16 * j + n) * kHeadDim + 16 * (block0 + block) + 4 * g) = result;
         }
     }
+    if constexpr (BOTH_POSITIVE) return false;
+    if (__any(!(finite == 0.f))) *LDS_AT(int, lds_base, S::kVote) = 1;
+    __syncthreads();
+    return *LDS_AT(int, lds_base, S::kVote) != 0;
+}
+
+template <bool PAGED, int BITS, int NH, int DS, bool CUT>
+__global__ __launch_bounds__((BriefShape<BITS, NH, DS>::kThreads)) __attribute__((amdgpu_waves_per_eu(NH == 2 ? 1 : 2, NH == 2 ? 1 : 2))) void brief_attn_kernel(AttnArgs a)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const lds_ptr_t lds_base = (lds_ptr_t)smem;
+    if (!brief_attn<PAGED, BITS, NH, DS, CUT, false>(a, lds_base)) return;
+    __syncthreads();                                                    // everyone has read the vote; units may come in
+    brief_attn<PAGED, BITS, NH, DS, CUT, true>(a, lds_base);
 }
 
 }  // namespace mfa

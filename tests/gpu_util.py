@@ -49,6 +49,27 @@ def run_oracle(case, rows=None):
                          k_scale=opt(case.k_scale), v_scale=opt(case.v_scale), kv_dtype=kd, rows=rows)
 
 
+_E2M1 = torch.tensor([0, .5, 1, 1.5, 2, 3, 4, 6, -0., -.5, -1, -1.5, -2, -3, -4, -6], dtype=torch.float64)
+
+
+def _rows64(codes, scales):
+    """Cache rows of a sequence in 64 bits."""
+    if codes.dtype == torch.uint8:
+        x = torch.stack([_E2M1[(codes & 15).long()], _E2M1[(codes >> 4).long()]], dim=-1).flatten(-2)
+    else:
+        x = codes.float().double()
+    return x if scales is None else x * scales.double()[..., None]
+
+
+def exact_heads(case, b, q, n):
+    """Attention of the queries q [heads, D] over the first n tokens of sequence b (contiguous cache), in 64 bits: the rows (a plain sum of weights times
+    values, with its infinities and NaN) and sum_t w_t |v_t|, which is what rounding errors of the weights are relative to."""
+    k, v = [_rows64(t[b, :n], None if sc is None else sc[b, :n]) for t, sc in ((case.k, case.k_scale), (case.v, case.v_scale))]
+    w = torch.softmax(q.double() @ k.T * case.scale, dim=-1)
+    rows = torch.stack([(w[h][:, None] * v).sum(0) for h in range(len(w))])
+    return rows, w @ torch.where(torch.isfinite(v), v, torch.zeros_like(v)).abs()
+
+
 def row_normalised_error(got, ref):
     """max over rows of max_d|got-ref| / max_d|ref| (rows whose reference is all zero must match exactly)."""
     got = np.asarray(got, dtype=np.float64).reshape(-1, got.shape[-1])

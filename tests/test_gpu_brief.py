@@ -77,3 +77,40 @@ def test_scores_of_minus_infinity_and_growing_ones(B, kv):
     err = U.row_normalised_error(np.stack([got[b, 0, h].numpy() for b, h in rows]), U.run_oracle(case, rows=rows))
     print(f"\n[case] -inf and growing scores, {B} sequences, {kv}: error {err:.2e}", flush=True)
     assert err <= (U.TOL_BF16 if kv == "bf16" else U.TOL_FP8)
+
+
+# (sequences, longest): each form of the uncut kernel, and runs
+@pytest.mark.parametrize("B,S", [(3, 300), (20, 300), (40, 300), (70, 300), (3, 2500)])
+@pytest.mark.parametrize("kv", ["bf16", "fp8", "fp4"])
+def test_infinite_values(B, S, kv):
+    """An infinite value (or value scale) makes the elements it meets infinite, not NaN, as in the plain sum of weights times values; NaN is only what
+    that has too (infinities of both signs, an infinite scale over a code of 0).  The rest of such a row keeps 16 bits of every weight."""
+    print(f"\n[case] infinite values, {B} x {S}, {kv}", flush=True)
+    lens = [S, 1, S - 1] + [40] * (B - 3)
+    case = W.make_contiguous_case("inf values", 50 + B, B=B, S=S, seq_lens=lens, kv_dtype=kv, poison=True)
+    inf = float("inf")
+    if kv == "bf16":
+        case.v[0, 7, 5] = inf                                           # once; of either sign; of both; at the end of the sequence, and in its first unit and another
+        case.v[0, 40, 6] = -inf
+        case.v[0, 7, 100], case.v[0, S - 1, 100] = inf, -inf
+        case.v[0, S - 1, 255], case.v[0, 33, 9], case.v[0, 3, 9] = inf, inf, inf
+        case.v[1, 0, 77], case.v[1, 0, 78] = inf, -inf                  # the only token
+    else:
+        case.v_scale[0, S - 1] = inf
+        case.v_scale[1, 0] = inf
+    case.q[0] *= 0.25                                                   # (no weight underflows)
+    got = _attend(U.get_ctx(), case, case.q.view(B, 1, 64, 256), S)[:, 0].double()
+    worst = 0.0
+    for b, n in enumerate(lens):
+        want, magnitude = U.exact_heads(case, b, case.q[b], n)
+        same = torch.isnan(got[b]) == torch.isnan(want)
+        assert same.all(), (b, int((~same).sum()))
+        infinite, finite = torch.isinf(want), torch.isfinite(want)
+        assert torch.equal(torch.isinf(got[b]), infinite) and torch.equal(got[b][infinite], want[infinite])
+        if n == 1 and kv == "bf16":
+            assert torch.equal(got[b][finite], want[finite])            # a row of one token is that token's value row
+        if finite.any():
+            worst = max(worst, float(((got[b] - want).abs() / magnitude)[finite].max()))
+    print(f"   error {worst:.2e} of sum w |v|", flush=True)
+    # a weight loses 2^-16 of itself at most in two terms that are both positive; as much again for its score, its exponential and the sums
+    assert worst <= 2.0 ** -15
