@@ -114,3 +114,14 @@ def test_infinite_values(B, S, kv):
     print(f"   error {worst:.2e} of sum w |v|", flush=True)
     # a weight loses 2^-16 of itself at most in two terms that are both positive; as much again for its score, its exponential and the sums
     assert worst <= 2.0 ** -15
+
+
+@pytest.mark.parametrize("q_len,lens,hint", [(1, [70, 0, 1, 64, 300], 900), (1, [2100, 1, 65], 4096), (3, [2, 500, 64], 1000)])
+def test_block_table_entries_past_the_length_do_not_matter(q_len, lens, hint):
+    case = W.make_paged_case("garbage", 77, lens, spare_pages=3, poison=True, max_blocks=(hint + 63) // 64)
+    q = W.make_multi_query(case, q_len, 7) if q_len > 1 else case.q.view(len(lens), 1, 64, 256)
+    want = _attend(U.get_ctx(), case, q, hint)
+    for b, n in enumerate(lens):
+        past = case.block_table[b, (n + 63) // 64:]
+        past.copy_(torch.arange(len(past)) * 99991 - (1 << 30))
+    assert torch.isfinite(want).all() and torch.equal(want, _attend(U.get_ctx(), case, q, hint))
