@@ -163,33 +163,13 @@ __global__ __launch_bounds__(kAttnThreads) void decode_bf16_kernel(AttnArgs a)
 // summed in split order (m* is reached batch by batch, rescaling what has been summed).  One thread per float4 of the partial's lane-order layout; splits are
 // taken four at a time so that their loads are independent and in flight together.
 //
-// merge_waves: few rows have many partial results each, and a thread that takes them four at a time is a chain of round trips (1 x 32768: 256 of them, 29 us); then a
-// block takes a quarter as many positions, and each of its waves a run of the partial results, eight at a time.  us per call, one wave / this: 1 x 32768 43.8/21.8,
-// 2 x 8000 28.3/16.9, 4 x 4096 21.5/16.8, 6 x 6000 ragged 25.4/22.0, 8 bit, two tokens 2 x 8000 30.9/21.8, four tokens 1 x 16000 53.6/34.4, 3 x 8000 ragged 40.3/32.6;
-// 12 x 8000 ragged 25.8/24.3, two tokens 8 x 4000 25.5/24.6; from there on one wave is ahead (16 x 4096 24.7/25.1, 20 x 8000 38.9/40, 32 x 4096 33.9/36.3, 128 x 8192 ragged 110/119), and with few
-// partial results per row (16 x 256, four 10.3/12.0; 2 x 512, eight 10.5/11.1; 4 x 1024, sixteen 13.0/12.4).
-// The runs of brief_attn_kernel, 64 at most, one / four / eight waves: 1 x 4096, 64 of them 16.3/11.2/10.8, 24 13.0/11.1/11.7; 4 x 1536, sixteen 11.8/10.8/11.4;
-// 5 x 1536, nine 12.2/12.4/13.2; 8 x 4096, eight 16.2/16.6/17.6.
+// How many waves share a row's partial results, and whether the blocks of a die take the rows of that die: mfa_merge_place.hpp, with both sides measured.
 int merge_waves(const AttnArgs& a)
 {
-    const int rows = a.B * a.n_here, pieces = a.n_wgs > 0 ? a.n_wgs / a.B : a.n_splits;
-    if (a.n_wgs == 0 && a.chunk_tokens == kUnitTokens) return pieces < 12 ? 1 : pieces < 48 ? 4 : 8;     // (runs: brief_cut_runs)
-    return rows > 16 || pieces < (rows <= 8 ? 12 : 17) ? 1 : rows <= 8 ? 8 : 4;
+    if (a.n_wgs == 0 && a.chunk_tokens == kUnitTokens) return merge_waves_of_runs(a.n_splits);           // (brief_cut_runs)
+    return merge_waves(a.B, a.n_here, a.q_len, a.n_wgs > 0 ? a.n_wgs / a.B : a.n_splits);
 }
-// merge_by_die: whether the blocks of a die take the rows of that die (mfa_merge_place.hpp).  us per call so / with rows in order:
-//   one token   23 x 4096 28.4/33.0   30 x 6000 ragged 31.9/36.0   8 bit, ragged 23 x 20011 35.3/39.2   bf16 127 x 4000 44.0/45.1
-//   several waves a block  5 x 8000 21.3/21.5   6 x 3000 ragged 17.9/19.1   8 bit, two tokens, 4 x 8000 24.4/24.7   16 x 4096 24.7/25.2
-// Not where it would leave dies idle or give some of them twice the rows of others: 1 x 32768 30.2/21.7, 3 x 8000 20.8/19.1, 4 x 16000 ragged 25.9/23.5, 12 x 8000 ragged 24.7/24.1, four
-// tokens 3 x 8000 ragged 38.1/32.4.  Looked up in the records, which is exact for ragged lengths, with what a die has
-// beyond its share given to others: the same for most, but 122.2 against 120.5 at 128 x 8192 ragged and 24.8 against 22.6 at 128 x 400.
-// Not by die with less than a tile for every compute unit, where a sequence's many one-tile pieces lie on several dies anyway (5 x 1500
-// ragged: 16.7, in order 16.2), unless the batch divides evenly.
-bool merge_by_die(const AttnArgs& a, int waves)
-{
-    const int rows = a.B * a.n_here;
-    if (waves > 1 && (rows <= 4 || (rows > 8 && (a.B & 7) != 0))) return false;
-    return a.n_wgs > 0 && (a.n_wgs & 7) == 0 && (a.n_wgs >= 256 || (a.B & 7) == 0);
-}
+bool merge_by_die(const AttnArgs& a, int waves) { return merge_by_die(a.B, a.n_here, a.q_len, a.n_wgs, waves); }
 
 // With many short sequences nearly every block only finds that a workgroup has written its row's result, and what counts is the way there:
 // the rule is a template argument, the division by 1 .. 4 a shift or a multiplication, length and record one round trip.  us of the kernel

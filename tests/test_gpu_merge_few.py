@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 # (lengths, query tokens, workgroups): a row's partial results are about tiles * workgroups / all tiles
 @pytest.mark.parametrize("lens,q_len,n_wgs", [
     ([768], 1, 12), ([64 * 63], 1, 63), ([64 * 65 + 1], 2, 65), ([16384], 1, 256), ([4096, 0, 5], 1, 256), ([64 * 12] * 2, 1, 24),
-    ([2000, 3000, 1], 3, 200), ([1500] * 8, 1, 256), ([900, 64, 5000, 1, 2, 700, 3000, 65, 4000], 1, 256), ([1400, 3], 4, 40), ([800] * 16, 1, 208)])
+    ([2000, 3000, 1], 3, 200), ([1500] * 8, 1, 256), ([900, 64, 5000, 1, 2, 700, 3000, 65, 4000], 1, 256), ([1400, 3], 4, 40), ([800] * 16, 1, 208),
+    ([2000, 1, 1300, 64, 3000, 2, 900], 2, 256), ([900] * 6, 2, 256), ([1200, 1, 1300, 64, 2000, 2], 4, 256), ([700] * 7, 3, 256)])
 @pytest.mark.parametrize("kv", ["bf16", "fp4"])
 def test_few_rows(lens, q_len, n_wgs, kv):
     print(f"\n[case] few rows {len(lens)} x {max(lens)}, {q_len} query tokens, {n_wgs} workgroups, {kv}", flush=True)
