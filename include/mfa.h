@@ -231,7 +231,7 @@ MFA_API mfa_status mfa_out_proj(mfa_ctx* ctx, const float* attn_out, const void*
  * context created with schedule = MFA_SCHEDULE_FIXED, cut every sequence
  * into the same number of equal chunks of max_seq_len_hint instead.  Pieces of a
  * sequence are merged in order of position by the library.  Little work (by the hint) is
- * distributed otherwise: short contexts (up to 512 .. 2048 tokens with up to 128 sequences,
+ * distributed otherwise: short contexts (up to 384 .. 2048 tokens with up to 128 sequences,
  * and further with three or four query tokens) are not cut: workgroups share the heads and
  * output dims of a sequence, and a single launch writes the result; longer ones of few
  * sequences (up to 21, up to about 65536 tokens in all, more with three or four query

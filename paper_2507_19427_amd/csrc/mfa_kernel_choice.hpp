@@ -8,30 +8,39 @@ namespace mfa {
 // Short contexts: into how many workgroups brief_attn_kernel cuts a row (a query token of a sequence), or 0 where the kernels that cut the cache
 // are ahead.  As many as leave a workgroup per compute unit, 16 at most: each part reads all keys of its row.
 //
-// The lines, in tokens of the hint, lie where neither equal lengths nor lengths drawn from 1 .. hint lose.  us per call, the other kernels (streaming
-// kernel and merge) / this one, equal and drawn lengths; in brackets what lies beyond a line:
-//   bf16, one token    2 x 256  9.8/6.6     2 x 1024  11.6/11.0 11.7/10.9    (3 x 1280  12.4/12.6 12.2/12.3)    6 x 1536  17.2/13.8 15.9/13.5    16 x 1536  18.3/16.5 19.1/14.1    (16 x 2048  19.9/20.1 20.2/17.8)
-//                      18 x 1536  19.2/17.9 18.9/16.9    (18 x 2048  21.0/20.9 20.2/20.2)    34 x 1280  22.1/20.7 20.2/19.7    (34 x 1536  24.1/22.8 20.7/21.7)    48 x 1536  28.7/23.1 22.7/21.9
-//                      66 x 512  21.1/18.0 20.0/18.6    (66 x 640  23.0/20.0 20.8/21.0)    100 x 768  30.3/23.5 24.8/23.8    128 x 768  32.7/24.7 27.6/24.6
-//   8 bit, one token   2 x 256  10.9/6.2    1 x 1280  12.3/11.6     (1 x 1536  12.5/12.9)    6 x 2048  20.4/15.6 16.4/15.4    16 x 2048  19.1/17.6 19.2/15.9    18 x 2048  20.3/18.3 18.0/17.4
-//                      34 x 1536  22.3/18.8 18.2/17.5    (34 x 2048  24.4/22.2 19.0/20.6)    64 x 2048  30.2/24.3 23.8/22.6    (48 x 2048  28.4/22.5 22.0/22.1)
-//                      66 x 512  20.9/17.1 17.8/17.5    (66 x 640  21.3/19.2 19.5/19.8)    100 x 640  25.4/19.8 22.0/20.4    128 x 640  26.4/20.5 23.7/21.0
-//   4 bit, one token   1 x 1536  12.3/11.9    (1 x 1792  12.3/13.1)    6 x 2048  20.7/14.6 15.7/14.2    16 x 2048  18.1/15.9 19.4/14.9    32 x 2048  20.5/17.9 17.6/16.1    34 x 1536  20.2/17.0 17.0/15.4    48 x 2048  25.2/20.8 20.7/20.0
-//                      66 x 640  20.1/17.9 18.8/18.3    100 x 768  24.5/20.5 21.2/20.6    128 x 768  25.3/21.0 23.5/21.2
+// The lines, in tokens of the hint, lie where equal lengths and lengths drawn from 1 .. hint gain, and one sequence of the hint's length among others of 32 tokens loses 5 % at most: uncut, a
+// long row has its fixed share of the chip, where the balanced schedule gives it most of it.  us per call, the other kernels (streaming kernel and merge) / this one; in brackets what lies beyond a line.
+// Equal and drawn lengths:
+//   bf16, one token    2 x 256  9.8/6.6     2 x 1024  11.6/11.0 11.7/10.9    (3 x 1280  12.4/12.6 12.2/12.3)    (6 x 1536  17.2/13.8 15.9/13.5    16 x 1536  18.3/16.5 19.1/14.1: runs, below)
+//                      32 x 1536  21.9/18.3    64 x 960  24.5/18.2 21.8/18.0    (64 x 1152  26.9/20.6 23.1/20.2    64 x 1536  30.0/24.2 25.5/22.9)
+//                      128 x 384  23.5/17.6 22.4/18.2    (66 x 512  20.7/18.1 19.7/18.6    128 x 512  26.1/20.2 24.2/20.3    128 x 768  31.1/24.8 27.1/24.6)
+//   8 bit, one token   2 x 256  10.9/6.2    1 x 1280  12.3/11.6     (1 x 1536  12.5/12.9)    18 x 2048  20.3/18.3 18.0/17.4    34 x 1536  22.3/18.8 18.2/17.5    64 x 1536  24.0/19.1 21.6/18.6
+//                      (48 x 2048  28.4/22.5 22.0/22.1    64 x 1792  26.1/21.6 22.0/20.7)    (99 x 512  23.3/17.8 20.8/18.2    128 x 640  24.2/20.8 23.7/21.0)
+//   4 bit, one token   1 x 1536  12.3/11.9    (1 x 1792  12.3/13.1)    32 x 2048  20.5/17.9 17.6/16.1    34 x 1536  20.2/17.0 17.0/15.4    64 x 1792  23.1/19.1 20.6/18.8    (64 x 2048  24.3/21.3 21.6/20.9)
+//                      128 x 512  21.5/17.0 21.7/17.2    (128 x 768  23.7/21.0 23.2/21.2)
 //   two tokens within 1 us of twice the sequences
+// One sequence of the hint's length, the others of 32 tokens, contiguous and paged (paged: with the wait for the length, asks_ahead_of_the_length):
+//   bf16               16 x 1152  16.8/11.4 16.2/11.4    32 x 1536  17.8/16.8 16.8/16.6    33 x 960  16.3/15.6 15.5/16.0    64 x 960  17.0/17.0 16.0/16.2    (64 x 1152  17.3/18.8    64 x 1536  18.1/22.1)
+//                      71 x 384  15.7/14.8 14.8/15.3    128 x 384  16.8/16.4 16.3/15.7    (66 x 512  15.9/16.9    128 x 448  16.7/18.5    128 x 768  17.4/23.0)
+//   8 bit              32 x 2048  17.9/17.2 18.3/17.5    47 x 1536  16.9/17.5 17.2/17.2    64 x 1536  16.9/17.8 17.4/17.4    (64 x 1792  17.5/19.5)    71 x 384  15.1/13.9 15.5/14.6    128 x 384  16.2/15.2 16.6/15.2    (72 x 512  15.1/16.2 15.5/16.8)
+//   4 bit              32 x 2048  17.6/15.9 18.0/16.8    64 x 1792  17.4/17.4 17.8/18.3    (64 x 2048  17.9/19.0)    71 x 512  14.9/15.2 15.2/15.3    128 x 512  15.7/16.0 16.0/15.7    (128 x 768  16.4/19.3)
+//   two tokens         bf16 32 x 960  19.9/17.2 18.4/17.0   8 bit 32 x 1536  19.4/18.4 19.8/17.8   just above where the parts of a row halve up to a tenth slower: bf16 17 x 960  16.2/16.3 15.3/16.6    33 x 384  15.2/15.6 14.3/16.0
+//   three and four     bf16, four 16 x 1536  26.5/22.6    24 x 768  25.0/23.1 25.1/23.7    17 x 512  21.0/18.0 21.2/18.5    (17 x 768  21.4/22.8 21.8/23.5)    three 24 x 768  22.1/22.4 22.0/23.3    33 x 768  22.8/23.5 22.8/23.9
+//                      8 bit, four 16 x 6144  55.9/51.3    32 x 1792  39.5/39.2 40.0/40.6    (32 x 2048  40.6/43.4)    4 bit, four 32 x 2048  39.8/39.4 40.7/40.5
 // Three and four tokens: the other kernels have more to merge (bf16) or take two passes (8 and 4 bit).  (With weights rounded to bf16 and rolled loads, up to a tenth slower
-// than now:)
+// than now; equal and drawn lengths:)
 //   bf16, four   1 x 2048  20.7/17.9    8 x 2048  34.8/22.7 31.7/22.1    16 x 1536  36.3/25.9 33.4/25.0    64 x 256  36.9/29.0 31.8/26.7      three  33 x 768  31.7/25.6 28.1/25.3
-//   8 bit, four  1 x 4096  31.7/27.5    (1 x 6144  36.9/38.7)    4 x 6144  46.7/41.0 48.9/38.6    8 x 6144  52.4/43.9 50.5/43.2    16 x 6144  66.0/54.8 55.5/53.1    32 x 2048  58.3/45.2 45.8/44.1    64 x 1024  60.6/53.7 54.7/48.2
+//   8 bit, four  1 x 4096  31.7/27.5    (1 x 6144  36.9/38.7)    4 x 6144  46.7/41.0 48.9/38.6    8 x 6144  52.4/43.9 50.5/43.2    16 x 6144  66.0/54.8 55.5/53.1    32 x 1792  54.4/40.5 47.9/39.9    (32 x 2048  54.8/44.8 45.7/43.7)
+//                64 x 1024  60.6/53.7 54.7/48.2
 //   4 bit, four  1 x 4096  30.9/24.6    4 x 6144  45.4/38.1 47.9/36.7    8 x 6144  49.2/39.8 49.2/39.3    16 x 6144  60.6/47.1 52.1/46.3    32 x 2048  54.2/39.9 42.9/38.8    (64 x 2048  72.4/76.8 60.9/68.6)
 //   8 bit, three  128 x 256  53.6/37.1 54.1/35.9
 // Up to 32 rows the lines lie lower than these figures would have them, where brief_runs (below) has something better.
-constexpr int kBriefBands = 10;
-constexpr int kBriefRows[kBriefBands] = {4, 16, 21, 32, 47, 64, 99, 128, 256, 384};
-constexpr int kBriefParts[kBriefBands] = {16, 16, 8, 8, 4, 4, 2, 2, 2, 2};
+constexpr int kBriefBands = 11;
+constexpr int kBriefRows[kBriefBands] = {4, 16, 21, 32, 47, 64, 71, 99, 128, 256, 384};
+constexpr int kBriefParts[kBriefBands] = {16, 16, 8, 8, 4, 4, 2, 2, 2, 2, 2};
 constexpr int kBriefLines[2][3][kBriefBands] = {                        // [three or four tokens][16, 8, 4 bits]
-    {{768, 1152, 1280, 1536, 1280, 1536, 512, 768, 0, 0}, {896, 1280, 1536, 2048, 1536, 1792, 512, 640, 0, 0}, {1024, 1280, 1536, 2048, 1536, 2048, 640, 768, 0, 0}},
-    {{768, 1152, 1280, 2048, 1536, 1536, 768, 768, 256, 0}, {896, 1280, 1536, 2048, 6144, 6144, 2048, 2048, 1024, 256}, {1024, 1280, 1536, 2048, 6144, 6144, 2048, 2048, 1024, 256}}};
+    {{768, 1152, 1280, 1536, 960, 960, 384, 384, 384, 0, 0}, {896, 1280, 1536, 2048, 1536, 1536, 384, 384, 384, 0, 0}, {1024, 1280, 1536, 2048, 1536, 1792, 512, 512, 512, 0, 0}},
+    {{768, 1152, 1280, 2048, 1536, 1536, 512, 768, 768, 256, 0}, {896, 1280, 1536, 2048, 6144, 6144, 1792, 1792, 1792, 1024, 256}, {1024, 1280, 1536, 2048, 6144, 6144, 2048, 2048, 2048, 1024, 256}}};
 constexpr int brief_parts(int bits, int q_len, int64_t rows, int64_t hint)
 {
     for (int band = 0; band < kBriefBands; ++band)
@@ -41,7 +50,8 @@ constexpr int brief_parts(int bits, int q_len, int64_t rows, int64_t hint)
 
 // Beyond those lines, up to 32 rows (21 with one token, or two of longer contexts): into how many runs brief_attn_kernel cuts a row, or 0 where the other kernels are ahead.  A run takes
 // kBriefCutParts workgroups; the runs of all rows fill the compute units once (a second round is a loss: 2 x 8192 with 32 runs 13.2, with 48 19.2), but with no
-// less than 64 tokens each, 128 from three rows on (5 x 1536, of 12/9/6 runs 12.9/12.3/11.9 us).  Each compute unit reads rows * hint / 64 tokens' keys and values
+// less than 64 tokens each, 128 from three rows on (5 x 1536, of 12/9/6 runs 11.8/12.2/11.9 us, drawn 11.5/11.7/11.9; 8 x 2048, of 8/6/4 13.1/13.8/14.8; 3 x 1024, of 16/8 bf16 9.8/10.0, 8 bit
+// 9.7/9.6).  Each compute unit reads rows * hint / 64 tokens' keys and values
 // whole, through its own 107 GB/s: that is what the limits on rows * hint are.  us per call, uncut / the other kernels / runs, equal and drawn lengths:
 //   bf16, one token    1 x 512 8.2/10.5/8.5   1 x 1024 10.9/11.4/9.2   1 x 1536 13.5/11.5/9.0   1 x 4096 -/12.7/10.8   1 x 32768 -/22.0/16.5   2 x 8192 -/18.1/13.7 -/18.9/13.7   4 x 768 10.1/12.4/10.2
 //                      4 x 16384 -/25.1/22.3 -/22.5/21.9   (4 x 32768 -/34.6/37.2 -/27.7/32.5)   5 x 1536 13.9/16.2/11.9 13.4/14.1/12.0   8 x 8192 -/25.4/22.1 -/22.2/21.5   (8 x 16384 -/35.2/37.0)
@@ -52,6 +62,8 @@ constexpr int brief_parts(int bits, int q_len, int64_t rows, int64_t hint)
 //                      (12 x 3400 -/25.4/24.7 -/22.7/24.0)   bf16 16 x 2048 22.9/25.8/23.4 21.2/24.2/21.5   (16 x 3072 -/27.8/29.2 -/25.0/26.6)
 //   four tokens        bf16 1 x 32768 -/39.8/32.4   2 x 16384 -/38.9/32.3 -/37.5/32.2   4 x 8192 -/40.0/32.3 -/35.6/31.6   (4 x 16384 -/46.4/55.0)   (8 x 4096 -/38.7/33.0 -/39.3/32.2)   three (10 x 4300, drawn -/32.0/33.5)
 //                      8 bit 1 x 8192 -/41.0/15.5   2 x 32768 -/64.6/41.6 -/60.1/41.0   4 x 16384 -/57.2/41.3 -/55.9/40.4   8 x 8192 -/55.4/42.3 -/55.8/40.9
+// One sequence of the hint's length, the others of 32 tokens, the other kernels before several waves merged / runs: bf16 2 x 8192 28.8/12.4   8 x 8000 29.5/20.4   16 x 3500 21.0/18.6   20 x 2400 19.0/18.2   8 bit 21 x 3000 19.4/16.7
+//   two tokens bf16 16 x 2048 20.6/20.2   8 bit 16 x 2816 21.7/19.7   four tokens bf16 4 x 8192 40.6/30.7   8 bit 8 x 8000 63.0/39.6
 // The units of a row are dealt out to its runs, so shorter lengths than the hint cost less: 1 x 4096 under a hint of 32768 15.9/11.9, 16 x 512 under 4096 18.0/11.5.
 constexpr int kBriefCutParts = 4;
 constexpr int kMostBriefRuns = 64;                                      // of all rows: 256 compute units
