@@ -70,6 +70,39 @@ def exact_heads(case, b, q, n):
     return rows, w @ torch.where(torch.isfinite(v), v, torch.zeros_like(v)).abs()
 
 
+WEIGHT_ERROR = 2.0 ** -16
+# of sum_t w_t |v_t|: what a result may differ by where weights meet the values as two bf16 terms.  The terms lose 2^-17 of a weight; scores (256 exact
+# products summed in 32 bits, about 10 in size), exponentials and sums as much again.  One bf16 term would lose 2^-9: 3e-4 .. 2e-3
+# of that sum in the worst of some thousand elements, at 1152 .. 20 tokens.
+
+
+def weight_error(case, q, got, n_heads=8, n_seqs=4):
+    """Largest error of got [B, q_len, H, D] relative to sum_t w_t |v_t|, over some heads of the longest, the first, the last and other sequences of a contiguous case."""
+    B, q_len = q.shape[:2]
+    worst = 0.0
+    for b in sorted({int(case.seq_lens.argmax()), 0, B - 1, *range(0, B, max(1, B // n_seqs))}):
+        for j in range(q_len):
+            n = int(case.seq_lens[b]) - (q_len - 1 - j)
+            if n <= 0:
+                assert (got[b, j] == 0).all()
+                continue
+            heads = torch.arange(n_heads) * (64 // n_heads) + b % (64 // n_heads)
+            want, magnitude = exact_heads(case, b, q[b, j, heads], n)
+            worst = max(worst, float(((got[b, j, heads].double() - want).abs() / magnitude).max()))
+    return worst
+
+
+def attend(ctx, case, q, hint):
+    """Queries q [B, q_len, H, D] through the multi-token entry point of the case's layout; the result on the host."""
+    d = to_dev
+    f = mfa.mfa_decode_attn_paged_multi if case.paged else mfa.mfa_decode_attn_multi
+    cache = (case.k_pool, case.v_pool, case.block_table) if case.paged else (case.k, case.v)
+    scales = (case.k_scale_pool, case.v_scale_pool) if case.paged else (case.k_scale, case.v_scale)
+    out = f(ctx, d(q), *[d(t) for t in cache], d(case.seq_lens), hint, *[d(t) for t in scales])
+    torch.cuda.synchronize()
+    return out.cpu()
+
+
 def row_normalised_error(got, ref):
     """max over rows of max_d|got-ref| / max_d|ref| (rows whose reference is all zero must match exactly)."""
     got = np.asarray(got, dtype=np.float64).reshape(-1, got.shape[-1])

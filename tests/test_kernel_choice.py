@@ -106,3 +106,23 @@ def test_block_table_entries_past_the_length_are_not_asked_for(tmp_path):
                 pages = {unit * 32 // 64 for unit in units if unit * 32 < limit}
                 assert max(pages, default=-1) < ((length if paged else hint) + 63) // 64
     assert ahead(False)
+
+
+def test_the_gpu_tests_of_little_work_take_the_forms_they_name(tmp_path):
+    """Every size of test_short_contexts goes uncut, with all four numbers of parts and sixteen up to the longest context that has them; every size of test_runs goes in runs; the infinities
+    are tested in each form."""
+    import test_gpu_brief, test_gpu_brief_runs
+    (tmp_path / "shim.cpp").write_text('#include "mfa_kernel_choice.hpp"\nextern "C" int parts(int bits, int q_len, long rows, long hint) { return mfa::brief_parts(bits, q_len, rows, hint); }\n'
+                                       'extern "C" int runs(int bits, int q_len, long rows, long hint) { return mfa::brief_runs(bits, q_len, rows, hint); }\n')
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", str(tmp_path / "shim.so"), str(tmp_path / "shim.cpp")], check=True)
+    lib = ctypes.CDLL(str(tmp_path / "shim.so"))
+    parts = lambda bits, B, q_len, hint: lib.parts(bits, q_len, ctypes.c_long(B * q_len), ctypes.c_long(hint))
+    for bits in (16, 8, 4):
+        seen = {case: parts(bits, *case) for case in test_gpu_brief.CASES}
+        assert set(seen.values()) == {16, 8, 4, 2}, seen
+        assert max(hint for (_, q_len, hint), p in seen.items() if p == 16 and q_len == 1) == 1152
+        for lens, q_len, hint, kv in test_gpu_brief_runs.RUNS:
+            if {"bf16": 16, "fp8": 8, "fp4": 4}[kv] == bits:
+                runs = lib.runs(bits, q_len, ctypes.c_long(len(lens) * q_len), ctypes.c_long(hint))
+                assert parts(bits, len(lens), q_len, hint) == 0 and runs >= 2, (bits, lens, q_len, hint)
+        assert [parts(bits, B, 1, S) for B, S in test_gpu_brief.INFINITIES] == [16, 8, 4, 2, 0]
