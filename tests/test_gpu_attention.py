@@ -26,10 +26,10 @@ def test_library_is_loaded_in_tree():
     assert mfa.binding.lib() is not None
 
 
-def test_config1_tiny_full_compare():
+def test_config1_tiny_full_compare(get_ctx):
     _announce("cfg1 tiny B=2 ctx=256")
     case = W.config1_tiny()
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     got = U.run_gpu(ctx, case)
     ref = U.run_oracle(case)
     assert got.shape == (2, 64, 256) and got.dtype == np.float32
@@ -41,11 +41,11 @@ def test_config1_tiny_full_compare():
     [1, 2, 64, 65, 700, 1500, 1023, 1024, 1025],
     [0, 5, 0, 300],
 ])
-def test_ragged_contiguous_with_poisoned_padding(lens):
+def test_ragged_contiguous_with_poisoned_padding(get_ctx, lens):
     _announce(f"ragged contiguous lens={lens}")
     S = max(max(lens), 1) + 7            # padding rows past the longest sequence, all NaN
     case = W.make_contiguous_case("ragged", 100 + len(lens), B=len(lens), S=S, seq_lens=lens, poison=True)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     got = U.run_gpu(ctx, case)
     ref = U.run_oracle(case)
     assert U.row_normalised_error(got, ref) <= U.TOL_BF16
@@ -56,10 +56,10 @@ def test_ragged_contiguous_with_poisoned_padding(lens):
             assert np.array_equal(got[b], np.broadcast_to(case.v[b, 0].float().numpy(), (64, 256)))
 
 
-def test_hint_larger_than_lengths_and_clamping():
+def test_hint_larger_than_lengths_and_clamping(get_ctx):
     _announce("hint > lens, and lens > hint are clamped")
     case = W.make_contiguous_case("hint", 131, B=3, S=512, seq_lens=[100, 257, 512], poison=False)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     ref = U.run_oracle(case)
     got = U.run_gpu(ctx, case, hint=512)
     assert U.row_normalised_error(got, ref) <= U.TOL_BF16
@@ -81,22 +81,22 @@ def test_single_split_path():
     ctx.close()
 
 
-def test_many_splits_merge():
+def test_many_splits_merge(get_ctx):
     """Few sequences, long context: every sequence is cut into many work items and merged."""
     _announce("many splits")
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     case = W.make_contiguous_case("splits", 151, B=2, S=6000, seq_lens=[6000, 4321], poison=True)
     assert mfa.mfa_decode_num_splits(ctx, 2, 6000) > 16
     got = U.run_gpu(ctx, case)
     assert U.row_normalised_error(got, U.run_oracle(case)) <= U.TOL_BF16
 
 
-def test_paged_equals_contiguous_bitwise_and_matches_oracle():
+def test_paged_equals_contiguous_bitwise_and_matches_oracle(get_ctx):
     _announce("paged vs contiguous")
     lens = [1, 64, 65, 200, 0, 127, 1000, 513]
     case = W.make_paged_case("paged", 161, lens, spare_pages=9, poison=True)
     contig = W.paged_to_contiguous(case, S=1024, poison=True)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     got_p = U.run_gpu(ctx, case, hint=1000)
     got_c = U.run_gpu(ctx, contig, hint=1000)
     assert np.array_equal(got_p, got_c)
@@ -119,21 +119,21 @@ def test_paged_gather_moves_bytes_exactly():
         assert (got[b, L:] == 0).all()
 
 
-def test_run_to_run_determinism():
+def test_run_to_run_determinism(get_ctx):
     _announce("determinism")
     case = W.make_contiguous_case("det", 171, B=3, S=3000, seq_lens=[3000, 2999, 17], poison=True)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     a = U.run_gpu(ctx, case)
     b = U.run_gpu(ctx, case)
     assert np.array_equal(a, b)
 
 
-def test_invariants_on_gpu_results():
+def test_invariants_on_gpu_results(get_ctx):
     """Properties that hold at any size: zero query gives the mean value row; outputs are convex combinations."""
     _announce("invariants")
     case = W.make_contiguous_case("inv", 181, B=2, S=900, seq_lens=[900, 333], poison=True)
     case.q[0].zero_()
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     got = U.run_gpu(ctx, case)
     v = case.v.float().numpy()
     mean0 = v[0, :900].astype(np.float64).mean(0)
@@ -166,7 +166,7 @@ def test_argument_errors_through_the_c_abi():
     torch.cuda.synchronize()
 
 
-def test_page_ids_outside_the_pool_touch_nothing_outside_it():
+def test_page_ids_outside_the_pool_touch_nothing_outside_it(get_ctx):
     """A block table with garbage ids for one sequence: reads are clamped into the pool (that sequence's result
     is meaningless), the other sequences are unaffected, and the append writes nothing for a bad id."""
     print("\n[case] bad page ids", flush=True)
@@ -175,7 +175,7 @@ def test_page_ids_outside_the_pool_touch_nothing_outside_it():
     ref = U.run_oracle(case)
     bad = case.block_table.clone()
     bad[1, 0], bad[1, 1], bad[1, 2] = -7, 2 ** 30, case.k_pool.shape[0]
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     d = U.to_dev
     out = mfa.mfa_decode_attn_paged(ctx, d(case.q), d(case.k_pool), d(case.v_pool), d(bad), d(case.seq_lens), 300)
     torch.cuda.synchronize()
@@ -214,11 +214,11 @@ def test_scores_of_minus_infinity_ahead_of_finite_ones(workgroups, n_masked):
     ctx.close()
 
 
-def test_the_stream_of_a_call_is_the_current_one(monkeypatch):
+def test_the_stream_of_a_call_is_the_current_one(get_ctx, monkeypatch):
     """By torch's undocumented functions and by its public one alike: on the default stream, a stream of the caller's and a stream under capture."""
     from paper_2507_19427_amd import binding as B
     case = W.make_contiguous_case("stream", 28, B=2, S=300, seq_lens=[300, 65])
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     args = [U.to_dev(t) for t in (case.q, case.k, case.v, case.seq_lens)]
     want = mfa.mfa_decode_attn(ctx, *args, 300)
     assert B._stream() == B._public_stream() == torch.cuda.current_stream().cuda_stream

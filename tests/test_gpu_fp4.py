@@ -34,11 +34,11 @@ def _check(case, ctx, hint=None):
     [5, 0, 1, 64, 65, 129, 128, 63],
     [0, 3000, 1, 0, 64, 2500, 129, 0, 2048, 65],
 ])
-def test_fp4_mixed_lengths(lens):
+def test_fp4_mixed_lengths(get_ctx, lens):
     _announce(f"fp4 mixed lens={lens}")
     case = W.make_contiguous_case("fp4mixed", 800 + len(lens), B=len(lens), S=max(lens) + 8, seq_lens=lens, kv_dtype="fp4",
                                   poison=True)
-    _check(case, U.get_ctx())
+    _check(case, get_ctx())
 
 
 def test_fp4_more_sequences_than_workgroups():
@@ -64,14 +64,14 @@ def test_fp4_paged_bitwise_equal_to_contiguous():
     assert np.array_equal(got_p, got_c)
 
 
-def test_fp4_key_and_value_bytes_are_taken_in_the_documented_order():
+def test_fp4_key_and_value_bytes_are_taken_in_the_documented_order(get_ctx):
     """A sequence of one token: the output of every head is that token's value row, element by element (pins
     the nibble order and the chunk placement of V independently of K).  The weight 1 carries the value scale
     rounded to bf16, hence the 2^-8 relative allowance."""
     _announce("fp4 element order")
     B, S = 2, 64
     case = W.make_contiguous_case("fp4order", 831, B=B, S=S, seq_lens=[1, 64], kv_dtype="fp4", poison=False)
-    got = U.run_gpu(U.get_ctx(), case)
+    got = U.run_gpu(get_ctx(), case)
     codes = torch.stack([case.v[0, 0] & 15, case.v[0, 0] >> 4], dim=-1).reshape(-1).long()
     table = torch.tensor([0, .5, 1, 1.5, 2, 3, 4, 6, -0.0, -.5, -1, -1.5, -2, -3, -4, -6], dtype=torch.float64)
     want = (table[codes] * float(case.v_scale[0, 0])).numpy()
@@ -79,13 +79,13 @@ def test_fp4_key_and_value_bytes_are_taken_in_the_documented_order():
         assert np.allclose(got[0, h], want, rtol=2.0 ** -8, atol=0)
 
 
-def test_fp4_two_query_tokens():
+def test_fp4_two_query_tokens(get_ctx):
     _announce("fp4, two query tokens")
     lens = [0, 1500, 1, 2, 64, 129, 65, 700]
     case = W.make_contiguous_case("fp4mtp", 841, B=len(lens), S=1504, seq_lens=lens, kv_dtype="fp4", poison=True)
     qm = W.make_multi_query(case, 2, 842)
     d = U.to_dev
-    out = mfa.mfa_decode_attn_multi(U.get_ctx(), d(qm), d(case.k), d(case.v), d(case.seq_lens), max(lens),
+    out = mfa.mfa_decode_attn_multi(get_ctx(), d(qm), d(case.k), d(case.v), d(case.seq_lens), max(lens),
                                     d(case.k_scale), d(case.v_scale))
     torch.cuda.synchronize()
     got = out.cpu().numpy()
@@ -155,12 +155,12 @@ def test_fp4_record_is_bit_exact_on_given_rows():
         assert np.array_equal(kph[int(table[b, 0]), int(lens[b])], kc[b]) and ksph[int(table[b, 0]), int(lens[b])] == ksc[b]
 
 
-def test_fp4_append_then_attend():
+def test_fp4_append_then_attend(get_ctx):
     """Projection + 4-bit record + attention over the lengthened cache, against the oracle's chain with the
     record taken from the GPU's own fp32 projection tolerance: the dequantised record must lie within half a
     code step of the fp64 projection, and attention over the GPU-written cache must match the oracle over it."""
     _announce("fp4 append + attention")
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     lens = [40, 0, 63, 64, 200]
     B, S = len(lens), 256
     case = W.make_contiguous_case("fp4app", 871, B=B, S=S, seq_lens=lens, kv_dtype="fp4", poison=False)

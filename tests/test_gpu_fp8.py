@@ -14,11 +14,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("lens", [[1], [33], [64], [65], [1, 2, 64, 65, 700, 1500, 1023, 1024, 1025], [0, 5, 0, 300]])
-def test_fp8_ragged_contiguous_with_poisoned_padding(lens):
+def test_fp8_ragged_contiguous_with_poisoned_padding(get_ctx, lens):
     print(f"\n[case] fp8 ragged contiguous lens={lens}", flush=True)
     S = max(max(lens), 1) + 9
     case = W.make_contiguous_case("fp8", 200 + len(lens), B=len(lens), S=S, seq_lens=lens, kv_dtype="fp8", poison=True)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     got = U.run_gpu(ctx, case)
     ref = U.run_oracle(case)
     err = U.row_normalised_error(got, ref)
@@ -29,23 +29,23 @@ def test_fp8_ragged_contiguous_with_poisoned_padding(lens):
             assert (got[b] == 0).all()
 
 
-def test_fp8_scales_matter():
+def test_fp8_scales_matter(get_ctx):
     """Scaling one token's key scale must move the result the way the oracle says (scales are per token)."""
     print("\n[case] fp8 per-token scales", flush=True)
     case = W.make_contiguous_case("fp8s", 211, B=2, S=200, kv_dtype="fp8", poison=False)
     case.k_scale[0, 17] *= 6.0
     case.v_scale[1, 3] *= 0.25
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     got = U.run_gpu(ctx, case)
     assert U.row_normalised_error(got, U.run_oracle(case)) <= U.TOL_FP8
 
 
-def test_fp8_paged_equals_contiguous_bitwise_and_matches_oracle():
+def test_fp8_paged_equals_contiguous_bitwise_and_matches_oracle(get_ctx):
     print("\n[case] fp8 paged vs contiguous", flush=True)
     lens = [1, 64, 65, 200, 0, 127, 1000, 513]
     case = W.make_paged_case("fp8paged", 221, lens, kv_dtype="fp8", spare_pages=9, poison=True)
     contig = W.paged_to_contiguous(case, S=1024, poison=True)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     got_p = U.run_gpu(ctx, case, hint=1000)
     got_c = U.run_gpu(ctx, contig, hint=1000)
     assert np.array_equal(got_p, got_c)
@@ -60,14 +60,14 @@ def test_fp8_without_scales_is_rejected():
     assert e.value.status == mfa.MFA_ERR_INVALID_ARG
 
 
-def test_fp8_run_to_run_determinism_and_prepared_calls():
+def test_fp8_run_to_run_determinism_and_prepared_calls(get_ctx):
     """Same inputs, same bits; and the pre-marshalled call objects bench.py uses give the same result as the
     checked wrappers (single query token and a pair)."""
     print("\n[case] fp8 determinism / prepared calls", flush=True)
     import paper_2507_19427_amd as mfa
     lens = [700, 64, 1500, 2, 129, 0]
     case = W.make_contiguous_case("fp8det", 911, B=len(lens), S=1504, seq_lens=lens, kv_dtype="fp8", poison=True)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     a = U.run_gpu(ctx, case)
     b = U.run_gpu(ctx, case)
     assert np.array_equal(a, b)

@@ -147,7 +147,7 @@ def test_output_projection(B, d_model):
     assert err <= TOL_LINEAR
 
 
-def test_decode_layer_chain_on_a_paged_fp8_cache():
+def test_decode_layer_chain_on_a_paged_fp8_cache(get_ctx):
     """query path, append, attention over the lengthened sequences, output projection: one decode step."""
     print("\n[case] decode layer chain", flush=True)
     B = 6
@@ -157,7 +157,7 @@ def test_decode_layer_chain_on_a_paged_fp8_cache():
     g = torch.Generator().manual_seed(432)
     w_kv = (torch.randn(7168, 512, generator=g) * 0.02).to(torch.bfloat16)
     w_o = (torch.randn(16384, 7168, generator=g) * 0.02).to(torch.bfloat16)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     kp, vp = pc.k_pool.cuda(), pc.v_pool.cuda()
     ksp, vsp = pc.k_scale_pool.cuda(), pc.v_scale_pool.cuda()
     table = pc.block_table.cuda()

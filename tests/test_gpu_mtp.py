@@ -66,10 +66,10 @@ def _check(case, ctx, tol, hint=None, q_seed=900, q_len=2):
     [4096, 0, 0, 1, 0, 0, 0, 2],
     [63, 1, 1, 2, 1, 1, 2, 1, 1, 1, 2, 1, 1, 1, 1, 1, 1, 65],
 ])
-def test_two_tokens_bf16_mixed_lengths(lens):
+def test_two_tokens_bf16_mixed_lengths(get_ctx, lens):
     _announce(f"two query tokens, bf16, lens={lens}")
     case = W.make_contiguous_case("mtp", 700 + len(lens), B=len(lens), S=max(lens) + 3, seq_lens=lens, poison=True)
-    _check(case, U.get_ctx(), U.TOL_BF16)
+    _check(case, get_ctx(), U.TOL_BF16)
 
 
 def test_two_tokens_more_sequences_than_workgroups():
@@ -82,11 +82,11 @@ def test_two_tokens_more_sequences_than_workgroups():
     _check(case, U.get_ctx(max_batch=512, max_seq_len=4096), U.TOL_BF16)
 
 
-def test_two_tokens_fp8_mixed_lengths():
+def test_two_tokens_fp8_mixed_lengths(get_ctx):
     _announce("two query tokens, fp8 mixed")
     lens = [0, 3000, 1, 2, 64, 2500, 129, 0, 2048, 65]
     case = W.make_contiguous_case("mtpfp8", 721, B=len(lens), S=3008, seq_lens=lens, kv_dtype="fp8", poison=True)
-    _check(case, U.get_ctx(), U.TOL_FP8)
+    _check(case, get_ctx(), U.TOL_FP8)
 
 
 @pytest.mark.parametrize("kv_dtype,tol", [("bf16", U.TOL_BF16), ("fp8", U.TOL_FP8)])
@@ -103,14 +103,14 @@ def test_two_tokens_paged_bitwise_equal_to_contiguous(kv_dtype, tol):
     assert np.array_equal(got_p, got_c)
 
 
-def test_each_token_agrees_with_the_single_token_entry_point():
+def test_each_token_agrees_with_the_single_token_entry_point(get_ctx):
     """Token j of the two-token step against the one-token step run on the same query and its own length.
     The two launches visit the tokens in different groupings, so the bf16-rounded weights are taken against
     different running maxima: agreement to a fraction of the bf16 tolerance, not bitwise."""
     _announce("two-token step vs two one-token steps")
     lens = [777, 64, 1500, 2, 129]
     case = W.make_contiguous_case("mtpvs1", 741, B=len(lens), S=1504, seq_lens=lens, poison=True)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     qm = W.make_multi_query(case, 2, 742)
     got = _run_gpu(ctx, case, qm)
     for j in range(2):
@@ -121,11 +121,11 @@ def test_each_token_agrees_with_the_single_token_entry_point():
         assert err <= 0.5 * U.TOL_BF16
 
 
-def test_one_token_through_the_multi_entry_point_is_the_single_token_path():
+def test_one_token_through_the_multi_entry_point_is_the_single_token_path(get_ctx):
     _announce("q_len=1 through the multi entry point")
     lens = [300, 0, 65, 4000]
     case = W.make_contiguous_case("mtpq1", 751, B=4, S=4000, seq_lens=lens, poison=True)
-    ctx = U.get_ctx()
+    ctx = get_ctx()
     a = U.run_gpu(ctx, case)
     b = _run_gpu(ctx, case, case.q.unsqueeze(1).contiguous())
     assert np.array_equal(a, b[:, 0])
@@ -133,13 +133,13 @@ def test_one_token_through_the_multi_entry_point_is_the_single_token_path():
 
 @pytest.mark.parametrize("q_len", [3, 4])
 @pytest.mark.parametrize("kv_dtype,tol", [("bf16", U.TOL_BF16), ("fp8", U.TOL_FP8)])
-def test_three_and_four_tokens(q_len, kv_dtype, tol):
+def test_three_and_four_tokens(get_ctx, q_len, kv_dtype, tol):
     """Three and four query tokens: one pass over a bf16 cache (the kernel that keeps all query tokens of a sequence
-    in one wave); pair by pair over the 8-bit cache, an odd count ending with an overlapping pair."""
+    in one wave); pair by pair over the 8-bit cache, an odd count ending with an overlapping pair.  (As little work, "any": a pass of its own for every query token.)"""
     _announce(f"{q_len} query tokens, {kv_dtype}")
     lens = [0, 1, 2, 3, 4, 64, 65, 66, 67, 129, 1500, 700]
     case = W.make_contiguous_case("mtp34", 780 + q_len, B=len(lens), S=1504, seq_lens=lens, kv_dtype=kv_dtype, poison=True)
-    _check(case, U.get_ctx(), tol, q_len=q_len)
+    _check(case, get_ctx(), tol, q_len=q_len)
 
 
 def test_four_tokens_paged_bitwise_equal_to_contiguous():
@@ -155,12 +155,13 @@ def test_four_tokens_paged_bitwise_equal_to_contiguous():
 
 
 @pytest.mark.parametrize("q_len", [3, 4])
-def test_one_pass_kernel_restarts_a_segment_whose_scores_outrun_the_reference(q_len):
+def test_one_pass_kernel_restarts_a_segment_whose_scores_outrun_the_reference(get_ctx, q_len):
     """The one-pass kernel fixes a head's reference exponent at its first unit and starts the segment again with
     a higher one when a later score exceeds it by more than 2^40.  Planted: keys aligned with the queries of some
     heads, far into the sequence and in different tiles, whose scores lie 60 to 140 (natural units) above the
     rest -- for a few heads of one head group only, for all heads, twice in a row (a second, larger outlier after
-    the first), and in the last tile.  The result must be the usual softmax: practically the outlier's value row."""
+    the first), and in the last tile.  The result must be the usual softmax: practically the outlier's value row.
+    (As little work, "any": runs, which move their reference instead of restarting.)"""
     _announce(f"{q_len} query tokens, outlier scores force restarts")
     lens = [700, 300, 130, 2000]
     case = W.make_contiguous_case("mtprestart", 795 + q_len, B=len(lens), S=2000, seq_lens=lens, poison=True)
@@ -180,14 +181,14 @@ def test_one_pass_kernel_restarts_a_segment_whose_scores_outrun_the_reference(q_
     plant(2, 127, [17], 1, 140.0)                        # a second, larger outlier later in the same sequence
     plant(3, 1990, [60, 61, 62, 63], 0, 100.0)           # in the last tile of a long sequence cut over workgroups
     case.k = k.to(torch.bfloat16)
-    got = _run_gpu(U.get_ctx(), case, qm)
+    got = _run_gpu(get_ctx(), case, qm)
     ref = _oracle(case, qm)
     err = U.row_normalised_error(got, ref)
     print(f"   row-normalised max error {err:.3e}", flush=True)
     assert err <= U.TOL_BF16
     # the planted key dominates its head: the output is that token's value row
     assert np.abs(got[0, 0, 4] - case.v[0, 333].float().numpy()).max() <= 1e-2 * np.abs(case.v[0, 333].float().numpy()).max()
-    assert np.array_equal(got, _run_gpu(U.get_ctx(), case, qm))           # and bitwise reproducible
+    assert np.array_equal(got, _run_gpu(get_ctx(), case, qm))           # and bitwise reproducible
 
 
 @pytest.mark.parametrize("q_len", [3, 4])

@@ -64,9 +64,9 @@ def _one_case(rng, i, ctx):
 
 
 @pytest.mark.parametrize("seed", [11, 12, 13, 14])
-def test_random_sweep(seed):
+def test_random_sweep(get_ctx, seed):
     print(f"\n[case] random sweep, seed {seed}", flush=True)
     rng = np.random.default_rng(seed)
-    ctx = U.get_ctx(max_batch=512, max_seq_len=8192)
+    ctx = get_ctx(max_batch=512, max_seq_len=8192)
     worst = max(_one_case(rng, i, ctx) for i in range(15))
     print(f"   worst error as a fraction of the tolerance: {worst:.2f}", flush=True)

@@ -1,7 +1,7 @@
 """GPU parity for the way work is spread over workgroups.  The balanced schedule lays the tiles of all
 sequences end to end and gives every workgroup an equal range, so a workgroup may hold the end of one
 sequence, several whole sequences and the start of another; sequences without tokens belong to nobody.
-These cases exercise those boundaries, the fixed-split schedule that remains for very large batches,
+These cases exercise those boundaries ("cut": little work would not be laid out so by itself), the fixed-split schedule that remains for very large batches,
 and the agreement of the two.  Same oracle, same tolerances as the other parity tests."""
 import numpy as np
 import pytest
@@ -53,20 +53,20 @@ def test_more_sequences_than_workgroups():
     [4096, 0, 0, 0, 0, 0, 0, 1],
     [63, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 65],
 ])
-def test_mixed_lengths_cross_workgroup_boundaries(lens):
+def test_mixed_lengths_cross_workgroup_boundaries(get_ctx, lens):
     _announce(f"mixed lens={lens}")
     S = max(lens) + 5
     case = W.make_contiguous_case("mixed", 310 + len(lens), B=len(lens), S=S, seq_lens=lens, poison=True)
-    _check(case, U.get_ctx(), U.TOL_BF16)
+    _check(case, get_ctx(), U.TOL_BF16)
 
 
-def test_fewer_tiles_than_workgroups_and_hint_far_above_lengths():
+def test_fewer_tiles_than_workgroups_and_hint_far_above_lengths(get_ctx):
     """The grid is sized from the hint; with short sequences most workgroups find an empty range."""
     _announce("tiny lens under a large hint")
     lens = [70, 1, 0, 130]
     case = W.make_contiguous_case("tinyhint", 321, B=4, S=256, seq_lens=lens, poison=True)
-    _check(case, U.get_ctx(), U.TOL_BF16, hint=256)
-    ctx = U.get_ctx(max_batch=128, max_seq_len=32768)
+    _check(case, get_ctx(), U.TOL_BF16, hint=256)
+    ctx = get_ctx(max_batch=128, max_seq_len=32768)
     q, lens_d = case.q.cuda(), case.seq_lens.cuda()
     k = torch.full((4, 30000, 256), float("nan"), dtype=torch.bfloat16)
     v = k.clone()
@@ -113,11 +113,11 @@ def test_fp8_more_sequences_than_workgroups():
     _check(case, ctx, U.TOL_FP8)
 
 
-def test_fp8_mixed_lengths():
+def test_fp8_mixed_lengths(get_ctx):
     _announce("fp8 mixed")
     lens = [0, 3000, 1, 0, 64, 2500, 129, 0, 2048, 65]
     case = W.make_contiguous_case("fp8mixed", 343, B=len(lens), S=3008, seq_lens=lens, kv_dtype="fp8", poison=True)
-    _check(case, U.get_ctx(), U.TOL_FP8)
+    _check(case, get_ctx(), U.TOL_FP8)
 
 
 @pytest.mark.parametrize("B,hi,kv_dtype", [(1000, 150, "bf16"), (4096, 70, "bf16"), (700, 200, "fp8")])
@@ -151,7 +151,7 @@ def test_two_query_tokens_with_a_thousand_sequences():
     ctx.close()
 
 
-def test_fixed_split_schedule_agrees(monkeypatch):
+def test_fixed_split_schedule_agrees(get_ctx, monkeypatch):
     """schedule = MFA_SCHEDULE_FIXED selects the schedule with equal chunks per sequence; both must match the
     oracle.  The environment override (MFA_SCHEDULE=fixed at context creation) selects the same code path."""
     _announce("fixed-split schedule")
@@ -166,7 +166,7 @@ def test_fixed_split_schedule_agrees(monkeypatch):
     ctx.close()
     monkeypatch.delenv("MFA_SCHEDULE")
     assert np.array_equal(got_fixed, got_env)
-    got_bal = _check(case, U.get_ctx(), U.TOL_BF16)
+    got_bal = _check(case, get_ctx(), U.TOL_BF16)
     assert U.row_normalised_error(got_fixed, got_bal.astype(np.float64)) <= U.TOL_BF16
 
 

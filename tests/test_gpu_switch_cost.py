@@ -28,11 +28,11 @@ def _lens(kind):
 @pytest.mark.parametrize("q_len", [1, 2, 3, 4])
 @pytest.mark.parametrize("kv", ["bf16", "fp8", "fp4"])
 @pytest.mark.parametrize("kind", ["odd equal", "one past", "short among empty", "three groups", "long tail"])
-def test_against_the_oracle(kind, kv, q_len):
+def test_against_the_oracle(get_ctx, kind, kv, q_len):
     lens = _lens(kind)
     print(f"\n[case] switch cost {kind} {kv} q_len={q_len} B={len(lens)}", flush=True)
     case = W.make_paged_case("sw", 60 + q_len, lens, kv_dtype=kv, spare_pages=3, poison=True)
-    ctx = U.get_ctx(max_batch=512)
+    ctx = get_ctx(max_batch=512)
     qm = W.make_multi_query(case, q_len, 61) if q_len > 1 else case.q.unsqueeze(1)
     dev = [U.to_dev(t) for t in (case.k_pool, case.v_pool, case.block_table, case.seq_lens)]
     scales = (U.to_dev(case.k_scale_pool), U.to_dev(case.v_scale_pool))

@@ -28,7 +28,7 @@ def _both(ctx, case, hint):
 
 
 @pytest.mark.parametrize("kv_dtype,tol", [("bf16", TOL_BF16), ("fp8", TOL_FP8)])
-def test_static_scratch_entry_matches_workspace_entry_twice(kv_dtype, tol):
+def test_static_scratch_entry_matches_workspace_entry_twice(get_ctx, kv_dtype, tol):
     ctx = get_ctx(max_batch=128, max_seq_len=8192)
     # first call: several sequences cut over many workgroups (every partial slot of the call is written)
     big = W.make_contiguous_case("noalloc_big", 21, B=6, S=2100, seq_lens=[2100, 1, 777, 0, 64, 1500],
