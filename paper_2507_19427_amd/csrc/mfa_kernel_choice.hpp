@@ -77,11 +77,6 @@ constexpr int brief_runs(int bits, int q_len, int64_t rows, int64_t hint)
     return (int)(by_length < fill ? by_length : fill);
 }
 
-// Whether brief_attn_kernel's waves ask for their first units before they know the sequence's length.  Rows of a contiguous cache exist up to the hint, whatever the length
-// is.  A block table's entries are never read past the pages that the length fills, so a paged call waits for the length first, one round trip more: us per call, without / with
-// the wait, 5 x 1500 bf16 11.3/11.8, 8 bit 4 x 2048 11.2/11.7, 4 bit 64 x 1024 13.9/14.4, 2 x 256 bf16 no difference.
-constexpr bool asks_ahead_of_the_length(bool paged) { return !paged; }
-
 // short_lowbit_kernel below so many 64-token tiles per workgroup, counted at the length of the hint, else decode_lowbit_kernel.  The lines lie where lengths
 // drawn from 1 .. hint, half the hint on average, no longer lose more than 1 %; lengths equal to the hint would have them lower.  us per call, short / decode, 50 sequences of the length of the hint and drawn:
 //                                12 tiles                16 tiles                20 tiles                24 tiles                30 tiles

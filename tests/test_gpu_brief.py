@@ -116,6 +116,7 @@ def test_infinite_values(B, S, kv):
 
 @pytest.mark.parametrize("q_len,lens,hint", [(1, [70, 0, 1, 64, 300], 900), (1, [2100, 1, 65], 4096), (3, [2, 500, 64], 1000)])
 def test_block_table_entries_past_the_length_do_not_matter(q_len, lens, hint):
+    """Those below the hint may be looked up before the length is known; whatever they hold, the result is the same."""
     case = W.make_paged_case("garbage", 77, lens, spare_pages=3, poison=True, max_blocks=(hint + 63) // 64)
     q = W.make_multi_query(case, q_len, 7) if q_len > 1 else case.q.view(len(lens), 1, 64, 256)
     want = U.attend(U.get_ctx(), case, q, hint)

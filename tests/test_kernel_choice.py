@@ -91,23 +91,6 @@ def test_runs_of_few_rows(tmp_path):
     assert runs(8, 2, 32, 2816) == 2 and runs(8, 2, 32, 2817) == 0 and runs(16, 2, 22, 2048) == 2 and runs(16, 2, 22, 2049) == 0
 
 
-def test_block_table_entries_past_the_length_are_not_asked_for(tmp_path):
-    """The header promises that entries at or past ceil(seq_len / page_size) are never read.  With little work a wave asks for its first unit by the hint alone where that
-    is allowed, which is over contiguous caches; the pages of every unit that run s, wave w asks for under the resulting limit lie below the length."""
-    (tmp_path / "shim.cpp").write_text('#include "mfa_kernel_choice.hpp"\nextern "C" int ahead(int paged) { return mfa::asks_ahead_of_the_length(paged != 0); }\n')
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", str(tmp_path / "shim.so"), str(tmp_path / "shim.cpp")], check=True)
-    ahead = ctypes.CDLL(str(tmp_path / "shim.so")).ahead
-    hint, waves = 2500, 8
-    for paged in (False, True):
-        for length in (0, 1, 31, 64, 65, 700, 2500):
-            limit = hint if ahead(paged) else length
-            for runs in (1, 3, 16):
-                units = [run + runs * wave for run in range(runs) for wave in range(waves)]
-                pages = {unit * 32 // 64 for unit in units if unit * 32 < limit}
-                assert max(pages, default=-1) < ((length if paged else hint) + 63) // 64
-    assert ahead(False)
-
-
 def test_the_gpu_tests_of_little_work_take_the_forms_they_name(tmp_path):
     """Every size of test_short_contexts goes uncut, with all four numbers of parts and sixteen up to the longest context that has them; every size of test_runs goes in runs; the infinities
     are tested in each form."""
