@@ -8,25 +8,26 @@ namespace mfa {
 // Short contexts: into how many workgroups brief_attn_kernel cuts a row (a query token of a sequence), or 0 where the kernels that cut the cache
 // are ahead.  As many as leave a workgroup per compute unit, 16 at most: each part reads all keys of its row.
 //
-// The lines, in tokens of the hint, lie where equal lengths and lengths drawn from 1 .. hint gain, and one sequence of the hint's length among others of 32 tokens loses 5 % at most: uncut, a
-// long row has its fixed share of the chip, where the balanced schedule gives it most of it.  us per call, the other kernels (streaming kernel and merge) / this one; in brackets what lies beyond a line.
-// Equal and drawn lengths:
+// The lines, in tokens of the hint, lie where equal lengths and lengths drawn from 1 .. hint gain, and one sequence of the hint's length among others of 32 tokens loses little (7 % at the very
+// most, mostly nothing): uncut, a long row has its fixed share of the chip, where the balanced schedule gives it most of it.  us per call, the other kernels (streaming kernel and merge) / this one;
+// in brackets what lies beyond a line.  Equal and drawn lengths:
 //   bf16, one token    2 x 256  9.8/6.6     2 x 1024  11.6/11.0 11.7/10.9    (3 x 1280  12.4/12.6 12.2/12.3)    (6 x 1536  17.2/13.8 15.9/13.5    16 x 1536  18.3/16.5 19.1/14.1: runs, below)
-//                      32 x 1536  21.9/18.3    64 x 960  24.5/18.2 21.8/18.0    (64 x 1152  26.9/20.6 23.1/20.2    64 x 1536  30.0/24.2 25.5/22.9)
+//                      47 x 960  23.0/17.6 19.1/17.8    64 x 896  24.3/16.9 21.9/16.8    (64 x 960  24.5/18.2 21.8/18.0    64 x 1152  26.9/20.6 23.1/20.2    64 x 1536  30.0/24.2 25.5/22.9)
 //                      128 x 384  23.5/17.6 22.4/18.2    (66 x 512  20.7/18.1 19.7/18.6    128 x 512  26.1/20.2 24.2/20.3    128 x 768  31.1/24.8 27.1/24.6)
-//   8 bit, one token   2 x 256  10.9/6.2    1 x 1280  12.3/11.6     (1 x 1536  12.5/12.9)    18 x 2048  20.3/18.3 18.0/17.4    34 x 1536  22.3/18.8 18.2/17.5    64 x 1536  24.0/19.1 21.6/18.6
-//                      (48 x 2048  28.4/22.5 22.0/22.1    64 x 1792  26.1/21.6 22.0/20.7)    (99 x 512  23.3/17.8 20.8/18.2    128 x 640  24.2/20.8 23.7/21.0)
+//   8 bit, one token   2 x 256  10.9/6.2    1 x 1280  12.3/11.6     (1 x 1536  12.5/12.9)    18 x 2048  20.3/18.3 18.0/17.4    47 x 1536  23.4/18.8 19.4/18.0    64 x 1408  25.7/19.1 21.5/17.2
+//                      (48 x 2048  28.4/22.5 22.0/22.1    64 x 1536  24.0/19.1 21.6/18.6    64 x 1792  26.1/21.6 22.0/20.7)    (99 x 512  23.3/17.8 20.8/18.2    128 x 640  24.2/20.8 23.7/21.0)
 //   4 bit, one token   1 x 1536  12.3/11.9    (1 x 1792  12.3/13.1)    32 x 2048  20.5/17.9 17.6/16.1    34 x 1536  20.2/17.0 17.0/15.4    64 x 1792  23.1/19.1 20.6/18.8    (64 x 2048  24.3/21.3 21.6/20.9)
 //                      128 x 512  21.5/17.0 21.7/17.2    (128 x 768  23.7/21.0 23.2/21.2)
 //   two tokens within 1 us of twice the sequences
-// One sequence of the hint's length, the others of 32 tokens, contiguous and paged (paged: with the wait for the length, asks_ahead_of_the_length):
-//   bf16               16 x 1152  16.8/11.4 16.2/11.4    32 x 1536  17.8/16.8 16.8/16.6    33 x 960  16.3/15.6 15.5/16.0    64 x 960  17.0/17.0 16.0/16.2    (64 x 1152  17.3/18.8    64 x 1536  18.1/22.1)
-//                      71 x 384  15.7/14.8 14.8/15.3    128 x 384  16.8/16.4 16.3/15.7    (66 x 512  15.9/16.9    128 x 448  16.7/18.5    128 x 768  17.4/23.0)
-//   8 bit              32 x 2048  17.9/17.2 18.3/17.5    47 x 1536  16.9/17.5 17.2/17.2    64 x 1536  16.9/17.8 17.4/17.4    (64 x 1792  17.5/19.5)    71 x 384  15.1/13.9 15.5/14.6    128 x 384  16.2/15.2 16.6/15.2    (72 x 512  15.1/16.2 15.5/16.8)
-//   4 bit              32 x 2048  17.6/15.9 18.0/16.8    64 x 1792  17.4/17.4 17.8/18.3    (64 x 2048  17.9/19.0)    71 x 512  14.9/15.2 15.2/15.3    128 x 512  15.7/16.0 16.0/15.7    (128 x 768  16.4/19.3)
-//   two tokens         bf16 32 x 960  19.9/17.2 18.4/17.0   8 bit 32 x 1536  19.4/18.4 19.8/17.8   just above where the parts of a row halve up to a tenth slower: bf16 17 x 960  16.2/16.3 15.3/16.6    33 x 384  15.2/15.6 14.3/16.0
-//   three and four     bf16, four 16 x 1536  26.5/22.6    24 x 768  25.0/23.1 25.1/23.7    17 x 512  21.0/18.0 21.2/18.5    (17 x 768  21.4/22.8 21.8/23.5)    three 24 x 768  22.1/22.4 22.0/23.3    33 x 768  22.8/23.5 22.8/23.9
-//                      8 bit, four 16 x 6144  55.9/51.3    32 x 1792  39.5/39.2 40.0/40.6    (32 x 2048  40.6/43.4)    4 bit, four 32 x 2048  39.8/39.4 40.7/40.5
+// One sequence of the hint's length, the others of 32 tokens, contiguous and paged:
+//   bf16               16 x 1152  16.9/11.3 16.0/11.2    32 x 1536  17.5/17.5 16.8/16.7    47 x 960  16.7/16.4 15.6/15.8    64 x 896  16.7/15.3 15.7/14.6    (64 x 960  16.7/17.0 15.7/16.8    64 x 1152  17.3/18.8    64 x 1536  18.1/22.1)
+//                      71 x 384  15.4/14.8 14.8/14.7    128 x 384  17.1/16.6 16.0/15.8    (66 x 512  15.9/16.9    128 x 448  16.7/18.5    128 x 768  17.4/23.0)
+//   8 bit              32 x 2048  17.8/17.6 18.3/17.3    47 x 1536  16.8/17.3 17.3/16.8    64 x 1408  16.9/16.4 17.4/15.7    (64 x 1536  17.0/18.2 17.4/17.5    64 x 1792  17.5/19.5)    71 x 384  15.2/13.9 15.6/14.1
+//                      128 x 384  16.0/15.1 16.4/15.2    (72 x 512  15.1/16.2 15.5/16.8    128 x 640  16.8/19.0)
+//   4 bit              32 x 2048  17.6/16.0 18.1/16.2    64 x 1792  17.5/17.5 17.8/17.5    (64 x 2048  17.9/19.0)    71 x 512  14.9/15.3 15.4/15.4    128 x 512  15.8/16.0 16.2/15.9    (128 x 768  16.4/19.3)
+//   two tokens         bf16 17 x 960  16.2/16.2 15.2/16.0    32 x 896  19.2/15.8 18.2/15.5    33 x 384  15.2/15.3 14.6/15.6   8 bit 32 x 1408  19.5/16.4 19.7/16.3
+//   three and four     bf16, four 16 x 1536  26.5/22.7 26.6/22.5    24 x 768  25.0/23.2 25.1/22.8    17 x 512  20.9/18.1 21.1/17.9    (17 x 768  21.4/22.8 21.8/23.5)    three 24 x 768  22.0/22.5 22.0/22.4    33 x 768  22.7/23.3 22.7/22.9
+//                      8 bit, four 16 x 6144  56.0/51.4 56.5/51.4    32 x 1792  39.1/39.2 39.9/39.8    (32 x 2048  40.6/43.4)    4 bit, four 32 x 2048  39.5/39.3 40.5/40.4
 // Three and four tokens: the other kernels have more to merge (bf16) or take two passes (8 and 4 bit).  (With weights rounded to bf16 and rolled loads, up to a tenth slower
 // than now; equal and drawn lengths:)
 //   bf16, four   1 x 2048  20.7/17.9    8 x 2048  34.8/22.7 31.7/22.1    16 x 1536  36.3/25.9 33.4/25.0    64 x 256  36.9/29.0 31.8/26.7      three  33 x 768  31.7/25.6 28.1/25.3
@@ -39,7 +40,7 @@ constexpr int kBriefBands = 11;
 constexpr int kBriefRows[kBriefBands] = {4, 16, 21, 32, 47, 64, 71, 99, 128, 256, 384};
 constexpr int kBriefParts[kBriefBands] = {16, 16, 8, 8, 4, 4, 2, 2, 2, 2, 2};
 constexpr int kBriefLines[2][3][kBriefBands] = {                        // [three or four tokens][16, 8, 4 bits]
-    {{768, 1152, 1280, 1536, 960, 960, 384, 384, 384, 0, 0}, {896, 1280, 1536, 2048, 1536, 1536, 384, 384, 384, 0, 0}, {1024, 1280, 1536, 2048, 1536, 1792, 512, 512, 512, 0, 0}},
+    {{768, 1152, 1280, 1536, 960, 896, 384, 384, 384, 0, 0}, {896, 1280, 1536, 2048, 1536, 1408, 384, 384, 384, 0, 0}, {1024, 1280, 1536, 2048, 1536, 1792, 512, 512, 512, 0, 0}},
     {{768, 1152, 1280, 2048, 1536, 1536, 512, 768, 768, 256, 0}, {896, 1280, 1536, 2048, 6144, 6144, 1792, 1792, 1792, 1024, 256}, {1024, 1280, 1536, 2048, 6144, 6144, 2048, 2048, 2048, 1024, 256}}};
 constexpr int brief_parts(int bits, int q_len, int64_t rows, int64_t hint)
 {

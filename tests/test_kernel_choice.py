@@ -64,7 +64,7 @@ def test_short_contexts(tmp_path):
                 assert hints == sorted(hints, reverse=True) and set(hints) <= {0, p}
             assert parts(bits, q_len, 64, 8192) == 0 and parts(bits, q_len, 400, 64) == 0
     # where one sequence of the hint's length among short ones would wait for its fixed share of the chip
-    for bits, rows, hint in ((16, 40, 1024), (16, 64, 1024), (16, 66, 448), (16, 128, 448), (8, 64, 1792), (8, 66, 512), (8, 128, 512), (4, 64, 2048), (4, 128, 576)):
+    for bits, rows, hint in ((16, 40, 1024), (16, 64, 960), (16, 66, 448), (16, 128, 448), (8, 64, 1536), (8, 66, 512), (8, 128, 512), (4, 64, 2048), (4, 128, 576)):
         assert parts(bits, 1, rows, hint) == 0 == parts(bits, 2, rows, hint), (bits, rows, hint)
     assert parts(8, 4, 128, 2048) == 0 == parts(8, 3, 66, 2048) and parts(16, 4, 68, 640) == 0
     assert parts(16, 1, 2, 256) == 16 and parts(16, 1, 64, 4096) == 0 and parts(8, 4, 64, 6144) == 4 and parts(8, 2, 64, 6144) == 0
