@@ -231,13 +231,15 @@ MFA_API mfa_status mfa_out_proj(mfa_ctx* ctx, const float* attn_out, const void*
  * context created with schedule = MFA_SCHEDULE_FIXED, cut every sequence
  * into the same number of equal chunks of max_seq_len_hint instead.  Pieces of a
  * sequence are merged in order of position by the library.  Little work (by the hint) is
- * distributed otherwise: short contexts (up to 384 .. 2048 tokens with up to 128 sequences,
- * and further with three or four query tokens) are not cut: workgroups share the heads and
- * output dims of a sequence, and a single launch writes the result; longer ones of few
- * sequences (up to 21, up to about 65536 tokens in all, more with three or four query
- * tokens) are dealt out in units of 32 tokens to at most 64 pieces, merged in a fixed
- * order.  So it is unless the context was created with target_workgroups or a schedule of
- * its own.
+ * distributed otherwise, by rows, a row being a query token of a sequence.  Short contexts
+ * (up to 384 .. 2048 tokens with up to 128 rows; with three or four query tokens up to 6144
+ * tokens, and 256 tokens with up to 256 rows, 384 over 8-bit and 4-bit caches) are not cut:
+ * workgroups share the heads and output dims of a row, and a single launch writes the
+ * result.  Longer ones of few rows (up to 21 rows and about 50000 .. 65000 tokens in all, i.e.
+ * rows times hint; 22 to 32 rows with two query tokens up to 2048 tokens, 2816 over 8-bit and
+ * 4-bit caches; up to 32 rows and 114688 .. 262144 tokens in all with three or four) are
+ * dealt out in units of 32 tokens to at most 64 pieces, merged in a fixed order.  So it is
+ * unless the context was created with target_workgroups or a schedule of its own.
  */
 MFA_API mfa_status mfa_decode_attn(mfa_ctx* ctx, const void* q, const void* k_cache, const void* v_cache,
                            const float* k_scale, const float* v_scale, mfa_kv_dtype kv_dtype,
@@ -291,7 +293,8 @@ MFA_API mfa_status mfa_debug_gather_paged(mfa_ctx* ctx, const void* pool, int32_
  * 1 <= q_len <= 4 (larger: MFA_ERR_UNSUPPORTED); q_len = 1 is mfa_decode_attn[_paged].  Two query
  * tokens share one pass over the cache; three and four share one pass over a bf16 cache when
  * B <= 512, and are otherwise (8-bit and 4-bit caches, larger batches) worked off as two pairs, i.e.
- * two passes.  Several query tokens need the balanced work distribution (B <= 4096, schedule
+ * two passes.  With little work (mfa_decode_attn) every query token is a row of its own and reads the
+ * cache by itself.  Several query tokens need the balanced work distribution (B <= 4096, schedule
  * MFA_SCHEDULE_BALANCED).
  * Everything else as for q_len = 1.
  */
@@ -346,12 +349,13 @@ MFA_API mfa_status mfa_debug_set_kernel_events(mfa_ctx* ctx, void* ev_before, vo
 MFA_API mfa_status mfa_debug_stream_read(mfa_ctx* ctx, const void* a, const void* b, size_t bytes_each,
                                          void* hip_stream);
 
-/* Number of pieces into which the next mfa_decode_attn* call with these host
- * arguments cuts a sequence of the full length max_seq_len_hint when every
- * sequence has that length (shorter sequences get proportionally fewer; each
- * piece's partial result is merged by the library).  Calls with little work
- * (mfa_decode_attn) have pieces of their own, 64 at most, whatever it returns.  Pure
- * host function; 0 on invalid arguments. */
+/* Number of pieces into which an mfa_decode_attn* call with these host
+ * arguments that is more than little work (mfa_decode_attn) cuts a sequence of the
+ * full length max_seq_len_hint when every sequence has that length (shorter sequences
+ * get proportionally fewer; each piece's partial result is merged by the library).  Which
+ * calls are little work depends on the cache type and the query tokens too, which this
+ * function does not know: those have one piece or pieces of their own, 64 at most over all rows.
+ * Pure host function; 0 on invalid arguments. */
 MFA_API int32_t mfa_decode_num_splits(const mfa_ctx* ctx, int32_t B, int32_t max_seq_len_hint);
 
 #ifdef __cplusplus

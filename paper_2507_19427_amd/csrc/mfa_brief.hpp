@@ -14,10 +14,11 @@
 // likewise; two units of LDS per wave instead: the same within 2 % (the issue of the two waves of a SIMD is the limit, then a compute unit's way to
 // L2: 107 GB/s of it at 16 parts and bf16).  Two head groups per wave with less of the dims each instead of one: 10 .. 50 % slower.
 //
-// Weights (times value scales) meet the values as two bf16 terms, 16 significant bits: the error against 64 bits is 2e-6 of a result, where weights
-// rounded once leave 1.2 .. 1.7e-3.  It costs up to 8 %: 64 x 1024 bf16 19.7 -> 21.7 us, now, with the loads unrolled by eight, 18.3.
+// Weights (times value scales) meet the values as two bf16 terms, 16 significant bits: the error against 64 bits is about 2e-6 of a result in the 2-norm (1.8 .. 2.4e-6 in calls of 1 .. 128 rows), 3 .. 6e-6 of a
+// row's largest in single elements, where weights rounded once leave 1.2 .. 1.7e-3.  It costs up to 8 %: 64 x 1024 bf16, taken uncut, 19.7 -> 21.7 us, now, with the loads unrolled by eight, 18.3.
 // The second term may be negative or zero, which an infinite value (or value scale) would turn into NaN.  So where a sum is not finite the workgroup
-// works its tokens off once more, with terms that are both positive (two_terms); every other call pays a vote of the waves at its end.
+// works its tokens off once more, with terms that are both positive (two_terms); every other call pays a vote of the waves at its end, 0.1 us, 0.4 with two parts (75 x 72 8 bit 9.6 -> 10.0).
+// The body stands in the code twice for that: a branch in its loop instead costs 8-bit calls 5 .. 8 %.
 //
 // MFMA shapes as in mfa_attn_core.hpp (v_mfma_f32_16x16x32_bf16; lane = 16*g + n): scores S^T[token, head], two blocks of 16 tokens; a lane's eight weights,
 // tokens 16*tb + 4*g + i, are its operand of O^T[d, head] += V^T . P^T.  8-bit and 4-bit codes are expanded to bf16 (exactly) between LDS and the matrix
@@ -39,7 +40,7 @@ struct BriefShape {
     static constexpr int kVBytes = 1024 * kVLoads;
     static constexpr int kScales = kKBytes + kVBytes;                   // key scales, value scales (256 bytes each, the second half a repetition)
     static constexpr int kSlotBytes = kScales + (BITS == 16 ? 0 : 512);
-    // Eight waves, each with a unit of its own, where registers (256 a wave) and LDS allow it
+    // Eight waves, each with a unit of its own, where registers (256 a wave) and LDS allow it: not with NH = 2 (four), nor over bf16 caches with 8 parts (six) and 4 (five, on four SIMDs)
     static constexpr int kLds = 160 * 1024;
     static constexpr int kMostWaves = NH == 1 ? 8 : 4;
     static constexpr int kWaves = kMostWaves * kSlotBytes <= kLds ? kMostWaves : kLds / kSlotBytes;
@@ -78,7 +79,7 @@ __device__ __forceinline__ void two_terms(float w, __bf16& first, __bf16& rest)
 // CUT: few rows of longer contexts leave most of the chip idle so.  Then a row's units are dealt out to a.n_splits runs (of kParts workgroups; run s has units
 // s, s + n_splits, ..: as even as it can be for every length, and the first units still lie where the hint alone says), which leave partial results;
 // merge_splits_kernel adds those up in the order of the runs.  Against the streaming kernels, where a compute unit takes all heads of a
-// range: a quarter as many ranges, so a quarter of the partial results to write and merge, and eight waves with 16 heads each where there are four with all.  us per call, 64 runs of
+// range: a quarter as many ranges, so a quarter of the partial results to write and merge.  (Eight waves over 8-bit and 4-bit caches, five over a bf16 one.)  us per call, 64 runs of
 // 1 x 32768 bf16 22.0 -> 16.5, 8 bit 22.3 -> 15.0; 12 of 5 x 4096 bf16 18.6 -> 14.8; 16 of four tokens, 1 x 8192 8 bit 41.0 -> 15.5 (two passes before).  Runs of
 // consecutive tokens, cut by the hint, take the same at its length, but no less wherever a length fills the first of them.
 //
@@ -112,7 +113,7 @@ __device__ __forceinline__ bool brief_attn(const AttnArgs& a, lds_ptr_t lds_base
     };
     // The direct loads of the unit whose first row is row0.  Rows at or past `left` re-read the last one before it.  From one load to
     // the next a lane's row moves by a constant, and its chunk by an exclusive or with one.  (Unrolled by eight: wholly, the first ones cost 0.2 .. 0.5 us, since
-    // code that runs once comes cold from the instruction cache, about 100 cycles per 64 bytes; not at all, 64 x 1024 takes 21.5 us in place of 18.3.)
+    // code that runs once comes cold from the instruction cache, about 100 cycles per 64 bytes; not at all, 64 x 1024, taken uncut, takes 21.5 us in place of 18.3.)
     auto request = [&](int64_t row0, int left, auto value) {
         constexpr bool V = decltype(value)::value;
         constexpr int kRow = S::kKRow, kChunks = (V ? S::kVRow : kRow) / 16, kRowStep = 64 / kChunks, kLoads = V ? S::kVLoads : S::kKLoads;

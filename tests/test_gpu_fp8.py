@@ -1,6 +1,6 @@
 """GPU parity for the fp8 (OCP e4m3, per-token fp32 scales) cache.  Parity is defined on the
 dequantised values: oracle and GPU read the same codes and scales.  Tolerance: row-normalised max
-error <= 3e-2 (fp32 accumulation, weights times value scale rounded to bf16)."""
+error <= 3e-2 (fp32 accumulation, weights times value scale rounded to bf16; little work keeps 16 bits of them, test_gpu_brief.py)."""
 import numpy as np
 import pytest
 import torch

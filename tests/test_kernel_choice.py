@@ -1,4 +1,4 @@
-"""The choice between the two kernels of the 8-bit and 4-bit caches, which is by sizes alone."""
+"""Which kernel a call takes, which is by sizes alone: the two of the 8-bit and 4-bit caches, and little work uncut or in runs."""
 import ctypes
 import os
 import subprocess
